@@ -74,12 +74,14 @@ __device__ __forceinline__ void publish_f32(float *p, float x)
 }
 // Four floats as one 16-byte store that goes through to the same level (the sc1 bit is what the
 // agent-scope store above carries); p is 16-byte aligned.  A quarter of the write transactions.
-// The compiler does not see this store: drain_vmem() waits for it.
+// The compiler does not see this store: drain_vmem() waits for it, and the s_nop stands for the two wait states it
+// would keep between a store of more than 8 bytes and an instruction that overwrites the store's data registers
+// (without it a build in which the very next vector instruction did so stored that instruction's result).
 __device__ __forceinline__ void publish_f32x4(float *p, float4 x)
 {
     typedef __attribute__((ext_vector_type(4))) float f4;
     const f4 v = {x.x, x.y, x.z, x.w};
-    asm volatile("global_store_dwordx4 %0, %1, off sc1" ::"v"(p), "v"(v) : "memory");
+    asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" ::"v"(p), "v"(v) : "memory");
 }
 __device__ __forceinline__ float fetch_f32(const float *p)
 {
