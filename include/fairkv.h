@@ -50,8 +50,8 @@ typedef enum {
 
 enum { FAIRKV_BF16 = 0, FAIRKV_F32 = 1,
        FAIRKV_E4M3 = 2, /* one byte per element: fairkv_pack and fairkv_append only (they move bytes) */
-       FAIRKV_BF16_VALU = 3 /* in_dtype of fairkv_decode_attn only: bf16 inputs through the vector-ALU kernel that
-                               serves fp32 instead of the matrix-core kernel; for A/B measurements of the two */ };
+       FAIRKV_BF16_VALU = 3 /* in_dtype of fairkv_decode_attn only: bf16 inputs through a vector-ALU kernel instead of
+                               the matrix-core kernel; for A/B measurements of the two */ };
 enum { FAIRKV_SHORT_PAIR_TOKENS = 96 }; /* a whole pair of at most this many tokens is a "short pair": the bf16 and 8-bit
                                            kernels let one wave run it alone (four such pairs stream side by side,
                                            no fold across waves), and the planner may charge it its own overhead */

@@ -148,12 +148,12 @@ __device__ __forceinline__ size_t out_row(const DecodeArgs &a, int b, int h, int
     return (static_cast<size_t>(b) * a.q_len + tok) * a.Hq + (h << a.g_shift) + g;
 }
 
-// Layout facts shared by the stages.  A row of K or V is LPR 16-byte pieces; one wave-wide
+// Layout facts of the vector-ALU kernel.  A bf16 row of K or V is LPR 16-byte pieces; one wave-wide
 // 16-byte-per-lane access covers RPI whole rows, so every global access is a run of
 // contiguous, fully used cache lines.
-template <int IN_DT, int D>
+template <int D>
 struct Geo {
-    static constexpr int ES = IN_DT == FAIRKV_BF16 ? 2 : 4;
+    static constexpr int ES = 2;
     static constexpr int ROW_BYTES = D * ES;
     static constexpr int LPR = ROW_BYTES / 16;   // lanes (16-byte pieces) per row
     static constexpr int RPI = 64 / LPR;         // rows per wave-wide access

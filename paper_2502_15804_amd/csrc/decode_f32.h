@@ -1,0 +1,270 @@
+// Decode kernel for fp32 K/V/q on the matrix cores.
+//
+// What bounds it: HBM.  With G = 8 query heads per KV head a retained token is 1 KB and 4096 flop; as 16x16x4 fp32
+// MFMA tiles (the G heads padded to 16 columns) that is 8 KB of matrix work per KB streamed, i.e. a third of the
+// fp32 matrix rate at 6 TB/s.  On the vector ALU the same token cost the softmax of its 64-token tile, one scalar
+// load of q per multiply and the reduction over lanes, and a wave waited for each tile before it asked for the next.
+//
+// Measured against the vector-ALU kernel that served fp32 before: the Llama-70B shape
+// (B 16, 64 / 8 heads, D 128, lognormal budgets, 135 MB) 537 -> 31.7 us per layer, 128 x 8 pairs of 1024 tokens (1.07 GB)
+// 6.7 TB/s.  Four waves (one per SIMD) against eight: 0.3-1.5 % faster at every size tried, 3 % at 1 GB.
+//
+// Everything stays in 32 bits: an fp32 MFMA multiplies and adds like a chain of fused multiply-adds.
+//
+// Shapes.  A wave works on tiles of 16 tokens, lane = (l16, lq) with l16 = lane % 16, lq = lane / 16:
+//     S^T[token][head] = K[token][:] . q[head][:]    D/4 x mfma_16x16x4: A row = token l16, contraction index lq
+//     O^T[d][head]    += V^T[d][token] P[token][head]  D/4 x mfma_16x16x4: A row stands for a d, contraction index lq
+// The order of a contraction and the meaning of an output row are free, so they are chosen such that every operand is
+// a 16-byte load straight from memory into the registers that the matrix instruction reads, with no trip through LDS:
+//     step (c, j) of the scores contracts d = 16 c + 4 lq + j: lane loads K[token l16][16 c + 4 lq .. + 3] (and q alike);
+//     step r of the sum contracts token 4 lq + r, which is the token whose score the lane holds in register r;
+//     row i of output block (u, j) is d = 64 u + 4 i + j: lane loads V[token 4 lq + r][64 u + 4 l16 .. + 3].
+//
+// Pipelining.  The registers of K are requested again (the wave's next tile, of the next item when this one is done)
+// as soon as the scores have been issued, those of V after the weighted sum, so a tile is in flight while the other
+// half of the arithmetic runs.
+#pragma once
+#include "decode_mfma.h"
+
+namespace fairkv {
+
+template <int D, int G, bool DEEP>
+__global__ __launch_bounds__(kThreads, 1) void fairkv_decode_f32_kernel(DecodeArgs a)
+{
+    static_assert(D == 64 || D == 128, "head_dim");
+    static_assert(G >= 1 && G <= 8, "query heads of a group");
+    constexpr int ROWB = D * 4;
+    constexpr int NC = D / 16;      // 16-byte pieces of a K row (or q row) per lane
+    constexpr int NU = D / 64;      // 16-byte pieces of a V row per lane
+
+    __shared__ __attribute__((aligned(16))) ItemSlot table[kTable];
+    __shared__ __attribute__((aligned(16))) float st_o[kWaves * G * D];
+    __shared__ __attribute__((aligned(16))) float st_ml[kWaves * G * 2];
+    __shared__ PendingParts<D, G> pend;
+    int n_pend = 0;
+
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int l16 = lane & 15, lq = lane >> 4;
+
+    const int i_begin = a.slot_ptr[blockIdx.x], i_end = a.slot_ptr[blockIdx.x + 1];
+    if (i_end <= i_begin) return;   // an idle slot
+
+    // tiles of an n-token item that fall to this wave: wave, wave + kWaves, ...
+    auto tiles_of = [&](int n) __attribute__((always_inline)) {
+        const int n_tiles = (n + kTok - 1) / kTok;
+        return n_tiles > wave ? (n_tiles - wave + kWaves - 1) / kWaves : 0;
+    };
+
+    // The fetch cursor: the wave's next tile, f_t of f_tiles of item f_item (n tokens from row on).
+    int f_item = 0, f_t = 0, f_tiles = 0, f_n = 0, f_b = 0, f_h = 0;
+    int64_t f_row = 0;
+    f32x4_t kr[NC], vr[4][NU], qr[NC];
+    // One tile: 16 rows from `row` on, of which those up to `last` are the item's.  Rows past it re-read that row;
+    // their scores are masked and their V is replaced by zeros.
+    auto load_k = [&](int64_t row, int last) __attribute__((always_inline)) {
+        const char *base = static_cast<const char *>(a.k) + row * ROWB;
+        const uint32_t off = min(l16, last) * ROWB + lq * 16;
+#pragma unroll
+        for (int c = 0; c < NC; ++c) kr[c] = __builtin_nontemporal_load(reinterpret_cast<const f32x4_t *>(base + off + c * 64));
+    };
+    auto load_v = [&](int64_t row, int last) __attribute__((always_inline)) {
+        const char *base = static_cast<const char *>(a.v) + row * ROWB;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const uint32_t off = min(4 * lq + r, last) * ROWB + l16 * 16;
+#pragma unroll
+            for (int u = 0; u < NU; ++u) vr[r][u] = __builtin_nontemporal_load(reinterpret_cast<const f32x4_t *>(base + off + u * 256));
+        }
+    };
+    auto f_tok0 = [&]() __attribute__((always_inline)) { return (wave + f_t * kWaves) * kTok; };
+    auto load_q = [&]() __attribute__((always_inline)) {      // columns past the group repeat its last head; they are never stored
+        const char *base = static_cast<const char *>(a.q) + (static_cast<size_t>(f_b) * a.Hq + f_h * G) * ROWB;
+        const uint32_t off = min(l16, G - 1) * ROWB + lq * 16;
+#pragma unroll
+        for (int c = 0; c < NC; ++c) qr[c] = *reinterpret_cast<const f32x4_t *>(base + off + c * 64);
+    };
+
+    // Early start: the first item's rows are requested from what the kernel arguments say of it, before the item list is here.
+    const uint32_t np0 = a.first_np[blockIdx.x];
+    const int n0 = static_cast<int>(np0 & 0x1ffu);
+    const bool seeded = n0 > 0;
+    if (seeded) {
+        const int pair0 = static_cast<int>(np0 >> 9);
+        f_b = __builtin_amdgcn_readfirstlane(pair0 / a.Hkv);
+        f_h = pair0 - f_b * a.Hkv;
+        f_row = a.first_row[blockIdx.x];
+        f_n = n0;
+        f_tiles = tiles_of(n0);
+        if (f_tiles > 0) {
+            load_q();
+            load_k(f_row + f_tok0(), f_n - 1 - f_tok0());
+            load_v(f_row + f_tok0(), f_n - 1 - f_tok0());
+        }
+    }
+
+    for (int batch = i_begin; batch < i_end; batch += kTable) {
+        const int nb = min(kTable, i_end - batch);
+        const bool early = seeded && batch == i_begin;
+        if (batch != i_begin) __syncthreads();                  // nobody still reads the previous table
+        if (threadIdx.x < nb) {
+            const fairkv_item it = a.items[batch + threadIdx.x];
+            const bool ok = it.b >= 0 && it.b < a.B && it.h >= 0 && it.h < a.Hkv && it.row >= 0 && it.part >= 0 &&
+                            it.part < a.n_parts && it.n_chunks >= 1 && it.chunk >= 0 && it.chunk <= it.part &&
+                            it.row + max(it.tok_count, 0) <= a.n_rows;
+            int n = ok ? max(it.tok_count, 0) : 0;              // a foreign item reads nothing
+            if (early && threadIdx.x == 0)                      // its first tiles are on their way, as many as n0 said
+                n = n0 < kEarlyTok ? n0 : max(n, kEarlyTok);
+            table[threadIdx.x] = ItemSlot{it.row, n, ok ? 1 : 0, ok ? it.b : 0, ok ? it.h : 0, it.chunk, it.n_chunks, it.part, -1, {0, 0}};
+        }
+        __syncthreads();
+
+        auto seek = [&](int item) __attribute__((always_inline)) {
+            f_item = item;
+            f_t = 0;
+            f_tiles = 0;
+            if (item < nb) {
+                f_row = uniform64(table[item].row);
+                f_n = __builtin_amdgcn_readfirstlane(table[item].n);
+                f_b = __builtin_amdgcn_readfirstlane(table[item].b);
+                f_h = __builtin_amdgcn_readfirstlane(table[item].h);
+                f_tiles = tiles_of(f_n);
+            }
+        };
+        auto skip_done = [&]() __attribute__((always_inline)) {   // on to the next item that has a tile for this wave
+            while (f_t >= f_tiles && f_item < nb) seek(f_item + 1);
+            return f_item < nb;
+        };
+        const bool loaded = early && f_tiles > 0;               // the first tile is on its way already
+        if (early) {
+            f_item = 0;
+            f_n = __builtin_amdgcn_readfirstlane(table[0].n);   // its full length
+            f_tiles = tiles_of(f_n);
+        } else {
+            seek(0);
+        }
+        if (!loaded && skip_done()) {
+            load_q();
+            load_k(f_row + f_tok0(), f_n - 1 - f_tok0());
+            load_v(f_row + f_tok0(), f_n - 1 - f_tok0());
+        }
+
+        for (int ci = 0; ci < nb; ++ci) {
+            fairkv_item it;
+            it.row = 0;
+            it.tok_count = 0;
+            it.b = __builtin_amdgcn_readfirstlane(table[ci].b);
+            it.h = __builtin_amdgcn_readfirstlane(table[ci].h);
+            it.chunk = __builtin_amdgcn_readfirstlane(table[ci].chunk);
+            it.n_chunks = __builtin_amdgcn_readfirstlane(table[ci].n_chunks);
+            it.part = __builtin_amdgcn_readfirstlane(table[ci].part);
+            const int n = __builtin_amdgcn_readfirstlane(table[ci].n);
+            const int my_tiles = tiles_of(n);
+
+            f32x4_t o[NU][4];
+#pragma unroll
+            for (int u = 0; u < NU; ++u)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) o[u][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+            float m_run = -INFINITY, l_run = 0.f;   // reference maximum of the lane's head, this lane's share of the weights
+
+            for (int t = 0; t < my_tiles; ++t) {
+                // ---- scores: S^T[token 4 lq + r][head l16]; two chains of sums --------------------------
+                f32x4_t s0 = {0.f, 0.f, 0.f, 0.f}, s1 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int c = 0; c < NC; ++c) {
+                    s0 = __builtin_amdgcn_mfma_f32_16x16x4f32(kr[c][0], qr[c][0], s0, 0, 0, 0);
+                    s1 = __builtin_amdgcn_mfma_f32_16x16x4f32(kr[c][1], qr[c][1], s1, 0, 0, 0);
+                    s0 = __builtin_amdgcn_mfma_f32_16x16x4f32(kr[c][2], qr[c][2], s0, 0, 0, 0);
+                    s1 = __builtin_amdgcn_mfma_f32_16x16x4f32(kr[c][3], qr[c][3], s1, 0, 0, 0);
+                }
+                const int tok0 = (wave + t * kWaves) * kTok;
+                const bool masked = n - tok0 < kTok;
+
+                // ---- the K registers are free: the next tile's rows, and its query rows if it is another item's.
+                // Without a next tile one row of this one is read again: with the same number of loads on every path
+                // the compiler can wait for V below while the rows of K stay in flight.
+                __builtin_amdgcn_sched_barrier(0);
+                int64_t next = f_row + tok0;
+                int next_last = 0;
+                ++f_t;
+                if (skip_done()) {
+                    next = f_row + f_tok0();
+                    next_last = f_n - 1 - f_tok0();
+                    if (f_t == 0) load_q();
+                }
+                load_k(next, next_last);
+                __builtin_amdgcn_sched_barrier(0);
+
+                float sv[4];
+#pragma unroll
+                for (int r = 0; r < 4; ++r) sv[r] = (s0[r] + s1[r]) * a.scale_log2;
+                if (masked) {
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+                        if (4 * lq + r >= n - tok0) {
+                            sv[r] = -INFINITY;
+#pragma unroll
+                            for (int u = 0; u < NU; ++u) vr[r][u] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+                        }
+                }
+
+                // ---- raise the reference maximum to the largest score (at once, unlike the bf16 kernel: weights stay at
+                //      or below 1, so the sums reach no further than the largest V; a tile is long enough to hide it)
+                float mx = fmaxf(fmaxf(sv[0], sv[1]), fmaxf(sv[2], sv[3]));
+                if (__builtin_amdgcn_ballot_w64(mx > m_run) != 0) {
+                    mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
+                    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+                    const float m_new = fmaxf(m_run, mx);
+                    const float alpha = m_new == m_run ? 1.f : __builtin_amdgcn_exp2f(m_run - m_new);   // 0 on the first tile
+                    l_run *= alpha;
+#pragma unroll
+                    for (int u = 0; u < NU; ++u)
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) o[u][j] *= alpha;
+                    m_run = m_new;
+                }
+                float p[4];
+                const float m_ref = m_run == -INFINITY ? 0.f : m_run;     // nothing but -inf so far: weights 0, not exp2(nan)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    p[r] = __builtin_amdgcn_exp2f(sv[r] - m_ref);
+                    l_run += p[r];
+                }
+
+                // ---- O^T[64 u + 4 i + j][head] += V^T P -----------------------------------------------
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+#pragma unroll
+                    for (int u = 0; u < NU; ++u)
+#pragma unroll
+                        for (int j = 0; j < 4; ++j)
+                            o[u][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(vr[r][u][j], p[r], o[u][j], 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
+                load_v(next, next_last);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+
+            // ---- fold the four token quarters of l, stage this wave's result, finish the item ------
+            l_run += __shfl_xor(l_run, 16, 64);
+            l_run += __shfl_xor(l_run, 32, 64);
+            if (l16 < G) {
+#pragma unroll
+                for (int u = 0; u < NU; ++u)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)      // rows 4 lq + r of the four blocks j: four consecutive coordinates
+                        *reinterpret_cast<float4 *>(st_o + (wave * G + l16) * D + 64 * u + 16 * lq + 4 * r) =
+                            make_float4(o[u][0][r], o[u][1][r], o[u][2][r], o[u][3][r]);
+                if (lq == 0) {
+                    st_ml[(wave * G + l16) * 2 + 0] = m_run;
+                    st_ml[(wave * G + l16) * 2 + 1] = l_run;
+                }
+            }
+            if (__builtin_amdgcn_readfirstlane(table[ci].valid))
+                item_epilogue<D, G, DEEP>(a, it, st_o, st_ml, pend, n_pend, a.v_scale);
+        }
+    }
+    if (n_pend > 0) flush_pending<D, G, DEEP>(a, pend, n_pend);
+}
+
+}  // namespace fairkv

@@ -1,14 +1,14 @@
-// Decode kernel on the vector ALU: any supported element type.  It is the path for fp32
-// inputs; bf16 inputs normally take the matrix-core kernel instead.
+// Decode kernel for bf16 inputs on the vector ALU: the second implementation behind FAIRKV_BF16_VALU, for
+// measurements against the matrix-core kernel that bf16 caches normally take.
 #pragma once
 #include "common.h"
 
 namespace fairkv {
 
-template <int IN_DT, int D, int G>
+template <int D, int G>
 __global__ __launch_bounds__(kThreads, 2) void fairkv_decode_valu_kernel(DecodeArgs a)
 {
-    using geo = Geo<IN_DT, D>;
+    using geo = Geo<D>;
     constexpr int LPR = geo::LPR, RPI = geo::RPI, NI = geo::NI, EPC = geo::EPC, DW = geo::DW;
     constexpr int ROW_BYTES = geo::ROW_BYTES;
 
@@ -92,12 +92,8 @@ __global__ __launch_bounds__(kThreads, 2) void fairkv_decode_valu_kernel(DecodeA
 #pragma unroll
                 for (int g = 0; g < G; ++g) {
                     const uint32_t qw = qrow[g * DW + c * 4 + j];   // wave-uniform: a scalar load
-                    if constexpr (IN_DT == FAIRKV_BF16) {
-                        s[g] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, qw),
-                                                               __builtin_bit_cast(bf16x2_t, kw[j]), s[g], false);
-                    } else {
-                        s[g] = fmaf(__uint_as_float(qw), __uint_as_float(kw[j]), s[g]);
-                    }
+                    s[g] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, qw),
+                                                           __builtin_bit_cast(bf16x2_t, kw[j]), s[g], false);
                 }
             }
         }
@@ -125,15 +121,10 @@ __global__ __launch_bounds__(kThreads, 2) void fairkv_decode_valu_kernel(DecodeA
             const int r = i * RPI + my_sub;
             float vf[EPC];
             const uint32_t vw[4] = {vreg[i].x, vreg[i].y, vreg[i].z, vreg[i].w};
-            if constexpr (IN_DT == FAIRKV_BF16) {
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    vf[2 * j] = bf16_lo(vw[j]);
-                    vf[2 * j + 1] = bf16_hi(vw[j]);
-                }
-            } else {
-#pragma unroll
-                for (int j = 0; j < 4; ++j) vf[j] = __uint_as_float(vw[j]);
+            for (int j = 0; j < 4; ++j) {
+                vf[2 * j] = bf16_lo(vw[j]);
+                vf[2 * j + 1] = bf16_hi(vw[j]);
             }
             if (r >= nv) {   // the re-read row must not contribute, even if it holds inf or NaN
 #pragma unroll

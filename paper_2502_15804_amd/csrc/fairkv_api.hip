@@ -16,6 +16,7 @@
 #include <cstdlib>
 #include <vector>
 
+#include "decode_f32.h"
 #include "decode_mfma.h"
 #include "decode_valu.h"
 #include "pack.h"
@@ -28,15 +29,29 @@ namespace {
 using namespace fairkv;
 static_assert(kTraceStamps == FAIRKV_TRACE_STAMPS, "the header's stamp count is the kernel's");
 
-template <int IN_DT, int D>
+template <int D>
 hipError_t launch_valu(int G, const DecodeArgs &a, int n_slots, hipStream_t st)
 {
     const dim3 grid(static_cast<unsigned>(n_slots)), block(kThreads);
     switch (G) {
-    case 1: hipLaunchKernelGGL((fairkv_decode_valu_kernel<IN_DT, D, 1>), grid, block, 0, st, a); break;
-    case 2: hipLaunchKernelGGL((fairkv_decode_valu_kernel<IN_DT, D, 2>), grid, block, 0, st, a); break;
-    case 4: hipLaunchKernelGGL((fairkv_decode_valu_kernel<IN_DT, D, 4>), grid, block, 0, st, a); break;
-    case 8: hipLaunchKernelGGL((fairkv_decode_valu_kernel<IN_DT, D, 8>), grid, block, 0, st, a); break;
+    case 1: hipLaunchKernelGGL((fairkv_decode_valu_kernel<D, 1>), grid, block, 0, st, a); break;
+    case 2: hipLaunchKernelGGL((fairkv_decode_valu_kernel<D, 2>), grid, block, 0, st, a); break;
+    case 4: hipLaunchKernelGGL((fairkv_decode_valu_kernel<D, 4>), grid, block, 0, st, a); break;
+    case 8: hipLaunchKernelGGL((fairkv_decode_valu_kernel<D, 8>), grid, block, 0, st, a); break;
+    default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+}
+
+template <int D, bool DEEP>
+hipError_t launch_f32(int G, const DecodeArgs &a, int n_slots, hipStream_t st)
+{
+    const dim3 grid(static_cast<unsigned>(n_slots)), block(kThreads);
+    switch (G) {
+    case 1: hipLaunchKernelGGL((fairkv_decode_f32_kernel<D, 1, DEEP>), grid, block, 0, st, a); break;
+    case 2: hipLaunchKernelGGL((fairkv_decode_f32_kernel<D, 2, DEEP>), grid, block, 0, st, a); break;
+    case 4: hipLaunchKernelGGL((fairkv_decode_f32_kernel<D, 4, DEEP>), grid, block, 0, st, a); break;
+    case 8: hipLaunchKernelGGL((fairkv_decode_f32_kernel<D, 8, DEEP>), grid, block, 0, st, a); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
@@ -430,9 +445,10 @@ int decode_common(const DecodeCall &c)
                        : (deep ? launch_mfma<64, true, false>(static_cast<int>(cols), solo, a, n_wg, st)
                                : launch_mfma<64, false, false>(static_cast<int>(cols), solo, a, n_wg, st));
     else if (in_dtype == FAIRKV_BF16)
-        e = D == 128 ? launch_valu<FAIRKV_BF16, 128>(G, a, n_wg, st) : launch_valu<FAIRKV_BF16, 64>(G, a, n_wg, st);
+        e = D == 128 ? launch_valu<128>(G, a, n_wg, st) : launch_valu<64>(G, a, n_wg, st);
     else
-        e = D == 128 ? launch_valu<FAIRKV_F32, 128>(G, a, n_wg, st) : launch_valu<FAIRKV_F32, 64>(G, a, n_wg, st);
+        e = D == 128 ? (deep ? launch_f32<128, true>(G, a, n_wg, st) : launch_f32<128, false>(G, a, n_wg, st))
+                     : (deep ? launch_f32<64, true>(G, a, n_wg, st) : launch_f32<64, false>(G, a, n_wg, st));
     return e == hipSuccess ? FAIRKV_OK : FAIRKV_EHIP;
 }
 }  // namespace
