@@ -44,77 +44,94 @@ __device__ __forceinline__ uint16_t f32_to_bf16_rne(float f)
     return static_cast<uint16_t>(u >> 16);
 }
 
-// four consecutive outputs, idx a multiple of 4 (out is 16-byte aligned).  Results are written once and not read
-// again by this launch: non-temporal stores keep them from waiting in the L2 for the write-back at the end of the
-// kernel (0.45 us per launch on a layer of whole pairs, 0.25 us on the many-small-pairs workload).
-__device__ __forceinline__ void store_out4(void *out, int out_dtype, size_t idx, float4 x)
+// Four consecutive outputs: element base + off of out, both multiples of 4 (out is 16-byte aligned), base the same for
+// the whole wave.  Results are written once and not read again by this launch: non-temporal stores keep them from
+// waiting in the L2 for the write-back at the end of the kernel (0.45 us per launch on a layer of whole pairs, 0.25 us
+// on the many-small-pairs workload).
+__device__ __forceinline__ void store_out4(void *out, int out_dtype, size_t base, uint32_t off, float4 x)
 {
     if (out_dtype == FAIRKV_F32) {
         typedef __attribute__((ext_vector_type(4))) float f4;
-        __builtin_nontemporal_store(f4{x.x, x.y, x.z, x.w}, reinterpret_cast<f4 *>(static_cast<float *>(out) + idx));
+        __builtin_nontemporal_store(f4{x.x, x.y, x.z, x.w}, reinterpret_cast<f4 *>(static_cast<float *>(out) + base + off));
     } else {
         typedef __attribute__((ext_vector_type(2))) uint32_t u2;
         const u2 w = {f32_to_bf16_rne(x.x) | (static_cast<uint32_t>(f32_to_bf16_rne(x.y)) << 16),
                       f32_to_bf16_rne(x.z) | (static_cast<uint32_t>(f32_to_bf16_rne(x.w)) << 16)};
-        __builtin_nontemporal_store(w, reinterpret_cast<u2 *>(static_cast<uint16_t *>(out) + idx));
+        __builtin_nontemporal_store(w, reinterpret_cast<u2 *>(static_cast<uint16_t *>(out) + base + off));
     }
 }
 
-struct DecodeArgs;
-// Where column c of pair (b, h) lives in out (times D) and in lse: [B][q_len][Hq].
-__device__ __forceinline__ size_t out_row(const DecodeArgs &a, int b, int h, int c);
+__device__ __forceinline__ int64_t uniform64(int64_t x)   // a wave-uniform value, moved to scalar registers
+{
+    const uint32_t lo = __builtin_amdgcn_readfirstlane(static_cast<int>(x));
+    const uint32_t hi = __builtin_amdgcn_readfirstlane(static_cast<int>(x >> 32));
+    return static_cast<int64_t>((static_cast<uint64_t>(hi) << 32) | lo);
+}
+// ... and a pointer
+template <class T>
+__device__ __forceinline__ T *uniform_ptr(T *p)
+{
+    return reinterpret_cast<T *>(uniform64(static_cast<int64_t>(reinterpret_cast<uintptr_t>(p))));
+}
 
 // Partial results travel between workgroups that may sit on different XCDs, whose L2 caches
-// are not coherent with each other.  Agent-scope relaxed atomics are plain 4-byte stores and
-// loads that go through to the level all XCDs share, without the cache-wide write-back and
-// invalidate that a device fence costs (measured: tens of microseconds per launch).
-__device__ __forceinline__ void publish_f32(float *p, float x)
-{
-    __hip_atomic_store(p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-// Four floats as one 16-byte store that goes through to the same level (the sc1 bit is what the
-// agent-scope store above carries); p is 16-byte aligned.  A quarter of the write transactions.
-// The compiler does not see this store: drain_vmem() waits for it, and the s_nop stands for the two wait states it
+// are not coherent with each other.  Stores and loads at agent scope (the sc1 bit) go through to the
+// level all XCDs share, without the cache-wide write-back and invalidate that a device fence costs
+// (measured: tens of microseconds per launch).
+// Stores of four (two) floats at byte off of a base that is the same for the wave; 16-byte (8-byte) aligned.
+// The compiler does not see these stores: drain_vmem() waits for them, and the s_nop stands for the two wait states it
 // would keep between a store of more than 8 bytes and an instruction that overwrites the store's data registers
 // (without it a build in which the very next vector instruction did so stored that instruction's result).
-__device__ __forceinline__ void publish_f32x4(float *p, float4 x)
+typedef __attribute__((ext_vector_type(4))) float f4_t;
+typedef __attribute__((ext_vector_type(2))) float f2_t;
+__device__ __forceinline__ void publish_f32x4(float *base, uint32_t off, float4 x)
 {
-    typedef __attribute__((ext_vector_type(4))) float f4;
-    const f4 v = {x.x, x.y, x.z, x.w};
-    asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" ::"v"(p), "v"(v) : "memory");
+    const f4_t v = {x.x, x.y, x.z, x.w};
+    asm volatile("global_store_dwordx4 %0, %1, %2 sc1\n\ts_nop 1" ::"v"(off), "v"(v), "s"(uniform_ptr(base)) : "memory");
 }
-__device__ __forceinline__ float fetch_f32(const float *p)
+__device__ __forceinline__ void publish_f32x2(float *base, uint32_t off, float x, float y)
 {
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const f2_t v = {x, y};
+    asm volatile("global_store_dwordx2 %0, %1, %2 sc1" ::"v"(off), "v"(v), "s"(uniform_ptr(base)) : "memory");
+}
+// Loads go through a buffer resource at the first of the partials: one instruction each, lane offset in a vector
+// register, partial in a scalar one.  kAgent is the sc1 bit in the cache-policy operand.
+constexpr int kAgent = 16;
+constexpr uint32_t kRsrcFlags = 0x00027000;      // untyped 32-bit elements
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t parts_rsrc(float *base, uint32_t bytes)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(uniform_ptr(base), 0, bytes, kRsrcFlags);
 }
 
 constexpr int kScaleHeads = 8;            // KV heads that may carry scales of their own (8-bit caches)
 
 struct DecodeArgs {
+    // What the first requests of a workgroup need comes first: it is read with one round trip (see slot below).
     const void *q, *k, *v;
     const fairkv_item *items;   // grouped by slot
+    int32_t q_len, g_shift;     // new tokens per sequence; log2 of the query heads per KV head.  A kernel's
+                                // template parameter G counts columns: q_len * (1 << g_shift), column
+                                // c = new token (c >> g_shift), head (c & mask) of the group
+    int32_t Hq, Hkv;
+    int32_t B, out_dtype, n_parts, n_group_counters;
+    int64_t n_rows;             // rows of k and of v
     float *part_o;              // [n_parts][G][D]   unnormalised outputs relative to the item's maximum
     float *part_ml;             // [n_parts][G][2]   (maximum in log2 units, sum of weights)
     int32_t *arrivals;          // [B*Hkv] items (or groups of items) of a cut pair that have delivered; 0 between calls
     int32_t *group_arrivals;    // [n_group_counters] the same per group of kGroup items, index first part + group
     void *out;
     float *lse;
-    int32_t B, Hq, Hkv, out_dtype, n_parts, n_group_counters;
-    int64_t n_rows;             // rows of k and of v
-    int32_t q_len, g_shift;     // new tokens per sequence; log2 of the query heads per KV head.  A kernel's
-                                // template parameter G counts columns: q_len * (1 << g_shift), column
-                                // c = new token (c >> g_shift), head (c & mask) of the group
     float scale_log2;           // scale * log2(e) (times the K scale of an 8-bit cache): scores are kept in log2
                                 // units so exp is one v_exp_f32
     float v_scale;              // 1, or the V scale of an 8-bit cache: multiplies out
     float k_head[kScaleHeads];  // 8-bit caches with a scale per KV head: further factors on scale_log2 and v_scale,
     float v_head[kScaleHeads];  // indexed h % kScaleHeads (all 1 otherwise; read by the 8-bit kernels only)
-    // What a workgroup needs before it has read anything from memory, riding in the kernel arguments:
-    int32_t slot_ptr[FAIRKV_MAX_SLOTS + 1];   // slot j runs items[slot_ptr[j] .. slot_ptr[j+1])
-    uint32_t first_row[FAIRKV_MAX_SLOTS];     // first K/V row of slot j's first item ...
-    uint32_t first_np[FAIRKV_MAX_SLOTS];      // ... its pair b*Hkv+h in bits 9..31 and min(tok_count, kEarlyTok) in
-                                              // bits 0..8; 0 = no early start for this slot
     unsigned long long *trace;                // fairkv_decode_attn_trace only: [workgroups][kTraceStamps], else null
+    // What a workgroup needs before it has read anything from memory, riding in the kernel arguments.  Slot j has words
+    // 3 j ...: the index of its first item (its last is the one before slot j + 1's first), the first K/V row of that
+    // item, and in one word its query group (b * q_len * Hkv + h, bits 9..31) and min(tok_count, kEarlyTok) (bits
+    // 0..8; 0 = no early start for this slot).
+    uint32_t slot[3 * FAIRKV_MAX_SLOTS + 1];
 };
 
 // Phases a traced launch stamps with the 100 MHz wall clock, per workgroup (thread 0 of wave 0).  A stamp
@@ -142,10 +159,35 @@ __device__ __forceinline__ void trace_stamp(const DecodeArgs &a, int what, bool 
 constexpr int kEarlyTok = 384;            // tokens of a slot's first item that the early start may request
 static_assert(sizeof(DecodeArgs) <= 4096, "kernel arguments are limited to 4 KiB");
 
-__device__ __forceinline__ size_t out_row(const DecodeArgs &a, int b, int h, int c)
+// The query rows of pair (b, h) start at row qg << g_shift of q, and its outputs at the same row of out and lse, where
+// qg = b * q_len * Hkv + h is its query group; column c of the pair is this many rows further.
+__device__ __forceinline__ uint32_t col_row(int g_shift, int Hq, int c)
 {
-    const int tok = c >> a.g_shift, g = c & ((1 << a.g_shift) - 1);
-    return (static_cast<size_t>(b) * a.q_len + tok) * a.Hq + (h << a.g_shift) + g;
+    return static_cast<uint32_t>((c >> g_shift) * Hq + (c & ((1 << g_shift) - 1)));
+}
+__device__ __forceinline__ size_t group_row(const DecodeArgs &a, int qg) { return static_cast<size_t>(qg) << a.g_shift; }
+
+// out = o / l (times the output's factor) and lse for coordinates d .. d + 3 of column c of a pair, from its
+// unnormalised output, maximum and weight sum.
+template <int D>
+__device__ __forceinline__ void write_out4(const DecodeArgs &a, int qg, int c, int d, float4 o, float m, float l, float v_mul)
+{
+    const size_t row = group_row(a, qg);
+    const uint32_t col = col_row(a.g_shift, a.Hq, c);
+    const float inv = l > 0.f ? v_mul / l : 0.f;
+    store_out4(a.out, a.out_dtype, row * D, col * D + d, make_float4(o.x * inv, o.y * inv, o.z * inv, o.w * inv));
+    if (d == 0 && a.lse) a.lse[row + col] = l > 0.f ? (m + __builtin_amdgcn_logf(l)) * kLn2 : -INFINITY;
+}
+
+// A slot's words of the kernel arguments.
+struct SlotStart {
+    int i_begin, i_end;     // its items
+    uint32_t row, np;       // of the first item: first row; query group and capped length
+};
+__device__ __forceinline__ SlotStart slot_start(const DecodeArgs &a)
+{
+    const uint32_t *w = a.slot + 3 * blockIdx.x;
+    return SlotStart{static_cast<int>(w[0]), static_cast<int>(w[3]), w[1], w[2]};
 }
 
 // Layout facts of the vector-ALU kernel.  A bf16 row of K or V is LPR 16-byte pieces; one wave-wide
@@ -163,32 +205,14 @@ struct Geo {
 };
 
 
-constexpr int kMergeBatch = 8;   // partials of a cut pair fetched at once by the merging workgroup
-
-// Two floats fetched as one 8-byte agent-scope load (see publish_f32 / fetch_f32 above).
-__device__ __forceinline__ float2 fetch_f32x2(const float *p)
-{
-    const uint64_t w = __hip_atomic_load(reinterpret_cast<const uint64_t *>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    return make_float2(__uint_as_float(static_cast<uint32_t>(w)), __uint_as_float(static_cast<uint32_t>(w >> 32)));
-}
-
-// Partial results of cut pairs that a workgroup has finished but not yet handed over.  They
-// wait in LDS until the slot's list is done (or the buffer is full) and are then published
-// together, so that the hand-over, which costs several memory round trips, happens once per
-// workgroup and not in the middle of the stream.
-// Two: a line cut leaves a slot at most two pieces of cut pairs (its first and its last item).  A third
-// slot made the hand-over code half as long again, and that code runs cold on the critical tail:
-// 0.15 us per launch on the headline workload.
-constexpr int pend_slots(int, int) { return 2; }
-
-template <int D, int G>
-struct PendingParts {
-    static constexpr int kPend = pend_slots(D, G);
-    __attribute__((aligned(16))) float o[kPend][G * D];
-    float ml[kPend][G * 2];
-    int32_t pair[kPend], part[kPend], first_part[kPend], n_chunks[kPend];
-    int32_t role[kPend], src_first[kPend], src_stride[kPend], src_count[kPend];   // what this workgroup merges, if anything
-    float v_mul[kPend];      // what multiplies the pair's output (1, or the V scale of an 8-bit cache)
+// A cut piece that a workgroup has finished: its partial is stored (see item_epilogue) but not yet counted in.  The
+// hand-over, which costs several memory round trips, happens once per workgroup, when the slot's list is done or kPend
+// pieces are waiting, and not in the middle of the stream.  Every field is the same for all threads.
+// Two: a line cut leaves a slot at most two pieces of cut pairs (its first and its last item).
+constexpr int kPend = 2;
+struct Piece {
+    int32_t pair, qg, part, chunk, n_chunks;
+    float v_mul;      // what multiplies the pair's output (1, or the V scale of an 8-bit cache)
 };
 
 // s_waitcnt vmcnt(0), once as an instruction the compiler accounts for (simm16 of gfx9: vmcnt 0,
@@ -199,11 +223,11 @@ __device__ __forceinline__ void drain_vmem()
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 }
 
-// Hand over the pending partials.  Called by all threads of the workgroup.
+// Hand over the pending pieces.  Called by all threads of the workgroup.
 //
-// A pair cut into fewer than kDeepFrom pieces: publish the partial, wait until the stores are
+// A pair cut into fewer than kDeepFrom pieces: the partials are stored, wait until the stores are
 // acknowledged, count in on the pair's counter; the workgroup that finds itself last merges the
-// pair's partials (all of them were published before their workgroups counted in):
+// pair's partials (all of them were stored before their workgroups counted in):
 //   m* = max_c m_c,  l* = sum_c l_c 2^(m_c - m*),  out = sum_c o_c 2^(m_c - m*) / l*
 // (exact in real arithmetic, so a cut pair gives what the whole pair would) and sets the counter
 // back to zero.
@@ -216,284 +240,172 @@ __device__ __forceinline__ void drain_vmem()
 // pair's counter, on which the last GROUP to arrive merges the group partials.  Two short merges
 // by different workgroups instead of one long one.
 constexpr int kGroup = 8;
-// One merge by one workgroup costs about 0.7 us per kMergeBatch partials; the two-level way costs about
-// 4 us of fixed round trips plus the short final merge.  It pays from about 30 pieces on.
 constexpr int kDeepFrom = 32;
 enum { kRoleNone = 0, kRoleFinal = 1, kRoleGroup = 2 };
 
-template <int D, int G, bool DEEP, bool TRACE = false>
-__device__ __forceinline__ void merge_round_one(const DecodeArgs &a, PendingParts<D, G> &pend, int n_pend)
+constexpr int kMergeBatch = 8;   // partials of a cut pair fetched at once by the merging workgroup
+
+// A partial goes to the workspace: four consecutive coordinates (the idx-th four of [G][D]) and, with the first of a
+// column, its maximum and weight sum.  Nothing waits for the stores here.
+template <int D, int G>
+__device__ __forceinline__ void publish_part(const DecodeArgs &a, int part, int idx, float4 o, float m, float l)
 {
-    // A thread owns four consecutive coordinates of one column.  The first batch of loads of ALL
-    // pending merges is issued before any is used: one memory round trip, not one per pair.
-    constexpr int D4 = D / 4;
-    constexpr int kPend = pend_slots(D, G);
+    publish_f32x4(a.part_o + static_cast<size_t>(part) * (G * D), idx * 16, o);
+    if (idx % (D / 4) == 0) publish_f32x2(a.part_ml + static_cast<size_t>(part) * (G * 2), idx / (D / 4) * 8, m, l);
+}
+
+// Partials first, first + step, ... (count of them) into one: a thread owns four consecutive coordinates of one column.
+// What bounds it: one memory round trip per batch, and the instructions of a wave that is alone on its SIMD (4 cycles
+// each).  So everything that is the same for the wave stays in scalar registers, and a partial that is not there costs
+// one branch.  (With 8-byte loads, an address per thread and load, and batches of 8 worked through whatever the number
+// of partials, the last merge of a launch took 2.2 us on the headline workload; 1.6 us like this.)
+template <int D, int G, bool DEEP, bool TRACE = false>
+__device__ __forceinline__ void merge_parts(const DecodeArgs &a, const Piece &pc, int first, int step, int count, bool to_group)
+{
+    constexpr int D4 = D / 4, OB = G * D * 4, MB = G * 2 * 4;      // bytes of a partial's outputs and of its statistics
     for (int idx = threadIdx.x; idx < G * D4; idx += kThreads) {
-        const int g = idx / D4, d = (idx % D4) * 4;
-        float2 ml[kPend][kMergeBatch], o01[kPend][kMergeBatch], o23[kPend][kMergeBatch];
-#pragma unroll
-        for (int p = 0; p < kPend; ++p) {
-            if (p >= n_pend || pend.role[p] == kRoleNone || pend.src_count[p] < 2) continue;
-            const int nc = pend.src_count[p], p0 = pend.src_first[p], st = pend.src_stride[p];
+        const int g = idx / D4;
+        float m_star = -INFINITY, l_star = 0.f, acc[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+        for (int c0 = 0; c0 < count; c0 += kMergeBatch) {
+            const size_t part = static_cast<size_t>(first) + static_cast<size_t>(step) * c0;
+            const uint32_t span = static_cast<uint32_t>(step * (min(kMergeBatch, count - c0) - 1) + 1);
+            const __amdgpu_buffer_rsrc_t ro = parts_rsrc(a.part_o + part * (G * D), span * OB);
+            const __amdgpu_buffer_rsrc_t rm = parts_rsrc(a.part_ml + part * (G * 2), span * MB);
+            f4_t o[kMergeBatch];
+            f2_t ml[kMergeBatch];
 #pragma unroll
             for (int j = 0; j < kMergeBatch; ++j) {
-                ml[p][j] = make_float2(-INFINITY, 0.f);        // past the end: weight 0 below, and no load
-                o01[p][j] = o23[p][j] = make_float2(0.f, 0.f);
-                if (j < nc) {
-                    const size_t pg = static_cast<size_t>(p0 + st * j) * G + g;
-                    ml[p][j] = fetch_f32x2(a.part_ml + pg * 2);
-                    o01[p][j] = fetch_f32x2(a.part_o + pg * D + d);
-                    o23[p][j] = fetch_f32x2(a.part_o + pg * D + d + 2);
-                }
+                if (c0 + j >= count) break;
+                ml[j] = __builtin_bit_cast(f2_t, __builtin_amdgcn_raw_buffer_load_b64(rm, g * 8, step * j * MB, kAgent));
+                o[j] = __builtin_bit_cast(f4_t, __builtin_amdgcn_raw_buffer_load_b128(ro, idx * 16, step * j * OB, kAgent));
             }
-        }
-        if constexpr (TRACE) {      // measurement only: when the first batch of partials has landed
-            drain_vmem();
-            trace_stamp(a, kTraceMergeLoaded, threadIdx.x == 0);
-        }
-#pragma unroll
-        for (int p = 0; p < kPend; ++p) {
-            if (p >= n_pend || pend.role[p] == kRoleNone || pend.src_count[p] < 2) continue;
-            const int nc = pend.src_count[p], p0 = pend.src_first[p], st = pend.src_stride[p], pair = pend.pair[p];
-            float m_star = -INFINITY, l_star = 0.f, acc[4] = {0.f, 0.f, 0.f, 0.f};
-            for (int c0 = 0; c0 < nc; c0 += kMergeBatch) {
-                if (c0 > 0) {   // more than kMergeBatch partials: fetch the next batch
-#pragma unroll
-                    for (int j = 0; j < kMergeBatch; ++j) {
-                        ml[p][j] = make_float2(-INFINITY, 0.f);
-                        o01[p][j] = o23[p][j] = make_float2(0.f, 0.f);
-                        if (c0 + j < nc) {
-                            const size_t pg = static_cast<size_t>(p0 + st * (c0 + j)) * G + g;
-                            ml[p][j] = fetch_f32x2(a.part_ml + pg * 2);
-                            o01[p][j] = fetch_f32x2(a.part_o + pg * D + d);
-                            o23[p][j] = fetch_f32x2(a.part_o + pg * D + d + 2);
-                        }
-                    }
+            if constexpr (TRACE)
+                if (c0 == 0) {
+                    drain_vmem();
+                    trace_stamp(a, kTraceMergeLoaded, threadIdx.x == 0);
                 }
-                float m_new = m_star;
+            float m_new = m_star;
 #pragma unroll
-                for (int j = 0; j < kMergeBatch; ++j)
-                    if (c0 + j < nc) m_new = fmaxf(m_new, ml[p][j].x);
-                const float keep = m_star == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_star - m_new);
-                l_star *= keep;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) acc[e] *= keep;
-#pragma unroll
-                for (int j = 0; j < kMergeBatch; ++j) {
-                    const bool live = c0 + j < nc && ml[p][j].x != -INFINITY;
-                    const float f = live ? __builtin_amdgcn_exp2f(ml[p][j].x - m_new) : 0.f;
-                    l_star = fmaf(ml[p][j].y, f, l_star);
-                    acc[0] = fmaf(o01[p][j].x, f, acc[0]);
-                    acc[1] = fmaf(o01[p][j].y, f, acc[1]);
-                    acc[2] = fmaf(o23[p][j].x, f, acc[2]);
-                    acc[3] = fmaf(o23[p][j].y, f, acc[3]);
-                }
-                m_star = m_new;
+            for (int j = 0; j < kMergeBatch; ++j) {
+                if (c0 + j >= count) break;
+                m_new = fmaxf(m_new, ml[j][0]);
             }
-            if (DEEP && pend.role[p] == kRoleGroup) {  // the group's partial, in the slot of its first piece
-                const size_t pg = static_cast<size_t>(p0) * G + g;
-                publish_f32x4(a.part_o + pg * D + d, make_float4(acc[0], acc[1], acc[2], acc[3]));
-                if (d == 0) {
-                    publish_f32(a.part_ml + pg * 2 + 0, m_star);
-                    publish_f32(a.part_ml + pg * 2 + 1, l_star);
-                }
-                continue;
+            const float keep = m_star == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_star - m_new);
+            l_star *= keep;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[e] *= keep;
+#pragma unroll
+            for (int j = 0; j < kMergeBatch; ++j) {
+                if (c0 + j >= count) break;
+                const float f = ml[j][0] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(ml[j][0] - m_new);
+                l_star = fmaf(ml[j][1], f, l_star);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) acc[e] = fmaf(o[j][e], f, acc[e]);
             }
-            const int b = pair / a.Hkv, h = pair % a.Hkv;
-            const size_t orow = out_row(a, b, h, g);
-            const float inv = l_star > 0.f ? pend.v_mul[p] / l_star : 0.f;
-            store_out4(a.out, a.out_dtype, orow * D + d, make_float4(acc[0] * inv, acc[1] * inv, acc[2] * inv, acc[3] * inv));
-            if (d == 0 && a.lse)
-                a.lse[orow] = l_star > 0.f ? (m_star + __builtin_amdgcn_logf(l_star)) * kLn2 : -INFINITY;
+            m_star = m_new;
         }
+        const float4 sum = make_float4(acc[0], acc[1], acc[2], acc[3]);
+        if (DEEP && to_group)      // the group's partial, in the slot of its first piece
+            publish_part<D, G>(a, first, idx, sum, m_star, l_star);
+        else
+            write_out4<D>(a, pc.qg, g, idx % D4 * 4, sum, m_star, l_star, pc.v_mul);
     }
 }
 
-template <int D, int G, bool DEEP>
-__device__ __forceinline__ void merge_round_many(const DecodeArgs &a, PendingParts<D, G> &pend, int n_pend)
-{
-    // A thread owns four consecutive coordinates of one column (of two columns, when there are 16 of them).
-    // The first batch of loads of ALL pending merges and of all the thread's coordinates is issued before
-    // any is used: one memory round trip, not one per pair or per coordinate.
-    constexpr int D4 = D / 4, NC4 = G * D4;
-    constexpr int kPend = pend_slots(D, G);
-    constexpr int IT = (NC4 + kThreads - 1) / kThreads;            // coordinates per thread
-    constexpr int MB = IT > 1 ? kMergeBatch / 2 : kMergeBatch;     // 6 IT kPend MB registers hold the batches
-    float2 ml[IT][kPend][MB], o01[IT][kPend][MB], o23[IT][kPend][MB];
-    auto fetch_batch = [&](int it, int p, int c0) __attribute__((always_inline)) {
-        const int idx = threadIdx.x + it * kThreads, g = idx / D4, d = (idx % D4) * 4;
-        const int nc = pend.src_count[p], p0 = pend.src_first[p], st = pend.src_stride[p];
-#pragma unroll
-        for (int j = 0; j < MB; ++j) {
-            ml[it][p][j] = make_float2(-INFINITY, 0.f);        // past the end: weight 0 below, and no load
-            o01[it][p][j] = o23[it][p][j] = make_float2(0.f, 0.f);
-            if (c0 + j < nc) {
-                const size_t pg = static_cast<size_t>(p0 + st * (c0 + j)) * G + g;
-                ml[it][p][j] = fetch_f32x2(a.part_ml + pg * 2);
-                o01[it][p][j] = fetch_f32x2(a.part_o + pg * D + d);
-                o23[it][p][j] = fetch_f32x2(a.part_o + pg * D + d + 2);
-            }
-        }
-    };
-#pragma unroll
-    for (int it = 0; it < IT; ++it) {
-        if (threadIdx.x + it * kThreads >= NC4) continue;
-#pragma unroll
-        for (int p = 0; p < kPend; ++p) {
-            if (p >= n_pend || pend.role[p] == kRoleNone || pend.src_count[p] < 2) continue;
-            fetch_batch(it, p, 0);
-        }
-    }
-#pragma unroll
-    for (int it = 0; it < IT; ++it) {
-        const int idx = threadIdx.x + it * kThreads, g = idx / D4, d = (idx % D4) * 4;
-        if (idx >= NC4) continue;
-#pragma unroll
-        for (int p = 0; p < kPend; ++p) {
-            if (p >= n_pend || pend.role[p] == kRoleNone || pend.src_count[p] < 2) continue;
-            const int nc = pend.src_count[p], p0 = pend.src_first[p], pair = pend.pair[p];
-            float m_star = -INFINITY, l_star = 0.f, acc[4] = {0.f, 0.f, 0.f, 0.f};
-            for (int c0 = 0; c0 < nc; c0 += MB) {
-                if (c0 > 0) fetch_batch(it, p, c0);     // more than MB partials: the next batch
-                float m_new = m_star;
-#pragma unroll
-                for (int j = 0; j < MB; ++j)
-                    if (c0 + j < nc) m_new = fmaxf(m_new, ml[it][p][j].x);
-                const float keep = m_star == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_star - m_new);
-                l_star *= keep;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) acc[e] *= keep;
-#pragma unroll
-                for (int j = 0; j < MB; ++j) {
-                    const bool live = c0 + j < nc && ml[it][p][j].x != -INFINITY;
-                    const float f = live ? __builtin_amdgcn_exp2f(ml[it][p][j].x - m_new) : 0.f;
-                    l_star = fmaf(ml[it][p][j].y, f, l_star);
-                    acc[0] = fmaf(o01[it][p][j].x, f, acc[0]);
-                    acc[1] = fmaf(o01[it][p][j].y, f, acc[1]);
-                    acc[2] = fmaf(o23[it][p][j].x, f, acc[2]);
-                    acc[3] = fmaf(o23[it][p][j].y, f, acc[3]);
-                }
-                m_star = m_new;
-            }
-            if (DEEP && pend.role[p] == kRoleGroup) {  // the group's partial, in the slot of its first piece
-                const size_t pg = static_cast<size_t>(p0) * G + g;
-                publish_f32x4(a.part_o + pg * D + d, make_float4(acc[0], acc[1], acc[2], acc[3]));
-                if (d == 0) {
-                    publish_f32(a.part_ml + pg * 2 + 0, m_star);
-                    publish_f32(a.part_ml + pg * 2 + 1, l_star);
-                }
-                continue;
-            }
-            const int b = pair / a.Hkv, h = pair % a.Hkv;
-            const size_t orow = out_row(a, b, h, g);
-            const float inv = l_star > 0.f ? pend.v_mul[p] / l_star : 0.f;
-            store_out4(a.out, a.out_dtype, orow * D + d, make_float4(acc[0] * inv, acc[1] * inv, acc[2] * inv, acc[3] * inv));
-            if (d == 0 && a.lse)
-                a.lse[orow] = l_star > 0.f ? (m_star + __builtin_amdgcn_logf(l_star)) * kLn2 : -INFINITY;
-        }
-    }
-}
-
-// Up to 256 float4 coordinates (G * D <= 1024) a thread owns at most one: the plain loop, whose code is the
-// shorter (0.2 us per launch on the headline workload: this code runs cold, on the tail).  With more, all of
-// a thread's coordinates are fetched together.
+// DEEP: the plan has a pair in kDeepFrom pieces or more.  Without it the group code is not even compiled in.
 template <int D, int G, bool DEEP, bool TRACE = false>
-__device__ __forceinline__ void merge_round(const DecodeArgs &a, PendingParts<D, G> &pend, int n_pend)
+__device__ __forceinline__ void flush_pending(const DecodeArgs &a, const Piece (&pend)[kPend], int &n_pend, int32_t *roles /* LDS [kPend] */)
 {
-    if constexpr (G * D / 4 <= kThreads)
-        merge_round_one<D, G, DEEP, TRACE>(a, pend, n_pend);
-    else
-        merge_round_many<D, G, DEEP>(a, pend, n_pend);
-}
-
-// DEEP: the plan has a pair in kDeepFrom pieces or more.  Without it the group code is not even compiled
-// in: on the headline workload its mere presence cost 0.8 us per launch (longer cold code on the
-// critical tail, more registers in the main loop).
-template <int D, int G, bool DEEP, bool TRACE = false>
-__device__ __forceinline__ void flush_pending(const DecodeArgs &a, PendingParts<D, G> &pend, int &n_pend)
-{
-    __syncthreads();
     if constexpr (TRACE) trace_stamp(a, kTraceFlushBegin, threadIdx.x == 0);
-    for (int p = 0; p < n_pend; ++p) {
-        const size_t base = static_cast<size_t>(pend.part[p]) * G;
-        for (int idx = threadIdx.x; idx < G * D / 4; idx += kThreads)
-            publish_f32x4(a.part_o + base * D + idx * 4, *reinterpret_cast<const float4 *>(&pend.o[p][idx * 4]));
-        if (threadIdx.x < G * 2) publish_f32(a.part_ml + base * 2 + threadIdx.x, pend.ml[p][threadIdx.x]);
-    }
     drain_vmem();                                      // this thread's stores have reached the shared level ...
     __syncthreads();                                   // ... and every other thread's, before the workgroup counts itself in
     if constexpr (TRACE) trace_stamp(a, kTraceFlushPublished, threadIdx.x == 0);
     // Round 0: every pending piece counts in (a piece of a deeply cut pair on its group's counter) and
     // the last arrivals merge.  Round 1, only if this workgroup merged a group: that group counts in on
-    // the pair's counter.  One copy of the merge code serves both rounds: the hand-over runs once per
-    // workgroup, on cold instruction-cache lines, so its length is paid for in full.
+    // the pair's counter.  Whoever finds itself last sets the counter back for the next call on this workspace.
+    int role[kPend] = {kRoleNone, kRoleNone};
     for (int round = 0; round < (DEEP ? 2 : 1); ++round) {
-        if (threadIdx.x < n_pend) {
-            const int p = threadIdx.x;
-            const int nc = pend.n_chunks[p], p0 = pend.first_part[p], chunk = pend.part[p] - p0;
-            const bool ok = p0 >= 0 && chunk >= 0 && chunk < nc && p0 + nc <= a.n_parts;
-            // two levels only if every group of the pair has a counter
-            const bool deep = DEEP && nc >= kDeepFrom && static_cast<int64_t>(p0) + (nc - 1) / kGroup < a.n_group_counters;
-            int role = kRoleNone;
-            if (round == 0 && ok && !deep) {
-                if (__hip_atomic_fetch_add(a.arrivals + pend.pair[p], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == nc - 1)
-                    role = kRoleFinal;
-                pend.src_first[p] = p0;
-                pend.src_stride[p] = 1;
-                pend.src_count[p] = nc;
-            } else if (round == 0 && ok) {
-                const int k = chunk / kGroup, gs = min(kGroup, nc - k * kGroup);
-                if (__hip_atomic_fetch_add(a.group_arrivals + p0 + k, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == gs - 1)
-                    role = kRoleGroup;
-                pend.src_first[p] = p0 + k * kGroup;
-                pend.src_stride[p] = 1;
-                pend.src_count[p] = gs;
-            } else if (round == 1 && pend.role[p] == kRoleGroup) {
-                const int ng = (nc + kGroup - 1) / kGroup;
-                __hip_atomic_store(a.group_arrivals + p0 + chunk / kGroup, 0, __ATOMIC_RELAXED,
-                                   __HIP_MEMORY_SCOPE_AGENT);      // the group's counter: ready for the next call
-                if (__hip_atomic_fetch_add(a.arrivals + pend.pair[p], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == ng - 1)
-                    role = kRoleFinal;
-                pend.src_first[p] = p0;
-                pend.src_stride[p] = kGroup;
-                pend.src_count[p] = ng;
+        if (threadIdx.x < static_cast<unsigned>(n_pend)) {
+            const Piece &pc0 = pend[0], &pc1 = pend[1];
+            const bool second = threadIdx.x != 0;
+            const int pair = second ? pc1.pair : pc0.pair, nc = second ? pc1.n_chunks : pc0.n_chunks;
+            int32_t *counter = a.arrivals + pair;
+            int last = nc - 1, role_if_last = kRoleFinal;
+            bool counts = round == 0;
+            if constexpr (DEEP) {
+                const int chunk = second ? pc1.chunk : pc0.chunk, first = (second ? pc1.part : pc0.part) - chunk;
+                // two levels only if every group of the pair has a counter
+                const bool deep = nc >= kDeepFrom && static_cast<int64_t>(first) + (nc - 1) / kGroup < a.n_group_counters;
+                if (round == 0 && deep) {
+                    counter = a.group_arrivals + first + chunk / kGroup;
+                    last = min(kGroup, nc - chunk / kGroup * kGroup) - 1;
+                    role_if_last = kRoleGroup;
+                } else if (round == 1) {
+                    counts = (second ? role[1] : role[0]) == kRoleGroup;
+                    last = (nc + kGroup - 1) / kGroup - 1;
+                }
             }
-            pend.role[p] = role;
+            int mine = kRoleNone;
+            if (counts && __hip_atomic_fetch_add(counter, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == last) {
+                mine = role_if_last;
+                __hip_atomic_store(counter, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+            roles[threadIdx.x] = mine;
         }
         __syncthreads();
         if constexpr (TRACE) trace_stamp(a, kTraceFlushCounted, threadIdx.x == 0);
-        merge_round<D, G, DEEP, TRACE>(a, pend, n_pend);
-        if constexpr (TRACE) trace_stamp(a, kTraceFlushMerged, threadIdx.x == 0);
         bool any_group = false;
-        if (DEEP)
-            for (int p = 0; p < n_pend; ++p) any_group |= pend.role[p] == kRoleGroup;
-        if (threadIdx.x < n_pend && pend.role[threadIdx.x] == kRoleFinal)   // ready for the next call on this workspace
-            __hip_atomic_store(a.arrivals + pend.pair[threadIdx.x], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (!any_group) break;                             // uniform: the roles are in LDS
+        role[0] = __builtin_amdgcn_readfirstlane(roles[0]);
+        role[1] = n_pend > 1 ? __builtin_amdgcn_readfirstlane(roles[1]) : kRoleNone;
+#pragma unroll 1
+        for (int p = 0; p < n_pend; ++p) {                 // one copy of the merge's code
+            const int what = p == 0 ? role[0] : role[1];
+            if (what == kRoleNone) continue;
+            const Piece pc = p == 0 ? pend[0] : pend[1];
+            int first = pc.part - pc.chunk, step = 1, count = pc.n_chunks;
+            if (DEEP && what == kRoleGroup) {
+                any_group = true;
+                const int k = pc.chunk / kGroup;
+                first += k * kGroup;
+                count = min(kGroup, pc.n_chunks - k * kGroup);
+                if (count == 1) continue;                  // its partial is the group's already
+            } else if (DEEP && round == 1) {
+                step = kGroup;
+                count = (pc.n_chunks + kGroup - 1) / kGroup;
+            }
+            merge_parts<D, G, DEEP, TRACE>(a, pc, first, step, count, what == kRoleGroup);
+        }
+        if constexpr (TRACE) trace_stamp(a, kTraceFlushMerged, threadIdx.x == 0);
+        if (!DEEP || !any_group) break;                    // the same for all threads
         drain_vmem();                                      // the group partials are acknowledged ...
         __syncthreads();                                   // ... all of them, before the groups count in
     }
     n_pend = 0;
     drain_vmem();     // the compiler stops tracking the loads above: no guard waits on their registers later on
-    __syncthreads();
     if constexpr (TRACE) trace_stamp(a, kTraceFlushEnd, threadIdx.x == 0);
 }
 
-// End of one item, called by all threads of the workgroup after every wave has put its
-// unnormalised output, running maximum (log2 units) and weight sum into st_o [kWaves][G][D]
-// and st_ml [kWaves][G][2] in LDS.  Folds the waves:
+// The waves' results of an item in LDS: unnormalised outputs [kWaves][G][kStRow<D>], and per column the running
+// maximum (log2 units) and the weight sum [kWaves][G][2].  A row is 16 bytes longer than its D floats: the lanes of a
+// wave write the same coordinates of all its columns at once, which would all fall on the same banks.
+template <int D>
+constexpr int kStRow = D + 4;
+
+// End of one item, called by all threads of the workgroup after every wave has put its result into st_o and st_ml.
+// Folds the waves:
 //   m* = max_w m_w,  l* = sum_w l_w 2^(m_w - m*),  o* = sum_w o_w 2^(m_w - m*).
-// An item that is a whole pair writes out = o*/l* and lse.  An item of a cut pair leaves its
-// partial (m*, l*, o*) in `pend`.  Ends with a barrier, so st_o/st_ml may be reused at once.
+// An item that is a whole pair writes out = o*/l* and lse.  An item of a cut pair stores its partial (m*, l*, o*) in
+// the workspace, without waiting for it, and joins `pend`.  One barrier, before the fold: st_o and st_ml may be
+// written again after the next barrier only.
 template <int D, int G, bool DEEP, bool TRACE = false>
-__device__ __forceinline__ void item_epilogue(const DecodeArgs &a, const fairkv_item &it, const float *st_o,
-                                              const float *st_ml, PendingParts<D, G> &pend, int &n_pend, float v_mul)
+__device__ __forceinline__ void item_epilogue(const DecodeArgs &a, const Piece &pc, const float *st_o, const float *st_ml,
+                                              Piece (&pend)[kPend], int &n_pend, int32_t *roles)
 {
-    const int b = it.b, h = it.h;
-    const bool whole_pair = it.n_chunks == 1;
+    const bool whole_pair = pc.n_chunks == 1;
     constexpr int D4 = D / 4;
     __syncthreads();
-    // a thread owns four consecutive coordinates of one query head; all its LDS reads are issued together
+    // a thread owns four consecutive coordinates of one column; all its LDS reads are issued together
     for (int idx = threadIdx.x; idx < G * D4; idx += kThreads) {
         const int g = idx / D4, d = (idx % D4) * 4;
         float2 ml[kWaves];
@@ -501,7 +413,7 @@ __device__ __forceinline__ void item_epilogue(const DecodeArgs &a, const fairkv_
 #pragma unroll
         for (int w = 0; w < kWaves; ++w) {
             ml[w] = *reinterpret_cast<const float2 *>(st_ml + (w * G + g) * 2);
-            ow[w] = *reinterpret_cast<const float4 *>(st_o + (w * G + g) * D + d);
+            ow[w] = *reinterpret_cast<const float4 *>(st_o + (w * G + g) * kStRow<D> + d);
         }
         float m_star = -INFINITY;
 #pragma unroll
@@ -518,34 +430,18 @@ __device__ __forceinline__ void item_epilogue(const DecodeArgs &a, const fairkv_
             l_star += ml[w].y * f;
         }
         if (whole_pair) {
-            const size_t orow = out_row(a, b, h, g);
-            const float inv = l_star > 0.f ? v_mul / l_star : 0.f;
-            store_out4(a.out, a.out_dtype, orow * D + d, make_float4(acc.x * inv, acc.y * inv, acc.z * inv, acc.w * inv));
-            if (d == 0 && a.lse)
-                a.lse[orow] = l_star > 0.f ? (m_star + __builtin_amdgcn_logf(l_star)) * kLn2 : -INFINITY;
+            write_out4<D>(a, pc.qg, g, d, acc, m_star, l_star, pc.v_mul);
         } else {
-            *reinterpret_cast<float4 *>(&pend.o[n_pend][idx * 4]) = acc;
-            if (d == 0) {
-                pend.ml[n_pend][g * 2 + 0] = m_star;
-                pend.ml[n_pend][g * 2 + 1] = l_star;
-            }
+            publish_part<D, G>(a, pc.part, idx, acc, m_star, l_star);
         }
     }
     if (!whole_pair) {
-        if (threadIdx.x == 0) {
-            pend.pair[n_pend] = b * a.Hkv + h;
-            pend.part[n_pend] = it.part;
-            pend.first_part[n_pend] = it.part - it.chunk;   // the partials of a pair are consecutive
-            pend.n_chunks[n_pend] = it.n_chunks;
-            pend.v_mul[n_pend] = v_mul;
-        }
-        ++n_pend;
-        if (n_pend == pend_slots(D, G)) {
-            flush_pending<D, G, DEEP, TRACE>(a, pend, n_pend);
-            return;
-        }
+        if (n_pend == 0)
+            pend[0] = pc;
+        else
+            pend[1] = pc;
+        if (++n_pend == kPend) flush_pending<D, G, DEEP, TRACE>(a, pend, n_pend, roles);
     }
-    __syncthreads();
 }
 
 }  // namespace fairkv

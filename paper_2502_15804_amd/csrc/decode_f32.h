@@ -38,16 +38,20 @@ __global__ __launch_bounds__(kThreads, 1) void fairkv_decode_f32_kernel(DecodeAr
     constexpr int NU = D / 64;      // 16-byte pieces of a V row per lane
 
     __shared__ __attribute__((aligned(16))) ItemSlot table[kTable];
-    __shared__ __attribute__((aligned(16))) float st_o[kWaves * G * D];
-    __shared__ __attribute__((aligned(16))) float st_ml[kWaves * G * 2];
-    __shared__ PendingParts<D, G> pend;
-    int n_pend = 0;
+    __shared__ __attribute__((aligned(16))) float st_o[2][kWaves * G * kStRow<D>];      // two sets, used in turn
+    __shared__ __attribute__((aligned(16))) float st_ml[2][kWaves * G * 2];
+    __shared__ int32_t roles[kPend];
+    Piece pend[kPend] = {};
+    int n_pend = 0, set = 0;
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int l16 = lane & 15, lq = lane >> 4;
 
-    const int i_begin = a.slot_ptr[blockIdx.x], i_end = a.slot_ptr[blockIdx.x + 1];
+    const SlotStart slot = slot_start(a);            // one round trip for all that the first requests need
+    const int i_begin = slot.i_begin, i_end = slot.i_end;
+    asm volatile("" ::"s"(slot.i_begin), "s"(slot.i_end), "s"(slot.row), "s"(slot.np), "s"(a.q), "s"(a.k), "s"(a.v), "s"(a.items),
+                 "s"(a.g_shift));
     if (i_end <= i_begin) return;   // an idle slot
 
     // tiles of an n-token item that fall to this wave: wave, wave + kWaves, ...
@@ -57,7 +61,7 @@ __global__ __launch_bounds__(kThreads, 1) void fairkv_decode_f32_kernel(DecodeAr
     };
 
     // The fetch cursor: the wave's next tile, f_t of f_tiles of item f_item (n tokens from row on).
-    int f_item = 0, f_t = 0, f_tiles = 0, f_n = 0, f_b = 0, f_h = 0;
+    int f_item = 0, f_t = 0, f_tiles = 0, f_n = 0, f_qg = 0;
     int64_t f_row = 0;
     f32x4_t kr[NC], vr[4][NU], qr[NC];
     // One tile: 16 rows from `row` on, of which those up to `last` are the item's.  Rows past it re-read that row;
@@ -79,21 +83,18 @@ __global__ __launch_bounds__(kThreads, 1) void fairkv_decode_f32_kernel(DecodeAr
     };
     auto f_tok0 = [&]() __attribute__((always_inline)) { return (wave + f_t * kWaves) * kTok; };
     auto load_q = [&]() __attribute__((always_inline)) {      // columns past the group repeat its last head; they are never stored
-        const char *base = static_cast<const char *>(a.q) + (static_cast<size_t>(f_b) * a.Hq + f_h * G) * ROWB;
+        const char *base = static_cast<const char *>(a.q) + group_row(a, f_qg) * ROWB;
         const uint32_t off = min(l16, G - 1) * ROWB + lq * 16;
 #pragma unroll
         for (int c = 0; c < NC; ++c) qr[c] = *reinterpret_cast<const f32x4_t *>(base + off + c * 64);
     };
 
     // Early start: the first item's rows are requested from what the kernel arguments say of it, before the item list is here.
-    const uint32_t np0 = a.first_np[blockIdx.x];
-    const int n0 = static_cast<int>(np0 & 0x1ffu);
+    const int n0 = static_cast<int>(slot.np & 0x1ffu);
     const bool seeded = n0 > 0;
     if (seeded) {
-        const int pair0 = static_cast<int>(np0 >> 9);
-        f_b = __builtin_amdgcn_readfirstlane(pair0 / a.Hkv);
-        f_h = pair0 - f_b * a.Hkv;
-        f_row = a.first_row[blockIdx.x];
+        f_qg = static_cast<int>(slot.np >> 9);
+        f_row = slot.row;
         f_n = n0;
         f_tiles = tiles_of(n0);
         if (f_tiles > 0) {
@@ -107,15 +108,10 @@ __global__ __launch_bounds__(kThreads, 1) void fairkv_decode_f32_kernel(DecodeAr
         const int nb = min(kTable, i_end - batch);
         const bool early = seeded && batch == i_begin;
         if (batch != i_begin) __syncthreads();                  // nobody still reads the previous table
-        if (threadIdx.x < nb) {
-            const fairkv_item it = a.items[batch + threadIdx.x];
-            const bool ok = it.b >= 0 && it.b < a.B && it.h >= 0 && it.h < a.Hkv && it.row >= 0 && it.part >= 0 &&
-                            it.part < a.n_parts && it.n_chunks >= 1 && it.chunk >= 0 && it.chunk <= it.part &&
-                            it.row + max(it.tok_count, 0) <= a.n_rows;
-            int n = ok ? max(it.tok_count, 0) : 0;              // a foreign item reads nothing
-            if (early && threadIdx.x == 0)                      // its first tiles are on their way, as many as n0 said
-                n = n0 < kEarlyTok ? n0 : max(n, kEarlyTok);
-            table[threadIdx.x] = ItemSlot{it.row, n, ok ? 1 : 0, ok ? it.b : 0, ok ? it.h : 0, it.chunk, it.n_chunks, it.part, -1, {0, 0}};
+        if (static_cast<int>(threadIdx.x) < nb) {
+            ItemSlot e = item_slot(a, a.items[batch + threadIdx.x]);
+            if (early && threadIdx.x == 0) e.n = n0 < kEarlyTok ? n0 : max(e.n, kEarlyTok);   // its first tiles are on their way, as many as n0 said
+            table[threadIdx.x] = e;
         }
         __syncthreads();
 
@@ -126,8 +122,7 @@ __global__ __launch_bounds__(kThreads, 1) void fairkv_decode_f32_kernel(DecodeAr
             if (item < nb) {
                 f_row = uniform64(table[item].row);
                 f_n = __builtin_amdgcn_readfirstlane(table[item].n);
-                f_b = __builtin_amdgcn_readfirstlane(table[item].b);
-                f_h = __builtin_amdgcn_readfirstlane(table[item].h);
+                f_qg = __builtin_amdgcn_readfirstlane(table[item].qg);
                 f_tiles = tiles_of(f_n);
             }
         };
@@ -150,14 +145,6 @@ __global__ __launch_bounds__(kThreads, 1) void fairkv_decode_f32_kernel(DecodeAr
         }
 
         for (int ci = 0; ci < nb; ++ci) {
-            fairkv_item it;
-            it.row = 0;
-            it.tok_count = 0;
-            it.b = __builtin_amdgcn_readfirstlane(table[ci].b);
-            it.h = __builtin_amdgcn_readfirstlane(table[ci].h);
-            it.chunk = __builtin_amdgcn_readfirstlane(table[ci].chunk);
-            it.n_chunks = __builtin_amdgcn_readfirstlane(table[ci].n_chunks);
-            it.part = __builtin_amdgcn_readfirstlane(table[ci].part);
             const int n = __builtin_amdgcn_readfirstlane(table[ci].n);
             const int my_tiles = tiles_of(n);
 
@@ -213,9 +200,7 @@ __global__ __launch_bounds__(kThreads, 1) void fairkv_decode_f32_kernel(DecodeAr
                 //      or below 1, so the sums reach no further than the largest V; a tile is long enough to hide it)
                 float mx = fmaxf(fmaxf(sv[0], sv[1]), fmaxf(sv[2], sv[3]));
                 if (__builtin_amdgcn_ballot_w64(mx > m_run) != 0) {
-                    mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
-                    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-                    const float m_new = fmaxf(m_run, mx);
+                    const float m_new = fmaxf(m_run, quarters_max(mx));
                     const float alpha = m_new == m_run ? 1.f : __builtin_amdgcn_exp2f(m_run - m_new);   // 0 on the first tile
                     l_run *= alpha;
 #pragma unroll
@@ -246,25 +231,25 @@ __global__ __launch_bounds__(kThreads, 1) void fairkv_decode_f32_kernel(DecodeAr
             }
 
             // ---- fold the four token quarters of l, stage this wave's result, finish the item ------
-            l_run += __shfl_xor(l_run, 16, 64);
-            l_run += __shfl_xor(l_run, 32, 64);
+            l_run = quarters_sum(l_run);
             if (l16 < G) {
 #pragma unroll
                 for (int u = 0; u < NU; ++u)
 #pragma unroll
                     for (int r = 0; r < 4; ++r)      // rows 4 lq + r of the four blocks j: four consecutive coordinates
-                        *reinterpret_cast<float4 *>(st_o + (wave * G + l16) * D + 64 * u + 16 * lq + 4 * r) =
+                        *reinterpret_cast<float4 *>(st_o[set] + (wave * G + l16) * kStRow<D> + 64 * u + 16 * lq + 4 * r) =
                             make_float4(o[u][0][r], o[u][1][r], o[u][2][r], o[u][3][r]);
                 if (lq == 0) {
-                    st_ml[(wave * G + l16) * 2 + 0] = m_run;
-                    st_ml[(wave * G + l16) * 2 + 1] = l_run;
+                    *reinterpret_cast<float2 *>(st_ml[set] + (wave * G + l16) * 2) = make_float2(m_run, l_run);
                 }
             }
-            if (__builtin_amdgcn_readfirstlane(table[ci].valid))
-                item_epilogue<D, G, DEEP>(a, it, st_o, st_ml, pend, n_pend, a.v_scale);
+            if (__builtin_amdgcn_readfirstlane(table[ci].valid)) {
+                item_epilogue<D, G, DEEP>(a, piece_of(table[ci], a.v_scale), st_o[set], st_ml[set], pend, n_pend, roles);
+                set ^= 1;
+            }
         }
     }
-    if (n_pend > 0) flush_pending<D, G, DEEP>(a, pend, n_pend);
+    if (n_pend > 0) flush_pending<D, G, DEEP>(a, pend, n_pend, roles);
 }
 
 }  // namespace fairkv

@@ -104,13 +104,6 @@ __device__ __forceinline__ void wait_all_but(int tiles, int qs)
     }
 }
 
-__device__ __forceinline__ int64_t uniform64(int64_t x)   // a wave-uniform value, moved to scalar registers
-{
-    const uint32_t lo = __builtin_amdgcn_readfirstlane(static_cast<int>(x));
-    const uint32_t hi = __builtin_amdgcn_readfirstlane(static_cast<int>(x >> 32));
-    return static_cast<int64_t>((static_cast<uint64_t>(hi) << 32) | lo);
-}
-
 // Eight E4M3 bytes widened to eight bf16 (exact; v_cvt_scalef32_pk_bf16_fp8 with scale 1 takes two bytes
 // at a time: the low or the high half of a dword).
 __device__ __forceinline__ bf16x8_t widen8(uint2 w)
@@ -127,10 +120,45 @@ struct ItemSlot {
     int64_t row;
     int32_t n;        // tokens to read; 0 for an item that does not belong to this problem
     int32_t valid;    // 0: such an item; it is skipped
-    int32_t b, h, chunk, n_chunks, part;
+    int32_t qg, pair, h, chunk, n_chunks, part;     // qg: the pair's query group (see group_row)
     int32_t owner;    // -1: the four waves share the item's tiles; else the wave that runs the whole item alone
-    int32_t pad[2];
+    int32_t pad;
 };
+// The entry of a fetched item; owner is filled in by the caller.  An item that does not belong to this problem gets
+// valid 0 and no tokens.
+__device__ __forceinline__ ItemSlot item_slot(const DecodeArgs &a, const fairkv_item &it)
+{
+    const bool ok = it.b >= 0 && it.b < a.B && it.h >= 0 && it.h < a.Hkv && it.row >= 0 && it.part >= 0 &&
+                    it.chunk >= 0 && it.chunk < it.n_chunks && it.chunk <= it.part &&
+                    it.part - it.chunk + it.n_chunks <= a.n_parts && it.row + max(it.tok_count, 0) <= a.n_rows;
+    return ItemSlot{it.row, ok ? max(it.tok_count, 0) : 0, ok ? 1 : 0, ok ? it.b * a.q_len * a.Hkv + it.h : 0,
+                    ok ? it.b * a.Hkv + it.h : 0, ok ? it.h : 0, it.chunk, it.n_chunks, it.part, -1, 0};
+}
+// What the end of an item needs of its entry, in scalar registers.
+__device__ __forceinline__ Piece piece_of(const ItemSlot &e, float v_mul)
+{
+    return Piece{__builtin_amdgcn_readfirstlane(e.pair), __builtin_amdgcn_readfirstlane(e.qg), __builtin_amdgcn_readfirstlane(e.part),
+                 __builtin_amdgcn_readfirstlane(e.chunk), __builtin_amdgcn_readfirstlane(e.n_chunks), v_mul};
+}
+// The maximum / sum over the four lanes of a wave that hold the same column (16 lanes apart).
+__device__ __forceinline__ float quarters_max(float x)
+{
+    const uint32_t u = __float_as_uint(x);
+    const auto a = __builtin_amdgcn_permlane16_swap(u, u, false, false);      // rows 0 0 2 2 and 1 1 3 3
+    const float y = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+    const uint32_t w = __float_as_uint(y);
+    const auto b = __builtin_amdgcn_permlane32_swap(w, w, false, false);
+    return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
+}
+__device__ __forceinline__ float quarters_sum(float x)
+{
+    const uint32_t u = __float_as_uint(x);
+    const auto a = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+    const float y = __uint_as_float(a[0]) + __uint_as_float(a[1]);
+    const uint32_t w = __float_as_uint(y);
+    const auto b = __builtin_amdgcn_permlane32_swap(w, w, false, false);
+    return __uint_as_float(b[0]) + __uint_as_float(b[1]);
+}
 // A whole pair of at most this many tokens is run by one wave alone: it streams all the pair's tiles through its
 // own ring and writes the output straight from its registers, with no fold across waves and no barrier.  Short
 // pairs shared by four waves leave most of the rings empty (a 32-token pair is two tiles: two waves have nothing
@@ -190,9 +218,14 @@ __global__ __launch_bounds__(kThreads, 1) void fairkv_decode_mfma_kernel(DecodeA
                                                                                     // the ring may belong to kStages different items
     __shared__ __attribute__((aligned(1024))) fairkv_item raw[kTable];        // items as fetched
     __shared__ __attribute__((aligned(16))) ItemSlot table[kTable];           // items as checked
-    __shared__ __attribute__((aligned(16))) float st_o[kWaves * G * D];
-    __shared__ __attribute__((aligned(16))) float st_ml[kWaves * G * 2];
-    __shared__ PendingParts<D, G> pend;
+    // Two sets, used in turn, so that one barrier per item is enough (one set and a second barrier where 16 columns
+    // would not leave room for two).
+    constexpr int kSets = G <= 8 ? 2 : 1;
+    __shared__ __attribute__((aligned(16))) float st_o[kSets][kWaves * G * kStRow<D>];
+    __shared__ __attribute__((aligned(16))) float st_ml[kSets][kWaves * G * 2];
+    __shared__ int32_t roles[kPend];
+    Piece pend[kPend] = {};
+    int set = 0;
     __shared__ float head_mul[2 * kScaleHeads];      // 8-bit caches: the per-head factors, out of the kernel arguments
     int n_pend = 0;
 
@@ -202,7 +235,13 @@ __global__ __launch_bounds__(kThreads, 1) void fairkv_decode_mfma_kernel(DecodeA
     const int lq = lane >> 4;       // which quarter of the contraction index this lane feeds
 
     if constexpr (TRACE) trace_stamp(a, kTraceStart, threadIdx.x == 0);
-    const int i_begin = a.slot_ptr[blockIdx.x], i_end = a.slot_ptr[blockIdx.x + 1];
+    // Everything the first requests need, in one round trip: left to itself the compiler asks for each kernel argument
+    // where it is first used, five dependent trips of 0.25 us before the first row of K is requested.
+    const SlotStart slot = slot_start(a);
+    const int i_begin = slot.i_begin, i_end = slot.i_end;
+    int g_shift = a.g_shift, Hq = a.Hq;
+    asm volatile("" : "+s"(g_shift), "+s"(Hq)
+                 : "s"(slot.i_begin), "s"(slot.i_end), "s"(slot.row), "s"(slot.np), "s"(a.q), "s"(a.k), "s"(a.v), "s"(a.items));
     if (i_end <= i_begin) return;   // an idle slot
     if constexpr (KV8) {
         // Fixed indices: scalar loads that come back with the other kernel arguments.  Indexed by the item's head
@@ -296,18 +335,15 @@ __global__ __launch_bounds__(kThreads, 1) void fairkv_decode_mfma_kernel(DecodeA
         }
     };
 
-    // Fetch of the G query rows of pair (b, h) into one of the wave's q buffers: exactly QL loads.
+    // Fetch of the G query rows of query group qg into one of the wave's q buffers: exactly QL loads.
     // Column c = (new token c >> g_shift, head c & mask) of q [B][q_len][Hq][D]: the heads of one new
     // token are contiguous, the new tokens are Hq rows apart.
-    auto fetch_q = [&](int b, int h, int buf) __attribute__((always_inline)) {
-        const char *src = static_cast<const char *>(a.q) +
-                          (static_cast<size_t>(b) * a.q_len * a.Hq + (h << a.g_shift)) * QROWB;
+    auto fetch_q = [&](int qg, int buf) __attribute__((always_inline)) {
+        const char *src = static_cast<const char *>(a.q) + (static_cast<size_t>(qg) << g_shift) * QROWB;
 #pragma unroll
         for (int i = 0; i < QL; ++i) {
             const int o = min(i * 1024 + lane * 16, QBYTES - 16);      // byte o of the [G][QROWB] image in LDS
-            const int c = o / QROWB;
-            const int row = (c >> a.g_shift) * a.Hq + (c & ((1 << a.g_shift) - 1));
-            load16_to_lds_keep(src, row * QROWB + o % QROWB, q_lds + buf * QBUF + i * 1024);
+            load16_to_lds_keep(src, col_row(g_shift, Hq, o / QROWB) * QROWB + o % QROWB, q_lds + buf * QBUF + i * 1024);
         }
     };
 
@@ -322,13 +358,13 @@ __global__ __launch_bounds__(kThreads, 1) void fairkv_decode_mfma_kernel(DecodeA
     // later items; `ahead` tiles are fetched and not yet consumed.  The query block of an item is
     // requested right before the item's first tile, into the q buffer of that tile's stage, so it
     // has landed when the tile has; bit s of q_mask says that the tile now in stage s came with one.
-    int f_item = 0, f_t = 0, f_stage = 0, c_stage = 0, ahead = 0, f_n = 0, f_tiles = 0, f_b = 0, f_h = 0, f_owner = -1;
+    int f_item = 0, f_t = 0, f_stage = 0, c_stage = 0, ahead = 0, f_n = 0, f_tiles = 0, f_qg = 0, f_owner = -1;
     int64_t f_row = 0;
     uint32_t q_mask = 0;
     auto fetch_next = [&]() __attribute__((always_inline)) {      // the cursor's tile, f_t < f_tiles
         if (f_t == 0) {
             // (scalar registers for the load's base address, wherever the compiler kept these wave-uniform values)
-            fetch_q(__builtin_amdgcn_readfirstlane(f_b), __builtin_amdgcn_readfirstlane(f_h), f_stage);
+            fetch_q(__builtin_amdgcn_readfirstlane(f_qg), f_stage);
             q_mask |= 1u << f_stage;
         }
         fetch(f_row, f_n, f_t, f_owner, f_stage);
@@ -337,18 +373,15 @@ __global__ __launch_bounds__(kThreads, 1) void fairkv_decode_mfma_kernel(DecodeA
         ++ahead;
     };
 
-    // Early start: the kernel arguments carry pair, first row and the first kEarlyTok tokens' worth
+    // Early start: the kernel arguments carry query group, first row and the first kEarlyTok tokens' worth
     // of the length of the slot's first item, so the item list, the first query block and the first
     // tiles are all requested at once, before anything has come back from memory.
     fetch_items(i_begin);
-    const uint32_t np0 = a.first_np[blockIdx.x];
-    const int n0 = static_cast<int>(np0 & 0x1ffu);
+    const int n0 = static_cast<int>(slot.np & 0x1ffu);
     const bool seeded = n0 > 0;
     if (seeded) {
-        const int pair0 = static_cast<int>(np0 >> 9);
-        f_b = __builtin_amdgcn_readfirstlane(pair0 / a.Hkv);      // the division runs on the vector ALU
-        f_h = pair0 - f_b * a.Hkv;
-        f_row = a.first_row[blockIdx.x];
+        f_qg = static_cast<int>(slot.np >> 9);
+        f_row = slot.row;
         f_n = n0;
         f_tiles = tiles_of(n0, -1);          // the early start always shares the first item among the waves
         while (ahead < kEarly && f_t < f_tiles) fetch_next();
@@ -364,18 +397,13 @@ __global__ __launch_bounds__(kThreads, 1) void fairkv_decode_mfma_kernel(DecodeA
         // the items have landed once only what was requested after them is outstanding
         wait_all_but<LOADS, QL>(ahead, __builtin_popcount(q_mask));
         __syncthreads();
-        if (threadIdx.x < nb) {
-            const fairkv_item it = raw[threadIdx.x];
-            const bool ok = it.b >= 0 && it.b < a.B && it.h >= 0 && it.h < a.Hkv && it.row >= 0 && it.part >= 0 &&
-                            it.part < a.n_parts && it.n_chunks >= 1 && it.chunk >= 0 && it.chunk <= it.part &&
-                            it.row + max(it.tok_count, 0) <= a.n_rows;
-            int n = ok ? max(it.tok_count, 0) : 0;      // a foreign item reads nothing
-            if (early && threadIdx.x == 0)              // its first tiles are on their way, as many as n0 said
-                n = n0 < kEarlyTok ? n0 : max(n, kEarlyTok);
+        if (static_cast<int>(threadIdx.x) < nb) {
+            ItemSlot e = item_slot(a, raw[threadIdx.x]);
+            const bool first = early && threadIdx.x == 0;
+            if (first) e.n = n0 < kEarlyTok ? n0 : max(e.n, kEarlyTok);      // its first tiles are on their way, as many as n0 said
             // short whole pairs go to single waves in turn (not the item the early start has already shared out)
-            const bool solo = SOLO && ok && it.n_chunks == 1 && n <= kSoloTokens && !(early && threadIdx.x == 0);
-            table[threadIdx.x] = ItemSlot{it.row, n, ok ? 1 : 0, ok ? it.b : 0, ok ? it.h : 0,
-                                          it.chunk, it.n_chunks, it.part, solo ? static_cast<int32_t>(threadIdx.x % kWaves) : -1, {0, 0}};
+            if (SOLO && e.valid && e.n_chunks == 1 && e.n <= kSoloTokens && !first) e.owner = threadIdx.x % kWaves;
+            table[threadIdx.x] = e;
         }
         __syncthreads();
         if constexpr (TRACE)
@@ -387,8 +415,7 @@ __global__ __launch_bounds__(kThreads, 1) void fairkv_decode_mfma_kernel(DecodeA
             if (item < nb) {
                 f_row = uniform64(table[item].row);
                 f_n = __builtin_amdgcn_readfirstlane(table[item].n);
-                f_b = __builtin_amdgcn_readfirstlane(table[item].b);
-                f_h = __builtin_amdgcn_readfirstlane(table[item].h);
+                f_qg = __builtin_amdgcn_readfirstlane(table[item].qg);
                 f_owner = SOLO ? __builtin_amdgcn_readfirstlane(table[item].owner) : -1;
             } else {
                 f_n = 0;
@@ -413,27 +440,20 @@ __global__ __launch_bounds__(kThreads, 1) void fairkv_decode_mfma_kernel(DecodeA
         top_up();
 
         for (int ci = 0; ci < nb; ++ci) {
-            fairkv_item it;
-            it.row = 0;
-            it.tok_count = 0;
-            it.b = __builtin_amdgcn_readfirstlane(table[ci].b);
-            it.h = __builtin_amdgcn_readfirstlane(table[ci].h);
-            it.chunk = __builtin_amdgcn_readfirstlane(table[ci].chunk);
-            it.n_chunks = __builtin_amdgcn_readfirstlane(table[ci].n_chunks);
-            it.part = __builtin_amdgcn_readfirstlane(table[ci].part);
             const int n = __builtin_amdgcn_readfirstlane(table[ci].n);
             const int owner = SOLO ? __builtin_amdgcn_readfirstlane(table[ci].owner) : -1;
             if (SOLO && owner >= 0 && owner != wave) continue;      // another wave runs this pair alone
             const int my_tiles = tiles_of(n, owner);
             // scores to log2 units, and what multiplies the output: the same for every pair unless an 8-bit cache has
             // a scale per KV head
-            const float s_mul = KV8 ? head_mul[it.h % kScaleHeads] : a.scale_log2;
-            const float v_mul = KV8 ? head_mul[kScaleHeads + it.h % kScaleHeads] : a.v_scale;
+            const int scale_h = KV8 ? __builtin_amdgcn_readfirstlane(table[ci].h) % kScaleHeads : 0;
+            const float s_mul = KV8 ? head_mul[scale_h] : a.scale_log2;
+            const Piece pc = piece_of(table[ci], KV8 ? head_mul[kScaleHeads + scale_h] : a.v_scale);
             // Several new tokens per sequence: their K/V rows are the last q_len rows of the pair, and
             // new token j does not see the rows of the new tokens after it.  Only the pair's last
             // chunk holds such rows; n_col = tokens of this item the lane's column may see.
-            const int hidden_max = it.chunk == it.n_chunks - 1 ? a.q_len - 1 : 0;
-            const int n_col = n - (it.chunk == it.n_chunks - 1 ? a.q_len - 1 - (min(l16, G - 1) >> a.g_shift) : 0);
+            const int hidden_max = pc.chunk == pc.n_chunks - 1 ? a.q_len - 1 : 0;
+            const int n_col = n - (pc.chunk == pc.n_chunks - 1 ? a.q_len - 1 - (min(l16, G - 1) >> a.g_shift) : 0);
             bf16x8_t qb[NSL];
 #pragma unroll
             for (int s = 0; s < NSL; ++s) qb[s] = bf16x8_t{0, 0, 0, 0, 0, 0, 0, 0};
@@ -493,9 +513,7 @@ __global__ __launch_bounds__(kThreads, 1) void fairkv_decode_mfma_kernel(DecodeA
                     // ---- raise the reference maximum if some score is far above it ------------------
                     float mx = fmaxf(fmaxf(fmaxf(sv[0], sv[1]), fmaxf(sv[2], sv[3])), fmaxf(fmaxf(sv[4], sv[5]), fmaxf(sv[6], sv[7])));
                     if (__builtin_amdgcn_ballot_w64(mx > m_run + kBump) != 0) {
-                        mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
-                        mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-                        const float m_new = fmaxf(m_run, mx);
+                        const float m_new = fmaxf(m_run, quarters_max(mx));
                         const float alpha = m_new == m_run ? 1.f : __builtin_amdgcn_exp2f(m_run - m_new);
                         l_run *= alpha;
 #pragma unroll
@@ -554,9 +572,7 @@ __global__ __launch_bounds__(kThreads, 1) void fairkv_decode_mfma_kernel(DecodeA
                     // ---- raise the reference maximum if some score is far above it (always on the first tile)
                     float mx = fmaxf(fmaxf(sv[0], sv[1]), fmaxf(sv[2], sv[3]));
                     if (__builtin_amdgcn_ballot_w64(mx > m_run + kBump) != 0) {
-                        mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
-                        mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-                        const float m_new = fmaxf(m_run, mx);
+                        const float m_new = fmaxf(m_run, quarters_max(mx));
                         const float alpha = m_new == m_run ? 1.f : __builtin_amdgcn_exp2f(m_run - m_new);   // 0 on the first tile
                         l_run *= alpha;
     #pragma unroll
@@ -594,40 +610,40 @@ __global__ __launch_bounds__(kThreads, 1) void fairkv_decode_mfma_kernel(DecodeA
                 if (batch + ci == i_end - 1) trace_stamp(a, kTraceLastStreamed, threadIdx.x == 0);
             }
             // ---- fold the four token quarters of l, stage this wave's result, finish the item ------
-            l_run += __shfl_xor(l_run, 16, 64);
-            l_run += __shfl_xor(l_run, 32, 64);
+            l_run = quarters_sum(l_run);
             if (SOLO && owner >= 0) {
                 // This wave has seen the whole pair: out = O / l and lse straight from its registers.  A lane holds
                 // coordinates 16 nb + 4 lq .. + 3 of head l16.
                 if (l16 < G && __builtin_amdgcn_readfirstlane(table[ci].valid)) {
-                    const size_t orow = out_row(a, it.b, it.h, l16);
-                    const float inv = l_run > 0.f ? v_mul / l_run : 0.f;
 #pragma unroll
                     for (int nb_ = 0; nb_ < NDB; ++nb_)
-                        store_out4(a.out, a.out_dtype, orow * D + 16 * nb_ + 4 * lq,
-                                   make_float4(o[nb_][0] * inv, o[nb_][1] * inv, o[nb_][2] * inv, o[nb_][3] * inv));
-                    if (lq == 0 && a.lse)
-                        a.lse[orow] = l_run > 0.f ? (m_run + __builtin_amdgcn_logf(l_run)) * kLn2 : -INFINITY;
+                        write_out4<D>(a, pc.qg, l16, 16 * nb_ + 4 * lq, make_float4(o[nb_][0], o[nb_][1], o[nb_][2], o[nb_][3]), m_run,
+                                      l_run, pc.v_mul);
                 }
                 continue;
             }
             if (l16 < G) {
 #pragma unroll
                 for (int nb_ = 0; nb_ < NDB; ++nb_)
-                    *reinterpret_cast<float4 *>(st_o + (wave * G + l16) * D + 16 * nb_ + 4 * lq) =
+                    *reinterpret_cast<float4 *>(st_o[set] + (wave * G + l16) * kStRow<D> + 16 * nb_ + 4 * lq) =
                         make_float4(o[nb_][0], o[nb_][1], o[nb_][2], o[nb_][3]);
                 if (lq == 0) {
-                    st_ml[(wave * G + l16) * 2 + 0] = m_run;
-                    st_ml[(wave * G + l16) * 2 + 1] = l_run;
+                    *reinterpret_cast<float2 *>(st_ml[set] + (wave * G + l16) * 2) = make_float2(m_run, l_run);
                 }
             }
-            if (__builtin_amdgcn_readfirstlane(table[ci].valid)) item_epilogue<D, G, DEEP, TRACE>(a, it, st_o, st_ml, pend, n_pend, v_mul);
+            if (__builtin_amdgcn_readfirstlane(table[ci].valid)) {
+                item_epilogue<D, G, DEEP, TRACE>(a, pc, st_o[set], st_ml[set], pend, n_pend, roles);
+                if constexpr (kSets == 2)
+                    set ^= 1;
+                else
+                    __syncthreads();
+            }
             if constexpr (TRACE)
                 if (batch == i_begin && ci == 0) trace_stamp(a, kTraceItem0Done, threadIdx.x == 0);
         }
         wait_vmcnt<0>();   // nothing of this batch may still be landing in the rings
     }
-    if (n_pend > 0) flush_pending<D, G, DEEP, TRACE>(a, pend, n_pend);
+    if (n_pend > 0) flush_pending<D, G, DEEP, TRACE>(a, pend, n_pend, roles);
     if constexpr (TRACE) trace_stamp(a, kTraceEnd, threadIdx.x == 0);
 }
 

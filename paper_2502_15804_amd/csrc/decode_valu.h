@@ -1,7 +1,7 @@
 // Decode kernel for bf16 inputs on the vector ALU: the second implementation behind FAIRKV_BF16_VALU, for
 // measurements against the matrix-core kernel that bf16 caches normally take.
 #pragma once
-#include "common.h"
+#include "decode_mfma.h"
 
 namespace fairkv {
 
@@ -16,33 +16,30 @@ __global__ __launch_bounds__(kThreads, 2) void fairkv_decode_valu_kernel(DecodeA
     // both the row-contiguous fill and the one-row-per-lane read are free of bank conflicts.
     __shared__ uint4 lds_k[kWaves][kTile * LPR];
     __shared__ float lds_p[kWaves][kTile][G];
-    __shared__ PendingParts<D, G> pend;
+    __shared__ int32_t roles[kPend];
+    Piece pend[kPend] = {};
     int n_pend = 0;
 
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
     const int my_piece = lane % LPR;   // which 16 bytes of a row this lane moves / accumulates
     const int my_sub = lane / LPR;     // which of the RPI rows of a wave-wide access
-    float *st_o = reinterpret_cast<float *>(&lds_k[0][0]);   // [kWaves][G][D], reuses the K tiles
-    float *st_ml = st_o + kWaves * G * D;                    // [kWaves][G][2]
-    static_assert(sizeof(float) * (kWaves * G * (D + 2)) <= sizeof(uint4) * kWaves * kTile * LPR,
+    float *st_o = reinterpret_cast<float *>(&lds_k[0][0]);   // [kWaves][G][kStRow], reuses the K tiles
+    float *st_ml = st_o + kWaves * G * kStRow<D>;            // [kWaves][G][2]
+    static_assert(sizeof(float) * (kWaves * G * (kStRow<D> + 2)) <= sizeof(uint4) * kWaves * kTile * LPR,
                   "merge staging must fit in the K tiles");
 
     // persistent workgroup: walk the items the planner gave this slot
-    const int i_begin = a.slot_ptr[blockIdx.x], i_end = a.slot_ptr[blockIdx.x + 1];
-    for (int ii = i_begin; ii < i_end; ++ii) {
-    const fairkv_item it = a.items[ii];
-    const int b = it.b, h = it.h;
-    // an item that does not belong to this problem is skipped by the whole workgroup
-    if (b < 0 || b >= a.B || h < 0 || h >= a.Hkv || it.row < 0 || it.part < 0 || it.part >= a.n_parts ||
-        it.row + max(it.tok_count, 0) > a.n_rows)
-        continue;
-    const int n = max(it.tok_count, 0);
+    const SlotStart slot = slot_start(a);
+    for (int ii = slot.i_begin; ii < slot.i_end; ++ii) {
+    const ItemSlot it = item_slot(a, a.items[ii]);
+    if (!it.valid) continue;   // an item that does not belong to this problem is skipped by the whole workgroup
+    const int n = it.n;
     const int n_tiles = (n + kTile - 1) / kTile;
 
     const char *kbase = static_cast<const char *>(a.k) + it.row * ROW_BYTES;
     const char *vbase = static_cast<const char *>(a.v) + it.row * ROW_BYTES;
-    const uint32_t *qrow = static_cast<const uint32_t *>(a.q) + static_cast<size_t>(b * a.Hq + h * G) * DW;
+    const uint32_t *qrow = static_cast<const uint32_t *>(a.q) + group_row(a, it.qg) * DW;
 
     float o[G][EPC];
     float m_run[G], l_lane[G];
@@ -156,7 +153,7 @@ __global__ __launch_bounds__(kThreads, 2) void fairkv_decode_valu_kernel(DecodeA
 #pragma unroll
         for (int g = 0; g < G; ++g)
 #pragma unroll
-            for (int e = 0; e < EPC; ++e) st_o[(wave * G + g) * D + my_piece * EPC + e] = o[g][e];
+            for (int e = 0; e < EPC; ++e) st_o[(wave * G + g) * kStRow<D> + my_piece * EPC + e] = o[g][e];
     }
     if (lane == 0) {
 #pragma unroll
@@ -165,9 +162,10 @@ __global__ __launch_bounds__(kThreads, 2) void fairkv_decode_valu_kernel(DecodeA
             st_ml[(wave * G + g) * 2 + 1] = l_lane[g];
         }
     }
-    item_epilogue<D, G, true>(a, it, st_o, st_ml, pend, n_pend, a.v_scale);
+    item_epilogue<D, G, true>(a, piece_of(it, a.v_scale), st_o, st_ml, pend, n_pend, roles);
+    __syncthreads();   // the K tiles may be written again
     }   // items of the slot
-    if (n_pend > 0) flush_pending<D, G, true>(a, pend, n_pend);
+    if (n_pend > 0) flush_pending<D, G, true>(a, pend, n_pend, roles);
 }
 
 }  // namespace fairkv

@@ -395,17 +395,20 @@ int decode_common(const DecodeCall &c)
     // One workgroup per slot while the slot pointer fits the kernel arguments; beyond that, consecutive slots
     // share a workgroup (their items are consecutive in the list, and a workgroup walks a list of any length).
     const int32_t n_wg = n_slots < FAIRKV_MAX_SLOTS ? n_slots : FAIRKV_MAX_SLOTS;
-    for (int32_t j = 0; j <= n_wg; ++j) a.slot_ptr[j] = slot_ptr[static_cast<int64_t>(j) * n_slots / n_wg];
     for (int32_t j = 0; j < n_wg; ++j) {
-        a.first_row[j] = 0;
-        a.first_np[j] = 0;
-        if (a.slot_ptr[j] == a.slot_ptr[j + 1]) continue;
-        const fairkv_item &it = items_host[a.slot_ptr[j]];
-        const int64_t pair = static_cast<int64_t>(it.b) * Hkv + it.h;
-        if (it.row > static_cast<int64_t>(UINT32_MAX) || pair >= (1 << 23)) continue;   // does not fit: normal start
-        a.first_row[j] = static_cast<uint32_t>(it.row);
-        a.first_np[j] = (static_cast<uint32_t>(pair) << 9) | static_cast<uint32_t>(it.tok_count < kEarlyTok ? it.tok_count : kEarlyTok);
+        uint32_t *w = a.slot + 3 * j;
+        const int32_t begin = slot_ptr[static_cast<int64_t>(j) * n_slots / n_wg];
+        const int32_t end = slot_ptr[(static_cast<int64_t>(j) + 1) * n_slots / n_wg];
+        w[0] = static_cast<uint32_t>(begin);
+        w[1] = w[2] = 0;
+        if (begin == end) continue;
+        const fairkv_item &it = items_host[begin];
+        const int64_t qg = static_cast<int64_t>(it.b) * q_len * Hkv + it.h;
+        if (it.row > static_cast<int64_t>(UINT32_MAX) || qg >= (1 << 23)) continue;   // does not fit: normal start
+        w[1] = static_cast<uint32_t>(it.row);
+        w[2] = (static_cast<uint32_t>(qg) << 9) | static_cast<uint32_t>(it.tok_count < kEarlyTok ? it.tok_count : kEarlyTok);
     }
+    a.slot[3 * n_wg] = static_cast<uint32_t>(n_items);
     a.arrivals = reinterpret_cast<int32_t *>(ws);
     a.group_arrivals = a.arrivals + static_cast<size_t>(B) * Hkv;
     a.n_group_counters = B * Hkv + FAIRKV_MAX_SLOTS;
