@@ -480,11 +480,11 @@ extern "C" int fairkv_pack(const void *k_dense, const void *v_dense, int32_t B, 
                static_cast<char *>(v_out), keep_ptr, keep_t, off, items, slot_ptr, bad, n_rows, B, Hkv, T};
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     if (rb == 128)
-        hipLaunchKernelGGL(fairkv_pack_kernel<128>, dim3(n_slots), dim3(256), 0, st, a);
+        hipLaunchKernelGGL(fairkv_pack_kernel<128>, dim3(n_slots, kPackParts), dim3(256), 0, st, a);
     else if (rb == 256)
-        hipLaunchKernelGGL(fairkv_pack_kernel<256>, dim3(n_slots), dim3(256), 0, st, a);
+        hipLaunchKernelGGL(fairkv_pack_kernel<256>, dim3(n_slots, kPackParts), dim3(256), 0, st, a);
     else
-        hipLaunchKernelGGL(fairkv_pack_kernel<512>, dim3(n_slots), dim3(256), 0, st, a);
+        hipLaunchKernelGGL(fairkv_pack_kernel<512>, dim3(n_slots, kPackParts), dim3(256), 0, st, a);
     return hipGetLastError() == hipSuccess ? FAIRKV_OK : FAIRKV_EHIP;
 }
 

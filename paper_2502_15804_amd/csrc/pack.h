@@ -24,15 +24,20 @@ struct PackArgs {
     int32_t B, Hkv, T;
 };
 
-// One workgroup per slot of the work list.  An item is a run of rows of one pair; the workgroup
-// moves kRowsPerPass rows per pass and keeps kUnroll passes in flight.
+// kPackParts workgroups per slot of the work list (grid.y); of an item, which is a run of rows of one pair, workgroup y
+// moves passes y, y + kPackParts, ... of kRowsPerPass rows.
+// What bounds it: the memory's rate for reads and writes mixed (a plain copy reaches 4.8 TB/s).  One workgroup per slot,
+// i.e. one per compute unit, has 8 KB of rows on the way and waits for each pass: 39.9 us for the 136 MB of a layer of
+// the Llama-70B shape, 3.4 TB/s.  Two, four, eight: 29.5, 28.3 (4.8 TB/s), 29.8 us; more passes in flight per workgroup
+// instead: 28.5 us for two workgroups with four, slower on small caches (5.5 -> 6.3 us for one sequence).
+constexpr int kPackParts = 4;
 template <int ROWB>
 __global__ __launch_bounds__(256) void fairkv_pack_kernel(PackArgs a)
 {
     typedef __attribute__((ext_vector_type(4))) uint32_t u4;   // rows are read once and written once: non-temporal both ways
     constexpr int PPR = ROWB / 16;            // 16-byte pieces per row
     constexpr int kRowsPerPass = 256 / PPR;
-    constexpr int kUnroll = 1;   // measured: 1 -> 36.7 us, 2 -> 42, 4 -> 48, 8 -> 61 for the 140 MB of the llama70b layer
+    const int first_row = blockIdx.y * kRowsPerPass;
     const int piece = threadIdx.x % PPR, sub = threadIdx.x / PPR;
     for (int i = a.slot_ptr[blockIdx.x]; i < a.slot_ptr[blockIdx.x + 1]; ++i) {
         const fairkv_item it = a.items[i];
@@ -47,7 +52,7 @@ __global__ __launch_bounds__(256) void fairkv_pack_kernel(PackArgs a)
             ok = begin >= 0 && first >= 0 && begin + n <= a.keep_ptr[pair + 1] - first;
         }
         if (!ok) {
-            if (threadIdx.x == 0 && a.bad) atomicAdd(a.bad, 1);
+            if (threadIdx.x == 0 && blockIdx.y == 0 && a.bad) atomicAdd(a.bad, 1);
             continue;
         }
         const int32_t *kt = a.keep_t + first + begin;
@@ -55,39 +60,24 @@ __global__ __launch_bounds__(256) void fairkv_pack_kernel(PackArgs a)
         const char *vsrc = a.v_dense + pair * a.T * ROWB + piece * 16;
         char *kdst = a.k_out + it.row * ROWB + piece * 16;
         char *vdst = a.v_out + it.row * ROWB + piece * 16;
-        // All indices of a round first, then all row loads, then the stores: nothing in a round waits
-        // for an earlier load of the same round.  Rows past the end and rows with a bad index are
-        // loaded from a clamped (valid) address and not stored.
-        // The indices of the next round are requested before the rows of this one, so a round costs one
-        // memory latency (the rows), not two (index, then rows).
-        int32_t t_next[kUnroll];
-#pragma unroll
-        for (int u = 0; u < kUnroll; ++u) t_next[u] = kt[min(u * kRowsPerPass + sub, n - 1)];
-        for (int r0 = 0; r0 < n; r0 += kRowsPerPass * kUnroll) {
-            int32_t t[kUnroll];
-#pragma unroll
-            for (int u = 0; u < kUnroll; ++u) {
-                t[u] = t_next[u];
-                t_next[u] = kt[min(r0 + (kUnroll + u) * kRowsPerPass + sub, n - 1)];
+        // The index of the next pass is requested before the row of this one, so a pass costs one memory latency (the
+        // row), not two (index, then row).  Rows past the end and rows with a bad index are loaded from a clamped
+        // (valid) address and not stored.
+        int32_t t_next = kt[min(first_row + sub, n - 1)];
+        for (int r0 = first_row; r0 < n; r0 += kPackParts * kRowsPerPass) {
+            const int32_t t = t_next;
+            t_next = kt[min(r0 + kPackParts * kRowsPerPass + sub, n - 1)];
+            const int64_t tc = min(max(t, 0), a.T - 1);
+            const u4 kk = __builtin_nontemporal_load(reinterpret_cast<const u4 *>(ksrc + tc * ROWB));
+            const u4 vv = __builtin_nontemporal_load(reinterpret_cast<const u4 *>(vsrc + tc * ROWB));
+            const int r = r0 + sub;
+            if (r >= n) continue;
+            if (t < 0 || t >= a.T) {
+                if (piece == 0 && a.bad) atomicAdd(a.bad, 1);
+                continue;
             }
-            u4 kk[kUnroll], vv[kUnroll];
-#pragma unroll
-            for (int u = 0; u < kUnroll; ++u) {
-                const int64_t tc = min(max(t[u], 0), a.T - 1);
-                kk[u] = __builtin_nontemporal_load(reinterpret_cast<const u4 *>(ksrc + tc * ROWB));
-                vv[u] = __builtin_nontemporal_load(reinterpret_cast<const u4 *>(vsrc + tc * ROWB));
-            }
-#pragma unroll
-            for (int u = 0; u < kUnroll; ++u) {
-                const int r = r0 + u * kRowsPerPass + sub;
-                if (r >= n) continue;
-                if (t[u] < 0 || t[u] >= a.T) {
-                    if (piece == 0 && a.bad) atomicAdd(a.bad, 1);
-                    continue;
-                }
-                __builtin_nontemporal_store(kk[u], reinterpret_cast<u4 *>(kdst + static_cast<int64_t>(r) * ROWB));
-                __builtin_nontemporal_store(vv[u], reinterpret_cast<u4 *>(vdst + static_cast<int64_t>(r) * ROWB));
-            }
+            __builtin_nontemporal_store(kk, reinterpret_cast<u4 *>(kdst + static_cast<int64_t>(r) * ROWB));
+            __builtin_nontemporal_store(vv, reinterpret_cast<u4 *>(vdst + static_cast<int64_t>(r) * ROWB));
         }
     }
 }
