@@ -249,8 +249,46 @@ def fairkv_workspace_bytes(n_parts: int, n_pairs: int, G: int, D: int) -> int:
     return int(lib().fairkv_workspace_bytes(int(n_parts), int(n_pairs), int(G), int(D)))
 
 
+# What every call needs of PyTorch, looked up once: (module, the element types of q and out, those of an 8-bit cache, those
+# that fairkv_pack and fairkv_append move, the function that gives a device's current stream as a number).  A call on the
+# GPU is worth 5 to 20 us, so the binding's own microseconds count: pointers travel as plain integers, which ctypes
+# converts by itself, and streams without a torch.cuda.Stream around them.
+_pt = None
+
+
+def _torch():
+    global _pt
+    if _pt is None:
+        import torch
+        _pt = (torch, {torch.bfloat16: FAIRKV_BF16, torch.float32: FAIRKV_F32}, (torch.uint8, torch.float8_e4m3fn),
+               {torch.bfloat16: FAIRKV_BF16, torch.float32: FAIRKV_F32, torch.uint8: FAIRKV_E4M3,
+                torch.float8_e4m3fn: FAIRKV_E4M3}, torch._C._cuda_getCurrentRawStream)
+    return _pt
+
+
 def _ptr(t):
-    return ctypes.c_void_p(t.data_ptr()) if t is not None else None
+    return t.data_ptr() if t is not None else None
+
+
+def _stream(stream, t):
+    """The stream to enqueue on: the caller's, or the current one of the device of tensor t."""
+    return stream.cuda_stream if stream is not None else _pt[4](t.get_device())
+
+
+def _plan_args(items, items_host, slot_ptr, n_parts):
+    """The plan's arguments of a decode call, checked: items, items_host, n_items, slot_ptr, n_slots, n_parts."""
+    if not isinstance(slot_ptr, np.ndarray) or slot_ptr.dtype != np.int32 or not slot_ptr.flags.c_contiguous:
+        raise TypeError("slot_ptr must be a contiguous host int32 array")
+    if slot_ptr.size < 2:
+        raise ValueError("shape mismatch")
+    item_bytes = items.nbytes
+    if item_bytes % 32 != 0:
+        raise ValueError("items must be a whole number of 32-byte records")
+    if (not isinstance(items_host, np.ndarray) or items_host.dtype != ITEM_DTYPE or not items_host.flags.c_contiguous
+            or items_host.size * 32 != item_bytes):
+        raise TypeError("items_host must be the plan's contiguous item array, as many records as `items`")
+    return (items.data_ptr(), items_host.ctypes.data, item_bytes // 32,
+            slot_ptr.ctypes.data, slot_ptr.size - 1, int(n_parts))
 
 
 def fairkv_decode_attn(q, k, v, items, items_host, slot_ptr, n_parts, workspace, out, lse, scale, Hkv, stream=None,
@@ -267,54 +305,38 @@ def fairkv_decode_attn(q, k, v, items, items_host, slot_ptr, n_parts, workspace,
     items_host and slot_ptr are the plan's HOST arrays (numpy: fairkv_item records, int32
     [n_slots+1]).  Nothing is allocated or synchronised here.
     """
-    import torch
-
-    if q.dim() == 4:
-        B, q_len, Hq, D = q.shape
+    torch, dt = _torch()[:2]
+    shape = q.shape
+    if len(shape) == 4:
+        B, q_len, Hq, D = shape
     else:
-        (B, Hq, D), q_len = q.shape, 1
-    dt = {torch.bfloat16: FAIRKV_BF16, torch.float32: FAIRKV_F32}
+        (B, Hq, D), q_len = shape, 1
     if q.dtype not in dt or k.dtype != q.dtype or v.dtype != q.dtype or out.dtype not in dt:
         raise TypeError("q/k/v must share bf16 or fp32; out must be bf16 or fp32")
-    for name, t in (("q", q), ("k", k), ("v", v), ("items", items), ("workspace", workspace), ("out", out),
-                    ("lse", lse), ("trace", trace)):
-        if t is None:
-            continue
-        if not t.is_cuda or not t.is_contiguous():
-            raise ValueError(f"{name} must be a contiguous device tensor")
-    if not isinstance(slot_ptr, np.ndarray) or slot_ptr.dtype != np.int32 or not slot_ptr.flags.c_contiguous:
-        raise TypeError("slot_ptr must be a contiguous host int32 array")
+    _check_dev(q=q, k=k, v=v, items=items, workspace=workspace, out=out, lse=lse, trace=trace)
     if lse is not None and lse.dtype != torch.float32:
         raise TypeError("lse must be float32")
-    if k.shape[1] != D or v.shape != k.shape or tuple(out.shape) != tuple(q.shape) or slot_ptr.size < 2:
+    k_shape = k.shape
+    if k_shape[1] != D or v.shape != k_shape or out.shape != shape:
         raise ValueError("shape mismatch")
-    if lse is not None and tuple(lse.shape) != tuple(q.shape[:-1]):
+    if lse is not None and lse.shape != shape[:-1]:
         raise ValueError("lse must have q's shape without the last dimension")
-    item_bytes = items.numel() * items.element_size()
-    if item_bytes % 32 != 0:
-        raise ValueError("items must be a whole number of 32-byte records")
-    if (not isinstance(items_host, np.ndarray) or items_host.dtype != ITEM_DTYPE or not items_host.flags.c_contiguous
-            or items_host.size * 32 != item_bytes):
-        raise TypeError("items_host must be the plan's contiguous item array, as many records as `items`")
-    if stream is None:
-        stream = torch.cuda.current_stream(q.device)
     in_dt = FAIRKV_BF16_VALU if (bf16_on_valu and q.dtype == torch.bfloat16) else dt[q.dtype]
-    head = (_ptr(q), _ptr(k), _ptr(v), k.shape[0], _ptr(items), items_host.ctypes.data, item_bytes // 32,
-            slot_ptr.ctypes.data, slot_ptr.size - 1, int(n_parts))
-    st = ctypes.c_void_p(stream.cuda_stream)
+    head = (q.data_ptr(), k.data_ptr(), v.data_ptr(), k_shape[0], *_plan_args(items, items_host, slot_ptr, n_parts))
+    st = _stream(stream, q)
     if trace is not None:
         if q_len != 1 or workspace is None or trace.dtype != torch.int64:
             raise ValueError("a traced call is a single-token call with a caller's workspace and an int64 trace buffer")
         name = "fairkv_decode_attn_trace"
-        rc = lib().fairkv_decode_attn_trace(*head, _ptr(workspace), workspace.numel() * workspace.element_size(), _ptr(out),
+        rc = lib().fairkv_decode_attn_trace(*head, workspace.data_ptr(), workspace.nbytes, out.data_ptr(),
                                             _ptr(lse), B, Hq, Hkv, D, float(scale), _ptr(trace), trace.numel() * 8, st)
     elif workspace is None:
         name = "fairkv_decode_attn_static"
-        rc = lib().fairkv_decode_attn_static(*head, _ptr(out), _ptr(lse), B, q_len, Hq, Hkv, D, in_dt, dt[out.dtype],
+        rc = lib().fairkv_decode_attn_static(*head, out.data_ptr(), _ptr(lse), B, q_len, Hq, Hkv, D, in_dt, dt[out.dtype],
                                              float(scale), st)
     else:
         name = "fairkv_decode_attn_multi" if q_len > 1 else "fairkv_decode_attn"
-        rc = lib().fairkv_decode_attn_multi(*head, _ptr(workspace), workspace.numel() * workspace.element_size(), _ptr(out),
+        rc = lib().fairkv_decode_attn_multi(*head, workspace.data_ptr(), workspace.nbytes, out.data_ptr(),
                                             _ptr(lse), B, q_len, Hq, Hkv, D, in_dt, dt[out.dtype], float(scale), st)
     if rc != FAIRKV_OK:
         raise FairKVError(rc, name)
@@ -329,53 +351,35 @@ def fairkv_decode_attn_kv8(q, k8, v8, k_scale, v_scale, items, items_host, slot_
     per KV head: fairkv_decode_attn_kv8_per_head).  q [B,Hq,D] or [B,q_len,Hq,D] bfloat16.  Everything else as in
     fairkv_decode_attn.
     """
-    import torch
-
-    if q.dim() == 4:
-        B, q_len, Hq, D = q.shape
+    torch, dt, bytes_ok = _torch()[:3]
+    shape = q.shape
+    if len(shape) == 4:
+        B, q_len, Hq, D = shape
     else:
-        (B, Hq, D), q_len = q.shape, 1
-    dt = {torch.bfloat16: FAIRKV_BF16, torch.float32: FAIRKV_F32}
-    bytes_ok = (torch.uint8, torch.float8_e4m3fn)
+        (B, Hq, D), q_len = shape, 1
     if q.dtype != torch.bfloat16 or k8.dtype not in bytes_ok or v8.dtype not in bytes_ok or out.dtype not in dt:
         raise TypeError("q must be bf16, k8/v8 float8_e4m3fn or uint8, out bf16 or fp32")
     _check_dev(q=q, k8=k8, v8=v8, items=items, workspace=workspace, out=out, lse=lse)
-    if not isinstance(slot_ptr, np.ndarray) or slot_ptr.dtype != np.int32 or not slot_ptr.flags.c_contiguous:
-        raise TypeError("slot_ptr must be a contiguous host int32 array")
     if lse is not None and lse.dtype != torch.float32:
         raise TypeError("lse must be float32")
-    if k8.dim() != 2 or k8.shape[1] != D or v8.shape != k8.shape or tuple(out.shape) != tuple(q.shape) or slot_ptr.size < 2:
+    k_shape = k8.shape
+    if len(k_shape) != 2 or k_shape[1] != D or v8.shape != k_shape or out.shape != shape:
         raise ValueError("shape mismatch")
-    if lse is not None and tuple(lse.shape) != tuple(q.shape[:-1]):
+    if lse is not None and lse.shape != shape[:-1]:
         raise ValueError("lse must have q's shape without the last dimension")
-    item_bytes = items.numel() * items.element_size()
-    if item_bytes % 32 != 0:
-        raise ValueError("items must be a whole number of 32-byte records")
-    if (not isinstance(items_host, np.ndarray) or items_host.dtype != ITEM_DTYPE or not items_host.flags.c_contiguous
-            or items_host.size * 32 != item_bytes):
-        raise TypeError("items_host must be the plan's contiguous item array, as many records as `items`")
-    if stream is None:
-        stream = torch.cuda.current_stream(q.device)
-    tail = (_ptr(items), items_host.ctypes.data, item_bytes // 32, slot_ptr.ctypes.data, slot_ptr.size - 1, int(n_parts),
-            _ptr(workspace), workspace.numel() * workspace.element_size(), _ptr(out), _ptr(lse), B, q_len, Hq, Hkv, D,
-            dt[out.dtype], float(scale), ctypes.c_void_p(stream.cuda_stream))
+    tail = (*_plan_args(items, items_host, slot_ptr, n_parts), workspace.data_ptr(), workspace.nbytes, out.data_ptr(),
+            _ptr(lse), B, q_len, Hq, Hkv, D, dt[out.dtype], float(scale), _stream(stream, q))
     if np.ndim(k_scale) or np.ndim(v_scale):
         ks = np.ascontiguousarray(np.broadcast_to(np.asarray(k_scale, dtype=np.float32), (Hkv,)))
         vs = np.ascontiguousarray(np.broadcast_to(np.asarray(v_scale, dtype=np.float32), (Hkv,)))
-        rc = lib().fairkv_decode_attn_kv8_per_head(_ptr(q), _ptr(k8), _ptr(v8), k8.shape[0], ks.ctypes.data, vs.ctypes.data,
+        rc = lib().fairkv_decode_attn_kv8_per_head(q.data_ptr(), k8.data_ptr(), v8.data_ptr(), k_shape[0], ks.ctypes.data, vs.ctypes.data,
                                                    *tail)
         name = "fairkv_decode_attn_kv8_per_head"
     else:
-        rc = lib().fairkv_decode_attn_kv8(_ptr(q), _ptr(k8), _ptr(v8), k8.shape[0], float(k_scale), float(v_scale), *tail)
+        rc = lib().fairkv_decode_attn_kv8(q.data_ptr(), k8.data_ptr(), v8.data_ptr(), k_shape[0], float(k_scale), float(v_scale), *tail)
         name = "fairkv_decode_attn_kv8"
     if rc != FAIRKV_OK:
         raise FairKVError(rc, name)
-
-
-def _dtype_code(t):
-    import torch
-    return {torch.bfloat16: FAIRKV_BF16, torch.float32: FAIRKV_F32, torch.uint8: FAIRKV_E4M3,
-            torch.float8_e4m3fn: FAIRKV_E4M3}[t.dtype]
 
 
 def _check_dev(**tensors):
@@ -388,8 +392,7 @@ def fairkv_pack(k_dense, v_dense, keep_ptr, keep_t, off, items, slot_ptr, k_out,
     """Enqueue the gather of the kept rows.  All arguments are device tensors: k_dense, v_dense
     [B][Hkv][T][D]; keep_ptr int64 [B*Hkv+1]; keep_t int32; off int64 [B*Hkv]; items uint8 view of a
     plan's item array; slot_ptr int32 [n_slots+1]; k_out, v_out [n_rows][D]; bad int32 [1] or None."""
-    import torch
-
+    torch, _, _, moved = _torch()[:4]
     B, Hkv, T, D = k_dense.shape
     _check_dev(k_dense=k_dense, v_dense=v_dense, keep_ptr=keep_ptr, keep_t=keep_t, off=off, items=items,
                slot_ptr=slot_ptr, k_out=k_out, v_out=v_out, bad=bad)
@@ -400,11 +403,9 @@ def fairkv_pack(k_dense, v_dense, keep_ptr, keep_t, off, items, slot_ptr, k_out,
             or slot_ptr.dtype != torch.int32 or keep_ptr.numel() != B * Hkv + 1 or off.numel() != B * Hkv
             or (bad is not None and bad.dtype != torch.int32)):
         raise TypeError("keep_ptr/off must be int64, keep_t/slot_ptr/bad int32, sized for B*Hkv pairs")
-    if stream is None:
-        stream = torch.cuda.current_stream(k_dense.device)
-    rc = lib().fairkv_pack(_ptr(k_dense), _ptr(v_dense), B, Hkv, T, D, _dtype_code(k_dense), _ptr(keep_ptr),
+    rc = lib().fairkv_pack(_ptr(k_dense), _ptr(v_dense), B, Hkv, T, D, moved[k_dense.dtype], _ptr(keep_ptr),
                            _ptr(keep_t), _ptr(off), _ptr(items), _ptr(slot_ptr), slot_ptr.numel() - 1, _ptr(k_out),
-                           _ptr(v_out), k_out.shape[0], _ptr(bad), ctypes.c_void_p(stream.cuda_stream))
+                           _ptr(v_out), k_out.shape[0], _ptr(bad), _stream(stream, k_dense))
     if rc != FAIRKV_OK:
         raise FairKVError(rc, "fairkv_pack")
 
@@ -412,8 +413,7 @@ def fairkv_pack(k_dense, v_dense, keep_ptr, keep_t, off, items, slot_ptr, k_out,
 def fairkv_append(k_new, v_new, off, lens, cap, k, v, full=None, stream=None):
     """Enqueue the append of one new row per pair.  Device tensors: k_new, v_new [B][Hkv][D]; off int64,
     lens int32 (updated in place), cap int32, all [B*Hkv]; k, v packed [n_rows][D]; full int32 [1] or None."""
-    import torch
-
+    torch, _, _, moved = _torch()[:4]
     B, Hkv, D = k_new.shape
     _check_dev(k_new=k_new, v_new=v_new, off=off, lens=lens, cap=cap, k=k, v=v, full=full)
     if (v_new.shape != k_new.shape or k.shape != v.shape or k.shape[1] != D or k.dtype != k_new.dtype
@@ -423,10 +423,8 @@ def fairkv_append(k_new, v_new, off, lens, cap, k, v, full=None, stream=None):
             or off.numel() != B * Hkv or lens.numel() != B * Hkv or cap.numel() != B * Hkv
             or (full is not None and full.dtype != torch.int32)):
         raise TypeError("off must be int64, lens/cap/full int32, sized for B*Hkv pairs")
-    if stream is None:
-        stream = torch.cuda.current_stream(k_new.device)
-    rc = lib().fairkv_append(_ptr(k_new), _ptr(v_new), B, Hkv, D, _dtype_code(k_new), _ptr(off), _ptr(lens), _ptr(cap),
-                             _ptr(k), _ptr(v), k.shape[0], _ptr(full), ctypes.c_void_p(stream.cuda_stream))
+    rc = lib().fairkv_append(_ptr(k_new), _ptr(v_new), B, Hkv, D, moved[k_new.dtype], _ptr(off), _ptr(lens), _ptr(cap),
+                             _ptr(k), _ptr(v), k.shape[0], _ptr(full), _stream(stream, k_new))
     if rc != FAIRKV_OK:
         raise FairKVError(rc, "fairkv_append")
 
