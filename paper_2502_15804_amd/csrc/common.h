@@ -254,62 +254,89 @@ __device__ __forceinline__ void publish_part(const DecodeArgs &a, int part, int 
     if (idx % (D / 4) == 0) publish_f32x2(a.part_ml + static_cast<size_t>(part) * (G * 2), idx / (D / 4) * 8, m, l);
 }
 
-// Partials first, first + step, ... (count of them) into one: a thread owns four consecutive coordinates of one column.
-// What bounds it: one memory round trip per batch, and the instructions of a wave that is alone on its SIMD (4 cycles
-// each).  So everything that is the same for the wave stays in scalar registers, and a partial that is not there costs
-// one branch.  (With 8-byte loads, an address per thread and load, and batches of 8 worked through whatever the number
-// of partials, the last merge of a launch took 2.2 us on the headline workload; 1.6 us like this.)
+// Partials first, first + step, ... (count of them; 0: nothing to do) of a pair into one: the pair's output or, if
+// to_group, the partial of a group of pieces.  The same for all threads.
+struct Merge {
+    Piece pc;
+    int first, step, count;
+    bool to_group;
+};
+// The merges of a workgroup: a thread owns four consecutive coordinates of one column (of two columns, when there are 16
+// of them).  What bounds it: memory round trips, and the instructions of a wave that is alone on its SIMD (4 cycles each).
+// So the first batch of partials is requested for two things at once before any is used, the two merges or, with two
+// columns per thread, the columns of a merge; what is the same for the wave stays in scalar registers, and a partial that
+// is not there costs one branch.  The last workgroup of a launch is usually the last of both its pairs: one merge after the
+// other cost it a round trip more (Llama-70B shape 0.1 us per launch, one sequence 0.2, 8-bit cache 0.2).
 template <int D, int G, bool DEEP, bool TRACE = false>
-__device__ __forceinline__ void merge_parts(const DecodeArgs &a, const Piece &pc, int first, int step, int count, bool to_group)
+__device__ __forceinline__ void merge_parts(const DecodeArgs &a, const Merge (&mg)[kPend])
 {
-    constexpr int D4 = D / 4, OB = G * D * 4, MB = G * 2 * 4;      // bytes of a partial's outputs and of its statistics
-    for (int idx = threadIdx.x; idx < G * D4; idx += kThreads) {
-        const int g = idx / D4;
-        float m_star = -INFINITY, l_star = 0.f, acc[4] = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll 1
-        for (int c0 = 0; c0 < count; c0 += kMergeBatch) {
-            const size_t part = static_cast<size_t>(first) + static_cast<size_t>(step) * c0;
-            const uint32_t span = static_cast<uint32_t>(step * (min(kMergeBatch, count - c0) - 1) + 1);
-            const __amdgpu_buffer_rsrc_t ro = parts_rsrc(a.part_o + part * (G * D), span * OB);
-            const __amdgpu_buffer_rsrc_t rm = parts_rsrc(a.part_ml + part * (G * 2), span * MB);
-            f4_t o[kMergeBatch];
-            f2_t ml[kMergeBatch];
+    constexpr int D4 = D / 4, NC4 = G * D4, OB = G * D * 4, MB = G * 2 * 4;      // bytes of a partial's outputs, of its statistics
+    constexpr int IT = (NC4 + kThreads - 1) / kThreads;                           // fours of coordinates per thread
+    static_assert(IT <= 2 && kPend == 2, "two things at once");
+    f4_t o[2][kMergeBatch];
+    f2_t ml[2][kMergeBatch];
+    auto fetch = [&](int u, int it, const Merge &m, int c0) __attribute__((always_inline)) {
+        const int idx = threadIdx.x + it * kThreads;      // past the last coordinate: loaded and not used
+        const size_t part = static_cast<size_t>(m.first) + static_cast<size_t>(m.step) * c0;
+        const uint32_t span = static_cast<uint32_t>(m.step * (min(kMergeBatch, m.count - c0) - 1) + 1);
+        const __amdgpu_buffer_rsrc_t ro = parts_rsrc(a.part_o + part * (G * D), span * OB);
+        const __amdgpu_buffer_rsrc_t rm = parts_rsrc(a.part_ml + part * (G * 2), span * MB);
 #pragma unroll
-            for (int j = 0; j < kMergeBatch; ++j) {
-                if (c0 + j >= count) break;
-                ml[j] = __builtin_bit_cast(f2_t, __builtin_amdgcn_raw_buffer_load_b64(rm, g * 8, step * j * MB, kAgent));
-                o[j] = __builtin_bit_cast(f4_t, __builtin_amdgcn_raw_buffer_load_b128(ro, idx * 16, step * j * OB, kAgent));
-            }
-            if constexpr (TRACE)
-                if (c0 == 0) {
-                    drain_vmem();
-                    trace_stamp(a, kTraceMergeLoaded, threadIdx.x == 0);
-                }
-            float m_new = m_star;
-#pragma unroll
-            for (int j = 0; j < kMergeBatch; ++j) {
-                if (c0 + j >= count) break;
-                m_new = fmaxf(m_new, ml[j][0]);
-            }
-            const float keep = m_star == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_star - m_new);
-            l_star *= keep;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) acc[e] *= keep;
-#pragma unroll
-            for (int j = 0; j < kMergeBatch; ++j) {
-                if (c0 + j >= count) break;
-                const float f = ml[j][0] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(ml[j][0] - m_new);
-                l_star = fmaf(ml[j][1], f, l_star);
-#pragma unroll
-                for (int e = 0; e < 4; ++e) acc[e] = fmaf(o[j][e], f, acc[e]);
-            }
-            m_star = m_new;
+        for (int j = 0; j < kMergeBatch; ++j) {
+            if (c0 + j >= m.count) break;
+            ml[u][j] = __builtin_bit_cast(f2_t, __builtin_amdgcn_raw_buffer_load_b64(rm, idx / D4 * 8, m.step * j * MB, kAgent));
+            o[u][j] = __builtin_bit_cast(f4_t, __builtin_amdgcn_raw_buffer_load_b128(ro, idx * 16, m.step * j * OB, kAgent));
         }
-        const float4 sum = make_float4(acc[0], acc[1], acc[2], acc[3]);
-        if (DEEP && to_group)      // the group's partial, in the slot of its first piece
-            publish_part<D, G>(a, first, idx, sum, m_star, l_star);
-        else
-            write_out4<D>(a, pc.qg, g, idx % D4 * 4, sum, m_star, l_star, pc.v_mul);
+    };
+#pragma unroll
+    for (int turn = 0; turn < IT; ++turn) {       // IT == 1: both merges at once; else merge `turn`, both columns at once
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const Merge &m = mg[IT == 1 ? u : turn];
+            if (m.count > 0) fetch(u, IT == 1 ? 0 : u, m, 0);
+        }
+        if constexpr (TRACE)
+            if (turn == 0) {
+                drain_vmem();
+                trace_stamp(a, kTraceMergeLoaded, threadIdx.x == 0);
+            }
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const Merge &m = mg[IT == 1 ? u : turn];
+            const int it = IT == 1 ? 0 : u, idx = threadIdx.x + it * kThreads;
+            if (m.count == 0) continue;
+            float m_star = -INFINITY, l_star = 0.f, acc[4] = {0.f, 0.f, 0.f, 0.f};
+            for (int c0 = 0;;) {
+                float m_new = m_star;
+#pragma unroll
+                for (int j = 0; j < kMergeBatch; ++j) {
+                    if (c0 + j >= m.count) break;
+                    m_new = fmaxf(m_new, ml[u][j][0]);
+                }
+                const float keep = m_star == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_star - m_new);
+                l_star *= keep;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) acc[e] *= keep;
+#pragma unroll
+                for (int j = 0; j < kMergeBatch; ++j) {
+                    if (c0 + j >= m.count) break;
+                    const float f = ml[u][j][0] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(ml[u][j][0] - m_new);
+                    l_star = fmaf(ml[u][j][1], f, l_star);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) acc[e] = fmaf(o[u][j][e], f, acc[e]);
+                }
+                m_star = m_new;
+                c0 += kMergeBatch;
+                if (c0 >= m.count) break;
+                fetch(u, it, m, c0);
+            }
+            if (idx >= NC4) continue;
+            const float4 sum = make_float4(acc[0], acc[1], acc[2], acc[3]);
+            if (DEEP && m.to_group)      // the group's partial, in the slot of its first piece
+                publish_part<D, G>(a, m.first, idx, sum, m_star, l_star);
+            else
+                write_out4<D>(a, m.pc.qg, idx / D4, idx % D4 * 4, sum, m_star, l_star, m.pc.v_mul);
+        }
     }
 }
 
@@ -358,24 +385,25 @@ __device__ __forceinline__ void flush_pending(const DecodeArgs &a, const Piece (
         bool any_group = false;
         role[0] = __builtin_amdgcn_readfirstlane(roles[0]);
         role[1] = n_pend > 1 ? __builtin_amdgcn_readfirstlane(roles[1]) : kRoleNone;
-#pragma unroll 1
-        for (int p = 0; p < n_pend; ++p) {                 // one copy of the merge's code
-            const int what = p == 0 ? role[0] : role[1];
-            if (what == kRoleNone) continue;
-            const Piece pc = p == 0 ? pend[0] : pend[1];
-            int first = pc.part - pc.chunk, step = 1, count = pc.n_chunks;
-            if (DEEP && what == kRoleGroup) {
-                any_group = true;
-                const int k = pc.chunk / kGroup;
-                first += k * kGroup;
-                count = min(kGroup, pc.n_chunks - k * kGroup);
-                if (count == 1) continue;                  // its partial is the group's already
-            } else if (DEEP && round == 1) {
-                step = kGroup;
-                count = (pc.n_chunks + kGroup - 1) / kGroup;
+        Merge mg[kPend];
+#pragma unroll
+        for (int p = 0; p < kPend; ++p) {
+            mg[p] = Merge{pend[p], pend[p].part - pend[p].chunk, 1, role[p] == kRoleNone ? 0 : pend[p].n_chunks, false};
+            if constexpr (DEEP) {
+                const int k = pend[p].chunk / kGroup, ng = (pend[p].n_chunks + kGroup - 1) / kGroup;
+                if (role[p] == kRoleGroup) {
+                    any_group = true;
+                    mg[p].first += k * kGroup;
+                    mg[p].count = min(kGroup, pend[p].n_chunks - k * kGroup);
+                    if (mg[p].count == 1) mg[p].count = 0;     // its partial is the group's already
+                    mg[p].to_group = true;
+                } else if (round == 1 && role[p] != kRoleNone) {
+                    mg[p].step = kGroup;
+                    mg[p].count = ng;
+                }
             }
-            merge_parts<D, G, DEEP, TRACE>(a, pc, first, step, count, what == kRoleGroup);
         }
+        if (mg[0].count + mg[1].count > 0) merge_parts<D, G, DEEP, TRACE>(a, mg);
         if constexpr (TRACE) trace_stamp(a, kTraceFlushMerged, threadIdx.x == 0);
         if (!DEEP || !any_group) break;                    // the same for all threads
         drain_vmem();                                      // the group partials are acknowledged ...
