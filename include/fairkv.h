@@ -150,7 +150,7 @@ int fairkv_plan(const int32_t *len, const int64_t *off, int32_t B, int32_t Hkv, 
 /* Bytes of device workspace fairkv_decode_attn needs: fp32 partial outputs and softmax
  * statistics for n_parts items, plus the arrival counters of the hand-over.  0 on bad arguments.
  * Layout: the counters first (fairkv_workspace_counter_bytes(n_pairs) bytes: one per pair and
- * one per group of 8 pieces of a pair cut 32 ways or more; their number depends on n_pairs alone),
+ * one per group of 8 pieces of a pair cut 16 ways or more; their number depends on n_pairs alone),
  * then statistics and partial outputs.  The counter bytes must be zero before the first use;
  * every completed call leaves them zero again, whatever its plan, so calls that are ordered on
  * one stream may share one workspace (the counter region of a smaller B * Hkv is a prefix of a

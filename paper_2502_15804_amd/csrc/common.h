@@ -232,15 +232,17 @@ __device__ __forceinline__ void drain_vmem()
 // (exact in real arithmetic, so a cut pair gives what the whole pair would) and sets the counter
 // back to zero.
 //
-// A pair cut into more pieces would make one workgroup fetch all of them at the rate of a single
-// compute unit (79 pieces of a 16k-token head: 14 us).  Its pieces form groups of kGroup
-// consecutive ones, each group with a counter of its own: the last piece of a group to arrive
-// merges the group into one partial (m*, l*, sum_c o_c 2^(m_c - m*), not divided), stores it in the
-// slot of the group's first piece, waits for the acknowledgement and only then counts in on the
-// pair's counter, on which the last GROUP to arrive merges the group partials.  Two short merges
-// by different workgroups instead of one long one.
+// A pair cut into more pieces would make one workgroup fetch all of them, batch after batch, at the rate of a single
+// compute unit.  Its pieces form groups of kGroup consecutive ones, each group with a counter of its own: the last piece of
+// a group to arrive merges the group into one partial (m*, l*, sum_c o_c 2^(m_c - m*), not divided), stores it in the slot
+// of the group's first piece, waits for the acknowledgement and only then counts in on the pair's counter, on which the
+// last GROUP to arrive merges the group partials.  Two short merges by different workgroups instead of one long one.
+// Measured (us per layer, one sequence of 8 pairs / 8 pairs of 4096 tokens / batch 4 / Fair-Copying share / Llama-70B
+// shape): from 64 pieces on 10.8 / 13.6 / 11.7 / - / 16.4, from 32 9.9 / 12.0 / 11.0 / 32.8 / 16.4, from 16 9.4 / 10.5 /
+// 10.2 / 32.8 / 16.4, from 12 9.4 / 10.4 / 10.1 / 33.3 / 16.4, from 9 9.6 / 10.4 / 10.2 / 33.4 / 16.9 (more plans then
+// need the instantiation with this code).  Groups of 4 or 6 instead of 8: one pair of 8192 tokens 11.0 -> 11.9, 11.3.
 constexpr int kGroup = 8;
-constexpr int kDeepFrom = 32;
+constexpr int kDeepFrom = 16;
 enum { kRoleNone = 0, kRoleFinal = 1, kRoleGroup = 2 };
 
 constexpr int kMergeBatch = 8;   // partials of a cut pair fetched at once by the merging workgroup
