@@ -19,20 +19,19 @@ def device_compute_units(device=None) -> int:
                .multi_processor_count)
 
 
-def _plan_params(n_cu, kv8, f32, tokens):
-    """The planner's parameters for a layer that brings none: the library's defaults are those of large bf16 caches.
+def _plan_params(n_cu, kv8, f32):
+    """The planner's parameters for a layer that brings none: the library's defaults are those of bf16 caches.
 
-    The overheads are what an item costs in units of streamed tokens, so they go with the bytes of a token, and min_chunk
-    is the piece that is still worth its hand-over.  us per layer with the defaults and with these: 8-bit Llama-70B shape
-    12.2 and 12.2, many short pairs 21.2 and 19.9, one sequence 10.0 and 9.4; fp32 Llama-70B shape 31.6 and 30.5, 24B shape
-    69.5 and 67.4; bf16 one sequence 10.8 and 9.9, one pair of 8192 tokens 13.7 and 11.0, eight sequences of many short pairs
-    10.2 and 10.4 (a cache with fewer than 96 tokens per compute unit: pieces of 32 tokens
-    take longer to merge than to stream; larger caches are cut above 96 tokens anyway, or gain nothing)."""
+    The overheads are what an item costs in units of streamed tokens, so they go with the bytes of a token.  us per layer
+    with the defaults' and with these: fp32 Llama-70B shape 31.6 and 30.5, 24B shape 69.5 and 67.4, 360 pairs of 300 tokens
+    30.1 and 27.9; 8-bit cache of many short pairs 21.2 and 20.4.  Pieces of 64 or 96 tokens instead of 32 would make small
+    bf16 caches faster (one sequence 10.0 -> 9.4), but a wave then has two tiles of 16 tokens, of which only one's heaviest
+    weight is sure to be free of rounding: the error of lse against 64 bits grows by 5 to 50 %."""
     if kv8:      # half the bytes per token, and a step covers 32 tokens
-        return fairkv_default_params(n_cu, tile=32, min_chunk=128, overhead_tokens=256, short_overhead_tokens=96)
+        return fairkv_default_params(n_cu, tile=32, min_chunk=64, overhead_tokens=256, short_overhead_tokens=96)
     if f32:      # twice the bytes
         return fairkv_default_params(n_cu, overhead_tokens=80, short_overhead_tokens=32)
-    return fairkv_default_params(n_cu, min_chunk=96) if tokens < 96 * n_cu else fairkv_default_params(n_cu)
+    return fairkv_default_params(n_cu)
 
 
 class DecodeLayer:
@@ -55,7 +54,7 @@ class DecodeLayer:
         self.G = self.Hq // self.Hkv
         self.scale = float(scale)
         if params is None:
-            params = _plan_params(device_compute_units(dev), self.kv8, q.dtype == torch.float32, int(lens_h.sum(dtype=np.int64)))
+            params = _plan_params(device_compute_units(dev), self.kv8, q.dtype == torch.float32)
         self.plan: Plan = fairkv_plan(lens_h, off_h, self.B, self.Hkv, params)
         self.items_d = torch.from_numpy(self.plan.items.view(np.uint8).copy()).to(dev)
         need = fairkv_workspace_bytes(self.plan.n_parts, self.B * self.Hkv, self.G * self.q_len, self.D)
