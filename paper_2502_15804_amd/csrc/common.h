@@ -79,20 +79,27 @@ __device__ __forceinline__ T *uniform_ptr(T *p)
 // level all XCDs share, without the cache-wide write-back and invalidate that a device fence costs
 // (measured: tens of microseconds per launch).
 // Stores of four (two) floats at byte off of a base that is the same for the wave; 16-byte (8-byte) aligned.
-// The compiler does not see these stores: drain_vmem() waits for them, and the s_nop stands for the two wait states it
-// would keep between a store of more than 8 bytes and an instruction that overwrites the store's data registers
-// (without it a build in which the very next vector instruction did so stored that instruction's result).
+// The compiler does not see these stores: drain_vmem() waits for them, and the wait states it would keep around them are
+// kept here.  Behind them: the s_nop stands for the two between a store of more than 8 bytes and an instruction that
+// overwrites the store's data registers (without it a build in which the very next vector instruction did so stored that
+// instruction's result).  In front: a memory instruction may read a scalar register no sooner than five wait states after
+// a vector instruction wrote it, which is what the base may be (uniform_ptr ends in a readfirstlane, a spilled register
+// comes back with a readlane); a scalar instruction waits for it by itself, so the base goes through a scalar move.
 typedef __attribute__((ext_vector_type(4))) float f4_t;
 typedef __attribute__((ext_vector_type(2))) float f2_t;
 __device__ __forceinline__ void publish_f32x4(float *base, uint32_t off, float4 x)
 {
     const f4_t v = {x.x, x.y, x.z, x.w};
-    asm volatile("global_store_dwordx4 %0, %1, %2 sc1\n\ts_nop 1" ::"v"(off), "v"(v), "s"(uniform_ptr(base)) : "memory");
+    uint64_t at;
+    asm volatile("s_mov_b64 %0, %3\n\tglobal_store_dwordx4 %1, %2, %0 sc1\n\ts_nop 1"
+                 : "=&s"(at) : "v"(off), "v"(v), "s"(uniform_ptr(base)) : "memory");
 }
 __device__ __forceinline__ void publish_f32x2(float *base, uint32_t off, float x, float y)
 {
     const f2_t v = {x, y};
-    asm volatile("global_store_dwordx2 %0, %1, %2 sc1" ::"v"(off), "v"(v), "s"(uniform_ptr(base)) : "memory");
+    uint64_t at;
+    asm volatile("s_mov_b64 %0, %3\n\tglobal_store_dwordx2 %1, %2, %0 sc1"
+                 : "=&s"(at) : "v"(off), "v"(v), "s"(uniform_ptr(base)) : "memory");
 }
 // Loads go through a buffer resource at the first of the partials: one instruction each, lane offset in a vector
 // register, partial in a scalar one.  kAgent is the sc1 bit in the cache-policy operand.

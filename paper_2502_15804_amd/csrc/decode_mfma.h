@@ -63,10 +63,13 @@ constexpr float kBump = 8.f;  // log2 units a score may exceed the reference max
 // The load is non-temporal (nt): K and V rows are read once per launch, and a stream marked that way does not
 // displace or wait on the L2's other contents.  Measured against the same kernel without the hint: 8 % less time per launch on the 188 MB and 174 MB layers, 4 % on the 68 MB layer,
 // 14 % on a layer of whole pairs of equal length; the sc0 / sc1 bits on top of it change nothing.
-// The s_nop is the wait state the hardware wants between a scalar write of M0 and an LDS load that uses it.
+// The base goes through a scalar move for the same reason as the stores of common.h (publish_f32x4); the move is also the
+// wait state the hardware wants between a scalar write of M0 and an LDS load that uses it.
 __device__ __forceinline__ void load16_to_lds(const void *base, uint32_t off, uint32_t lds_base)
 {
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 nt" ::"v"(off), "s"(base), "s"(lds_base) : "memory", "m0");
+    uint64_t from;
+    asm volatile("s_mov_b32 m0, %3\n\ts_mov_b64 %0, %2\n\tglobal_load_lds_dwordx4 %1, %0 nt"
+                 : "=&s"(from) : "v"(off), "s"(base), "s"(lds_base) : "memory", "m0");
 }
 // N such loads, 1 KB apart in LDS: the instruction's immediate offset moves the LDS address and the global one alike, so
 // M0 is written once.  off[i] + 1024 i is the byte offset of load i from base.
@@ -74,23 +77,26 @@ template <int N>
 __device__ __forceinline__ void load_tile_to_lds(const void *base, const uint32_t (&off)[N], uint32_t lds_base)
 {
     static_assert(N == 2 || N == 4, "loads per tile");
+    uint64_t from;
     if constexpr (N == 2)
-        asm volatile("s_mov_b32 m0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %2 nt\n\t"
-                     "global_load_lds_dwordx4 %1, %2 offset:1024 nt"
-                     ::"v"(off[0]), "v"(off[1]), "s"(base), "s"(lds_base) : "memory", "m0");
+        asm volatile("s_mov_b32 m0, %4\n\ts_mov_b64 %0, %3\n\tglobal_load_lds_dwordx4 %1, %0 nt\n\t"
+                     "global_load_lds_dwordx4 %2, %0 offset:1024 nt"
+                     : "=&s"(from) : "v"(off[0]), "v"(off[1]), "s"(base), "s"(lds_base) : "memory", "m0");
     else
-        asm volatile("s_mov_b32 m0, %5\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %4 nt\n\t"
-                     "global_load_lds_dwordx4 %1, %4 offset:1024 nt\n\t"
-                     "global_load_lds_dwordx4 %2, %4 offset:2048 nt\n\t"
-                     "global_load_lds_dwordx4 %3, %4 offset:3072 nt"
-                     ::"v"(off[0]), "v"(off[1]), "v"(off[2]), "v"(off[3]), "s"(base), "s"(lds_base) : "memory", "m0");
+        asm volatile("s_mov_b32 m0, %6\n\ts_mov_b64 %0, %5\n\tglobal_load_lds_dwordx4 %1, %0 nt\n\t"
+                     "global_load_lds_dwordx4 %2, %0 offset:1024 nt\n\t"
+                     "global_load_lds_dwordx4 %3, %0 offset:2048 nt\n\t"
+                     "global_load_lds_dwordx4 %4, %0 offset:3072 nt"
+                     : "=&s"(from) : "v"(off[0]), "v"(off[1]), "v"(off[2]), "v"(off[3]), "s"(base), "s"(lds_base) : "memory", "m0");
 }
 // The same without the hint, for what several workgroups read (the query rows of a pair whose pieces sit in
 // different slots) or what comes back on every decode step (a layer's item list): 0.3 us per launch less on the
 // workloads with many cut pairs or many items, 0.2 us more on a layer of whole pairs.
 __device__ __forceinline__ void load16_to_lds_keep(const void *base, uint32_t off, uint32_t lds_base)
 {
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base), "s"(lds_base) : "memory", "m0");
+    uint64_t from;
+    asm volatile("s_mov_b32 m0, %3\n\ts_mov_b64 %0, %2\n\tglobal_load_lds_dwordx4 %1, %0"
+                 : "=&s"(from) : "v"(off), "s"(base), "s"(lds_base) : "memory", "m0");
 }
 
 // s_waitcnt that waits for the vector-memory counter only (gfx9 encoding: vmcnt is split
