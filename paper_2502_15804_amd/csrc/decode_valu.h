@@ -5,8 +5,12 @@
 
 namespace fairkv {
 
+// One wave per SIMD: the outputs, K and V of a tile take up to 512 registers.  Held to the 256 of two waves per SIMD,
+// which the 74 KB of LDS would let share a compute unit, <128, 8> spilled 792 of them instead of 356, and the traffic to
+// scratch memory is what the time goes to.  us per layer with two waves and with one: Llama-70B shape 264 and
+// 174, the same with two query heads per KV head 63 and 25, the same with D = 64 87 and 30, 24B shape 273 and 84.
 template <int D, int G>
-__global__ __launch_bounds__(kThreads, 2) void fairkv_decode_valu_kernel(DecodeArgs a)
+__global__ __launch_bounds__(kThreads, 1) void fairkv_decode_valu_kernel(DecodeArgs a)
 {
     using geo = Geo<D>;
     constexpr int LPR = geo::LPR, RPI = geo::RPI, NI = geo::NI, EPC = geo::EPC, DW = geo::DW;
@@ -32,7 +36,8 @@ __global__ __launch_bounds__(kThreads, 2) void fairkv_decode_valu_kernel(DecodeA
     // persistent workgroup: walk the items the planner gave this slot
     const SlotStart slot = slot_start(a);
     for (int ii = slot.i_begin; ii < slot.i_end; ++ii) {
-    const ItemSlot it = item_slot(a, a.items[ii]);
+    const fairkv_item record = a.items[ii];   // a copy: one round trip, where a reference costs one per field checked
+    const ItemSlot it = item_slot(a, record);
     if (!it.valid) continue;   // an item that does not belong to this problem is skipped by the whole workgroup
     const int n = it.n;
     const int n_tiles = (n + kTile - 1) / kTile;

@@ -12,28 +12,43 @@ import subprocess
 
 import pytest
 
+import asm_hazards
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
-def test_hot_kernel_uses_no_scratch_and_fits_the_lds(tmp_path):
+@pytest.fixture(scope="module")
+def compiled(tmp_path_factory):
+    """{kernel: (a function that reads a figure of its resource report, its lines of assembly)}"""
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     if not (os.path.exists(hipcc) or shutil.which(hipcc)):
         pytest.skip("no hipcc")
-    out = str(tmp_path / "k.s")
+    out = str(tmp_path_factory.mktemp("asm") / "k.s")
     res = subprocess.run([hipcc, "--offload-arch=gfx950", "-O3", "-std=c++17", "-Xclang", "-target-feature", "-Xclang",
                           "-packed-fp32-ops", "-mllvm", "-amdgpu-mfma-vgpr-form=1", "-Wno-inline-asm",
                           "-I", os.path.join(ROOT, "include"), "-I", os.path.join(ROOT, "paper_2502_15804_amd", "csrc"),
                           "--cuda-device-only", "-S", "-x", "hip", os.path.join(ROOT, "tests", "kernel_resources.hip"),
                           "-o", out, "-Rpass-analysis=kernel-resource-usage"], capture_output=True, text=True)
     assert res.returncode == 0, res.stderr[-3000:]
-    kernels = re.split(r"remark: Function Name: ", res.stderr)[1:]
-    assert len(kernels) == 3
-    for k in kernels:
-        name = k.split()[0]
-        val = lambda key: int(re.search(key + r": (\d+)", k).group(1))
+    code = dict(asm_hazards.functions(open(out).read()))
+    reports = {k.split()[0]: k for k in re.split(r"remark: Function Name: ", res.stderr)[1:]}
+    assert set(reports) == set(code)
+    figure = lambda report: lambda key: int(re.search(key + r": (\d+)", report).group(1))
+    return {name: (figure(report), code[name]) for name, report in reports.items()}
+
+
+def test_hot_kernel_uses_no_scratch_and_fits_the_lds(compiled):
+    hot = {name: k for name, k in compiled.items() if "valu" not in name}
+    assert len(hot) == 3
+    for name, (val, code) in hot.items():
         assert val(r"ScratchSize \[bytes/lane\]") == 0, name
         assert val("VGPRs Spill") == 0, name
         assert val(r"LDS Size \[bytes/block\]") <= 160 * 1024, name
         assert val(r"Occupancy \[waves/SIMD\]") >= 1, name
-    asm = open(out).read()
-    assert "scratch_" not in asm and "buffer_store" not in asm      # nothing goes to private memory
+        assert not any("scratch_" in t or "buffer_store" in t for t in code), name      # nothing goes to private memory
+
+
+def test_vector_kernel_has_the_registers_of_a_whole_simd(compiled):
+    # with half of them it spills 792 and takes 1.5 to 3 times as long; 356 as built
+    (val, _), = (k for name, k in compiled.items() if "valu" in name)
+    assert val("VGPRs Spill") <= 400
