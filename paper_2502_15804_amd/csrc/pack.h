@@ -24,20 +24,38 @@ struct PackArgs {
     int32_t B, Hkv, T;
 };
 
-// kPackParts workgroups per slot of the work list (grid.y); of an item, which is a run of rows of one pair, workgroup y
-// moves passes y, y + kPackParts, ... of kRowsPerPass rows.
+// gridDim.y workgroups per slot of the work list (pack_parts); of an item, which is a run of rows of one pair, workgroup
+// y moves passes y, y + gridDim.y, ... of kRowsPerPass rows.
 // What bounds it: the memory's rate for reads and writes mixed (a plain copy reaches 4.8 TB/s).  One workgroup per slot,
 // i.e. one per compute unit, has 8 KB of rows on the way and waits for each pass: 39.9 us for the 136 MB of a layer of
 // the Llama-70B shape, 3.4 TB/s.  Two, four, eight: 29.5, 28.3 (4.8 TB/s), 29.8 us; more passes in flight per workgroup
 // instead: 28.5 us for two workgroups with four, slower on small caches (5.5 -> 6.3 us for one sequence).
 constexpr int kPackParts = 4;
+
+// Workgroups per slot.  A workgroup costs the fetches in front of its first pass (slot, item, pair, index), so a slot gets
+// no more of them than it has passes on the average, up to kPackParts; n_rows is what the host knows of the passes.  Up to
+// FAIRKV_MAX_SLOTS slots always get kPackParts: with about one workgroup per compute unit the chip is idle otherwise.
+// us for one, two and four workgroups per slot, L the Llama-70B shape, S 128 pairs of 100 tokens with D = 64:
+//   256 slots          L 40.6 30.1 29.3   S 6.9 6.2 6.2
+//   3072 (L: 2.7 passes a slot, S: 0.1)   L 28.9 28.4 31.0   S 6.3 6.5 6.8
+//   4096 slots of 64 tokens (L: 2)        L 31.4 29.5 30.3   S 6.7 6.9 7.5
+//   2048 slots of 64 tokens (L: 4)        L 30.3 28.8 29.3   S 6.2 6.2 6.5
+// Over 32 to 4096 slots of six caches, planned with the defaults and in pieces of at least 64 tokens, no plan takes more
+// than 2.5 % longer than with one workgroup per slot; four everywhere took up to 13 % longer.
+__host__ __device__ constexpr int pack_parts(int64_t n_rows, int n_slots, int row_bytes)
+{
+    const int64_t passes = n_rows / (4096 / row_bytes) / n_slots;      // of 4 KB of K and of V, per slot
+    return n_slots <= FAIRKV_MAX_SLOTS || passes >= kPackParts ? kPackParts : passes >= 1 || n_slots <= 2048 ? 2 : 1;
+}
+static_assert(kPackParts == 4, "pack_parts gives 4, 2 or 1");
+
 template <int ROWB>
 __global__ __launch_bounds__(256) void fairkv_pack_kernel(PackArgs a)
 {
     typedef __attribute__((ext_vector_type(4))) uint32_t u4;   // rows are read once and written once: non-temporal both ways
     constexpr int PPR = ROWB / 16;            // 16-byte pieces per row
     constexpr int kRowsPerPass = 256 / PPR;
-    const int first_row = blockIdx.y * kRowsPerPass;
+    const int first_row = blockIdx.y * kRowsPerPass, step = gridDim.y * kRowsPerPass;
     const int piece = threadIdx.x % PPR, sub = threadIdx.x / PPR;
     for (int i = a.slot_ptr[blockIdx.x]; i < a.slot_ptr[blockIdx.x + 1]; ++i) {
         const fairkv_item it = a.items[i];
@@ -64,9 +82,9 @@ __global__ __launch_bounds__(256) void fairkv_pack_kernel(PackArgs a)
         // row), not two (index, then row).  Rows past the end and rows with a bad index are loaded from a clamped
         // (valid) address and not stored.
         int32_t t_next = kt[min(first_row + sub, n - 1)];
-        for (int r0 = first_row; r0 < n; r0 += kPackParts * kRowsPerPass) {
+        for (int r0 = first_row; r0 < n; r0 += step) {
             const int32_t t = t_next;
-            t_next = kt[min(r0 + kPackParts * kRowsPerPass + sub, n - 1)];
+            t_next = kt[min(r0 + step + sub, n - 1)];
             const int64_t tc = min(max(t, 0), a.T - 1);
             const u4 kk = __builtin_nontemporal_load(reinterpret_cast<const u4 *>(ksrc + tc * ROWB));
             const u4 vv = __builtin_nontemporal_load(reinterpret_cast<const u4 *>(vsrc + tc * ROWB));

@@ -1,5 +1,6 @@
 """fairkv_pack at the edges of its passes: a workgroup moves 8, 16 or 32 rows per pass (rows of 512, 256 or 128 bytes) and
-four workgroups share an item's passes.  Byte for byte what indexing gives."""
+four, two (from 321 slots on) or one (from 2049 on, on a cache this small) workgroups share an item's passes.  Byte for byte
+what indexing gives."""
 import numpy as np
 import pytest
 
@@ -8,7 +9,7 @@ torch = pytest.importorskip("torch")
 
 
 @pytest.mark.parametrize("dtype,D", [(torch.float32, 128), (torch.bfloat16, 128), (torch.uint8, 128), (torch.bfloat16, 64)])
-@pytest.mark.parametrize("n_slots", [1, 5, 64])
+@pytest.mark.parametrize("n_slots", [1, 5, 64, 320, 321, 2048, 2049])
 def test_passes_and_their_remainders(dtype, D, n_slots):
     import paper_2502_15804_amd as F
     B, H, T = 3, 5, 300
