@@ -260,9 +260,12 @@ def _torch():
     global _pt
     if _pt is None:
         import torch
+        raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)    # not a public name: a build may lack it
+        if raw_stream is None:
+            raw_stream = lambda device: torch.cuda.current_stream(device).cuda_stream
         _pt = (torch, {torch.bfloat16: FAIRKV_BF16, torch.float32: FAIRKV_F32}, (torch.uint8, torch.float8_e4m3fn),
                {torch.bfloat16: FAIRKV_BF16, torch.float32: FAIRKV_F32, torch.uint8: FAIRKV_E4M3,
-                torch.float8_e4m3fn: FAIRKV_E4M3}, torch._C._cuda_getCurrentRawStream)
+                torch.float8_e4m3fn: FAIRKV_E4M3}, raw_stream)
     return _pt
 
 
