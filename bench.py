@@ -78,7 +78,7 @@ def parse():
     return ap.parse_args()
 
 
-KV8_PLAN_DEFAULTS = {"tile": 32, "min_chunk": 64, "overhead_tokens": 256}
+KV8_PLAN_DEFAULTS = {"tile": 32, "min_chunk": 64, "overhead_tokens": 256, "short_overhead_tokens": 96}
 
 
 class Rotation:
@@ -840,9 +840,9 @@ def main():
                      "traffic": None if (kv8 or valu or a.q_len > 1) else measured_traffic(a.workload)[0],
                      "traffic_source": None if (kv8 or valu or a.q_len > 1) else
                      f"not measured in this run: read from {measured_traffic(a.workload)[1]} (rocprofv3 FETCH_SIZE and WRITE_SIZE)",
-                     "kernel": f"fairkv_decode_valu_kernel<bf16, {w.D}, {w.G}>" if valu else
+                     "kernel": f"fairkv_decode_valu_kernel<{w.D}, {w.G}>" if valu else
                      f"fairkv_decode_mfma_kernel<{w.D}, {w.G * a.q_len}, DEEP, {'true' if kv8 else 'false'}, SOLO> (DEEP and SOLO "
-                     "are chosen per plan: pairs cut in 32 or more pieces, short whole pairs)",
+                     "are chosen per plan: pairs cut in 16 or more pieces, short whole pairs)",
                      "bytes_per_launch": round(moved / a.steps), "us_per_launch": round(1e3 * ms_step, 3)},
         "paper_context": "FairKV reports up to 1.66x throughput over plain tensor parallelism on 8x A100-80G "
                          "(Llama-3.3-70B, Section 5.2.2); other hardware, not this metric",

@@ -1,12 +1,12 @@
 // Decode kernel for fp32 K/V/q on the matrix cores.
 //
 // What bounds it: HBM.  With G = 8 query heads per KV head a retained token is 1 KB and 4096 flop; as 16x16x4 fp32
-// MFMA tiles (the G heads padded to 16 columns) that is 8 KB of matrix work per KB streamed, i.e. a third of the
+// MFMA tiles (the G heads padded to 16 columns) that is 8192 flop per KB streamed, i.e. a third of the
 // fp32 matrix rate at 6 TB/s.  On the vector ALU the same token cost the softmax of its 64-token tile, one scalar
 // load of q per multiply and the reduction over lanes, and a wave waited for each tile before it asked for the next.
 //
 // Measured against the vector-ALU kernel that served fp32 before: the Llama-70B shape
-// (B 16, 64 / 8 heads, D 128, lognormal budgets, 135 MB) 537 -> 31.7 us per layer, 128 x 8 pairs of 1024 tokens (1.07 GB)
+// (B 16, 64 / 8 heads, D 128, lognormal budgets, 135 MB; the planner's defaults) 537 -> 31.7 us per layer, 128 x 8 pairs of 1024 tokens (1.07 GB)
 // 6.7 TB/s.  Four waves (one per SIMD) against eight: 0.3-1.5 % faster at every size tried, 3 % at 1 GB.
 //
 // Everything stays in 32 bits: an fp32 MFMA multiplies and adds like a chain of fused multiply-adds.

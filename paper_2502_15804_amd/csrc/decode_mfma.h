@@ -242,8 +242,8 @@ __global__ __launch_bounds__(kThreads, 1) void fairkv_decode_mfma_kernel(DecodeA
                                                                                     // the ring may belong to kStages different items
     __shared__ __attribute__((aligned(1024))) fairkv_item raw[kTable];        // items as fetched
     __shared__ __attribute__((aligned(16))) ItemSlot table[kTable];           // items as checked
-    // Two sets, used in turn, so that one barrier per item is enough (one set and a second barrier where 16 columns
-    // would not leave room for two).
+    // Two sets, used in turn, so that one barrier per item is enough; one set and a second barrier with 16 columns, where
+    // at D = 128 two sets do not fit beside the rings (at D = 64 they would).
     constexpr int kSets = G <= 8 ? 2 : 1;
     __shared__ __attribute__((aligned(16))) float st_o[kSets][kWaves * G * kStRow<D>];
     __shared__ __attribute__((aligned(16))) float st_ml[kSets][kWaves * G * 2];

@@ -22,9 +22,12 @@ def device_compute_units(device=None) -> int:
 def _plan_params(n_cu, kv8, f32):
     """The planner's parameters for a layer that brings none: the library's defaults are those of bf16 caches.
 
-    The overheads are what an item costs in units of streamed tokens, so they go with the bytes of a token.  us per layer
-    with the defaults' and with these: fp32 Llama-70B shape 31.6 and 30.5, 24B shape 69.5 and 67.4, 360 pairs of 300 tokens
-    30.1 and 27.9; 8-bit cache of many short pairs 21.2 and 20.4.  Pieces of 64 or 96 tokens instead of 32 would make small
+    The overheads are what an item costs in units of streamed tokens, so they fall with the bytes of a token; the values are
+    measured, not scaled.  us per layer with the defaults' and with these: fp32 Llama-70B shape 31.4 and 30.3, 24B shape 67.2
+    and 64.9; 8-bit cache of many short pairs 21.2 and 20.4.  The fp32 kernel has no single-wave path for short pairs, and
+    what they should cost depends on the cache: with 32, 80 (as any item) and 24 tokens, Pareto budgets at batch 128 take
+    41.1, 43.3 and 41.9 us, 128 pairs of about 60 tokens 10.3, 10.8 and 10.0, 1024 pairs of 40 tokens 18.2, 16.5 and 18.5
+    (the defaults, 160 and 48: 42.9, 11.8, 18.6).  Pieces of 64 or 96 tokens instead of 32 would make small
     bf16 caches faster (one sequence 10.0 -> 9.4), but a wave then has two tiles of 16 tokens, of which only one's heaviest
     weight is sure to be free of rounding: the error of lse against 64 bits grows by 5 to 50 %."""
     if kv8:      # half the bytes per token, and a step covers 32 tokens
