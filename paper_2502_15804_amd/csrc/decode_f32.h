@@ -109,7 +109,8 @@ __global__ __launch_bounds__(kThreads, 1) void fairkv_decode_f32_kernel(DecodeAr
         const bool early = seeded && batch == i_begin;
         if (batch != i_begin) __syncthreads();                  // nobody still reads the previous table
         if (static_cast<int>(threadIdx.x) < nb) {
-            ItemSlot e = item_slot(a, a.items[batch + threadIdx.x]);
+            const fairkv_item record = a.items[batch + threadIdx.x];   // a copy: one round trip, where a reference costs one per field checked
+            ItemSlot e = item_slot(a, record);
             if (early && threadIdx.x == 0) e.n = n0 < kEarlyTok ? n0 : max(e.n, kEarlyTok);   // its first tiles are on their way, as many as n0 said
             table[threadIdx.x] = e;
         }
