@@ -477,9 +477,10 @@ extern "C" int fairkv_pack(const void *k_dense, const void *v_dense, int32_t B, 
     const int rb = row_bytes_of(D, dtype);
     if (rb == 0) return FAIRKV_EUNSUPPORTED;
     PackArgs a{static_cast<const char *>(k_dense), static_cast<const char *>(v_dense), static_cast<char *>(k_out),
-               static_cast<char *>(v_out), keep_ptr, keep_t, off, items, slot_ptr, bad, n_rows, B, Hkv, T};
+               static_cast<char *>(v_out), keep_ptr, keep_t, off, items, slot_ptr, bad, n_rows, B, Hkv, T,
+               pack_parts(n_rows, n_slots, rb)};
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
-    const dim3 grid(static_cast<unsigned>(n_slots), static_cast<unsigned>(pack_parts(n_rows, n_slots, rb)));
+    const dim3 grid(static_cast<unsigned>(n_slots), static_cast<unsigned>(a.parts));
     if (rb == 128)
         hipLaunchKernelGGL(fairkv_pack_kernel<128>, grid, dim3(256), 0, st, a);
     else if (rb == 256)

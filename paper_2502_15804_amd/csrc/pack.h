@@ -22,10 +22,11 @@ struct PackArgs {
     int32_t *bad;                     // rows and items skipped because they point outside; may be null
     int64_t n_rows;
     int32_t B, Hkv, T;
+    int32_t parts;                    // workgroups per slot, which is gridDim.y (read from there it costs the host 0.2 us a launch)
 };
 
-// gridDim.y workgroups per slot of the work list (pack_parts); of an item, which is a run of rows of one pair, workgroup
-// y moves passes y, y + gridDim.y, ... of kRowsPerPass rows.
+// `parts` workgroups per slot of the work list (pack_parts); of an item, which is a run of rows of one pair, workgroup
+// y moves passes y, y + parts, ... of kRowsPerPass rows.
 // What bounds it: the memory's rate for reads and writes mixed (a plain copy reaches 4.8 TB/s).  One workgroup per slot,
 // i.e. one per compute unit, has 8 KB of rows on the way and waits for each pass: 39.9 us for the 136 MB of a layer of
 // the Llama-70B shape, 3.4 TB/s.  Two, four, eight: 29.5, 28.3 (4.8 TB/s), 29.8 us; more passes in flight per workgroup
@@ -55,7 +56,7 @@ __global__ __launch_bounds__(256) void fairkv_pack_kernel(PackArgs a)
     typedef __attribute__((ext_vector_type(4))) uint32_t u4;   // rows are read once and written once: non-temporal both ways
     constexpr int PPR = ROWB / 16;            // 16-byte pieces per row
     constexpr int kRowsPerPass = 256 / PPR;
-    const int first_row = blockIdx.y * kRowsPerPass, step = gridDim.y * kRowsPerPass;
+    const int first_row = blockIdx.y * kRowsPerPass, step = a.parts * kRowsPerPass;
     const int piece = threadIdx.x % PPR, sub = threadIdx.x / PPR;
     for (int i = a.slot_ptr[blockIdx.x]; i < a.slot_ptr[blockIdx.x + 1]; ++i) {
         const fairkv_item it = a.items[i];
