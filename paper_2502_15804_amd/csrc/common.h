@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cmath>
+#include <cstddef>
 #include <cstdint>
 
 #include "fairkv.h"
@@ -112,8 +113,8 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t parts_rsrc(float *base, uint32
 
 constexpr int kScaleHeads = 8;            // KV heads that may carry scales of their own (8-bit caches)
 
-struct DecodeArgs {
-    // What the first requests of a workgroup need comes first: it is read with one round trip (see slot below).
+// What a kernel asks of its arguments at one time or another, 128 bytes: read whole, in one round trip (held_args).
+struct CallArgs {
     const void *q, *k, *v;
     const fairkv_item *items;   // grouped by slot
     int32_t q_len, g_shift;     // new tokens per sequence; log2 of the query heads per KV head.  A kernel's
@@ -124,16 +125,20 @@ struct DecodeArgs {
     int64_t n_rows;             // rows of k and of v
     float *part_o;              // [n_parts][G][D]   unnormalised outputs relative to the item's maximum
     float *part_ml;             // [n_parts][G][2]   (maximum in log2 units, sum of weights)
-    int32_t *arrivals;          // [B*Hkv] items (or groups of items) of a cut pair that have delivered; 0 between calls
-    int32_t *group_arrivals;    // [n_group_counters] the same per group of kGroup items, index first part + group
+    int32_t *arrivals;          // [B*Hkv] items (or groups of items) of a cut pair that have delivered; 0 between calls.
+                                // Behind them [n_group_counters] the same per group of kGroup items, index first part + group
     void *out;
     float *lse;
     float scale_log2;           // scale * log2(e) (times the K scale of an 8-bit cache): scores are kept in log2
                                 // units so exp is one v_exp_f32
     float v_scale;              // 1, or the V scale of an 8-bit cache: multiplies out
+    unsigned long long *trace;  // fairkv_decode_attn_trace only: [workgroups][kTraceStamps], else null
+};
+static_assert(sizeof(CallArgs) == 128, "two cache lines");
+
+struct DecodeArgs : CallArgs {
     float k_head[kScaleHeads];  // 8-bit caches with a scale per KV head: further factors on scale_log2 and v_scale,
     float v_head[kScaleHeads];  // indexed h % kScaleHeads (all 1 otherwise; read by the 8-bit kernels only)
-    unsigned long long *trace;                // fairkv_decode_attn_trace only: [workgroups][kTraceStamps], else null
     // What a workgroup needs before it has read anything from memory, riding in the kernel arguments.  Slot j has words
     // 3 j ...: the index of its first item (its last is the one before slot j + 1's first), the first K/V row of that
     // item, and in one word its query group (b * q_len * Hkv + h, bits 9..31) and min(tok_count, kEarlyTok) (bits
@@ -159,7 +164,7 @@ enum {
     kTraceMergeLoaded,       // the first batch of partials of the merges has landed (this stamp makes the merge wait for it)
     kTraceStamps = 16
 };
-__device__ __forceinline__ void trace_stamp(const DecodeArgs &a, int what, bool who)
+__device__ __forceinline__ void trace_stamp(const CallArgs &a, int what, bool who)
 {
     if (a.trace && who) a.trace[static_cast<size_t>(blockIdx.x) * kTraceStamps + what] = wall_clock64();
 }
@@ -172,12 +177,12 @@ __device__ __forceinline__ uint32_t col_row(int g_shift, int Hq, int c)
 {
     return static_cast<uint32_t>((c >> g_shift) * Hq + (c & ((1 << g_shift) - 1)));
 }
-__device__ __forceinline__ size_t group_row(const DecodeArgs &a, int qg) { return static_cast<size_t>(qg) << a.g_shift; }
+__device__ __forceinline__ size_t group_row(const CallArgs &a, int qg) { return static_cast<size_t>(qg) << a.g_shift; }
 
 // out = o / l (times the output's factor) and lse for coordinates d .. d + 3 of column c of a pair, from its
 // unnormalised output, maximum and weight sum.
 template <int D>
-__device__ __forceinline__ void write_out4(const DecodeArgs &a, int qg, int c, int d, float4 o, float m, float l, float v_mul)
+__device__ __forceinline__ void write_out4(const CallArgs &a, int qg, int c, int d, float4 o, float m, float l, float v_mul)
 {
     const size_t row = group_row(a, qg);
     const uint32_t col = col_row(a.g_shift, a.Hq, c);
@@ -196,6 +201,40 @@ __device__ __forceinline__ SlotStart slot_start(const DecodeArgs &a)
     const uint32_t *w = a.slot + 3 * blockIdx.x;
     return SlotStart{static_cast<int>(w[0]), static_cast<int>(w[3]), w[1], w[2]};
 }
+// The arguments, asked for in one round trip: left to itself the compiler asks for each where it is first used, and with one
+// wave per SIMD every such trip of 500-600 cycles is waited out.  The asm makes it need all of them here.
+__device__ __forceinline__ void arrive_together(const CallArgs &a, const SlotStart &s)
+{
+    asm volatile("" ::"s"(s.i_begin), "s"(s.i_end), "s"(s.row), "s"(s.np), "s"(a.q), "s"(a.k), "s"(a.v), "s"(a.items), "s"(a.q_len),
+                 "s"(a.g_shift), "s"(a.Hq), "s"(a.Hkv), "s"(a.B), "s"(a.out_dtype), "s"(a.n_parts), "s"(a.n_group_counters), "s"(a.n_rows),
+                 "s"(a.part_o), "s"(a.part_ml), "s"(a.arrivals), "s"(a.out), "s"(a.lse), "s"(a.scale_log2), "s"(a.v_scale));
+}
+// ... and kept in the lanes of one vector register (word i in lane i), so that neither another trip nor some twenty scalar
+// registers are spent on what is needed once per item or once per launch: reading a word back is one instruction.
+struct ArgLanes {
+    uint32_t lanes;
+    static constexpr int kWords = sizeof(CallArgs) / 4, kFirst = 6, kLast = 29;      // q, k and v stay in scalar registers; trace is read where it is used
+    __device__ __forceinline__ explicit ArgLanes(const CallArgs &a) : lanes(0)
+    {
+        uint32_t w[kWords];
+        __builtin_memcpy(w, &a, sizeof a);
+#pragma unroll
+        for (int i = kFirst; i <= kLast; i += 4)      // the s_nop is the wait state between a vector instruction and a v_readlane of its result
+            asm("v_writelane_b32 %0, %1, %5\n\tv_writelane_b32 %0, %2, %5+1\n\tv_writelane_b32 %0, %3, %5+2\n\tv_writelane_b32 %0, %4, %5+3\n\ts_nop 0"
+                : "+v"(lanes) : "s"(w[i]), "s"(w[i + 1]), "s"(w[i + 2]), "s"(w[i + 3]), "n"(i));
+    }
+    __device__ __forceinline__ CallArgs get() const
+    {
+        uint32_t w[kWords] = {};
+#pragma unroll
+        for (int i = kFirst; i <= kLast; ++i) w[i] = __builtin_amdgcn_readlane(lanes, i);
+        CallArgs a;
+        __builtin_memcpy(&a, w, sizeof a);
+        return a;
+    }
+};
+static_assert((ArgLanes::kLast + 1 - ArgLanes::kFirst) % 4 == 0, "four at a time");
+static_assert(offsetof(CallArgs, items) == 4 * ArgLanes::kFirst && offsetof(CallArgs, v_scale) == 4 * ArgLanes::kLast, "what the lanes hold");
 
 // Layout facts of the vector-ALU kernel.  A bf16 row of K or V is LPR 16-byte pieces; one wave-wide
 // 16-byte-per-lane access covers RPI whole rows, so every global access is a run of
@@ -257,7 +296,7 @@ constexpr int kMergeBatch = 8;   // partials of a cut pair fetched at once by th
 // A partial goes to the workspace: four consecutive coordinates (the idx-th four of [G][D]) and, with the first of a
 // column, its maximum and weight sum.  Nothing waits for the stores here.
 template <int D, int G>
-__device__ __forceinline__ void publish_part(const DecodeArgs &a, int part, int idx, float4 o, float m, float l)
+__device__ __forceinline__ void publish_part(const CallArgs &a, int part, int idx, float4 o, float m, float l)
 {
     publish_f32x4(a.part_o + static_cast<size_t>(part) * (G * D), idx * 16, o);
     if (idx % (D / 4) == 0) publish_f32x2(a.part_ml + static_cast<size_t>(part) * (G * 2), idx / (D / 4) * 8, m, l);
@@ -277,7 +316,7 @@ struct Merge {
 // is not there costs one branch.  The last workgroup of a launch is usually the last of both its pairs: one merge after the
 // other cost it a round trip more (Llama-70B shape 0.1 us per launch, one sequence 0.2, 8-bit cache 0.2).
 template <int D, int G, bool DEEP, bool TRACE = false>
-__device__ __forceinline__ void merge_parts(const DecodeArgs &a, const Merge (&mg)[kPend])
+__device__ __forceinline__ void merge_parts(const CallArgs &a, const Merge (&mg)[kPend])
 {
     constexpr int D4 = D / 4, NC4 = G * D4, OB = G * D * 4, MB = G * 2 * 4;      // bytes of a partial's outputs, of its statistics
     constexpr int IT = (NC4 + kThreads - 1) / kThreads;                           // fours of coordinates per thread
@@ -351,7 +390,7 @@ __device__ __forceinline__ void merge_parts(const DecodeArgs &a, const Merge (&m
 
 // DEEP: the plan has a pair in kDeepFrom pieces or more.  Without it the group code is not even compiled in.
 template <int D, int G, bool DEEP, bool TRACE = false>
-__device__ __forceinline__ void flush_pending(const DecodeArgs &a, const Piece (&pend)[kPend], int &n_pend, int32_t *roles /* LDS [kPend] */)
+__device__ __forceinline__ void flush_pending(const CallArgs &a, const Piece (&pend)[kPend], int &n_pend, int32_t *roles /* LDS [kPend] */)
 {
     if constexpr (TRACE) trace_stamp(a, kTraceFlushBegin, threadIdx.x == 0);
     drain_vmem();                                      // this thread's stores have reached the shared level ...
@@ -374,7 +413,7 @@ __device__ __forceinline__ void flush_pending(const DecodeArgs &a, const Piece (
                 // two levels only if every group of the pair has a counter
                 const bool deep = nc >= kDeepFrom && static_cast<int64_t>(first) + (nc - 1) / kGroup < a.n_group_counters;
                 if (round == 0 && deep) {
-                    counter = a.group_arrivals + first + chunk / kGroup;
+                    counter = a.arrivals + static_cast<size_t>(a.B) * a.Hkv + first + chunk / kGroup;
                     last = min(kGroup, nc - chunk / kGroup * kGroup) - 1;
                     role_if_last = kRoleGroup;
                 } else if (round == 1) {
@@ -436,7 +475,7 @@ constexpr int kStRow = D + 4;
 // the workspace, without waiting for it, and joins `pend`.  One barrier, before the fold: st_o and st_ml may be
 // written again after the next barrier only.
 template <int D, int G, bool DEEP, bool TRACE = false>
-__device__ __forceinline__ void item_epilogue(const DecodeArgs &a, const Piece &pc, const float *st_o, const float *st_ml,
+__device__ __forceinline__ void item_epilogue(const CallArgs &a, const Piece &pc, const float *st_o, const float *st_ml,
                                               Piece (&pend)[kPend], int &n_pend, int32_t *roles)
 {
     const bool whole_pair = pc.n_chunks == 1;

@@ -190,7 +190,53 @@ __device__ __forceinline__ float quarters_sum(float x)
 // and each cost a memory round trip; alone, four pairs stream side by side.
 constexpr int kSoloTokens = FAIRKV_SHORT_PAIR_TOKENS;
 static_assert(sizeof(ItemSlot) == 48, "item table entry");
-constexpr int kTable = 32 * kWaves;   // items per table fill (each wave fetches 32); longer slot lists go in batches
+constexpr int kTable = 128;           // items per fill of a table in LDS; longer slot lists go in batches
+constexpr int kList = 64;             // items per fill of a wave's list in registers (ItemList): one per lane
+
+// A wave's own copy of (part of) its slot's item list: lane j holds item j.  A field of an item is one v_readlane away,
+// where a table in LDS costs a wait of 130 cycles for each of the handful of fields that start an item, and a barrier
+// after the lanes that check the items have written it: with the arguments held (arrive_together), from a workgroup's first
+// instruction to its first tile 6100 -> 4500 cycles on an idle memory system, us per layer for one sequence 9.9 -> 9.4, for the
+// Llama-70B shape 16.5 -> 16.2, with an 8-bit cache 12.2 -> 11.6.  An item that does not belong to this problem gets n_chunks 0
+// and no tokens.
+struct ItemList {
+    uint32_t row_lo, row_hi;
+    int32_t n, b, h, chunk, n_chunks, part;
+    __device__ __forceinline__ int64_t row(int i) const
+    {
+        return static_cast<int64_t>((static_cast<uint64_t>(__builtin_amdgcn_readlane(row_hi, i)) << 32) | static_cast<uint32_t>(__builtin_amdgcn_readlane(row_lo, i)));
+    }
+    __device__ __forceinline__ int tokens(int i) const { return __builtin_amdgcn_readlane(n, i); }
+    __device__ __forceinline__ int head(int i) const { return __builtin_amdgcn_readlane(h, i); }
+    __device__ __forceinline__ bool valid(int i) const { return __builtin_amdgcn_readlane(n_chunks, i) != 0; }
+    __device__ __forceinline__ int query_group(int qg_stride, int i) const
+    {
+        return __builtin_amdgcn_readlane(b, i) * qg_stride + __builtin_amdgcn_readlane(h, i);
+    }
+    __device__ __forceinline__ bool last_chunk(int i) const
+    {
+        return __builtin_amdgcn_readlane(chunk, i) == __builtin_amdgcn_readlane(n_chunks, i) - 1;
+    }
+    __device__ __forceinline__ Piece piece(const CallArgs &a, int i, float v_mul) const
+    {
+        return Piece{__builtin_amdgcn_readlane(b, i) * a.Hkv + head(i), query_group(a.q_len * a.Hkv, i), __builtin_amdgcn_readlane(part, i),
+                     __builtin_amdgcn_readlane(chunk, i), __builtin_amdgcn_readlane(n_chunks, i), v_mul};
+    }
+};
+// Lane j's item out of the fetched records in LDS, checked without a branch (lanes past the list hold whatever is there).
+__device__ __forceinline__ ItemList item_list(const CallArgs &a, const fairkv_item *raw, int lane)
+{
+    const uint4 x = reinterpret_cast<const uint4 *>(raw + lane)[0], y = reinterpret_cast<const uint4 *>(raw + lane)[1];
+    ItemList e{x.x, x.y, max(static_cast<int>(x.z), 0), static_cast<int>(x.w), static_cast<int>(y.x), static_cast<int>(y.y),
+               static_cast<int>(y.z), static_cast<int>(y.w)};
+    const int64_t row = static_cast<int64_t>((static_cast<uint64_t>(e.row_hi) << 32) | e.row_lo);
+    const bool ok = (static_cast<uint32_t>(e.b) < static_cast<uint32_t>(a.B)) & (static_cast<uint32_t>(e.h) < static_cast<uint32_t>(a.Hkv)) &
+                    (row >= 0) & (row <= a.n_rows - e.n) & (e.chunk >= 0) & (e.chunk < e.n_chunks) & (e.chunk <= e.part) &
+                    (static_cast<int64_t>(e.part - e.chunk) + e.n_chunks <= a.n_parts);
+    e.n = ok ? e.n : 0;
+    e.n_chunks = ok ? e.n_chunks : 0;
+    return e;
+}
 
 // KV8: K and V are stored as 8-bit floats (E4M3), one byte per element, and widened to bf16 in registers
 // (exactly: every E4M3 value is a bf16 value), so the arithmetic is that of the bf16 path.  A row is half as
@@ -209,7 +255,7 @@ constexpr int kTable = 32 * kWaves;   // items per table fill (each wave fetches
 // without any run an instantiation without that code: its presence alone cost 0.3-0.4 us per launch on every
 // workload (measured side by side on one GPU), on a kernel of under 20 us.
 template <int D, int G, bool DEEP, bool KV8, bool SOLO, bool TRACE = false>
-__global__ __launch_bounds__(kThreads, 1) void fairkv_decode_mfma_kernel(DecodeArgs a)
+__global__ __launch_bounds__(kThreads, 1) void fairkv_decode_mfma_kernel(DecodeArgs args)
 {
     static_assert(D == 64 || D == 128, "head_dim");
     static_assert(G >= 1 && G <= 16, "query heads of a group fit the N dimension");
@@ -221,7 +267,7 @@ __global__ __launch_bounds__(kThreads, 1) void fairkv_decode_mfma_kernel(DecodeA
     // the work, finish that much later; the second stage is requested when the item list has landed instead.
     // Side by side on one GPU: 0.4-0.5 us per launch less on all four workloads.
     constexpr int kEarly = 1;
-    static_assert(kStages >= 2 && kStages <= 4 && kEarlyTok >= kEarly * kWaves * TOK && kEarlyTok < 512, "ring, early start");
+    static_assert(kStages == 2 && kEarlyTok >= kEarly * kWaves * TOK && kEarlyTok < 512, "ring, early start");
     static_assert(sizeof(fairkv_item) == 32, "two 16-byte pieces per item");
     constexpr int QROWB = D * 2;             // bytes per q row (bf16)
     constexpr int ROWB = KV8 ? D : D * 2;    // bytes per K or V row
@@ -240,8 +286,7 @@ __global__ __launch_bounds__(kThreads, 1) void fairkv_decode_mfma_kernel(DecodeA
     __shared__ __attribute__((aligned(1024))) char lds[kWaves * kStages * STAGEB];
     __shared__ __attribute__((aligned(1024))) char qlds[kWaves * kStages * QBUF];   // a query block per ring stage: the tiles in
                                                                                     // the ring may belong to kStages different items
-    __shared__ __attribute__((aligned(1024))) fairkv_item raw[kTable];        // items as fetched
-    __shared__ __attribute__((aligned(16))) ItemSlot table[kTable];           // items as checked
+    __shared__ __attribute__((aligned(1024))) fairkv_item raw[kList];         // items as fetched
     // Two sets, used in turn, so that one barrier per item is enough; one set and a second barrier with 16 columns, where
     // at D = 128 two sets do not fit beside the rings (at D = 64 they would).
     constexpr int kSets = G <= 8 ? 2 : 1;
@@ -258,35 +303,10 @@ __global__ __launch_bounds__(kThreads, 1) void fairkv_decode_mfma_kernel(DecodeA
     const int l16 = lane & 15;      // head in B/C operands, token row in the K operand, d in the V operand
     const int lq = lane >> 4;       // which quarter of the contraction index this lane feeds
 
-    if constexpr (TRACE) trace_stamp(a, kTraceStart, threadIdx.x == 0);
-    // Everything the first requests need, in one round trip: left to itself the compiler asks for each kernel argument
-    // where it is first used, five dependent trips of 0.25 us before the first row of K is requested.
-    const SlotStart slot = slot_start(a);
-    const int i_begin = slot.i_begin, i_end = slot.i_end;
-    int g_shift = a.g_shift, Hq = a.Hq;
-    asm volatile("" : "+s"(g_shift), "+s"(Hq)
-                 : "s"(slot.i_begin), "s"(slot.i_end), "s"(slot.row), "s"(slot.np), "s"(a.q), "s"(a.k), "s"(a.v), "s"(a.items));
-    if (i_end <= i_begin) return;   // an idle slot
-    if constexpr (KV8) {
-        // Fixed indices: scalar loads that come back with the other kernel arguments.  Indexed by the item's head
-        // they would be a scalar load per item, waited for in front of its first tile.
-        if (threadIdx.x == 0) {
-#pragma unroll
-            for (int i = 0; i < kScaleHeads; ++i) {
-                head_mul[i] = a.scale_log2 * a.k_head[i];
-                head_mul[kScaleHeads + i] = a.v_scale * a.v_head[i];
-            }
-        }                           // read after the barriers that precede the first item
-    }
-    const uint32_t ring_lds =
-        static_cast<uint32_t>(reinterpret_cast<uintptr_t>(FAIRKV_LDS_PTR(lds))) + wave * (kStages * STAGEB);
-    const char *ring = lds + wave * (kStages * STAGEB);
-    const uint32_t q_lds = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(FAIRKV_LDS_PTR(qlds))) + wave * (kStages * QBUF);
-    const char *q_ring = qlds + wave * (kStages * QBUF);
-    const uint32_t raw_lds = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(FAIRKV_LDS_PTR(raw))) + wave * 1024;
-
+    if constexpr (TRACE) trace_stamp(args, kTraceStart, threadIdx.x == 0);
     // Lane j of load i of a tile fills LDS slot (row i*RPI + j/PPR, column j%PPR); the piece it
-    // fetches is column ^ swizzle(row).  Byte offsets of that piece inside a full K and V tile:
+    // fetches is column ^ swizzle(row).  Byte offsets of that piece inside a full K and V tile (worked out while the kernel
+    // arguments are on their way):
     const int ld_row = lane / PPR, ld_col = lane % PPR;
     uint32_t k_off[LPT], v_off[LPT];
 #pragma unroll
@@ -294,8 +314,122 @@ __global__ __launch_bounds__(kThreads, 1) void fairkv_decode_mfma_kernel(DecodeA
         const int r = i * RPI + ld_row;
         k_off[i] = ld_row * ROWB + (ld_col ^ (r % PPR)) * 16;             // plus i * 1024, which the load adds
         v_off[i] = ld_row * ROWB + (ld_col ^ ((2 * r) % PPR)) * 16;
+        asm volatile("" : "+v"(k_off[i]), "+v"(v_off[i]));
     }
-    // ... and where a lane reads its operands: the K row l16 (pieces 4 s + lq) and, through the
+    const SlotStart slot = slot_start(args);
+    arrive_together(args, slot);
+    const char *const q_base = static_cast<const char *>(args.q), *const k_base = static_cast<const char *>(args.k), *const v_base = static_cast<const char *>(args.v);
+    const int g_shift = args.g_shift;
+    const int i_begin = slot.i_begin, i_end = slot.i_end;
+    if (i_end <= i_begin) return;   // an idle slot
+    const uint32_t ring_lds =
+        static_cast<uint32_t>(reinterpret_cast<uintptr_t>(FAIRKV_LDS_PTR(lds))) + wave * (kStages * STAGEB);
+    const char *ring = lds + wave * (kStages * STAGEB);
+    const uint32_t q_lds = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(FAIRKV_LDS_PTR(qlds))) + wave * (kStages * QBUF);
+    const char *q_ring = qlds + wave * (kStages * QBUF);
+    const uint32_t raw_lds = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(FAIRKV_LDS_PTR(raw))) + wave * 1024;
+
+    // Fetch of the kList items that start at `first`: one load by each of the first two waves (32 items each).  Past the end of
+    // the slot's list the last item is read again.
+    auto fetch_items = [&](const fairkv_item *items, int first) __attribute__((always_inline)) {
+        if (32 * wave >= min(kList, i_end - first)) return;
+        const int rel = min(32 * wave + (lane >> 1), i_end - 1 - first);
+        load16_to_lds_keep(items + first, rel * 32 + (lane & 1) * 16, raw_lds);
+    };
+    fetch_items(args.items, i_begin);
+
+    // tiles of an n-token item that fall to this wave: tiles wave, wave + kWaves, ... of an item the waves share;
+    // all of them, or none, of an item that one wave runs alone
+    auto tiles_of = [&](int n, int owner) __attribute__((always_inline)) {
+        const int n_tiles = (n + TOK - 1) / TOK;
+        if (SOLO && owner >= 0) return owner == wave ? n_tiles : 0;
+        return n_tiles > wave ? (n_tiles - wave + kWaves - 1) / kWaves : 0;
+    };
+    // first token of this wave's t-th tile of an item
+    auto tile_tok0 = [&](int t, int owner) __attribute__((always_inline)) { return (SOLO && owner >= 0 ? t : wave + t * kWaves) * TOK; };
+
+    // Fetch of this wave's t-th tile of an item into one stage: always exactly LOADS loads.
+    // Rows past the end of the item re-read its last row (finite data with weight 0).
+    auto fetch = [&](int64_t row, int n, int t, int owner, int stage) __attribute__((always_inline)) {
+        const int tok0 = tile_tok0(t, owner);
+        const int last = n - 1 - tok0;
+        const char *kbase = k_base + (row + tok0) * ROWB;
+        const char *vbase = v_base + (row + tok0) * ROWB;
+        const uint32_t kst = ring_lds + stage * STAGEB;
+        const uint32_t vst = kst + TILEB;
+        if (last >= TOK - 1) {
+            load_tile_to_lds<LPT>(kbase, k_off, kst);
+            load_tile_to_lds<LPT>(vbase, v_off, vst);
+        } else {
+#pragma unroll
+            for (int i = 0; i < LPT; ++i) {
+                const int r = i * RPI + ld_row;
+                const int rc = min(r, last);
+                load16_to_lds(kbase, rc * ROWB + (ld_col ^ (r % PPR)) * 16, kst + i * 1024);
+                load16_to_lds(vbase, rc * ROWB + (ld_col ^ ((2 * r) % PPR)) * 16, vst + i * 1024);
+            }
+        }
+    };
+
+    // Fetch of the G query rows of query group qg into one of the wave's q buffers: exactly QL loads.
+    // Column c = (new token c >> g_shift, head c & mask) of q [B][q_len][Hq][D]: the heads of one new
+    // token are contiguous, the new tokens are Hq rows apart.
+    uint32_t q_off[QL];
+#pragma unroll
+    for (int i = 0; i < QL; ++i) {
+        const int o = min(i * 1024 + lane * 16, QBYTES - 16);      // byte o of the [G][QROWB] image in LDS
+        q_off[i] = col_row(g_shift, args.Hq, o / QROWB) * QROWB + o % QROWB;
+    }
+    auto fetch_q = [&](int qg, int buf) __attribute__((always_inline)) {
+        const char *src = q_base + (static_cast<size_t>(qg) << g_shift) * QROWB;
+#pragma unroll
+        for (int i = 0; i < QL; ++i) load16_to_lds_keep(src, q_off[i], q_lds + buf * QBUF + i * 1024);
+    };
+
+    // Ring bookkeeping: the fetch cursor (f_*) runs ahead of the compute cursor, possibly into
+    // later items; `ahead` tiles are fetched and not yet consumed.  The query block of an item is
+    // requested right before the item's first tile, into the q buffer of that tile's stage, so it
+    // has landed when the tile has; bit s of q_mask says that the tile now in stage s came with one.
+    int f_item = 0, f_t = 0, f_stage = 0, c_stage = 0, ahead = 0, f_n = 0, f_tiles = 0, f_qg = 0, f_owner = -1;
+    int64_t f_row = 0;
+    uint32_t q_mask = 0;
+    auto fetch_next = [&]() __attribute__((always_inline)) {      // the cursor's tile, f_t < f_tiles
+        if (f_t == 0) {
+            fetch_q(f_qg, f_stage);
+            q_mask |= 1u << f_stage;
+        }
+        fetch(f_row, f_n, f_t, f_owner, f_stage);
+        f_stage = f_stage + 1 == kStages ? 0 : f_stage + 1;
+        ++f_t;
+        ++ahead;
+    };
+
+    // Early start: the kernel arguments carry query group, first row and the first kEarlyTok tokens' worth
+    // of the length of the slot's first item, so the item list, the first query block and the first
+    // tiles are all requested at once, before anything has come back from memory.
+    const int n0 = static_cast<int>(slot.np & 0x1ffu);
+    const bool seeded = n0 > 0;
+    if (seeded) {
+        f_qg = static_cast<int>(slot.np >> 9);
+        f_row = slot.row;
+        f_n = n0;
+        f_tiles = tiles_of(n0, -1);          // the early start always shares the first item among the waves
+        while (ahead < kEarly && f_t < f_tiles) fetch_next();
+    }
+    const ArgLanes arg_lanes(args);
+    const float scale_log2 = args.scale_log2;
+    const int q_len = args.q_len, qg_stride = q_len * args.Hkv;      // query groups of a sequence
+    if constexpr (KV8) {
+        if (threadIdx.x == 0) {
+#pragma unroll
+            for (int i = 0; i < kScaleHeads; ++i) {
+                head_mul[i] = args.scale_log2 * args.k_head[i];
+                head_mul[kScaleHeads + i] = args.v_scale * args.v_head[i];
+            }
+        }                           // read after the barriers that precede the first item
+    }
+
+    // Where a lane reads its operands in a tile: the K row l16 (pieces 4 s + lq) and, through the
     // transposing read, 4 d's of V row 4 lq + l16/4 (lane j of a 16-lane group receives element
     // j%4 of the rows its lanes 4i + j/4 address).
     // (8-bit caches: 8 bytes of K row l16 or 16 + l16 at byte 32 s + 8 lq; for V the fragment this
@@ -323,121 +457,36 @@ __global__ __launch_bounds__(kThreads, 1) void fairkv_decode_mfma_kernel(DecodeA
         for (int nb_ = 0; nb_ < NDB; ++nb_) v_rd[nb_] = TILEB + vrow * ROWB + ((nb_ ^ ((2 * vrow) % PPR)) * 16) + (l16 & 1) * 8;
     }
 
-    // tiles of an n-token item that fall to this wave: tiles wave, wave + kWaves, ... of an item the waves share;
-    // all of them, or none, of an item that one wave runs alone
-    auto tiles_of = [&](int n, int owner) __attribute__((always_inline)) {
-        const int n_tiles = (n + TOK - 1) / TOK;
-        if (SOLO && owner >= 0) return owner == wave ? n_tiles : 0;
-        return n_tiles > wave ? (n_tiles - wave + kWaves - 1) / kWaves : 0;
-    };
-    // first token of this wave's t-th tile of an item
-    auto tile_tok0 = [&](int t, int owner) __attribute__((always_inline)) { return (SOLO && owner >= 0 ? t : wave + t * kWaves) * TOK; };
-
-    // Fetch of this wave's t-th tile of an item into one stage: always exactly LOADS loads.
-    // Rows past the end of the item re-read its last row (finite data with weight 0).
-    auto fetch = [&](int64_t row, int n, int t, int owner, int stage) __attribute__((always_inline)) {
-        const int tok0 = tile_tok0(t, owner);
-        const int last = n - 1 - tok0;
-        const char *kbase = static_cast<const char *>(a.k) + (row + tok0) * ROWB;
-        const char *vbase = static_cast<const char *>(a.v) + (row + tok0) * ROWB;
-        const uint32_t kst = ring_lds + stage * STAGEB;
-        const uint32_t vst = kst + TILEB;
-        if (last >= TOK - 1) {
-            load_tile_to_lds<LPT>(kbase, k_off, kst);
-            load_tile_to_lds<LPT>(vbase, v_off, vst);
-        } else {
-#pragma unroll
-            for (int i = 0; i < LPT; ++i) {
-                const int r = i * RPI + ld_row;
-                const int rc = min(r, last);
-                load16_to_lds(kbase, rc * ROWB + (ld_col ^ (r % PPR)) * 16, kst + i * 1024);
-                load16_to_lds(vbase, rc * ROWB + (ld_col ^ ((2 * r) % PPR)) * 16, vst + i * 1024);
-            }
-        }
-    };
-
-    // Fetch of the G query rows of query group qg into one of the wave's q buffers: exactly QL loads.
-    // Column c = (new token c >> g_shift, head c & mask) of q [B][q_len][Hq][D]: the heads of one new
-    // token are contiguous, the new tokens are Hq rows apart.
-    auto fetch_q = [&](int qg, int buf) __attribute__((always_inline)) {
-        const char *src = static_cast<const char *>(a.q) + (static_cast<size_t>(qg) << g_shift) * QROWB;
-#pragma unroll
-        for (int i = 0; i < QL; ++i) {
-            const int o = min(i * 1024 + lane * 16, QBYTES - 16);      // byte o of the [G][QROWB] image in LDS
-            load16_to_lds_keep(src, col_row(g_shift, Hq, o / QROWB) * QROWB + o % QROWB, q_lds + buf * QBUF + i * 1024);
-        }
-    };
-
-    // Fetch of this wave's 32 of the kTable items that start at `first`: one load.  Past the end of
-    // the slot's list the last item is read again.
-    auto fetch_items = [&](int first) __attribute__((always_inline)) {
-        const int rel = min(32 * wave + (lane >> 1), i_end - 1 - first);
-        load16_to_lds_keep(a.items + first, rel * 32 + (lane & 1) * 16, raw_lds);
-    };
-
-    // Ring bookkeeping: the fetch cursor (f_*) runs ahead of the compute cursor, possibly into
-    // later items; `ahead` tiles are fetched and not yet consumed.  The query block of an item is
-    // requested right before the item's first tile, into the q buffer of that tile's stage, so it
-    // has landed when the tile has; bit s of q_mask says that the tile now in stage s came with one.
-    int f_item = 0, f_t = 0, f_stage = 0, c_stage = 0, ahead = 0, f_n = 0, f_tiles = 0, f_qg = 0, f_owner = -1;
-    int64_t f_row = 0;
-    uint32_t q_mask = 0;
-    auto fetch_next = [&]() __attribute__((always_inline)) {      // the cursor's tile, f_t < f_tiles
-        if (f_t == 0) {
-            // (scalar registers for the load's base address, wherever the compiler kept these wave-uniform values)
-            fetch_q(__builtin_amdgcn_readfirstlane(f_qg), f_stage);
-            q_mask |= 1u << f_stage;
-        }
-        fetch(f_row, f_n, f_t, f_owner, f_stage);
-        f_stage = f_stage + 1 == kStages ? 0 : f_stage + 1;
-        ++f_t;
-        ++ahead;
-    };
-
-    // Early start: the kernel arguments carry query group, first row and the first kEarlyTok tokens' worth
-    // of the length of the slot's first item, so the item list, the first query block and the first
-    // tiles are all requested at once, before anything has come back from memory.
-    fetch_items(i_begin);
-    const int n0 = static_cast<int>(slot.np & 0x1ffu);
-    const bool seeded = n0 > 0;
-    if (seeded) {
-        f_qg = static_cast<int>(slot.np >> 9);
-        f_row = slot.row;
-        f_n = n0;
-        f_tiles = tiles_of(n0, -1);          // the early start always shares the first item among the waves
-        while (ahead < kEarly && f_t < f_tiles) fetch_next();
-    }
-
-    for (int batch = i_begin; batch < i_end; batch += kTable) {
-        const int nb = min(kTable, i_end - batch);
+    for (int batch = i_begin; batch < i_end; batch += kList) {
+        const int nb = min(kList, i_end - batch);
         const bool early = seeded && batch == i_begin;
         if (batch != i_begin) {
             __syncthreads();                  // nobody still reads the previous table
-            fetch_items(batch);
+            fetch_items(arg_lanes.get().items, batch);
         }
-        // the items have landed once only what was requested after them is outstanding
-        wait_all_but<LOADS, QL>(ahead, __builtin_popcount(q_mask));
+        // the items have landed once only what was requested after them, the early start's tile and queries, is outstanding
+        if (ahead > 0)
+            wait_vmcnt<LOADS + QL>();
+        else
+            wait_vmcnt<0>();
         __syncthreads();
-        if (static_cast<int>(threadIdx.x) < nb) {
-            ItemSlot e = item_slot(a, raw[threadIdx.x]);
-            const bool first = early && threadIdx.x == 0;
-            if (first) e.n = n0 < kEarlyTok ? n0 : max(e.n, kEarlyTok);      // its first tiles are on their way, as many as n0 said
-            // short whole pairs go to single waves in turn (not the item the early start has already shared out)
-            if (SOLO && e.valid && e.n_chunks == 1 && e.n <= kSoloTokens && !first) e.owner = threadIdx.x % kWaves;
-            table[threadIdx.x] = e;
-        }
-        __syncthreads();
+        ItemList list = item_list(arg_lanes.get(), raw, lane);
+        if (early && lane == 0) list.n = n0 < kEarlyTok ? n0 : max(list.n, kEarlyTok);      // its first tiles are on their way, as many as n0 said
+        // short whole pairs go to single waves in turn (not the item the early start has already shared out)
+        auto owner_of = [&](int i, int n) __attribute__((always_inline)) {
+            return SOLO && __builtin_amdgcn_readlane(list.n_chunks, i) == 1 && n <= kSoloTokens && !(early && i == 0) ? i % kWaves : -1;
+        };
         if constexpr (TRACE)
-            if (batch == i_begin) trace_stamp(a, kTraceTable, threadIdx.x == 0);
+            if (batch == i_begin) trace_stamp(args, kTraceTable, threadIdx.x == 0);
 
-        auto seek = [&](int item) __attribute__((always_inline)) {           // point the fetch cursor at an item of the table
+        auto seek = [&](int item) __attribute__((always_inline)) {           // point the fetch cursor at an item of the list
             f_item = item;
             f_t = 0;
             if (item < nb) {
-                f_row = uniform64(table[item].row);
-                f_n = __builtin_amdgcn_readfirstlane(table[item].n);
-                f_qg = __builtin_amdgcn_readfirstlane(table[item].qg);
-                f_owner = SOLO ? __builtin_amdgcn_readfirstlane(table[item].owner) : -1;
+                f_row = list.row(item);
+                f_n = list.tokens(item);
+                f_qg = list.query_group(qg_stride, item);
+                f_owner = owner_of(item, f_n);
             } else {
                 f_n = 0;
                 f_owner = -1;
@@ -445,7 +494,7 @@ __global__ __launch_bounds__(kThreads, 1) void fairkv_decode_mfma_kernel(DecodeA
             f_tiles = tiles_of(f_n, f_owner);
         };
         if (early) {                          // the cursor is already inside item 0: learn its full length
-            f_n = __builtin_amdgcn_readfirstlane(table[0].n);
+            f_n = list.tokens(0);
             f_tiles = tiles_of(f_n, -1);
         } else {
             seek(0);
@@ -461,20 +510,20 @@ __global__ __launch_bounds__(kThreads, 1) void fairkv_decode_mfma_kernel(DecodeA
         top_up();
 
         for (int ci = 0; ci < nb; ++ci) {
-            const int n = __builtin_amdgcn_readfirstlane(table[ci].n);
-            const int owner = SOLO ? __builtin_amdgcn_readfirstlane(table[ci].owner) : -1;
+            const int n = list.tokens(ci);
+            const int owner = owner_of(ci, n);
             if (SOLO && owner >= 0 && owner != wave) continue;      // another wave runs this pair alone
             const int my_tiles = tiles_of(n, owner);
             // scores to log2 units, and what multiplies the output: the same for every pair unless an 8-bit cache has
             // a scale per KV head
-            const int scale_h = KV8 ? __builtin_amdgcn_readfirstlane(table[ci].h) % kScaleHeads : 0;
-            const float s_mul = KV8 ? head_mul[scale_h] : a.scale_log2;
-            const Piece pc = piece_of(table[ci], KV8 ? head_mul[kScaleHeads + scale_h] : a.v_scale);
+            const int scale_h = KV8 ? list.head(ci) % kScaleHeads : 0;
+            const float s_mul = KV8 ? head_mul[scale_h] : scale_log2;
             // Several new tokens per sequence: their K/V rows are the last q_len rows of the pair, and
             // new token j does not see the rows of the new tokens after it.  Only the pair's last
             // chunk holds such rows; n_col = tokens of this item the lane's column may see.
-            const int hidden_max = pc.chunk == pc.n_chunks - 1 ? a.q_len - 1 : 0;
-            const int n_col = n - (pc.chunk == pc.n_chunks - 1 ? a.q_len - 1 - (min(l16, G - 1) >> a.g_shift) : 0);
+            const bool last_chunk = list.last_chunk(ci);
+            const int hidden_max = last_chunk ? q_len - 1 : 0;
+            const int n_col = n - (last_chunk ? q_len - 1 - (min(l16, G - 1) >> g_shift) : 0);
             bf16x8_t qb[NSL];
 #pragma unroll
             for (int s = 0; s < NSL; ++s) qb[s] = bf16x8_t{0, 0, 0, 0, 0, 0, 0, 0};
@@ -486,12 +535,17 @@ __global__ __launch_bounds__(kThreads, 1) void fairkv_decode_mfma_kernel(DecodeA
 
             for (int t = 0; t < my_tiles; ++t) {
                 top_up();
-                // Tile t has landed once no more is outstanding than was requested after it: the later
-                // tiles in the ring and their query blocks.
-                wait_all_but<LOADS, QL>(ahead - 1, __builtin_popcount(q_mask & ~(1u << c_stage)));
+                // Tile t has landed once no more is outstanding than was requested after it: the other tile of the ring
+                // and its query block.
                 q_mask &= ~(1u << c_stage);
+                if (ahead == 1)
+                    wait_vmcnt<0>();
+                else if (q_mask == 0)
+                    wait_vmcnt<LOADS>();
+                else
+                    wait_vmcnt<LOADS + QL>();
                 if constexpr (TRACE)
-                    if (batch == i_begin && ci == 0 && t == 0) trace_stamp(a, kTraceFirstTile, threadIdx.x == 0);
+                    if (batch == i_begin && ci == 0 && t == 0) trace_stamp(args, kTraceFirstTile, threadIdx.x == 0);
                 if (t == 0) {
                     // q as the B operand of the score MFMA: lane holds q[head l16][32 s + 8 lq .. +8].  Heads
                     // >= G repeat head G-1: their columns of the products are computed and never stored.
@@ -627,15 +681,18 @@ __global__ __launch_bounds__(kThreads, 1) void fairkv_decode_mfma_kernel(DecodeA
             }
 
             if constexpr (TRACE) {
-                if (batch == i_begin && ci == 0) trace_stamp(a, kTraceItem0Streamed, threadIdx.x == 0);
-                if (batch + ci == i_end - 1) trace_stamp(a, kTraceLastStreamed, threadIdx.x == 0);
+                if (batch == i_begin && ci == 0) trace_stamp(args, kTraceItem0Streamed, threadIdx.x == 0);
+                if (batch + ci == i_end - 1) trace_stamp(args, kTraceLastStreamed, threadIdx.x == 0);
             }
             // ---- fold the four token quarters of l, stage this wave's result, finish the item ------
             l_run = quarters_sum(l_run);
+            const CallArgs a = arg_lanes.get();
+            const Piece pc = list.piece(a, ci, KV8 ? head_mul[kScaleHeads + scale_h] : a.v_scale);
+            const bool valid = pc.n_chunks != 0;
             if (SOLO && owner >= 0) {
                 // This wave has seen the whole pair: out = O / l and lse straight from its registers.  A lane holds
                 // coordinates 16 nb + 4 lq .. + 3 of head l16.
-                if (l16 < G && __builtin_amdgcn_readfirstlane(table[ci].valid)) {
+                if (l16 < G && valid) {
 #pragma unroll
                     for (int nb_ = 0; nb_ < NDB; ++nb_)
                         write_out4<D>(a, pc.qg, l16, 16 * nb_ + 4 * lq, make_float4(o[nb_][0], o[nb_][1], o[nb_][2], o[nb_][3]), m_run,
@@ -652,7 +709,7 @@ __global__ __launch_bounds__(kThreads, 1) void fairkv_decode_mfma_kernel(DecodeA
                     *reinterpret_cast<float2 *>(st_ml[set] + (wave * G + l16) * 2) = make_float2(m_run, l_run);
                 }
             }
-            if (__builtin_amdgcn_readfirstlane(table[ci].valid)) {
+            if (valid) {
                 item_epilogue<D, G, DEEP, TRACE>(a, pc, st_o[set], st_ml[set], pend, n_pend, roles);
                 if constexpr (kSets == 2)
                     set ^= 1;
@@ -660,12 +717,12 @@ __global__ __launch_bounds__(kThreads, 1) void fairkv_decode_mfma_kernel(DecodeA
                     __syncthreads();
             }
             if constexpr (TRACE)
-                if (batch == i_begin && ci == 0) trace_stamp(a, kTraceItem0Done, threadIdx.x == 0);
+                if (batch == i_begin && ci == 0) trace_stamp(args, kTraceItem0Done, threadIdx.x == 0);
         }
         wait_vmcnt<0>();   // nothing of this batch may still be landing in the rings
     }
-    if (n_pend > 0) flush_pending<D, G, DEEP, TRACE>(a, pend, n_pend, roles);
-    if constexpr (TRACE) trace_stamp(a, kTraceEnd, threadIdx.x == 0);
+    if (n_pend > 0) flush_pending<D, G, DEEP, TRACE>(arg_lanes.get(), pend, n_pend, roles);
+    if constexpr (TRACE) trace_stamp(args, kTraceEnd, threadIdx.x == 0);
 }
 
 }  // namespace fairkv

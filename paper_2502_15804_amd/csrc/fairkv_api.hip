@@ -410,7 +410,6 @@ int decode_common(const DecodeCall &c)
     }
     a.slot[3 * n_wg] = static_cast<uint32_t>(n_items);
     a.arrivals = reinterpret_cast<int32_t *>(ws);
-    a.group_arrivals = a.arrivals + static_cast<size_t>(B) * Hkv;
     a.n_group_counters = B * Hkv + FAIRKV_MAX_SLOTS;
     ws += fairkv_workspace_counter_bytes(B * Hkv);
     a.part_ml = reinterpret_cast<float *>(ws);
