@@ -236,6 +236,24 @@ struct ArgLanes {
 static_assert((ArgLanes::kLast + 1 - ArgLanes::kFirst) % 4 == 0, "four at a time");
 static_assert(offsetof(CallArgs, items) == 4 * ArgLanes::kFirst && offsetof(CallArgs, v_scale) == 4 * ArgLanes::kLast, "what the lanes hold");
 
+// The factors of the KV heads of an 8-bit cache, those of K in lanes 0 .. kScaleHeads - 1, those of V in the next lanes.
+__device__ __forceinline__ float lane_values(const float (&k)[kScaleHeads], const float (&v)[kScaleHeads])
+{
+    static_assert(kScaleHeads == 8, "sixteen lanes");
+    float lanes = 0.f;
+#pragma unroll
+    for (int i = 0; i < 2 * kScaleHeads; i += 4) {
+        const float *w = i < kScaleHeads ? k + i : v + (i - kScaleHeads);
+        asm("v_writelane_b32 %0, %1, %5\n\tv_writelane_b32 %0, %2, %5+1\n\tv_writelane_b32 %0, %3, %5+2\n\tv_writelane_b32 %0, %4, %5+3\n\ts_nop 0"
+            : "+v"(lanes) : "s"(w[0]), "s"(w[1]), "s"(w[2]), "s"(w[3]), "n"(i));
+    }
+    return lanes;
+}
+__device__ __forceinline__ float lane_value(float lanes, int i)
+{
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(lanes), i));
+}
+
 // Layout facts of the vector-ALU kernel.  A bf16 row of K or V is LPR 16-byte pieces; one wave-wide
 // 16-byte-per-lane access covers RPI whole rows, so every global access is a run of
 // contiguous, fully used cache lines.

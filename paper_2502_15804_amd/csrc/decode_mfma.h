@@ -11,12 +11,16 @@
 // Shapes.  A wave works on tiles of 16 tokens.  The G query heads sit in the N dimension,
 // padded to 16 with copies of the last head (their columns are computed and never stored):
 //     S^T[token][head] = K[token][:] . q[head][:]       4 x mfma_16x16x32 (contract over d)
-//     O^T[d][head]    += V^T[d][token] P[token][head]   8 x mfma_16x16x16 (contract over tokens)
+//     O^T[d][head]    += V^T[d][token] P[token][head]   8 x mfma_16x16x32 (contract over tokens, twice: see below)
+// A weight goes into the product as two bf16 numbers, its upper half and what that leaves: the contraction has room for
+// 32 numbers where a tile has 16 tokens, and the matrix cores are idle anyway.  Against weights rounded to one bf16 number
+// the error of an fp32 output falls from 1.5e-3 to 2.3e-6 of its norm (Llama-70B shape) and that of lse from 1.3e-5 to 4e-8, for
+// 0 to 0.6 % of the time; pieces of a pair may then be as large as is fast, where fewer and longer ones cost precision before.
 // A lane owns head (lane % 16) in the scores, in P and in O^T alike, so the reference
 // maximum, the rescaling and the bf16 weights never leave the lane.
 //
 // One wave per SIMD means nothing hides a wave's own latencies, so the work on a tile is
-// laid out as one LDS round trip (all K and V reads issued together), the score MFMAs, a
+// laid out as one LDS round trip, the score MFMAs, a
 // handful of vector instructions and the PV MFMAs.  To that end the softmax keeps a stale
 // reference maximum m per head: weights are 2^(s - m) with m raised (and O, l rescaled,
 // which needs the only cross-lane exchange) only when some score exceeds m by more than
@@ -99,6 +103,13 @@ __device__ __forceinline__ void load16_to_lds_keep(const void *base, uint32_t of
                  : "=&s"(from) : "v"(off), "s"(base), "s"(lds_base) : "memory", "m0");
 }
 
+// What lies at an LDS address.
+template <class T>
+__device__ __forceinline__ __attribute__((address_space(3))) T *lds_at(uint32_t address)
+{
+    return reinterpret_cast<__attribute__((address_space(3))) T *>(address);
+}
+
 // s_waitcnt that waits for the vector-memory counter only (gfx9 encoding: vmcnt is split
 // over bits [3:0] and [15:14]; expcnt [6:4] and lgkmcnt [11:8] are left at "no wait").
 template <int N>
@@ -130,12 +141,12 @@ __device__ __forceinline__ void wait_all_but(int tiles, int qs)
 
 // Eight E4M3 bytes widened to eight bf16 (exact; v_cvt_scalef32_pk_bf16_fp8 with scale 1 takes two bytes
 // at a time: the low or the high half of a dword).
-__device__ __forceinline__ bf16x8_t widen8(uint2 w)
+__device__ __forceinline__ bf16x8_t widen8(i32x2_t w)
 {
-    const bf16x2_v a0 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(w.x, 1.0f, false);
-    const bf16x2_v a1 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(w.x, 1.0f, true);
-    const bf16x2_v a2 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(w.y, 1.0f, false);
-    const bf16x2_v a3 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(w.y, 1.0f, true);
+    const bf16x2_v a0 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(w[0], 1.0f, false);
+    const bf16x2_v a1 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(w[0], 1.0f, true);
+    const bf16x2_v a2 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(w[1], 1.0f, false);
+    const bf16x2_v a3 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(w[1], 1.0f, true);
     return bf16x8_t{a0[0], a0[1], a1[0], a1[1], a2[0], a2[1], a3[0], a3[1]};
 }
 
@@ -295,7 +306,6 @@ __global__ __launch_bounds__(kThreads, 1) void fairkv_decode_mfma_kernel(DecodeA
     __shared__ int32_t roles[kPend];
     Piece pend[kPend] = {};
     int set = 0;
-    __shared__ float head_mul[2 * kScaleHeads];      // 8-bit caches: the per-head factors, out of the kernel arguments
     int n_pend = 0;
 
     const int lane = threadIdx.x & 63;
@@ -318,13 +328,13 @@ __global__ __launch_bounds__(kThreads, 1) void fairkv_decode_mfma_kernel(DecodeA
     }
     const SlotStart slot = slot_start(args);
     arrive_together(args, slot);
-    const char *const q_base = static_cast<const char *>(args.q), *const k_base = static_cast<const char *>(args.k), *const v_base = static_cast<const char *>(args.v);
+    const char *const q_base = static_cast<const char *>(args.q), *const k_base = static_cast<const char *>(args.k);
+    const int64_t v_minus_k = static_cast<const char *>(args.v) - k_base;
     const int g_shift = args.g_shift;
     const int i_begin = slot.i_begin, i_end = slot.i_end;
     if (i_end <= i_begin) return;   // an idle slot
     const uint32_t ring_lds =
         static_cast<uint32_t>(reinterpret_cast<uintptr_t>(FAIRKV_LDS_PTR(lds))) + wave * (kStages * STAGEB);
-    const char *ring = lds + wave * (kStages * STAGEB);
     const uint32_t q_lds = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(FAIRKV_LDS_PTR(qlds))) + wave * (kStages * QBUF);
     const char *q_ring = qlds + wave * (kStages * QBUF);
     const uint32_t raw_lds = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(FAIRKV_LDS_PTR(raw))) + wave * 1024;
@@ -332,101 +342,78 @@ __global__ __launch_bounds__(kThreads, 1) void fairkv_decode_mfma_kernel(DecodeA
     // Fetch of the kList items that start at `first`: one load by each of the first two waves (32 items each).  Past the end of
     // the slot's list the last item is read again.
     auto fetch_items = [&](const fairkv_item *items, int first) __attribute__((always_inline)) {
-        if (32 * wave >= min(kList, i_end - first)) return;
-        const int rel = min(32 * wave + (lane >> 1), i_end - 1 - first);
-        load16_to_lds_keep(items + first, rel * 32 + (lane & 1) * 16, raw_lds);
+        const int last = min(kList, i_end - first) - 32 * wave - 1;
+        if (last >= 0) load16_to_lds_keep(items + first + 32 * wave, min(lane >> 1, last) * 32 + (lane & 1) * 16, raw_lds);
     };
     fetch_items(args.items, i_begin);
 
-    // tiles of an n-token item that fall to this wave: tiles wave, wave + kWaves, ... of an item the waves share;
-    // all of them, or none, of an item that one wave runs alone
-    auto tiles_of = [&](int n, int owner) __attribute__((always_inline)) {
-        const int n_tiles = (n + TOK - 1) / TOK;
-        if (SOLO && owner >= 0) return owner == wave ? n_tiles : 0;
-        return n_tiles > wave ? (n_tiles - wave + kWaves - 1) / kWaves : 0;
-    };
-    // first token of this wave's t-th tile of an item
-    auto tile_tok0 = [&](int t, int owner) __attribute__((always_inline)) { return (SOLO && owner >= 0 ? t : wave + t * kWaves) * TOK; };
+    // The fetch cursor (f_*) stands on this wave's next tile of item f_item and runs ahead of the compute cursor, possibly into
+    // later items: f_left tokens of the item from that tile on (none or less: the wave is through with the item), f_k the address
+    // of its first K row, f_step tokens from one of the wave's tiles to the next.  An item's tiles go to the waves in turn (wave,
+    // wave + kWaves, ...), or all to one wave that runs the item alone.  `ahead` tiles are fetched and not yet consumed, the
+    // oldest in stage c_stage.  The query block of an item is requested together with the wave's first tile of it (f_new), into
+    // the q buffer of that tile's stage, so it has landed when the tile has; next_q says that the newest tile came with one.
+    constexpr int kShared = kWaves * TOK;
+    int f_item = 0, f_left = 0, f_step = kShared, f_qg = 0, f_stage = 0, c_stage = 0, ahead = 0;
+    uint64_t f_k = 0;
+    bool f_new = true, next_q = false;
 
-    // Fetch of this wave's t-th tile of an item into one stage: always exactly LOADS loads.
-    // Rows past the end of the item re-read its last row (finite data with weight 0).
-    auto fetch = [&](int64_t row, int n, int t, int owner, int stage) __attribute__((always_inline)) {
-        const int tok0 = tile_tok0(t, owner);
-        const int last = n - 1 - tok0;
-        const char *kbase = k_base + (row + tok0) * ROWB;
-        const char *vbase = v_base + (row + tok0) * ROWB;
-        const uint32_t kst = ring_lds + stage * STAGEB;
-        const uint32_t vst = kst + TILEB;
-        if (last >= TOK - 1) {
-            load_tile_to_lds<LPT>(kbase, k_off, kst);
-            load_tile_to_lds<LPT>(vbase, v_off, vst);
-        } else {
-#pragma unroll
-            for (int i = 0; i < LPT; ++i) {
-                const int r = i * RPI + ld_row;
-                const int rc = min(r, last);
-                load16_to_lds(kbase, rc * ROWB + (ld_col ^ (r % PPR)) * 16, kst + i * 1024);
-                load16_to_lds(vbase, rc * ROWB + (ld_col ^ ((2 * r) % PPR)) * 16, vst + i * 1024);
-            }
-        }
-    };
-
-    // Fetch of the G query rows of query group qg into one of the wave's q buffers: exactly QL loads.
-    // Column c = (new token c >> g_shift, head c & mask) of q [B][q_len][Hq][D]: the heads of one new
-    // token are contiguous, the new tokens are Hq rows apart.
+    // Lane offsets of the G query rows of a query group: column c = (new token c >> g_shift, head c & mask) of
+    // q [B][q_len][Hq][D]: the heads of one new token are contiguous, the new tokens are Hq rows apart.
     uint32_t q_off[QL];
 #pragma unroll
     for (int i = 0; i < QL; ++i) {
         const int o = min(i * 1024 + lane * 16, QBYTES - 16);      // byte o of the [G][QROWB] image in LDS
         q_off[i] = col_row(g_shift, args.Hq, o / QROWB) * QROWB + o % QROWB;
     }
-    auto fetch_q = [&](int qg, int buf) __attribute__((always_inline)) {
-        const char *src = q_base + (static_cast<size_t>(qg) << g_shift) * QROWB;
+    // The cursor's tile into the next stage: LOADS loads, QL more for the queries of another item.  Rows past the end of the item
+    // re-read its last row (finite data with weight 0).
+    auto fetch_next = [&]() __attribute__((always_inline)) {
+        next_q = f_new;
+        if (f_new) {
+            const char *src = q_base + (static_cast<size_t>(f_qg) << g_shift) * QROWB;
 #pragma unroll
-        for (int i = 0; i < QL; ++i) load16_to_lds_keep(src, q_off[i], q_lds + buf * QBUF + i * 1024);
-    };
-
-    // Ring bookkeeping: the fetch cursor (f_*) runs ahead of the compute cursor, possibly into
-    // later items; `ahead` tiles are fetched and not yet consumed.  The query block of an item is
-    // requested right before the item's first tile, into the q buffer of that tile's stage, so it
-    // has landed when the tile has; bit s of q_mask says that the tile now in stage s came with one.
-    int f_item = 0, f_t = 0, f_stage = 0, c_stage = 0, ahead = 0, f_n = 0, f_tiles = 0, f_qg = 0, f_owner = -1;
-    int64_t f_row = 0;
-    uint32_t q_mask = 0;
-    auto fetch_next = [&]() __attribute__((always_inline)) {      // the cursor's tile, f_t < f_tiles
-        if (f_t == 0) {
-            fetch_q(f_qg, f_stage);
-            q_mask |= 1u << f_stage;
+            for (int i = 0; i < QL; ++i) load16_to_lds_keep(src, q_off[i], q_lds + f_stage * QBUF + i * 1024);
+            f_new = false;
         }
-        fetch(f_row, f_n, f_t, f_owner, f_stage);
-        f_stage = f_stage + 1 == kStages ? 0 : f_stage + 1;
-        ++f_t;
+        const char *k = reinterpret_cast<const char *>(f_k), *v = k + v_minus_k;
+        const uint32_t k_lds = ring_lds + f_stage * STAGEB, v_lds = k_lds + TILEB;
+        if (f_left >= TOK) {
+            load_tile_to_lds<LPT>(k, k_off, k_lds);
+            load_tile_to_lds<LPT>(v, v_off, v_lds);
+        } else {
+#pragma unroll
+            for (int i = 0; i < LPT; ++i) {
+                const int r = i * RPI + ld_row, row = min(r, f_left - 1);
+                load16_to_lds(k, row * ROWB + (ld_col ^ (r % PPR)) * 16, k_lds + i * 1024);
+                load16_to_lds(v, row * ROWB + (ld_col ^ ((2 * r) % PPR)) * 16, v_lds + i * 1024);
+            }
+        }
+        f_left -= f_step;
+        f_k += static_cast<uint32_t>(f_step) * ROWB;
+        f_stage ^= 1;
         ++ahead;
     };
+    auto row_address = [&](int64_t row) __attribute__((always_inline)) { return reinterpret_cast<uint64_t>(k_base) + row * ROWB; };
 
-    // Early start: the kernel arguments carry query group, first row and the first kEarlyTok tokens' worth
-    // of the length of the slot's first item, so the item list, the first query block and the first
-    // tiles are all requested at once, before anything has come back from memory.
+    // Early start: the kernel arguments carry query group, first row and the first kEarlyTok tokens' worth of the length of the
+    // slot's first item, so the item list, the first query
+    // block and the first tile are all requested at once, before anything has come back from memory.
     const int n0 = static_cast<int>(slot.np & 0x1ffu);
-    const bool seeded = n0 > 0;
-    if (seeded) {
+    if (n0 > 0) {
         f_qg = static_cast<int>(slot.np >> 9);
-        f_row = slot.row;
-        f_n = n0;
-        f_tiles = tiles_of(n0, -1);          // the early start always shares the first item among the waves
-        while (ahead < kEarly && f_t < f_tiles) fetch_next();
+        f_k = row_address(static_cast<int64_t>(slot.row) + wave * TOK);      // the early start always shares the first item among the waves
+        f_left = n0 - wave * TOK;
+        if (f_left > 0) fetch_next();
     }
     const ArgLanes arg_lanes(args);
     const float scale_log2 = args.scale_log2;
     const int q_len = args.q_len, qg_stride = q_len * args.Hkv;      // query groups of a sequence
+    // 8-bit caches: lane h holds scale_log2 times the K factor of KV head h (modulo kScaleHeads), lane kScaleHeads + h v_scale
+    // times its V factor
+    float head_mul = 0.f;
     if constexpr (KV8) {
-        if (threadIdx.x == 0) {
-#pragma unroll
-            for (int i = 0; i < kScaleHeads; ++i) {
-                head_mul[i] = args.scale_log2 * args.k_head[i];
-                head_mul[kScaleHeads + i] = args.v_scale * args.v_head[i];
-            }
-        }                           // read after the barriers that precede the first item
+        head_mul = lane_values(args.k_head, args.v_head) * (lane < kScaleHeads ? scale_log2 : args.v_scale);
     }
 
     // Where a lane reads its operands in a tile: the K row l16 (pieces 4 s + lq) and, through the
@@ -434,34 +421,71 @@ __global__ __launch_bounds__(kThreads, 1) void fairkv_decode_mfma_kernel(DecodeA
     // j%4 of the rows its lanes 4i + j/4 address).
     // (8-bit caches: 8 bytes of K row l16 or 16 + l16 at byte 32 s + 8 lq; for V the fragment this
     // lane addresses in the transposing read, see above.)
+    // LDS addresses in the stage of the tile that is next to be consumed.
     constexpr int NKR = KV8 ? 2 * NSL : NSL;
     uint32_t k_rd[NKR], v_rd[NDB];
     if constexpr (!KV8) {
 #pragma unroll
-        for (int s = 0; s < NSL; ++s) k_rd[s] = l16 * ROWB + ((4 * s + lq) ^ (l16 % PPR)) * 16;
+        for (int s = 0; s < NSL; ++s) k_rd[s] = ring_lds + l16 * ROWB + ((4 * s + lq) ^ (l16 % PPR)) * 16;
         const int vrow = 4 * lq + (l16 >> 2), vsub = l16 & 3;
 #pragma unroll
         for (int nb_ = 0; nb_ < NDB; ++nb_)
-            v_rd[nb_] = TILEB + vrow * ROWB + (((2 * nb_ + (vsub >> 1)) ^ ((2 * vrow) % PPR)) * 16) + (vsub & 1) * 8;
+            v_rd[nb_] = ring_lds + TILEB + vrow * ROWB + (((2 * nb_ + (vsub >> 1)) ^ ((2 * vrow) % PPR)) * 16) + (vsub & 1) * 8;
     } else {
 #pragma unroll
         for (int u = 0; u < 2; ++u)
 #pragma unroll
             for (int s = 0; s < NSL; ++s) {
                 const int row = 16 * u + l16;
-                k_rd[u * NSL + s] = row * ROWB + (((2 * s + (lq >> 1)) ^ (row % PPR)) * 16) + (lq & 1) * 8;
+                k_rd[u * NSL + s] = ring_lds + row * ROWB + (((2 * s + (lq >> 1)) ^ (row % PPR)) * 16) + (lq & 1) * 8;
             }
         const int r = l16 >> 1;                                            // which of the lane group's 8 tokens
         const int vrow = r < 4 ? 4 * lq + r : 16 + 4 * lq + (r - 4);
 #pragma unroll
-        for (int nb_ = 0; nb_ < NDB; ++nb_) v_rd[nb_] = TILEB + vrow * ROWB + ((nb_ ^ ((2 * vrow) % PPR)) * 16) + (l16 & 1) * 8;
+        for (int nb_ = 0; nb_ < NDB; ++nb_)
+            v_rd[nb_] = ring_lds + TILEB + vrow * ROWB + ((nb_ ^ ((2 * vrow) % PPR)) * 16) + (l16 & 1) * 8;
     }
+#pragma unroll
+    for (int s = 0; s < NKR; ++s) asm volatile("" : "+v"(k_rd[s]));
+#pragma unroll
+    for (int nb_ = 0; nb_ < NDB; ++nb_) asm volatile("" : "+v"(v_rd[nb_]));
+    const char *q_rd = q_ring + min(l16, G - 1) * QROWB + lq * 16;
+    const int col_hidden = q_len - 1 - (min(l16, G - 1) >> g_shift);      // rows at a pair's end that the lane's column does not see
 
+    ItemList list{};
     for (int batch = i_begin; batch < i_end; batch += kList) {
         const int nb = min(kList, i_end - batch);
-        const bool early = seeded && batch == i_begin;
+        const bool early = n0 > 0 && batch == i_begin;
+        // short whole pairs go to single waves in turn (not the item the early start has already shared out)
+        auto owner_of = [&](int i, int n) __attribute__((always_inline)) {
+            return SOLO && __builtin_amdgcn_readlane(list.n_chunks, i) == 1 && n <= kSoloTokens && !(early && i == 0) ? i % kWaves : -1;
+        };
+        // first token of this wave's first tile of an item, as far from the end as `n` says: none left if another wave runs it
+        auto left_of = [&](int n, int owner) __attribute__((always_inline)) {
+            return SOLO && owner >= 0 ? (owner == wave ? n : 0) : n - wave * TOK;
+        };
+        auto seek = [&](int item) __attribute__((always_inline)) {           // point the fetch cursor at an item of the list
+            f_item = item;
+            f_left = 0;
+            f_new = true;
+            if (item < nb) {
+                const int n = list.tokens(item), owner = owner_of(item, n);
+                f_left = left_of(n, owner);
+                f_step = SOLO && owner >= 0 ? TOK : kShared;
+                f_k = row_address(list.row(item) + (SOLO && owner >= 0 ? 0 : wave * TOK));
+                f_qg = list.query_group(qg_stride, item);
+            }
+        };
+        auto top_up = [&]() __attribute__((always_inline)) {
+            while (ahead < kStages && f_item < nb) {
+                if (f_left > 0)
+                    fetch_next();
+                else
+                    seek(f_item + 1);
+            }
+        };
         if (batch != i_begin) {
-            __syncthreads();                  // nobody still reads the previous table
+            __syncthreads();                  // nobody still reads the previous list
             fetch_items(arg_lanes.get().items, batch);
         }
         // the items have landed once only what was requested after them, the early start's tile and queries, is outstanding
@@ -470,214 +494,163 @@ __global__ __launch_bounds__(kThreads, 1) void fairkv_decode_mfma_kernel(DecodeA
         else
             wait_vmcnt<0>();
         __syncthreads();
-        ItemList list = item_list(arg_lanes.get(), raw, lane);
-        if (early && lane == 0) list.n = n0 < kEarlyTok ? n0 : max(list.n, kEarlyTok);      // its first tiles are on their way, as many as n0 said
-        // short whole pairs go to single waves in turn (not the item the early start has already shared out)
-        auto owner_of = [&](int i, int n) __attribute__((always_inline)) {
-            return SOLO && __builtin_amdgcn_readlane(list.n_chunks, i) == 1 && n <= kSoloTokens && !(early && i == 0) ? i % kWaves : -1;
-        };
-        if constexpr (TRACE)
-            if (batch == i_begin) trace_stamp(args, kTraceTable, threadIdx.x == 0);
-
-        auto seek = [&](int item) __attribute__((always_inline)) {           // point the fetch cursor at an item of the list
-            f_item = item;
-            f_t = 0;
-            if (item < nb) {
-                f_row = list.row(item);
-                f_n = list.tokens(item);
-                f_qg = list.query_group(qg_stride, item);
-                f_owner = owner_of(item, f_n);
-            } else {
-                f_n = 0;
-                f_owner = -1;
-            }
-            f_tiles = tiles_of(f_n, f_owner);
-        };
-        if (early) {                          // the cursor is already inside item 0: learn its full length
-            f_n = list.tokens(0);
-            f_tiles = tiles_of(f_n, -1);
+        list = item_list(arg_lanes.get(), raw, lane);
+        if (early) {                          // the first tile of item 0 is on its way, as far as n0 said: on to its full length
+            const int n = n0 < kEarlyTok ? n0 : max(list.tokens(0), kEarlyTok);
+            if (lane == 0) list.n = n;
+            f_left += n - n0;
         } else {
             seek(0);
         }
-        auto top_up = [&]() __attribute__((always_inline)) {
-            while (ahead < kStages && f_item < nb) {
-                if (f_t < f_tiles)
-                    fetch_next();
-                else
-                    seek(f_item + 1);
-            }
-        };
-        top_up();
+        if constexpr (TRACE)
+            if (batch == i_begin) trace_stamp(args, kTraceTable, threadIdx.x == 0);
 
         for (int ci = 0; ci < nb; ++ci) {
-            const int n = list.tokens(ci);
-            const int owner = owner_of(ci, n);
+            const int n = list.tokens(ci), owner = owner_of(ci, n);
             if (SOLO && owner >= 0 && owner != wave) continue;      // another wave runs this pair alone
-            const int my_tiles = tiles_of(n, owner);
-            // scores to log2 units, and what multiplies the output: the same for every pair unless an 8-bit cache has
-            // a scale per KV head
-            const int scale_h = KV8 ? list.head(ci) % kScaleHeads : 0;
-            const float s_mul = KV8 ? head_mul[scale_h] : scale_log2;
+            const bool last_chunk = list.last_chunk(ci);
+            const int scale_h = list.head(ci) % kScaleHeads;
+            top_up();
+            // tokens of the item from the wave's next tile on
+            int left = left_of(n, owner);
+            const int step = SOLO && owner >= 0 ? TOK : kShared;
+            // scores to log2 units: the same factor for every pair unless an 8-bit cache has a scale per KV head
+            const float s_mul = KV8 ? lane_value(head_mul, scale_h) : scale_log2;
             // Several new tokens per sequence: their K/V rows are the last q_len rows of the pair, and
             // new token j does not see the rows of the new tokens after it.  Only the pair's last
-            // chunk holds such rows; n_col = tokens of this item the lane's column may see.
-            const bool last_chunk = list.last_chunk(ci);
+            // chunk holds such rows.
             const int hidden_max = last_chunk ? q_len - 1 : 0;
-            const int n_col = n - (last_chunk ? q_len - 1 - (min(l16, G - 1) >> g_shift) : 0);
+            const int hidden = last_chunk ? col_hidden : 0;
             bf16x8_t qb[NSL];
-#pragma unroll
-            for (int s = 0; s < NSL; ++s) qb[s] = bf16x8_t{0, 0, 0, 0, 0, 0, 0, 0};
-
             f32x4_t o[NDB];
 #pragma unroll
             for (int nb_ = 0; nb_ < NDB; ++nb_) o[nb_] = f32x4_t{0.f, 0.f, 0.f, 0.f};
             float m_run = -INFINITY, l_run = 0.f;   // reference maximum of the lane's head, this lane's share of the weights
 
-            for (int t = 0; t < my_tiles; ++t) {
-                top_up();
-                // Tile t has landed once no more is outstanding than was requested after it: the other tile of the ring
+            for (bool fresh = true; left > 0; fresh = false) {
+                // The tile has landed once no more is outstanding than was requested after it: the other tile of the ring
                 // and its query block.
-                q_mask &= ~(1u << c_stage);
                 if (ahead == 1)
                     wait_vmcnt<0>();
-                else if (q_mask == 0)
+                else if (!next_q)
                     wait_vmcnt<LOADS>();
                 else
                     wait_vmcnt<LOADS + QL>();
                 if constexpr (TRACE)
-                    if (batch == i_begin && ci == 0 && t == 0) trace_stamp(args, kTraceFirstTile, threadIdx.x == 0);
-                if (t == 0) {
+                    if (batch == i_begin && ci == 0 && fresh) trace_stamp(args, kTraceFirstTile, threadIdx.x == 0);
+                if (fresh) {
                     // q as the B operand of the score MFMA: lane holds q[head l16][32 s + 8 lq .. +8].  Heads
                     // >= G repeat head G-1: their columns of the products are computed and never stored.
-                    const char *qsrc = q_ring + c_stage * QBUF + min(l16, G - 1) * QROWB + lq * 16;
 #pragma unroll
                     for (int s = 0; s < NSL; ++s)
-                        qb[s] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const uint4 *>(qsrc + s * 64));
+                        qb[s] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const uint4 *>(q_rd + c_stage * QBUF + s * 64));
                 }
 
+                constexpr int NS = TOK / 4;                          // scores per lane
+                float sv[NS];
+                const bool masked = left - hidden_max < TOK;         // some column does not see the whole tile
+                // ---- every LDS read of the tile, issued together; scores: S^T[token][head l16], in log2 units
+                i32x2_t vt8[NDB];
+                i16x4_t vt[NDB];
                 if constexpr (KV8) {
-                    // ---- every LDS read of the step, issued together ---------------------------------
-                    const char *st = ring + c_stage * STAGEB;
-                    uint2 kw[NKR];
-                    i32x2_t vt[NDB];
+                    i32x2_t kw[NKR];
 #pragma unroll
-                    for (int s = 0; s < NKR; ++s) kw[s] = *reinterpret_cast<const uint2 *>(st + k_rd[s]);
+                    for (int s = 0; s < NKR; ++s) kw[s] = *lds_at<i32x2_t>(k_rd[s]);
 #pragma unroll
-                    for (int nb_ = 0; nb_ < NDB; ++nb_)
-                        vt[nb_] = __builtin_amdgcn_ds_read_tr8_b64_v2i32(
-                            (__attribute__((address_space(3))) i32x2_t *)FAIRKV_LDS_PTR(st + v_rd[nb_]));
-
-                    // ---- scores of two 16-token tiles: S^T[token 16 u + 4 lq + i][head l16] ----------
+                    for (int nb_ = 0; nb_ < NDB; ++nb_) vt8[nb_] = __builtin_amdgcn_ds_read_tr8_b64_v2i32(lds_at<i32x2_t>(v_rd[nb_]));
+                    // two 16-token tiles: token 16 u + 4 lq + i
                     f32x4_t sacc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
 #pragma unroll
                     for (int u = 0; u < 2; ++u)
 #pragma unroll
                         for (int s = 0; s < NSL; ++s)
                             sacc[u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(widen8(kw[u * NSL + s]), qb[s], sacc[u], 0, 0, 0);
-                    const int tok0 = tile_tok0(t, owner);
-                    const bool masked = n - hidden_max - tok0 < TOK;     // some column does not see the whole step
-                    float sv[8];
 #pragma unroll
-                    for (int r = 0; r < 8; ++r) sv[r] = sacc[r >> 2][r & 3] * s_mul;
-                    if (masked) {
+                    for (int r = 0; r < NS; ++r) sv[r] = sacc[r >> 2][r & 3] * s_mul;
+                } else {
+                    bf16x8_t kw[NSL];
 #pragma unroll
-                        for (int r = 0; r < 8; ++r)
-                            if (16 * (r >> 2) + 4 * lq + (r & 3) >= n_col - tok0) sv[r] = -INFINITY;
-                    }
+                    for (int s = 0; s < NSL; ++s) kw[s] = *lds_at<bf16x8_t>(k_rd[s]);
+#pragma unroll
+                    for (int nb_ = 0; nb_ < NDB; ++nb_) vt[nb_] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(lds_at<i16x4_t>(v_rd[nb_]));
+                    f32x4_t sacc = {0.f, 0.f, 0.f, 0.f};             // token 4 lq + i
+#pragma unroll
+                    for (int s = 0; s < NSL; ++s) sacc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kw[s], qb[s], sacc, 0, 0, 0);
+#pragma unroll
+                    for (int r = 0; r < NS; ++r) sv[r] = sacc[r] * s_mul;
+                }
+                if (masked) {
+                    const int seen = left - hidden - 4 * lq;
+#pragma unroll
+                    for (int r = 0; r < NS; ++r)
+                        if (16 * (r >> 2) + (r & 3) >= seen) sv[r] = -INFINITY;
+                }
 
-                    // ---- raise the reference maximum if some score is far above it ------------------
-                    float mx = fmaxf(fmaxf(fmaxf(sv[0], sv[1]), fmaxf(sv[2], sv[3])), fmaxf(fmaxf(sv[4], sv[5]), fmaxf(sv[6], sv[7])));
-                    if (__builtin_amdgcn_ballot_w64(mx > m_run + kBump) != 0) {
-                        const float m_new = fmaxf(m_run, quarters_max(mx));
+                // ---- raise the reference maximum if some score is far above it (always on the first tile, where there is
+                //      nothing to rescale yet)
+                float mx = fmaxf(fmaxf(sv[0], sv[1]), fmaxf(sv[2], sv[3]));
+                if constexpr (KV8) mx = fmaxf(mx, fmaxf(fmaxf(sv[4], sv[5]), fmaxf(sv[6], sv[7])));
+                if (__builtin_amdgcn_ballot_w64(mx > m_run + kBump) != 0) {
+                    const float m_new = fmaxf(m_run, quarters_max(mx));
+                    if (!fresh) {
                         const float alpha = m_new == m_run ? 1.f : __builtin_amdgcn_exp2f(m_run - m_new);
                         l_run *= alpha;
 #pragma unroll
                         for (int nb_ = 0; nb_ < NDB; ++nb_)
 #pragma unroll
                             for (int i = 0; i < 4; ++i) o[nb_][i] *= alpha;
-                        m_run = m_new;
                     }
-
-                    // ---- weights, rounded to bf16, in the order the contraction index wants them ------
-                    float p[8];
-#pragma unroll
-                    for (int r = 0; r < 8; ++r) p[r] = __builtin_amdgcn_exp2f(sv[r] - m_run);
-                    if (masked) {
-#pragma unroll
-                        for (int r = 0; r < 8; ++r)
-                            if (sv[r] == -INFINITY) p[r] = 0.f;
-                    }
-                    const bf16x8_t pb = __builtin_convertvector(f32x8_t{p[0], p[1], p[2], p[3], p[4], p[5], p[6], p[7]}, bf16x8_t);
-#pragma unroll
-                    for (int r = 0; r < 8; ++r) l_run += static_cast<float>(pb[r]);
-
-                    // ---- O^T[d][head] += V^T P over the 32 tokens ------------------------------------
-#pragma unroll
-                    for (int nb_ = 0; nb_ < NDB; ++nb_)
-                        o[nb_] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                            widen8(uint2{static_cast<uint32_t>(vt[nb_][0]), static_cast<uint32_t>(vt[nb_][1])}), pb, o[nb_], 0, 0, 0);
-                } else {
-                    // ---- every LDS read of the tile, issued together -----------------------------------
-                    const char *st = ring + c_stage * STAGEB;
-                    uint4 kw[NSL];
-                    i16x4_t vt[NDB];
-    #pragma unroll
-                    for (int s = 0; s < NSL; ++s) kw[s] = *reinterpret_cast<const uint4 *>(st + k_rd[s]);
-    #pragma unroll
-                    for (int nb_ = 0; nb_ < NDB; ++nb_)
-                        vt[nb_] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-                            (__attribute__((address_space(3))) i16x4_t *)FAIRKV_LDS_PTR(st + v_rd[nb_]));
-
-                    // ---- scores: S^T[token 4 lq + i][head l16], in log2 units --------------------------
-                    f32x4_t sacc = {0.f, 0.f, 0.f, 0.f};
-    #pragma unroll
-                    for (int s = 0; s < NSL; ++s)
-                        sacc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, kw[s]), qb[s], sacc, 0, 0, 0);
-                    const int tok0 = tile_tok0(t, owner);
-                    const bool masked = n - hidden_max - tok0 < TOK;    // some column does not see the whole tile
-                    float sv[4];
-    #pragma unroll
-                    for (int i = 0; i < 4; ++i) sv[i] = sacc[i] * s_mul;
-                    if (masked) {
-    #pragma unroll
-                        for (int i = 0; i < 4; ++i)
-                            if (4 * lq + i >= n_col - tok0) sv[i] = -INFINITY;
-                    }
-
-                    // ---- raise the reference maximum if some score is far above it (always on the first tile)
-                    float mx = fmaxf(fmaxf(sv[0], sv[1]), fmaxf(sv[2], sv[3]));
-                    if (__builtin_amdgcn_ballot_w64(mx > m_run + kBump) != 0) {
-                        const float m_new = fmaxf(m_run, quarters_max(mx));
-                        const float alpha = m_new == m_run ? 1.f : __builtin_amdgcn_exp2f(m_run - m_new);   // 0 on the first tile
-                        l_run *= alpha;
-    #pragma unroll
-                        for (int nb_ = 0; nb_ < NDB; ++nb_)
-    #pragma unroll
-                            for (int i = 0; i < 4; ++i) o[nb_][i] *= alpha;
-                        m_run = m_new;
-                    }
-
-                    // ---- weights, rounded to bf16; their sum uses the rounded values, so out is an exact
-                    //      convex combination of V rows -------------------------------------------------
-                    float p[4];
-    #pragma unroll
-                    for (int i = 0; i < 4; ++i) p[i] = __builtin_amdgcn_exp2f(sv[i] - m_run);
-                    if (masked) {     // a column that has seen nothing yet has m = -inf: its weights are 0, not exp2(nan)
-    #pragma unroll
-                        for (int i = 0; i < 4; ++i)
-                            if (sv[i] == -INFINITY) p[i] = 0.f;
-                    }
-                    const bf16x4_t pb = __builtin_convertvector(f32x4_t{p[0], p[1], p[2], p[3]}, bf16x4_t);
-    #pragma unroll
-                    for (int i = 0; i < 4; ++i) l_run += static_cast<float>(pb[i]);
-
-                    // ---- O^T[d][head] += V^T P ---------------------------------------------------------
-    #pragma unroll
-                    for (int nb_ = 0; nb_ < NDB; ++nb_)
-                        o[nb_] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(vt[nb_], __builtin_bit_cast(i16x4_t, pb), o[nb_], 0, 0, 0);
+                    m_run = m_new;
                 }
-                c_stage = c_stage + 1 == kStages ? 0 : c_stage + 1;
+
+                // ---- weights ----------------------------------------------------------------------
+                float p[NS];
+#pragma unroll
+                for (int r = 0; r < NS; ++r) p[r] = __builtin_amdgcn_exp2f(sv[r] - m_run);
+                if (masked) {     // a column that has seen nothing yet has m = -inf: its weights are 0, not exp2(nan)
+#pragma unroll
+                    for (int r = 0; r < NS; ++r)
+                        if (sv[r] == -INFINITY) p[r] = 0.f;
+                }
+
+                // ---- O^T[d][head] += V^T P ---------------------------------------------------------
+                if constexpr (KV8) {      // the sum of the weights is that of the rounded ones, so out is an exact convex combination of V rows
+                    uint32_t pw[NS / 2];
+#pragma unroll
+                    for (int r = 0; r < NS; r += 2) {
+                        pw[r / 2] = __builtin_bit_cast(uint32_t, __builtin_convertvector(f2_t{p[r], p[r + 1]}, bf16x2_v));
+                        l_run = l_run + bf16_lo(pw[r / 2]) + bf16_hi(pw[r / 2]);
+                    }
+                    const bf16x8_t pb = __builtin_bit_cast(bf16x8_t, uint4{pw[0], pw[1], pw[2], pw[3]});
+#pragma unroll
+                    for (int nb_ = 0; nb_ < NDB; ++nb_) o[nb_] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(widen8(vt8[nb_]), pb, o[nb_], 0, 0, 0);
+                } else {
+                    // A weight is the sum of two bf16 numbers: its upper half, and what that leaves, rounded, in the other half of the contraction.
+                    // Both are positive if the weight is (the rest exceeds the true one by 2^-22 of the weight), so an infinite V stays one.
+                    uint32_t upper[NS / 2], rest[NS / 2];
+#pragma unroll
+                    for (int r = 0; r < NS; r += 2) {
+                        l_run = l_run + p[r] + p[r + 1];
+                        upper[r / 2] = __builtin_amdgcn_perm(__float_as_uint(p[r + 1]), __float_as_uint(p[r]), 0x07060302u);
+                        const f2_t more = {fmaf(p[r], 1.f + 0x1p-22f, -bf16_hi(__float_as_uint(p[r]))), fmaf(p[r + 1], 1.f + 0x1p-22f, -bf16_hi(__float_as_uint(p[r + 1])))};
+                        rest[r / 2] = __builtin_bit_cast(uint32_t, __builtin_convertvector(more, bf16x2_v));
+                    }
+                    const bf16x8_t pb = __builtin_bit_cast(bf16x8_t, uint4{upper[0], upper[1], rest[0], rest[1]});
+#pragma unroll
+                    for (int nb_ = 0; nb_ < NDB; ++nb_) {
+                        const uint2 x = __builtin_bit_cast(uint2, vt[nb_]);
+                        o[nb_] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, uint4{x.x, x.y, x.x, x.y}), pb, o[nb_], 0, 0, 0);
+                    }
+                }
+                const uint32_t to_other = c_stage == 0 ? STAGEB : -STAGEB;
+#pragma unroll
+                for (int s = 0; s < NKR; ++s) k_rd[s] += to_other;
+#pragma unroll
+                for (int nb_ = 0; nb_ < NDB; ++nb_) v_rd[nb_] += to_other;
+                c_stage ^= 1;
                 --ahead;
+                left -= step;
+                if (left > 0) top_up();
             }
 
             if constexpr (TRACE) {
@@ -687,7 +660,7 @@ __global__ __launch_bounds__(kThreads, 1) void fairkv_decode_mfma_kernel(DecodeA
             // ---- fold the four token quarters of l, stage this wave's result, finish the item ------
             l_run = quarters_sum(l_run);
             const CallArgs a = arg_lanes.get();
-            const Piece pc = list.piece(a, ci, KV8 ? head_mul[kScaleHeads + scale_h] : a.v_scale);
+            const Piece pc = list.piece(a, ci, KV8 ? lane_value(head_mul, kScaleHeads + scale_h) : a.v_scale);
             const bool valid = pc.n_chunks != 0;
             if (SOLO && owner >= 0) {
                 // This wave has seen the whole pair: out = O / l and lse straight from its registers.  A lane holds

@@ -1,0 +1,47 @@
+"""A softmax weight of the bf16 kernel is two bf16 numbers, its upper half and the rounded rest: 2**-16 of it are lost, not the
+2**-9 of one bf16 number, and both are positive, so an infinite V gives an infinite output and not a NaN."""
+import numpy as np
+import pytest
+
+import workloads as W
+from oracle import attention as OA
+from test_gpu_parity import make_case
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+
+@pytest.mark.parametrize("D,G", [(128, 8), (128, 16), (64, 1), (64, 4)])
+@pytest.mark.parametrize("longest", [1, 15, 16, 17, 64, 65, 700])
+def test_weights_and_an_infinite_value(D, G, longest):
+    from paper_2502_15804_amd.runtime import DecodeLayer
+    B, Hkv, q_len = 3, 2, 2 if G == 16 else 1
+    rng = np.random.default_rng(longest + D)
+    lens = rng.integers(min(q_len, longest), longest + 1, size=(B, Hkv)).astype(np.int32)
+    lens[0, 0] = longest
+    lens = np.maximum(lens, q_len)
+    heads = G // q_len
+    w, off, q, k, v = make_case(B, Hkv * heads, Hkv, D, "bf16", lens, seed=G)
+    if q_len > 1:
+        q = torch.randn((B, q_len, Hkv * heads, D), generator=torch.Generator().manual_seed(5)).to(torch.bfloat16)
+    attention = OA.attention_multi if q_len > 1 else OA.attention
+    out, lse = attention(W.to_numpy_bits(q), W.to_numpy_bits(k), W.to_numpy_bits(v), off, lens, w.scale)
+
+    def run():
+        layer = DecodeLayer(q.cuda(), k.cuda(), v.cuda(), off, lens, w.scale)
+        layer.run()
+        return layer.out.cpu().numpy().astype(np.float64), layer.lse.cpu().numpy().astype(np.float64)
+
+    got, got_lse = run()
+    # 2**-16 of each weight, and less than as much again from fp32 sums of at most 700 terms and from the scores
+    assert np.abs(got - out).max() <= 2.0 ** -15 * float(v.float().abs().max())
+    assert np.abs(got_lse - lse).max() <= 1e-5
+    v[int(off[0, 0]), 5] = float("inf")          # the first row of a pair: every new token sees it
+    if longest % 16:                             # (a last tile that is not full reads its last row again, with weight 0)
+        v[int(off[0, 0]) + longest - 1, 5] = 1.0 if longest > 1 else float("inf")
+    got, _ = run()
+    inf = np.zeros(got.shape, dtype=bool)
+    inf[(0, slice(None), slice(0, heads), 5) if q_len > 1 else (0, slice(0, heads), 5)] = True
+    assert np.isfinite(got[~inf]).all()
+    if longest > 1:
+        assert np.isposinf(got[inf]).all()
