@@ -19,22 +19,26 @@ def device_compute_units(device=None) -> int:
                .multi_processor_count)
 
 
-def _plan_params(n_cu, kv8, f32):
-    """The planner's parameters for a layer that brings none: the library's defaults are those of bf16 caches.
+def _plan_params(n_cu, kv8, f32, D, tokens):
+    """The planner's parameters for a layer that brings none: the library's defaults with what was measured for the kind of cache.
 
     The overheads are what an item costs in units of streamed tokens, so they fall with the bytes of a token; the values are
     measured, not scaled.  us per layer with the defaults' and with these: fp32 Llama-70B shape 31.4 and 30.3, 24B shape 67.2
     and 64.9; 8-bit cache of many short pairs 21.2 and 20.4.  The fp32 kernel has no single-wave path for short pairs, and
     what they should cost depends on the cache: with 32, 80 (as any item) and 24 tokens, Pareto budgets at batch 128 take
     41.1, 43.3 and 41.9 us, 128 pairs of about 60 tokens 10.3, 10.8 and 10.0, 1024 pairs of 40 tokens 18.2, 16.5 and 18.5
-    (the defaults, 160 and 48: 42.9, 11.8, 18.6).  Pieces of 64 or 96 tokens instead of 32 would make small
-    bf16 caches faster (one sequence 10.0 -> 9.4), but a wave then has two tiles of 16 tokens, of which only one's heaviest
-    weight is sure to be free of rounding: the error of lse against 64 bits grows by 5 to 50 %."""
+    (the defaults, 160 and 48: 42.9, 11.8, 18.6).
+
+    The smallest piece of a bf16 pair: a smaller one fills more compute units and makes more partials to merge.  us per layer
+    with pieces of at least 32, 64, 96 and 128 tokens: one sequence of eight pairs of 1024 tokens 9.35, 8.75, 8.76, 8.92, of 256
+    6.82, 6.33, 6.85, 6.50, of 200 on the average 7.57, 7.00, 6.94, 7.31; Pareto budgets at batch 8 9.33, 9.31, 9.52, 9.52 and at
+    batch 128 21.62, 21.37, 21.16, 21.09; 24B shape 33.76, 33.53, 33.55, 33.47; with D = 64, where a token is half the bytes, one
+    sequence 8.87, 8.69, 8.53, 8.37 and the Llama-70B shape 11.34, 11.18, 11.08, 11.09.  Hence 64 up to 128 tokens per compute unit."""
     if kv8:      # half the bytes per token, and a step covers 32 tokens
         return fairkv_default_params(n_cu, tile=32, min_chunk=64, overhead_tokens=256, short_overhead_tokens=96)
     if f32:      # twice the bytes
         return fairkv_default_params(n_cu, overhead_tokens=80, short_overhead_tokens=32)
-    return fairkv_default_params(n_cu)
+    return fairkv_default_params(n_cu, min_chunk=64 if D == 128 and tokens < 128 * n_cu else 128)
 
 
 class DecodeLayer:
@@ -57,7 +61,7 @@ class DecodeLayer:
         self.G = self.Hq // self.Hkv
         self.scale = float(scale)
         if params is None:
-            params = _plan_params(device_compute_units(dev), self.kv8, q.dtype == torch.float32)
+            params = _plan_params(device_compute_units(dev), self.kv8, q.dtype == torch.float32, self.D, int(lens_h.sum(dtype=np.int64)))
         self.plan: Plan = fairkv_plan(lens_h, off_h, self.B, self.Hkv, params)
         self.items_d = torch.from_numpy(self.plan.items.view(np.uint8).copy()).to(dev)
         need = fairkv_workspace_bytes(self.plan.n_parts, self.B * self.Hkv, self.G * self.q_len, self.D)
