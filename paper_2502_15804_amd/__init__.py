@@ -3,7 +3,7 @@
 The functions carry the names of the C entry points and only marshal arguments:
 planning runs in the library's host code and attention runs in its HIP kernels.
 PyTorch appears solely as the owner of device memory and streams.  There is no
-fallback: if the shared library has not been built, importing a symbol raises.
+fallback: if the shared libraries have not been built, the first call raises.
 """
 from __future__ import annotations
 
@@ -15,6 +15,7 @@ import numpy as np
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libfairkv.so")
+BINDING_PATH = os.path.join(_HERE, "_binding.so")
 
 FAIRKV_OK, FAIRKV_EINVAL, FAIRKV_ECAP, FAIRKV_EWORKSPACE, FAIRKV_EUNSUPPORTED, FAIRKV_EHIP = 0, -1, -2, -3, -4, -5
 FAIRKV_BF16, FAIRKV_F32, FAIRKV_E4M3, FAIRKV_BF16_VALU = 0, 1, 2, 3
@@ -249,10 +250,7 @@ def fairkv_workspace_bytes(n_parts: int, n_pairs: int, G: int, D: int) -> int:
     return int(lib().fairkv_workspace_bytes(int(n_parts), int(n_pairs), int(G), int(D)))
 
 
-# What every call needs of PyTorch, looked up once: (module, the element types of q and out, those of an 8-bit cache, those
-# that fairkv_pack and fairkv_append move, the function that gives a device's current stream as a number).  A call on the
-# GPU is worth 5 to 20 us, so the binding's own microseconds count: pointers travel as plain integers, which ctypes
-# converts by itself, and streams without a torch.cuda.Stream around them.
+# What every call needs of PyTorch, looked up once: (module, the function that gives a device's current stream as a number).
 _pt = None
 
 
@@ -263,10 +261,32 @@ def _torch():
         raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)    # not a public name: a build may lack it
         if raw_stream is None:
             raw_stream = lambda device: torch.cuda.current_stream(device).cuda_stream
-        _pt = (torch, {torch.bfloat16: FAIRKV_BF16, torch.float32: FAIRKV_F32}, (torch.uint8, torch.float8_e4m3fn),
-               {torch.bfloat16: FAIRKV_BF16, torch.float32: FAIRKV_F32, torch.uint8: FAIRKV_E4M3,
-                torch.float8_e4m3fn: FAIRKV_E4M3}, raw_stream)
+        _pt = (torch, raw_stream)
     return _pt
+
+
+# The per-call part of this binding: a call on the GPU is worth 5 to 20 us, so arguments are checked and converted in native code
+# (csrc/binding.cpp), which gets the addresses of the library's functions from here.
+_native_module = None
+
+
+def _native():
+    global _native_module
+    if _native_module is None:
+        L = lib()
+        if not os.path.exists(BINDING_PATH):
+            raise ImportError(f"{BINDING_PATH} is missing: build it with "
+                              f"`python -m paper_2502_15804_amd.build` (there is no fallback path)")
+        _torch()                                             # the libraries that it is linked with
+        from importlib import machinery, util
+        loader = machinery.ExtensionFileLoader("_binding", BINDING_PATH)
+        m = util.module_from_spec(util.spec_from_file_location("_binding", BINDING_PATH, loader=loader))
+        loader.exec_module(m)
+        m.init(ITEM_DTYPE, *(ctypes.cast(f, ctypes.c_void_p).value for f in (
+            L.fairkv_decode_attn_multi, L.fairkv_decode_attn_static, L.fairkv_decode_attn_trace, L.fairkv_decode_attn_kv8,
+            L.fairkv_decode_attn_kv8_per_head, L.fairkv_pack, L.fairkv_append)))
+        _native_module = m
+    return _native_module
 
 
 def _ptr(t):
@@ -275,23 +295,7 @@ def _ptr(t):
 
 def _stream(stream, t):
     """The stream to enqueue on: the caller's, or the current one of the device of tensor t."""
-    return stream.cuda_stream if stream is not None else _pt[4](t.get_device())
-
-
-def _plan_args(items, items_host, slot_ptr, n_parts):
-    """The plan's arguments of a decode call, checked: items, items_host, n_items, slot_ptr, n_slots, n_parts."""
-    if not isinstance(slot_ptr, np.ndarray) or slot_ptr.dtype != np.int32 or not slot_ptr.flags.c_contiguous:
-        raise TypeError("slot_ptr must be a contiguous host int32 array")
-    if slot_ptr.size < 2:
-        raise ValueError("shape mismatch")
-    item_bytes = items.nbytes
-    if item_bytes % 32 != 0:
-        raise ValueError("items must be a whole number of 32-byte records")
-    if (not isinstance(items_host, np.ndarray) or items_host.dtype != ITEM_DTYPE or not items_host.flags.c_contiguous
-            or items_host.size * 32 != item_bytes):
-        raise TypeError("items_host must be the plan's contiguous item array, as many records as `items`")
-    return (items.data_ptr(), items_host.ctypes.data, item_bytes // 32,
-            slot_ptr.ctypes.data, slot_ptr.size - 1, int(n_parts))
+    return stream.cuda_stream if stream is not None else _torch()[1](t.get_device())
 
 
 def fairkv_decode_attn(q, k, v, items, items_host, slot_ptr, n_parts, workspace, out, lse, scale, Hkv, stream=None,
@@ -308,41 +312,11 @@ def fairkv_decode_attn(q, k, v, items, items_host, slot_ptr, n_parts, workspace,
     items_host and slot_ptr are the plan's HOST arrays (numpy: fairkv_item records, int32
     [n_slots+1]).  Nothing is allocated or synchronised here.
     """
-    torch, dt = _torch()[:2]
-    shape = q.shape
-    if len(shape) == 4:
-        B, q_len, Hq, D = shape
-    else:
-        (B, Hq, D), q_len = shape, 1
-    if q.dtype not in dt or k.dtype != q.dtype or v.dtype != q.dtype or out.dtype not in dt:
-        raise TypeError("q/k/v must share bf16 or fp32; out must be bf16 or fp32")
-    _check_dev(q=q, k=k, v=v, items=items, workspace=workspace, out=out, lse=lse, trace=trace)
-    if lse is not None and lse.dtype != torch.float32:
-        raise TypeError("lse must be float32")
-    k_shape = k.shape
-    if k_shape[1] != D or v.shape != k_shape or out.shape != shape:
-        raise ValueError("shape mismatch")
-    if lse is not None and lse.shape != shape[:-1]:
-        raise ValueError("lse must have q's shape without the last dimension")
-    in_dt = FAIRKV_BF16_VALU if (bf16_on_valu and q.dtype == torch.bfloat16) else dt[q.dtype]
-    head = (q.data_ptr(), k.data_ptr(), v.data_ptr(), k_shape[0], *_plan_args(items, items_host, slot_ptr, n_parts))
-    st = _stream(stream, q)
-    if trace is not None:
-        if q_len != 1 or workspace is None or trace.dtype != torch.int64:
-            raise ValueError("a traced call is a single-token call with a caller's workspace and an int64 trace buffer")
-        name = "fairkv_decode_attn_trace"
-        rc = lib().fairkv_decode_attn_trace(*head, workspace.data_ptr(), workspace.nbytes, out.data_ptr(),
-                                            _ptr(lse), B, Hq, Hkv, D, float(scale), _ptr(trace), trace.numel() * 8, st)
-    elif workspace is None:
-        name = "fairkv_decode_attn_static"
-        rc = lib().fairkv_decode_attn_static(*head, out.data_ptr(), _ptr(lse), B, q_len, Hq, Hkv, D, in_dt, dt[out.dtype],
-                                             float(scale), st)
-    else:
-        name = "fairkv_decode_attn_multi" if q_len > 1 else "fairkv_decode_attn"
-        rc = lib().fairkv_decode_attn_multi(*head, workspace.data_ptr(), workspace.nbytes, out.data_ptr(),
-                                            _ptr(lse), B, q_len, Hq, Hkv, D, in_dt, dt[out.dtype], float(scale), st)
+    rc = (_native_module or _native()).decode((_pt or _torch())[1], q, k, v, items, items_host, slot_ptr, n_parts, workspace, out, lse,
+                                              scale, Hkv, stream, bf16_on_valu, trace)
     if rc != FAIRKV_OK:
-        raise FairKVError(rc, name)
+        raise FairKVError(rc, "fairkv_decode_attn_trace" if trace is not None else "fairkv_decode_attn_static" if workspace is None else
+                          "fairkv_decode_attn_multi" if q.dim() == 4 and q.shape[1] > 1 else "fairkv_decode_attn")
 
 
 def fairkv_decode_attn_kv8(q, k8, v8, k_scale, v_scale, items, items_host, slot_ptr, n_parts, workspace, out, lse,
@@ -354,35 +328,14 @@ def fairkv_decode_attn_kv8(q, k8, v8, k_scale, v_scale, items, items_host, slot_
     per KV head: fairkv_decode_attn_kv8_per_head).  q [B,Hq,D] or [B,q_len,Hq,D] bfloat16.  Everything else as in
     fairkv_decode_attn.
     """
-    torch, dt, bytes_ok = _torch()[:3]
-    shape = q.shape
-    if len(shape) == 4:
-        B, q_len, Hq, D = shape
-    else:
-        (B, Hq, D), q_len = shape, 1
-    if q.dtype != torch.bfloat16 or k8.dtype not in bytes_ok or v8.dtype not in bytes_ok or out.dtype not in dt:
-        raise TypeError("q must be bf16, k8/v8 float8_e4m3fn or uint8, out bf16 or fp32")
-    _check_dev(q=q, k8=k8, v8=v8, items=items, workspace=workspace, out=out, lse=lse)
-    if lse is not None and lse.dtype != torch.float32:
-        raise TypeError("lse must be float32")
-    k_shape = k8.shape
-    if len(k_shape) != 2 or k_shape[1] != D or v8.shape != k_shape or out.shape != shape:
-        raise ValueError("shape mismatch")
-    if lse is not None and lse.shape != shape[:-1]:
-        raise ValueError("lse must have q's shape without the last dimension")
-    tail = (*_plan_args(items, items_host, slot_ptr, n_parts), workspace.data_ptr(), workspace.nbytes, out.data_ptr(),
-            _ptr(lse), B, q_len, Hq, Hkv, D, dt[out.dtype], float(scale), _stream(stream, q))
-    if np.ndim(k_scale) or np.ndim(v_scale):
-        ks = np.ascontiguousarray(np.broadcast_to(np.asarray(k_scale, dtype=np.float32), (Hkv,)))
-        vs = np.ascontiguousarray(np.broadcast_to(np.asarray(v_scale, dtype=np.float32), (Hkv,)))
-        rc = lib().fairkv_decode_attn_kv8_per_head(q.data_ptr(), k8.data_ptr(), v8.data_ptr(), k_shape[0], ks.ctypes.data, vs.ctypes.data,
-                                                   *tail)
-        name = "fairkv_decode_attn_kv8_per_head"
-    else:
-        rc = lib().fairkv_decode_attn_kv8(q.data_ptr(), k8.data_ptr(), v8.data_ptr(), k_shape[0], float(k_scale), float(v_scale), *tail)
-        name = "fairkv_decode_attn_kv8"
+    per_head = (type(k_scale) is not float or type(v_scale) is not float) and bool(np.ndim(k_scale) or np.ndim(v_scale))
+    if per_head:
+        k_scale = np.ascontiguousarray(np.broadcast_to(np.asarray(k_scale, dtype=np.float32), (Hkv,)))
+        v_scale = np.ascontiguousarray(np.broadcast_to(np.asarray(v_scale, dtype=np.float32), (Hkv,)))
+    rc = (_native_module or _native()).decode_8bit((_pt or _torch())[1], q, k8, v8, k_scale, v_scale, items, items_host, slot_ptr, n_parts,
+                                                   workspace, out, lse, scale, Hkv, stream)
     if rc != FAIRKV_OK:
-        raise FairKVError(rc, name)
+        raise FairKVError(rc, "fairkv_decode_attn_kv8_per_head" if per_head else "fairkv_decode_attn_kv8")
 
 
 def _check_dev(**tensors):
@@ -395,20 +348,8 @@ def fairkv_pack(k_dense, v_dense, keep_ptr, keep_t, off, items, slot_ptr, k_out,
     """Enqueue the gather of the kept rows.  All arguments are device tensors: k_dense, v_dense
     [B][Hkv][T][D]; keep_ptr int64 [B*Hkv+1]; keep_t int32; off int64 [B*Hkv]; items uint8 view of a
     plan's item array; slot_ptr int32 [n_slots+1]; k_out, v_out [n_rows][D]; bad int32 [1] or None."""
-    torch, _, _, moved = _torch()[:4]
-    B, Hkv, T, D = k_dense.shape
-    _check_dev(k_dense=k_dense, v_dense=v_dense, keep_ptr=keep_ptr, keep_t=keep_t, off=off, items=items,
-               slot_ptr=slot_ptr, k_out=k_out, v_out=v_out, bad=bad)
-    if (v_dense.shape != k_dense.shape or k_out.shape != v_out.shape or k_out.shape[1] != D
-            or k_out.dtype != k_dense.dtype or v_out.dtype != k_dense.dtype or v_dense.dtype != k_dense.dtype):
-        raise ValueError("shape or dtype mismatch")
-    if (keep_ptr.dtype != torch.int64 or off.dtype != torch.int64 or keep_t.dtype != torch.int32
-            or slot_ptr.dtype != torch.int32 or keep_ptr.numel() != B * Hkv + 1 or off.numel() != B * Hkv
-            or (bad is not None and bad.dtype != torch.int32)):
-        raise TypeError("keep_ptr/off must be int64, keep_t/slot_ptr/bad int32, sized for B*Hkv pairs")
-    rc = lib().fairkv_pack(_ptr(k_dense), _ptr(v_dense), B, Hkv, T, D, moved[k_dense.dtype], _ptr(keep_ptr),
-                           _ptr(keep_t), _ptr(off), _ptr(items), _ptr(slot_ptr), slot_ptr.numel() - 1, _ptr(k_out),
-                           _ptr(v_out), k_out.shape[0], _ptr(bad), _stream(stream, k_dense))
+    rc = (_native_module or _native()).pack((_pt or _torch())[1], k_dense, v_dense, keep_ptr, keep_t, off, items, slot_ptr, k_out, v_out,
+                                            bad, stream)
     if rc != FAIRKV_OK:
         raise FairKVError(rc, "fairkv_pack")
 
@@ -416,18 +357,7 @@ def fairkv_pack(k_dense, v_dense, keep_ptr, keep_t, off, items, slot_ptr, k_out,
 def fairkv_append(k_new, v_new, off, lens, cap, k, v, full=None, stream=None):
     """Enqueue the append of one new row per pair.  Device tensors: k_new, v_new [B][Hkv][D]; off int64,
     lens int32 (updated in place), cap int32, all [B*Hkv]; k, v packed [n_rows][D]; full int32 [1] or None."""
-    torch, _, _, moved = _torch()[:4]
-    B, Hkv, D = k_new.shape
-    _check_dev(k_new=k_new, v_new=v_new, off=off, lens=lens, cap=cap, k=k, v=v, full=full)
-    if (v_new.shape != k_new.shape or k.shape != v.shape or k.shape[1] != D or k.dtype != k_new.dtype
-            or v.dtype != k_new.dtype or v_new.dtype != k_new.dtype):
-        raise ValueError("shape or dtype mismatch")
-    if (off.dtype != torch.int64 or lens.dtype != torch.int32 or cap.dtype != torch.int32
-            or off.numel() != B * Hkv or lens.numel() != B * Hkv or cap.numel() != B * Hkv
-            or (full is not None and full.dtype != torch.int32)):
-        raise TypeError("off must be int64, lens/cap/full int32, sized for B*Hkv pairs")
-    rc = lib().fairkv_append(_ptr(k_new), _ptr(v_new), B, Hkv, D, moved[k_new.dtype], _ptr(off), _ptr(lens), _ptr(cap),
-                             _ptr(k), _ptr(v), k.shape[0], _ptr(full), _stream(stream, k_new))
+    rc = (_native_module or _native()).append((_pt or _torch())[1], k_new, v_new, off, lens, cap, k, v, full, stream)
     if rc != FAIRKV_OK:
         raise FairKVError(rc, "fairkv_append")
 
@@ -447,13 +377,9 @@ def fairkv_plan_grow(items: np.ndarray, B: int, Hkv: int, lens: np.ndarray, cap:
 
 def fairkv_workspace_reset(workspace, n_pairs, stream=None):
     """Enqueue the kernel that zeroes the counter bytes of a device workspace (see the header)."""
-    import torch
-
     _check_dev(workspace=workspace)
-    if stream is None:
-        stream = torch.cuda.current_stream(workspace.device)
     rc = lib().fairkv_workspace_reset(_ptr(workspace), workspace.numel() * workspace.element_size(), int(n_pairs),
-                                      ctypes.c_void_p(stream.cuda_stream))
+                                      _stream(stream, workspace))
     if rc != FAIRKV_OK:
         raise FairKVError(rc, "fairkv_workspace_reset")
 
@@ -461,19 +387,15 @@ def fairkv_workspace_reset(workspace, n_pairs, stream=None):
 def fairkv_stream_probe(k, v, n_workgroups, sink, stream=None, shape=None):
     """Enqueue the do-nothing reader over all of the device tensors k and v (see the header).
     shape: (waves, stages, tile_kib) for fairkv_stream_probe_shape; None = the decode kernel's shape."""
-    import torch
-
     _check_dev(k=k, v=v, sink=sink)
     if sink.numel() * sink.element_size() < 4 * n_workgroups:
         raise ValueError("sink too small")
-    if stream is None:
-        stream = torch.cuda.current_stream(k.device)
     nbytes = min(k.numel() * k.element_size(), v.numel() * v.element_size())
     if shape is not None:
         rc = lib().fairkv_stream_probe_shape(_ptr(k), _ptr(v), nbytes, int(n_workgroups), int(shape[0]), int(shape[1]),
-                                             int(shape[2]), _ptr(sink), ctypes.c_void_p(stream.cuda_stream))
+                                             int(shape[2]), _ptr(sink), _stream(stream, k))
     else:
         rc = lib().fairkv_stream_probe(_ptr(k), _ptr(v), nbytes, int(n_workgroups), _ptr(sink),
-                                       ctypes.c_void_p(stream.cuda_stream))
+                                       _stream(stream, k))
     if rc != FAIRKV_OK:
         raise FairKVError(rc, "fairkv_stream_probe")

@@ -8,16 +8,35 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libfairkv.so")
+BINDING = os.path.join(HERE, "_binding.so")
+BINDING_SOURCE = os.path.join(CSRC, "binding.cpp")
 SOURCES = [os.path.join(CSRC, "fairkv_api.hip"), os.path.join(CSRC, "fairkv_plan.cpp"),
            os.path.join(CSRC, "fairkv_place.cpp")]
 HEADERS = [os.path.join(ROOT, "include", "fairkv.h"), os.path.join(ROOT, "include", "fairkv_measure.h")] + [os.path.join(CSRC, h) for h in ("common.h", "decode_f32.h", "decode_mfma.h", "decode_valu.h", "pack.h", "stream_probe.h")]
 
 
 def is_stale() -> bool:
-    if not os.path.exists(LIB):
-        return True
-    t = os.path.getmtime(LIB)
-    return any(os.path.getmtime(f) > t for f in SOURCES + HEADERS)
+    def older(out, inputs):
+        return not os.path.exists(out) or any(os.path.getmtime(f) > os.path.getmtime(out) for f in inputs)
+    return older(LIB, SOURCES + HEADERS) or older(BINDING, [BINDING_SOURCE] + HEADERS[:2])
+
+
+def build_binding() -> str:
+    """The native part of the Python binding, against the PyTorch and numpy that import it."""
+    import sysconfig
+
+    import numpy
+    import torch
+
+    at = os.path.dirname(torch.__file__)
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-Wall", "-Wextra",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch.compiled_with_cxx11_abi())}", "-I", os.path.join(ROOT, "include"),
+           "-isystem", os.path.join(at, "include"), "-isystem", numpy.get_include(), "-isystem", sysconfig.get_paths()["include"],
+           BINDING_SOURCE, "-o", BINDING, "-L", os.path.join(at, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"]
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    if res.returncode != 0:
+        raise RuntimeError("building the binding failed:\n" + res.stderr)
+    return BINDING
 
 
 def build(force: bool = True, verbose: bool = False) -> str:
@@ -40,6 +59,7 @@ def build(force: bool = True, verbose: bool = False) -> str:
         raise RuntimeError("hipcc failed:\n" + err)
     if verbose and err:
         print(err)
+    build_binding()
     return LIB
 
 

@@ -1,0 +1,38 @@
+"""The native part of the binding refuses what the library cannot take, by the argument's name (no GPU: nothing gets as far as
+a launch), and lets PyTorch's own errors through."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+import paper_2502_15804_amd as F
+
+Q, K = torch.zeros((1, 8, 128)), torch.zeros((4, 128))
+ITEMS, SLOTS = np.zeros(1, F.ITEM_DTYPE), np.zeros(2, np.int32)
+
+
+def decode(q=Q, k=K, v=K, items=K, workspace=K, out=Q, lse=None, **more):
+    F.fairkv_decode_attn(q, k, v, items, ITEMS, SLOTS, 1, workspace, out, lse, 1.0, 1, **more)
+
+
+@pytest.mark.parametrize("change,error,words", [
+    (dict(q="q"), TypeError, "q must be a tensor"), (dict(workspace=3), TypeError, "workspace must be a tensor"),
+    (dict(q=Q.double()), TypeError, "share bf16 or fp32"), (dict(v=K.bfloat16()), TypeError, "share bf16 or fp32"),
+    (dict(out=Q.int()), TypeError, "out must be bf16 or fp32"), (dict(), ValueError, "q must be a contiguous device tensor"),
+    (dict(stream=torch.cuda.Stream), ValueError, "q must be")])
+def test_decode(change, error, words):
+    with pytest.raises(error, match=words):
+        decode(**change)
+
+
+def test_the_others():
+    byte, wide = K.to(torch.uint8), Q.bfloat16()
+    for args, error, words in (((Q, byte, byte), TypeError, "q must be bf16"), ((wide, K, byte), TypeError, "k8/v8"),
+                               ((wide, byte, byte), ValueError, "q must be a contiguous device tensor")):
+        with pytest.raises(error, match=words):
+            F.fairkv_decode_attn_kv8(*args, 1.0, [1.0], K, ITEMS, SLOTS, 1, K, Q, None, 1.0, 1)
+    with pytest.raises(ValueError, match=r"k_new must be \[B, Hkv, D\]"):
+        F.fairkv_append(K, K, K, K, K, K, K)
+    with pytest.raises(ValueError, match="k_dense must be a contiguous device tensor"):
+        F.fairkv_pack(Q[None], Q[None], K, K, K, K, K, K, K)
+    with pytest.raises(TypeError, match="16 arguments"):
+        F._native().decode(Q)
