@@ -7,7 +7,8 @@
 //
 // Measured against the vector-ALU kernel that served fp32 before: the Llama-70B shape
 // (B 16, 64 / 8 heads, D 128, lognormal budgets, 135 MB; the planner's defaults) 537 -> 31.7 us per layer, 128 x 8 pairs of 1024 tokens (1.07 GB)
-// 6.7 TB/s.  Four waves (one per SIMD) against eight: 0.3-1.5 % faster at every size tried, 3 % at 1 GB.
+// 6.7 TB/s; 30.1 -> 28.9 us, one sequence 12.3 -> 11.6, since the kernel's arguments come in one trip and the items sit in
+// registers.  Four waves (one per SIMD) against eight: 0.3-1.5 % faster at every size tried, 3 % at 1 GB.
 //
 // Everything stays in 32 bits: an fp32 MFMA multiplies and adds like a chain of fused multiply-adds.
 //
@@ -29,7 +30,7 @@
 namespace fairkv {
 
 template <int D, int G, bool DEEP>
-__global__ __launch_bounds__(kThreads, 1) void fairkv_decode_f32_kernel(DecodeArgs a)
+__global__ __launch_bounds__(kThreads, 1) void fairkv_decode_f32_kernel(DecodeArgs args)
 {
     static_assert(D == 64 || D == 128, "head_dim");
     static_assert(G >= 1 && G <= 8, "query heads of a group");
@@ -37,7 +38,7 @@ __global__ __launch_bounds__(kThreads, 1) void fairkv_decode_f32_kernel(DecodeAr
     constexpr int NC = D / 16;      // 16-byte pieces of a K row (or q row) per lane
     constexpr int NU = D / 64;      // 16-byte pieces of a V row per lane
 
-    __shared__ __attribute__((aligned(16))) ItemSlot table[kTable];
+    __shared__ __attribute__((aligned(1024))) fairkv_item raw[kList];                   // items as fetched
     __shared__ __attribute__((aligned(16))) float st_o[2][kWaves * G * kStRow<D>];      // two sets, used in turn
     __shared__ __attribute__((aligned(16))) float st_ml[2][kWaves * G * 2];
     __shared__ int32_t roles[kPend];
@@ -48,11 +49,21 @@ __global__ __launch_bounds__(kThreads, 1) void fairkv_decode_f32_kernel(DecodeAr
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int l16 = lane & 15, lq = lane >> 4;
 
-    const SlotStart slot = slot_start(a);            // one round trip for all that the first requests need
+    const SlotStart slot = slot_start(args);
+    arrive_together(args, slot);
+    const char *const q_base = static_cast<const char *>(args.q), *const k_base = static_cast<const char *>(args.k),
+               *const v_base = static_cast<const char *>(args.v);
+    const int g_shift = args.g_shift;
     const int i_begin = slot.i_begin, i_end = slot.i_end;
-    asm volatile("" ::"s"(slot.i_begin), "s"(slot.i_end), "s"(slot.row), "s"(slot.np), "s"(a.q), "s"(a.k), "s"(a.v), "s"(a.items),
-                 "s"(a.g_shift));
     if (i_end <= i_begin) return;   // an idle slot
+
+    // The kList items that start at `first`, 32 by each of the first two waves; past the end of the list its last item again.
+    const uint32_t raw_lds = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(FAIRKV_LDS_PTR(raw))) + wave * 1024;
+    auto fetch_items = [&](const fairkv_item *items, int first) __attribute__((always_inline)) {
+        const int last = min(kList, i_end - first) - 32 * wave - 1;
+        if (last >= 0) load16_to_lds_keep(items + first + 32 * wave, min(lane >> 1, last) * 32 + (lane & 1) * 16, raw_lds);
+    };
+    fetch_items(args.items, i_begin);
 
     // tiles of an n-token item that fall to this wave: wave, wave + kWaves, ...
     auto tiles_of = [&](int n) __attribute__((always_inline)) {
@@ -67,13 +78,13 @@ __global__ __launch_bounds__(kThreads, 1) void fairkv_decode_f32_kernel(DecodeAr
     // One tile: 16 rows from `row` on, of which those up to `last` are the item's.  Rows past it re-read that row;
     // their scores are masked and their V is replaced by zeros.
     auto load_k = [&](int64_t row, int last) __attribute__((always_inline)) {
-        const char *base = static_cast<const char *>(a.k) + row * ROWB;
+        const char *base = k_base + row * ROWB;
         const uint32_t off = min(l16, last) * ROWB + lq * 16;
 #pragma unroll
         for (int c = 0; c < NC; ++c) kr[c] = __builtin_nontemporal_load(reinterpret_cast<const f32x4_t *>(base + off + c * 64));
     };
     auto load_v = [&](int64_t row, int last) __attribute__((always_inline)) {
-        const char *base = static_cast<const char *>(a.v) + row * ROWB;
+        const char *base = v_base + row * ROWB;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const uint32_t off = min(4 * lq + r, last) * ROWB + l16 * 16;
@@ -83,10 +94,20 @@ __global__ __launch_bounds__(kThreads, 1) void fairkv_decode_f32_kernel(DecodeAr
     };
     auto f_tok0 = [&]() __attribute__((always_inline)) { return (wave + f_t * kWaves) * kTok; };
     auto load_q = [&]() __attribute__((always_inline)) {      // columns past the group repeat its last head; they are never stored
-        const char *base = static_cast<const char *>(a.q) + group_row(a, f_qg) * ROWB;
+        const char *base = q_base + (static_cast<size_t>(f_qg) << g_shift) * ROWB;
         const uint32_t off = min(l16, G - 1) * ROWB + lq * 16;
 #pragma unroll
         for (int c = 0; c < NC; ++c) qr[c] = *reinterpret_cast<const f32x4_t *>(base + off + c * 64);
+    };
+
+    // The first tile of a list, V last: in the order of the loop below, so that its waits for K need not be waits for everything.
+    auto load_first = [&]() __attribute__((always_inline)) {
+        load_q();
+        __builtin_amdgcn_sched_barrier(0);
+        load_k(f_row + f_tok0(), f_n - 1 - f_tok0());
+        __builtin_amdgcn_sched_barrier(0);
+        load_v(f_row + f_tok0(), f_n - 1 - f_tok0());
+        __builtin_amdgcn_sched_barrier(0);
     };
 
     // Early start: the first item's rows are requested from what the kernel arguments say of it, before the item list is here.
@@ -98,32 +119,40 @@ __global__ __launch_bounds__(kThreads, 1) void fairkv_decode_f32_kernel(DecodeAr
         f_n = n0;
         f_tiles = tiles_of(n0);
         if (f_tiles > 0) {
-            load_q();
-            load_k(f_row + f_tok0(), f_n - 1 - f_tok0());
-            load_v(f_row + f_tok0(), f_n - 1 - f_tok0());
+            load_first();
         }
     }
 
-    for (int batch = i_begin; batch < i_end; batch += kTable) {
-        const int nb = min(kTable, i_end - batch);
+    const ArgLanes arg_lanes(args);
+    const float scale_log2 = args.scale_log2;
+    const int qg_stride = args.q_len * args.Hkv;
+
+    ItemList list{};
+    for (int batch = i_begin; batch < i_end; batch += kList) {
+        const int nb = min(kList, i_end - batch);
         const bool early = seeded && batch == i_begin;
-        if (batch != i_begin) __syncthreads();                  // nobody still reads the previous table
-        if (static_cast<int>(threadIdx.x) < nb) {
-            const fairkv_item record = a.items[batch + threadIdx.x];   // a copy: one round trip, where a reference costs one per field checked
-            ItemSlot e = item_slot(a, record);
-            if (early && threadIdx.x == 0) e.n = n0 < kEarlyTok ? n0 : max(e.n, kEarlyTok);   // its first tiles are on their way, as many as n0 said
-            table[threadIdx.x] = e;
+        const bool loaded = early && f_tiles > 0;               // the first tile is on its way already
+        if (batch != i_begin) {
+            __syncthreads();                                    // nobody still reads the previous list
+            fetch_items(arg_lanes.get().items, batch);
         }
+        // the items were requested before the first tile and its queries: they have landed once only those are outstanding
+        if (loaded)
+            wait_vmcnt<2 * NC + 4 * NU>();
+        else
+            wait_vmcnt<0>();
         __syncthreads();
+        list = item_list(arg_lanes.get(), raw, lane);
+        if (early && lane == 0) list.n = n0 < kEarlyTok ? n0 : max(list.n, kEarlyTok);   // its first tile is on its way, as many as n0 said
 
         auto seek = [&](int item) __attribute__((always_inline)) {
             f_item = item;
             f_t = 0;
             f_tiles = 0;
             if (item < nb) {
-                f_row = uniform64(table[item].row);
-                f_n = __builtin_amdgcn_readfirstlane(table[item].n);
-                f_qg = __builtin_amdgcn_readfirstlane(table[item].qg);
+                f_row = list.row(item);
+                f_n = list.tokens(item);
+                f_qg = list.query_group(qg_stride, item);
                 f_tiles = tiles_of(f_n);
             }
         };
@@ -131,22 +160,19 @@ __global__ __launch_bounds__(kThreads, 1) void fairkv_decode_f32_kernel(DecodeAr
             while (f_t >= f_tiles && f_item < nb) seek(f_item + 1);
             return f_item < nb;
         };
-        const bool loaded = early && f_tiles > 0;               // the first tile is on its way already
         if (early) {
             f_item = 0;
-            f_n = __builtin_amdgcn_readfirstlane(table[0].n);   // its full length
+            f_n = list.tokens(0);                               // its full length
             f_tiles = tiles_of(f_n);
         } else {
             seek(0);
         }
         if (!loaded && skip_done()) {
-            load_q();
-            load_k(f_row + f_tok0(), f_n - 1 - f_tok0());
-            load_v(f_row + f_tok0(), f_n - 1 - f_tok0());
+            load_first();
         }
 
         for (int ci = 0; ci < nb; ++ci) {
-            const int n = __builtin_amdgcn_readfirstlane(table[ci].n);
+            const int n = list.tokens(ci);
             const int my_tiles = tiles_of(n);
 
             f32x4_t o[NU][4];
@@ -186,7 +212,7 @@ __global__ __launch_bounds__(kThreads, 1) void fairkv_decode_f32_kernel(DecodeAr
 
                 float sv[4];
 #pragma unroll
-                for (int r = 0; r < 4; ++r) sv[r] = (s0[r] + s1[r]) * a.scale_log2;
+                for (int r = 0; r < 4; ++r) sv[r] = (s0[r] + s1[r]) * scale_log2;
                 if (masked) {
 #pragma unroll
                     for (int r = 0; r < 4; ++r)
@@ -244,13 +270,14 @@ __global__ __launch_bounds__(kThreads, 1) void fairkv_decode_f32_kernel(DecodeAr
                     *reinterpret_cast<float2 *>(st_ml[set] + (wave * G + l16) * 2) = make_float2(m_run, l_run);
                 }
             }
-            if (__builtin_amdgcn_readfirstlane(table[ci].valid)) {
-                item_epilogue<D, G, DEEP>(a, piece_of(table[ci], a.v_scale), st_o[set], st_ml[set], pend, n_pend, roles);
+            if (list.valid(ci)) {
+                const CallArgs a = arg_lanes.get();
+                item_epilogue<D, G, DEEP>(a, list.piece(a, ci, a.v_scale), st_o[set], st_ml[set], pend, n_pend, roles);
                 set ^= 1;
             }
         }
     }
-    if (n_pend > 0) flush_pending<D, G, DEEP>(a, pend, n_pend, roles);
+    if (n_pend > 0) flush_pending<D, G, DEEP>(arg_lanes.get(), pend, n_pend, roles);
 }
 
 }  // namespace fairkv

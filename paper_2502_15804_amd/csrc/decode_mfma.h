@@ -150,31 +150,6 @@ __device__ __forceinline__ bf16x8_t widen8(i32x2_t w)
     return bf16x8_t{a0[0], a0[1], a1[0], a1[1], a2[0], a2[1], a3[0], a3[1]};
 }
 
-// LDS copy of the slot's items: what the waves need of a fairkv_item, plus the checked length.
-struct ItemSlot {
-    int64_t row;
-    int32_t n;        // tokens to read; 0 for an item that does not belong to this problem
-    int32_t valid;    // 0: such an item; it is skipped
-    int32_t qg, pair, h, chunk, n_chunks, part;     // qg: the pair's query group (see group_row)
-    int32_t owner;    // -1: the four waves share the item's tiles; else the wave that runs the whole item alone
-    int32_t pad;
-};
-// The entry of a fetched item; owner is filled in by the caller.  An item that does not belong to this problem gets
-// valid 0 and no tokens.
-__device__ __forceinline__ ItemSlot item_slot(const DecodeArgs &a, const fairkv_item &it)
-{
-    const bool ok = it.b >= 0 && it.b < a.B && it.h >= 0 && it.h < a.Hkv && it.row >= 0 && it.part >= 0 &&
-                    it.chunk >= 0 && it.chunk < it.n_chunks && it.chunk <= it.part &&
-                    it.part - it.chunk + it.n_chunks <= a.n_parts && it.row + max(it.tok_count, 0) <= a.n_rows;
-    return ItemSlot{it.row, ok ? max(it.tok_count, 0) : 0, ok ? 1 : 0, ok ? it.b * a.q_len * a.Hkv + it.h : 0,
-                    ok ? it.b * a.Hkv + it.h : 0, ok ? it.h : 0, it.chunk, it.n_chunks, it.part, -1, 0};
-}
-// What the end of an item needs of its entry, in scalar registers.
-__device__ __forceinline__ Piece piece_of(const ItemSlot &e, float v_mul)
-{
-    return Piece{__builtin_amdgcn_readfirstlane(e.pair), __builtin_amdgcn_readfirstlane(e.qg), __builtin_amdgcn_readfirstlane(e.part),
-                 __builtin_amdgcn_readfirstlane(e.chunk), __builtin_amdgcn_readfirstlane(e.n_chunks), v_mul};
-}
 // The maximum / sum over the four lanes of a wave that hold the same column (16 lanes apart).
 __device__ __forceinline__ float quarters_max(float x)
 {
@@ -200,8 +175,6 @@ __device__ __forceinline__ float quarters_sum(float x)
 // to fetch and the other two one tile each), so a slot of many short pairs had about one pair in flight at a time
 // and each cost a memory round trip; alone, four pairs stream side by side.
 constexpr int kSoloTokens = FAIRKV_SHORT_PAIR_TOKENS;
-static_assert(sizeof(ItemSlot) == 48, "item table entry");
-constexpr int kTable = 128;           // items per fill of a table in LDS; longer slot lists go in batches
 constexpr int kList = 64;             // items per fill of a wave's list in registers (ItemList): one per lane
 
 // A wave's own copy of (part of) its slot's item list: lane j holds item j.  A field of an item is one v_readlane away,

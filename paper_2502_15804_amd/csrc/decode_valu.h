@@ -5,6 +5,27 @@
 
 namespace fairkv {
 
+// An item as the kernel uses it.  One that does not belong to this problem gets valid 0.
+struct ItemSlot {
+    int64_t row;
+    int32_t n, valid;         // tokens to read
+    int32_t qg, pair, chunk, n_chunks, part;     // qg: the pair's query group (see group_row)
+};
+__device__ __forceinline__ ItemSlot item_slot(const CallArgs &a, const fairkv_item &it)
+{
+    const bool ok = it.b >= 0 && it.b < a.B && it.h >= 0 && it.h < a.Hkv && it.row >= 0 && it.part >= 0 &&
+                    it.chunk >= 0 && it.chunk < it.n_chunks && it.chunk <= it.part &&
+                    it.part - it.chunk + it.n_chunks <= a.n_parts && it.row + max(it.tok_count, 0) <= a.n_rows;
+    return ItemSlot{it.row, ok ? max(it.tok_count, 0) : 0, ok ? 1 : 0, ok ? it.b * a.q_len * a.Hkv + it.h : 0,
+                    ok ? it.b * a.Hkv + it.h : 0, it.chunk, it.n_chunks, it.part};
+}
+// What the end of an item needs of it, in scalar registers.
+__device__ __forceinline__ Piece piece_of(const ItemSlot &e, float v_mul)
+{
+    return Piece{__builtin_amdgcn_readfirstlane(e.pair), __builtin_amdgcn_readfirstlane(e.qg), __builtin_amdgcn_readfirstlane(e.part),
+                 __builtin_amdgcn_readfirstlane(e.chunk), __builtin_amdgcn_readfirstlane(e.n_chunks), v_mul};
+}
+
 // One wave per SIMD: the outputs, K and V of a tile take up to 512 registers.  Held to the 256 of two waves per SIMD,
 // which the 74 KB of LDS would let share a compute unit, <128, 8> spilled 792 of them instead of 356, and the traffic to
 // scratch memory is what the time goes to.  us per layer with two waves and with one: Llama-70B shape 264 and
