@@ -213,10 +213,17 @@ __device__ __forceinline__ ItemList item_list(const CallArgs &a, const fairkv_it
     const uint4 x = reinterpret_cast<const uint4 *>(raw + lane)[0], y = reinterpret_cast<const uint4 *>(raw + lane)[1];
     ItemList e{x.x, x.y, max(static_cast<int>(x.z), 0), static_cast<int>(x.w), static_cast<int>(y.x), static_cast<int>(y.y),
                static_cast<int>(y.z), static_cast<int>(y.w)};
-    const int64_t row = static_cast<int64_t>((static_cast<uint64_t>(e.row_hi) << 32) | e.row_lo);
-    const bool ok = (static_cast<uint32_t>(e.b) < static_cast<uint32_t>(a.B)) & (static_cast<uint32_t>(e.h) < static_cast<uint32_t>(a.Hkv)) &
-                    (row >= 0) & (row <= a.n_rows - e.n) & (e.chunk >= 0) & (e.chunk < e.n_chunks) & (e.chunk <= e.part) &
-                    (static_cast<int64_t>(e.part - e.chunk) + e.n_chunks <= a.n_parts);
+    // Unsigned compares, so that negative numbers fail; n_rows and n_parts are not negative.  With row's upper half no more than
+    // n_rows', row + n does not wrap around.
+    auto u = [](int32_t v) __attribute__((always_inline)) { return static_cast<uint32_t>(v); };
+    const uint64_t end = ((static_cast<uint64_t>(e.row_hi) << 32) | e.row_lo) + u(e.n), n_rows = static_cast<uint64_t>(a.n_rows);
+    bool ok = u(e.b) < u(a.B);       // combined without a branch
+    ok &= u(e.h) < u(a.Hkv);
+    ok &= e.row_hi <= static_cast<uint32_t>(n_rows >> 32);
+    ok &= end <= n_rows;
+    ok &= u(e.chunk) < u(e.n_chunks);
+    ok &= u(e.n_chunks) <= u(a.n_parts);
+    ok &= u(e.part - e.chunk) <= u(a.n_parts - e.n_chunks);
     e.n = ok ? e.n : 0;
     e.n_chunks = ok ? e.n_chunks : 0;
     return e;
@@ -299,6 +306,46 @@ __global__ __launch_bounds__(kThreads, 1) void fairkv_decode_mfma_kernel(DecodeA
         v_off[i] = ld_row * ROWB + (ld_col ^ ((2 * r) % PPR)) * 16;
         asm volatile("" : "+v"(k_off[i]), "+v"(v_off[i]));
     }
+    const uint32_t ring_lds =
+        static_cast<uint32_t>(reinterpret_cast<uintptr_t>(FAIRKV_LDS_PTR(lds))) + wave * (kStages * STAGEB);
+    const uint32_t q_lds = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(FAIRKV_LDS_PTR(qlds))) + wave * (kStages * QBUF);
+    const char *q_ring = qlds + wave * (kStages * QBUF);
+    const uint32_t raw_lds = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(FAIRKV_LDS_PTR(raw))) + (wave & 1) * 1024;
+    const int list_item = 32 * (wave & 1) + (lane >> 1);
+    // Where a lane reads its operands in a tile: the K row l16 (pieces 4 s + lq) and, through the
+    // transposing read, 4 d's of V row 4 lq + l16/4 (lane j of a 16-lane group receives element
+    // j%4 of the rows its lanes 4i + j/4 address).
+    // (8-bit caches: 8 bytes of K row l16 or 16 + l16 at byte 32 s + 8 lq; for V the fragment this
+    // lane addresses in the transposing read, see above.)
+    // LDS addresses in the stage of the tile that is next to be consumed.
+    constexpr int NKR = KV8 ? 2 * NSL : NSL;
+    uint32_t k_rd[NKR], v_rd[NDB];
+    if constexpr (!KV8) {
+#pragma unroll
+        for (int s = 0; s < NSL; ++s) k_rd[s] = ring_lds + l16 * ROWB + ((4 * s + lq) ^ (l16 % PPR)) * 16;
+        const int vrow = 4 * lq + (l16 >> 2), vsub = l16 & 3;
+#pragma unroll
+        for (int nb_ = 0; nb_ < NDB; ++nb_)
+            v_rd[nb_] = ring_lds + TILEB + vrow * ROWB + (((2 * nb_ + (vsub >> 1)) ^ ((2 * vrow) % PPR)) * 16) + (vsub & 1) * 8;
+    } else {
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+            for (int s = 0; s < NSL; ++s) {
+                const int row = 16 * u + l16;
+                k_rd[u * NSL + s] = ring_lds + row * ROWB + (((2 * s + (lq >> 1)) ^ (row % PPR)) * 16) + (lq & 1) * 8;
+            }
+        const int r = l16 >> 1;                                            // which of the lane group's 8 tokens
+        const int vrow = r < 4 ? 4 * lq + r : 16 + 4 * lq + (r - 4);
+#pragma unroll
+        for (int nb_ = 0; nb_ < NDB; ++nb_)
+            v_rd[nb_] = ring_lds + TILEB + vrow * ROWB + ((nb_ ^ ((2 * vrow) % PPR)) * 16) + (l16 & 1) * 8;
+    }
+#pragma unroll
+    for (int s = 0; s < NKR; ++s) asm volatile("" : "+v"(k_rd[s]));
+#pragma unroll
+    for (int nb_ = 0; nb_ < NDB; ++nb_) asm volatile("" : "+v"(v_rd[nb_]));
+
     const SlotStart slot = slot_start(args);
     arrive_together(args, slot);
     const char *const q_base = static_cast<const char *>(args.q), *const k_base = static_cast<const char *>(args.k);
@@ -306,17 +353,10 @@ __global__ __launch_bounds__(kThreads, 1) void fairkv_decode_mfma_kernel(DecodeA
     const int g_shift = args.g_shift;
     const int i_begin = slot.i_begin, i_end = slot.i_end;
     if (i_end <= i_begin) return;   // an idle slot
-    const uint32_t ring_lds =
-        static_cast<uint32_t>(reinterpret_cast<uintptr_t>(FAIRKV_LDS_PTR(lds))) + wave * (kStages * STAGEB);
-    const uint32_t q_lds = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(FAIRKV_LDS_PTR(qlds))) + wave * (kStages * QBUF);
-    const char *q_ring = qlds + wave * (kStages * QBUF);
-    const uint32_t raw_lds = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(FAIRKV_LDS_PTR(raw))) + wave * 1024;
-
-    // Fetch of the kList items that start at `first`: one load by each of the first two waves (32 items each).  Past the end of
-    // the slot's list the last item is read again.
+    // Fetch of the kList items that start at `first`: one load by each wave, 32 items by waves 0 and 2, the next 32 by waves 1 and 3
+    // (a condition on the wave costs more than the second load).  Past the end of the slot's list the last item is read again.
     auto fetch_items = [&](const fairkv_item *items, int first) __attribute__((always_inline)) {
-        const int last = min(kList, i_end - first) - 32 * wave - 1;
-        if (last >= 0) load16_to_lds_keep(items + first + 32 * wave, min(lane >> 1, last) * 32 + (lane & 1) * 16, raw_lds);
+        load16_to_lds_keep(items + first, min(list_item, i_end - first - 1) * 32 + (lane & 1) * 16, raw_lds);
     };
     fetch_items(args.items, i_begin);
 
@@ -380,6 +420,11 @@ __global__ __launch_bounds__(kThreads, 1) void fairkv_decode_mfma_kernel(DecodeA
         if (f_left > 0) fetch_next();
     }
     const ArgLanes arg_lanes(args);
+    auto call_args = [&]() __attribute__((always_inline)) {
+        CallArgs a = arg_lanes.get();
+        if constexpr (TRACE) a.trace = args.trace;
+        return a;
+    };
     const float scale_log2 = args.scale_log2;
     const int q_len = args.q_len, qg_stride = q_len * args.Hkv;      // query groups of a sequence
     // 8-bit caches: lane h holds scale_log2 times the K factor of KV head h (modulo kScaleHeads), lane kScaleHeads + h v_scale
@@ -389,42 +434,20 @@ __global__ __launch_bounds__(kThreads, 1) void fairkv_decode_mfma_kernel(DecodeA
         head_mul = lane_values(args.k_head, args.v_head) * (lane < kScaleHeads ? scale_log2 : args.v_scale);
     }
 
-    // Where a lane reads its operands in a tile: the K row l16 (pieces 4 s + lq) and, through the
-    // transposing read, 4 d's of V row 4 lq + l16/4 (lane j of a 16-lane group receives element
-    // j%4 of the rows its lanes 4i + j/4 address).
-    // (8-bit caches: 8 bytes of K row l16 or 16 + l16 at byte 32 s + 8 lq; for V the fragment this
-    // lane addresses in the transposing read, see above.)
-    // LDS addresses in the stage of the tile that is next to be consumed.
-    constexpr int NKR = KV8 ? 2 * NSL : NSL;
-    uint32_t k_rd[NKR], v_rd[NDB];
-    if constexpr (!KV8) {
-#pragma unroll
-        for (int s = 0; s < NSL; ++s) k_rd[s] = ring_lds + l16 * ROWB + ((4 * s + lq) ^ (l16 % PPR)) * 16;
-        const int vrow = 4 * lq + (l16 >> 2), vsub = l16 & 3;
-#pragma unroll
-        for (int nb_ = 0; nb_ < NDB; ++nb_)
-            v_rd[nb_] = ring_lds + TILEB + vrow * ROWB + (((2 * nb_ + (vsub >> 1)) ^ ((2 * vrow) % PPR)) * 16) + (vsub & 1) * 8;
-    } else {
-#pragma unroll
-        for (int u = 0; u < 2; ++u)
-#pragma unroll
-            for (int s = 0; s < NSL; ++s) {
-                const int row = 16 * u + l16;
-                k_rd[u * NSL + s] = ring_lds + row * ROWB + (((2 * s + (lq >> 1)) ^ (row % PPR)) * 16) + (lq & 1) * 8;
-            }
-        const int r = l16 >> 1;                                            // which of the lane group's 8 tokens
-        const int vrow = r < 4 ? 4 * lq + r : 16 + 4 * lq + (r - 4);
-#pragma unroll
-        for (int nb_ = 0; nb_ < NDB; ++nb_)
-            v_rd[nb_] = ring_lds + TILEB + vrow * ROWB + ((nb_ ^ ((2 * vrow) % PPR)) * 16) + (l16 & 1) * 8;
-    }
-#pragma unroll
-    for (int s = 0; s < NKR; ++s) asm volatile("" : "+v"(k_rd[s]));
-#pragma unroll
-    for (int nb_ = 0; nb_ < NDB; ++nb_) asm volatile("" : "+v"(v_rd[nb_]));
     const char *q_rd = q_ring + min(l16, G - 1) * QROWB + lq * 16;
     const int col_hidden = q_len - 1 - (min(l16, G - 1) >> g_shift);      // rows at a pair's end that the lane's column does not see
 
+    // A wave's share of an item: outputs, reference maximum of the lane's head, this lane's share of the weights.  Made ready while the
+    // first tile is on its way, and after an item for the next.
+    f32x4_t o[NDB];
+    float m_run, l_run;
+    auto begin_item = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int nb_ = 0; nb_ < NDB; ++nb_) o[nb_] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+        m_run = -INFINITY;
+        l_run = 0.f;
+    };
+    begin_item();
     ItemList list{};
     for (int batch = i_begin; batch < i_end; batch += kList) {
         const int nb = min(kList, i_end - batch);
@@ -495,10 +518,6 @@ __global__ __launch_bounds__(kThreads, 1) void fairkv_decode_mfma_kernel(DecodeA
             const int hidden_max = last_chunk ? q_len - 1 : 0;
             const int hidden = last_chunk ? col_hidden : 0;
             bf16x8_t qb[NSL];
-            f32x4_t o[NDB];
-#pragma unroll
-            for (int nb_ = 0; nb_ < NDB; ++nb_) o[nb_] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-            float m_run = -INFINITY, l_run = 0.f;   // reference maximum of the lane's head, this lane's share of the weights
 
             for (bool fresh = true; left > 0; fresh = false) {
                 // The tile has landed once no more is outstanding than was requested after it: the other tile of the ring
@@ -632,7 +651,7 @@ __global__ __launch_bounds__(kThreads, 1) void fairkv_decode_mfma_kernel(DecodeA
             }
             // ---- fold the four token quarters of l, stage this wave's result, finish the item ------
             l_run = quarters_sum(l_run);
-            const CallArgs a = arg_lanes.get();
+            const CallArgs a = call_args();
             const Piece pc = list.piece(a, ci, KV8 ? lane_value(head_mul, kScaleHeads + scale_h) : a.v_scale);
             const bool valid = pc.n_chunks != 0;
             if (SOLO && owner >= 0) {
@@ -644,6 +663,7 @@ __global__ __launch_bounds__(kThreads, 1) void fairkv_decode_mfma_kernel(DecodeA
                         write_out4<D>(a, pc.qg, l16, 16 * nb_ + 4 * lq, make_float4(o[nb_][0], o[nb_][1], o[nb_][2], o[nb_][3]), m_run,
                                       l_run, pc.v_mul);
                 }
+                begin_item();
                 continue;
             }
             if (l16 < G) {
@@ -662,12 +682,13 @@ __global__ __launch_bounds__(kThreads, 1) void fairkv_decode_mfma_kernel(DecodeA
                 else
                     __syncthreads();
             }
+            begin_item();
             if constexpr (TRACE)
                 if (batch == i_begin && ci == 0) trace_stamp(args, kTraceItem0Done, threadIdx.x == 0);
         }
         wait_vmcnt<0>();   // nothing of this batch may still be landing in the rings
     }
-    if (n_pend > 0) flush_pending<D, G, DEEP, TRACE>(arg_lanes.get(), pend, n_pend, roles);
+    if (n_pend > 0) flush_pending<D, G, DEEP, TRACE>(call_args(), pend, n_pend, roles);
     if constexpr (TRACE) trace_stamp(args, kTraceEnd, threadIdx.x == 0);
 }
 
