@@ -23,11 +23,15 @@ def _plan_params(n_cu, kv8, f32, D, tokens):
     """The planner's parameters for a layer that brings none: the library's defaults with what was measured for the kind of cache.
 
     The overheads are what an item costs in units of streamed tokens, so they fall with the bytes of a token; the values are
-    measured, not scaled.  us per layer with the defaults' and with these: fp32 Llama-70B shape 31.4 and 30.3, 24B shape 67.2
-    and 64.9; 8-bit cache of many short pairs 21.2 and 20.4.  The fp32 kernel has no single-wave path for short pairs, and
-    what they should cost depends on the cache: with 32, 80 (as any item) and 24 tokens, Pareto budgets at batch 128 take
-    41.1, 43.3 and 41.9 us, 128 pairs of about 60 tokens 10.3, 10.8 and 10.0, 1024 pairs of 40 tokens 18.2, 16.5 and 18.5
-    (the defaults, 160 and 48: 42.9, 11.8, 18.6).
+    measured, not scaled.  us per layer with the overhead of an item and of a short whole pair in tokens:
+
+                                      bf16 160/48   96/48   |  fp32 80/32   64/32  |  8-bit 256/96  256/128
+      Llama-70B shape                       16.04   16.01   |       28.89   28.49  |         11.05    11.08
+      24B shape, two heavy heads            33.19   32.87   |       65.81   65.12  |         20.55    20.55
+      Pareto budgets, batch 128             20.76   20.87   |       39.12   38.49  |         16.80    16.66
+      128 pairs of 60 (8-bit: 120) tokens       -       -   |        8.67    8.69  |          7.78     7.28
+      1024 pairs of 60 (fp32: 40) tokens    13.11   12.62   |       17.50   15.98  |             -        -
+      256 pairs of 64 tokens                 7.32    4.90   |        7.38    7.37  |          6.85     6.83
 
     The smallest piece of a bf16 pair: a smaller one fills more compute units and makes more partials to merge.  us per layer
     with pieces of at least 32, 64, 96 and 128 tokens: one sequence of eight pairs of 1024 tokens 9.35, 8.75, 8.76, 8.92, of 256
@@ -35,10 +39,10 @@ def _plan_params(n_cu, kv8, f32, D, tokens):
     batch 128 21.62, 21.37, 21.16, 21.09; 24B shape 33.76, 33.53, 33.55, 33.47; with D = 64, where a token is half the bytes, one
     sequence 8.87, 8.69, 8.53, 8.37 and the Llama-70B shape 11.34, 11.18, 11.08, 11.09.  Hence 64 up to 128 tokens per compute unit."""
     if kv8:      # half the bytes per token, and a step covers 32 tokens
-        return fairkv_default_params(n_cu, tile=32, min_chunk=64, overhead_tokens=256, short_overhead_tokens=96)
+        return fairkv_default_params(n_cu, tile=32, min_chunk=64, overhead_tokens=256, short_overhead_tokens=128)
     if f32:      # twice the bytes
-        return fairkv_default_params(n_cu, overhead_tokens=80, short_overhead_tokens=32)
-    return fairkv_default_params(n_cu, min_chunk=64 if D == 128 and tokens < 128 * n_cu else 128)
+        return fairkv_default_params(n_cu, overhead_tokens=64, short_overhead_tokens=32)
+    return fairkv_default_params(n_cu, overhead_tokens=96, min_chunk=64 if D == 128 and tokens < 128 * n_cu else 128)
 
 
 class DecodeLayer:
