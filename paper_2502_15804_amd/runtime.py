@@ -9,7 +9,7 @@ from __future__ import annotations
 
 import numpy as np
 
-from . import (Plan, fairkv_decode_attn, fairkv_decode_attn_kv8, fairkv_default_params, fairkv_plan,
+from . import (FAIRKV_SHORT_PAIR_TOKENS, Plan, fairkv_decode_attn, fairkv_decode_attn_kv8, fairkv_default_params, fairkv_plan,
                fairkv_workspace_bytes)
 
 
@@ -19,7 +19,7 @@ def device_compute_units(device=None) -> int:
                .multi_processor_count)
 
 
-def _plan_params(n_cu, kv8, f32, D, tokens):
+def _plan_params(n_cu, kv8, f32, D, lens):
     """The planner's parameters for a layer that brings none: the library's defaults with what was measured for the kind of cache.
 
     The overheads are what an item costs in units of streamed tokens, so they fall with the bytes of a token; the values are
@@ -37,12 +37,23 @@ def _plan_params(n_cu, kv8, f32, D, tokens):
     with pieces of at least 32, 64, 96 and 128 tokens: one sequence of eight pairs of 1024 tokens 9.35, 8.75, 8.76, 8.92, of 256
     6.82, 6.33, 6.85, 6.50, of 200 on the average 7.57, 7.00, 6.94, 7.31; Pareto budgets at batch 8 9.33, 9.31, 9.52, 9.52 and at
     batch 128 21.62, 21.37, 21.16, 21.09; 24B shape 33.76, 33.53, 33.55, 33.47; with D = 64, where a token is half the bytes, one
-    sequence 8.87, 8.69, 8.53, 8.37 and the Llama-70B shape 11.34, 11.18, 11.08, 11.09.  Hence 64 up to 128 tokens per compute unit."""
-    if kv8:      # half the bytes per token, and a step covers 32 tokens
-        return fairkv_default_params(n_cu, tile=32, min_chunk=64, overhead_tokens=256, short_overhead_tokens=128)
+    sequence 8.87, 8.69, 8.53, 8.37 and the Llama-70B shape 11.34, 11.18, 11.08, 11.09.  Hence 64 up to 128 tokens per compute unit.
+
+    With no more pairs than compute units a short pair costs what any item costs: two of them on one unit leave another idle.
+    us per layer with the short pairs' own overhead and without: 256 pairs of 64 tokens on an 8-bit cache 7.49 and 5.33, of 40 on
+    the average 8.34 and 6.15 (bf16 7.53 and 6.90), 200 of 100 8.48 and 7.53 (8.41 and 7.58), 64 of 90 6.98 and 7.04 (6.97 and 7.01);
+    with 384 pairs of 50 8.62 and 8.72 (8.87 and 9.08), with 512 of 64 7.91 and 7.59 (8.33 and 8.38).  On an fp32 cache it is the
+    other way round: 200 pairs of 30 8.14 and 8.81, 256 of 40 9.24 and 9.57."""
     if f32:      # twice the bytes
         return fairkv_default_params(n_cu, overhead_tokens=64, short_overhead_tokens=32)
-    return fairkv_default_params(n_cu, overhead_tokens=96, min_chunk=64 if D == 128 and tokens < 128 * n_cu else 128)
+    if kv8:      # half the bytes per token, and a step covers 32 tokens
+        p = fairkv_default_params(n_cu, tile=32, min_chunk=64, overhead_tokens=256, short_overhead_tokens=128)
+    else:
+        p = fairkv_default_params(n_cu, overhead_tokens=96,
+                                  min_chunk=64 if D == 128 and int(lens.sum(dtype=np.int64)) < 128 * n_cu else 128)
+    if np.count_nonzero(lens) <= n_cu and ((lens > 0) & (lens <= FAIRKV_SHORT_PAIR_TOKENS)).any():      # (empty pairs alone: 0.6 % slower)
+        p.short_overhead_tokens = p.overhead_tokens
+    return p
 
 
 class DecodeLayer:
@@ -65,7 +76,7 @@ class DecodeLayer:
         self.G = self.Hq // self.Hkv
         self.scale = float(scale)
         if params is None:
-            params = _plan_params(device_compute_units(dev), self.kv8, q.dtype == torch.float32, self.D, int(lens_h.sum(dtype=np.int64)))
+            params = _plan_params(device_compute_units(dev), self.kv8, q.dtype == torch.float32, self.D, lens_h)
         self.plan: Plan = fairkv_plan(lens_h, off_h, self.B, self.Hkv, params)
         self.items_d = torch.from_numpy(self.plan.items.view(np.uint8).copy()).to(dev)
         need = fairkv_workspace_bytes(self.plan.n_parts, self.B * self.Hkv, self.G * self.q_len, self.D)
