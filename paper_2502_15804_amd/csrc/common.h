@@ -123,7 +123,7 @@ struct CallArgs {
     float *part_o;              // [n_parts][G][D]   unnormalised outputs relative to the item's maximum
     float *part_ml;             // [n_parts][G][2]   (maximum in log2 units, sum of weights)
     int32_t *arrivals;          // [B*Hkv] items (or groups of items) of a cut pair that have delivered; 0 between calls.
-                                // Behind them [n_group_counters] the same per group of kGroup items, index first part + group
+                                // Behind them [n_group_counters] the same per group of kGroup items, index spread16(first part + group)
     void *out;
     float *lse;
     float scale_log2;           // scale * log2(e) (times the K scale of an 8-bit cache): scores are kept in log2
@@ -316,6 +316,15 @@ constexpr int kGroup = 8;
 constexpr int kDeepFrom = 16;
 enum { kRoleNone = 0, kRoleFinal = 1, kRoleGroup = 2 };
 
+// Where counter i of n lies: neighbours n / 16 counters apart, each on a cache line of its own, for the count-ins of one line
+// wait for one another (a permutation of 0 .. n - 1).  One pair in 128 pieces 10.8 -> 9.9 us, one sequence of eight pairs 8.66 -> 8.58; the
+// counters of whole pairs, of which one sees two or three count-ins, gain nothing from it.
+__device__ __forceinline__ int spread16(int i, int n)
+{
+    const int apart = n >> 4;
+    return i < 16 * apart ? (i & 15) * apart + (i >> 4) : i;
+}
+
 constexpr int kMergeBatch = 8;   // partials of a cut pair fetched at once by the merging workgroup
 
 // A partial goes to the workspace: four consecutive coordinates (the idx-th four of [G][D]) and, with the first of a
@@ -438,7 +447,7 @@ __device__ __forceinline__ void flush_pending(const CallArgs &a, const Piece (&p
                 // two levels only if every group of the pair has a counter
                 const bool deep = nc >= kDeepFrom && static_cast<int64_t>(first) + (nc - 1) / kGroup < a.n_group_counters;
                 if (round == 0 && deep) {
-                    counter = a.arrivals + static_cast<size_t>(a.B) * a.Hkv + first + chunk / kGroup;
+                    counter = a.arrivals + static_cast<size_t>(a.B) * a.Hkv + spread16(first + chunk / kGroup, a.n_group_counters);
                     last = min(kGroup, nc - chunk / kGroup * kGroup) - 1;
                     role_if_last = kRoleGroup;
                 } else if (round == 1) {
