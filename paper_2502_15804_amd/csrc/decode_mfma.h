@@ -48,6 +48,7 @@ typedef __attribute__((ext_vector_type(4))) float f32x4_t;
 typedef __attribute__((ext_vector_type(8))) float f32x8_t;
 typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2_v;
 typedef __attribute__((ext_vector_type(2))) int i32x2_t;
+typedef __attribute__((ext_vector_type(2))) uint16_t u16x2_t;
 
 constexpr int kTok = 16;      // tokens per tile (the M of the score MFMA, the K of the PV MFMA)
 // Tiles per wave resident in LDS: one being consumed, the other in flight; 64 KB per compute unit are on their way
@@ -618,14 +619,19 @@ __global__ __launch_bounds__(kThreads, 1) void fairkv_decode_mfma_kernel(DecodeA
                     for (int nb_ = 0; nb_ < NDB; ++nb_) o[nb_] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(widen8(vt8[nb_]), pb, o[nb_], 0, 0, 0);
                 } else {
                     // A weight is the sum of two bf16 numbers: its upper half, and what that leaves, rounded, in the other half of the contraction.
-                    // Both are positive if the weight is (the rest exceeds the true one by 2^-22 of the weight), so an infinite V stays one.
-                    uint32_t upper[NS / 2], rest[NS / 2];
+                    // Both are positive if the weight is, so an infinite V stays one: where nothing is left, or less than bf16 has, the
+                    // rest is the smallest number of bf16, 2^-133 (0 for a weight of 0).  The smallest weight is 2^-126 and the largest at least 1.
+                    // (The last row of a tile that is not full is read again with weight 0, which makes a NaN of an infinite V there.)  0 to 0.2 % of a launch.
+                    uint32_t upper[NS / 2], rest[NS / 2], ones = 0x00010001u;
+                    asm("" : "+s"(ones));      // a minimum with a known 1 becomes two compares and two selects
 #pragma unroll
                     for (int r = 0; r < NS; r += 2) {
                         l_run = l_run + p[r] + p[r + 1];
                         upper[r / 2] = __builtin_amdgcn_perm(__float_as_uint(p[r + 1]), __float_as_uint(p[r]), 0x07060302u);
-                        const f2_t more = {fmaf(p[r], 1.f + 0x1p-22f, -bf16_hi(__float_as_uint(p[r]))), fmaf(p[r + 1], 1.f + 0x1p-22f, -bf16_hi(__float_as_uint(p[r + 1])))};
-                        rest[r / 2] = __builtin_bit_cast(uint32_t, __builtin_convertvector(more, bf16x2_v));
+                        const f2_t left_over = {p[r] - bf16_hi(__float_as_uint(p[r])), p[r + 1] - bf16_hi(__float_as_uint(p[r + 1]))};      // exact
+                        const u16x2_t floor = __builtin_elementwise_min(__builtin_bit_cast(u16x2_t, upper[r / 2]), __builtin_bit_cast(u16x2_t, ones));
+                        rest[r / 2] = __builtin_bit_cast(uint32_t, __builtin_elementwise_max(
+                            __builtin_bit_cast(u16x2_t, __builtin_convertvector(left_over, bf16x2_v)), floor));
                     }
                     const bf16x8_t pb = __builtin_bit_cast(bf16x8_t, uint4{upper[0], upper[1], rest[0], rest[1]});
 #pragma unroll

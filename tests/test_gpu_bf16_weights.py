@@ -1,5 +1,8 @@
 """A softmax weight of the bf16 kernel is two bf16 numbers, its upper half and the rounded rest: 2**-16 of it are lost, not the
-2**-9 of one bf16 number, and both are positive, so an infinite V gives an infinite output and not a NaN."""
+2**-9 of one bf16 number, and both are positive, so an infinite V gives an infinite output and not a NaN, however small its
+weight (but not in the last row of a tile that is not full: that row is read again with weight 0)."""
+import math
+
 import numpy as np
 import pytest
 
@@ -9,6 +12,36 @@ from test_gpu_parity import make_case
 
 pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
+
+
+@pytest.mark.parametrize("D,G", [(128, 8), (64, 2)])
+@pytest.mark.parametrize("n", [16, 33])
+def test_an_infinite_value_under_small_weights(n, D, G):
+    """Row 0 of each pair has the largest score, row 1, whose V is infinite in one coordinate, lies `gap` log2 units below it and
+    the others as much: weights 2**-gap that are bf16 numbers themselves, and some that are not."""
+    from paper_2502_15804_amd.runtime import DecodeLayer
+    gaps = [1, 7, 60, 100.5, 110, 111, 111.5, 112, 112.5, 113, 118, 120.5, 125, 125.5]
+    B = len(gaps)
+    q, k, v = torch.zeros((B, G, D)), torch.zeros((B, n, D)), torch.ones((B, n, D))
+    q[:, :, 0] = 1
+    k[:, 1:, 0] = -torch.tensor(gaps)[:, None]
+    v[:, 1, 5] = float("inf")
+    off = (np.arange(B, dtype=np.int64) * n).reshape(B, 1)
+    layer = DecodeLayer(q.bfloat16().cuda(), k.bfloat16().reshape(-1, D).cuda(), v.bfloat16().reshape(-1, D).cuda(), off,
+                        np.full((B, 1), n, np.int32), math.log(2.0))
+    out = layer.run()[0].cpu().numpy()
+    assert np.isposinf(out[:, :, 5]).all()
+    # 2**-17 of each weight is lost where it is no bf16 number, and 2**-20 is more than the fp32 sums of 33 terms lose
+    assert np.abs(np.delete(out, 5, axis=2) - 1.0).max() <= 2.0 ** -17 + 2.0 ** -20
+
+
+@pytest.mark.parametrize("D,G", [(128, 8), (64, 1)])
+def test_one_token_gives_its_value(D, G):
+    from paper_2502_15804_amd.runtime import DecodeLayer
+    w, off, q, k, v = make_case(2, 2 * G, 2, D, "bf16", np.ones((2, 2), np.int32), seed=D)
+    out = DecodeLayer(q.cuda(), k.cuda(), v.cuda(), off, np.ones((2, 2), np.int32), w.scale).run()[0].cpu()
+    want = v[torch.from_numpy(off.reshape(-1))].float().reshape(2, 2, 1, D).expand(2, 2, G, D).reshape(2, 2 * G, D)
+    assert torch.equal(out, want)
 
 
 @pytest.mark.parametrize("D,G", [(128, 8), (128, 16), (64, 1), (64, 4)])
