@@ -332,8 +332,10 @@ def fairkv_decode_attn_kv8(q, k8, v8, k_scale, v_scale, items, items_host, slot_
     if per_head:
         k_scale = np.ascontiguousarray(np.broadcast_to(np.asarray(k_scale, dtype=np.float32), (Hkv,)))
         v_scale = np.ascontiguousarray(np.broadcast_to(np.asarray(v_scale, dtype=np.float32), (Hkv,)))
+    else:
+        k_scale, v_scale = float(k_scale), float(v_scale)    # also arrays and tensors of no dimension
     rc = (_native_module or _native()).decode_8bit((_pt or _torch())[1], q, k8, v8, k_scale, v_scale, items, items_host, slot_ptr, n_parts,
-                                                   workspace, out, lse, scale, Hkv, stream)
+                                                   workspace, out, lse, scale, Hkv, stream, per_head)
     if rc != FAIRKV_OK:
         raise FairKVError(rc, "fairkv_decode_attn_kv8_per_head" if per_head else "fairkv_decode_attn_kv8")
 

@@ -206,11 +206,31 @@ PyObject *decode(PyObject *, PyObject *const *a, Py_ssize_t n)
     });
 }
 
-// (current, q, k8, v8, k_scale, v_scale, items, items_host, slot_ptr, n_parts, workspace, out, lse, scale, Hkv, stream); the scales are two
-// numbers, or two contiguous float32 arrays of Hkv
+// The numbers of a scale per KV head.
+const float *scale_array(PyObject *o, int32_t Hkv, const char *name)
+{
+    auto *s = reinterpret_cast<PyArrayObject *>(o);
+    if (!PyArray_Check(o) || PyArray_TYPE(s) != NPY_FLOAT || !PyArray_ISCARRAY_RO(s) || PyArray_NDIM(s) != 1 || PyArray_SIZE(s) != Hkv) {
+        PyErr_Format(PyExc_TypeError, "%s must be a contiguous float32 array of one number per KV head", name);
+        throw Refused{};
+    }
+    return static_cast<const float *>(PyArray_DATA(s));
+}
+
+// (current, q, k8, v8, k_scale, v_scale, items, items_host, slot_ptr, n_parts, workspace, out, lse, scale, Hkv, stream, per_head); the scales
+// are two float32 arrays if per_head is true, else two numbers
 PyObject *decode_8bit(PyObject *, PyObject *const *a, Py_ssize_t n)
 {
-    return guarded(n, 16, [&]() -> int {
+    return guarded(n, 17, [&]() -> int {
+        const int32_t Hkv = int_of(a[14]);
+        const int per_head = PyObject_IsTrue(a[16]);
+        if (per_head < 0) throw Refused{};
+        const float *k_scales = nullptr, *v_scales = nullptr;
+        float k_scale = 1.f, v_scale = 1.f;
+        if (per_head)
+            k_scales = scale_array(a[4], Hkv, "k_scale"), v_scales = scale_array(a[5], Hkv, "v_scale");
+        else
+            k_scale = float_of(a[4]), v_scale = float_of(a[5]);
         const at::Tensor &q = tensor(a[1], "q"), &k = tensor(a[2], "k8"), &v = tensor(a[3], "v8"), &items = tensor(a[6], "items"),
                          &workspace = tensor(a[10], "workspace"), &out = tensor(a[11], "out"), &lse = tensor(a[12], "lse", true);
         if (!is(q, at::kBFloat16) || dtype_code(k) != FAIRKV_E4M3 || dtype_code(v) != FAIRKV_E4M3 || !is_q_or_out(out))
@@ -220,22 +240,17 @@ PyObject *decode_8bit(PyObject *, PyObject *const *a, Py_ssize_t n)
         const Shape s = shape_of(q, k, v, out, lse, true);
         const PlanArgs p = plan_args(items, a[7], a[8], a[9]);
         const float scale = float_of(a[13]);
-        const int32_t Hkv = int_of(a[14]);
         void *st = stream_of(a[15], a[0], q);
         float *l = static_cast<float *>(ptr(lse));
-        if (PyArray_Check(a[4])) {
-            const auto *ks = static_cast<const float *>(PyArray_DATA(reinterpret_cast<PyArrayObject *>(a[4])));
-            const auto *vs = static_cast<const float *>(PyArray_DATA(reinterpret_cast<PyArrayObject *>(a[5])));
+        if (per_head)
             return unlocked([&] {
-                return decode_kv8_per_head(q.data_ptr(), k.data_ptr(), v.data_ptr(), k.size(0), ks, vs, p.items, p.items_host, p.n_items, p.slot_ptr,
-                                           p.n_slots, p.n_parts, workspace.data_ptr(), workspace.nbytes(), out.data_ptr(), l, s.B, s.q_len,
-                                           s.Hq, Hkv, s.D, dtype_code(out), scale, st);
+                return decode_kv8_per_head(q.data_ptr(), k.data_ptr(), v.data_ptr(), k.size(0), k_scales, v_scales, p.items, p.items_host, p.n_items,
+                                           p.slot_ptr, p.n_slots, p.n_parts, workspace.data_ptr(), workspace.nbytes(), out.data_ptr(), l, s.B,
+                                           s.q_len, s.Hq, Hkv, s.D, dtype_code(out), scale, st);
             });
-        }
-        const float ks = float_of(a[4]), vs = float_of(a[5]);
         return unlocked([&] {
-            return decode_kv8(q.data_ptr(), k.data_ptr(), v.data_ptr(), k.size(0), ks, vs, p.items, p.items_host, p.n_items, p.slot_ptr, p.n_slots,
-                              p.n_parts, workspace.data_ptr(), workspace.nbytes(), out.data_ptr(), l, s.B, s.q_len, s.Hq, Hkv, s.D,
+            return decode_kv8(q.data_ptr(), k.data_ptr(), v.data_ptr(), k.size(0), k_scale, v_scale, p.items, p.items_host, p.n_items, p.slot_ptr,
+                              p.n_slots, p.n_parts, workspace.data_ptr(), workspace.nbytes(), out.data_ptr(), l, s.B, s.q_len, s.Hq, Hkv, s.D,
                               dtype_code(out), scale, st);
         });
     });
