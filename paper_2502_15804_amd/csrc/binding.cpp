@@ -168,7 +168,6 @@ int unlocked(Call call)
 PyObject *decode(PyObject *, PyObject *const *a, Py_ssize_t n)
 {
     return guarded(n, 16, [&]() -> int {
-        const int32_t Hkv = index_of(a[12]);
         const at::Tensor &q = tensor(a[1], "q"), &k = tensor(a[2], "k"), &v = tensor(a[3], "v"), &items = tensor(a[4], "items"),
                          &workspace = tensor(a[8], "workspace", true), &out = tensor(a[9], "out"), &lse = tensor(a[10], "lse", true),
                          &trace = tensor(a[15], "trace", true);
@@ -182,6 +181,7 @@ PyObject *decode(PyObject *, PyObject *const *a, Py_ssize_t n)
         const int32_t in_dt = on_valu && is(q, at::kBFloat16) ? FAIRKV_BF16_VALU : dtype_code(q);
         const PlanArgs p = plan_args(items, a[5], a[6], a[7]);
         const float scale = float_of(a[11]);
+        const int32_t Hkv = int_of(a[12]);
         void *st = stream_of(a[13], a[0], q);
         float *l = static_cast<float *>(ptr(lse));
         if (trace.defined()) {
@@ -222,7 +222,7 @@ const float *scale_array(PyObject *o, int32_t Hkv, const char *name)
 PyObject *decode_8bit(PyObject *, PyObject *const *a, Py_ssize_t n)
 {
     return guarded(n, 17, [&]() -> int {
-        const int32_t Hkv = index_of(a[14]);
+        const int32_t Hkv = int_of(a[14]);
         const int per_head = PyObject_IsTrue(a[16]);
         if (per_head < 0) throw Refused{};
         const float *k_scales = nullptr, *v_scales = nullptr;
