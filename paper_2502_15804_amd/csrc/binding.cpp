@@ -68,14 +68,15 @@ int32_t dtype_code(const at::Tensor &t)      // -1: none of the library's
 }
 bool is_q_or_out(const at::Tensor &t) { return is(t, at::kBFloat16) || is(t, at::kFloat); }
 
-int32_t int_of(PyObject *o)
+int32_t low_word(PyObject *i)      // of an int, whose reference it takes
 {
-    PyObject *i = PyNumber_Long(o);
     if (!i) throw Refused{};
     const auto v = static_cast<int32_t>(PyLong_AsUnsignedLongLongMask(i));
     Py_DECREF(i);
     return v;
 }
+int32_t int_of(PyObject *o) { return low_word(PyNumber_Long(o)); }        // whatever int() takes
+int32_t index_of(PyObject *o) { return low_word(PyNumber_Index(o)); }     // integers only
 float float_of(PyObject *o)
 {
     const double v = PyFloat_AsDouble(o);
@@ -168,6 +169,7 @@ int unlocked(Call call)
 PyObject *decode(PyObject *, PyObject *const *a, Py_ssize_t n)
 {
     return guarded(n, 16, [&]() -> int {
+        const int32_t Hkv = index_of(a[12]);
         const at::Tensor &q = tensor(a[1], "q"), &k = tensor(a[2], "k"), &v = tensor(a[3], "v"), &items = tensor(a[4], "items"),
                          &workspace = tensor(a[8], "workspace", true), &out = tensor(a[9], "out"), &lse = tensor(a[10], "lse", true),
                          &trace = tensor(a[15], "trace", true);
@@ -181,7 +183,6 @@ PyObject *decode(PyObject *, PyObject *const *a, Py_ssize_t n)
         const int32_t in_dt = on_valu && is(q, at::kBFloat16) ? FAIRKV_BF16_VALU : dtype_code(q);
         const PlanArgs p = plan_args(items, a[5], a[6], a[7]);
         const float scale = float_of(a[11]);
-        const int32_t Hkv = int_of(a[12]);
         void *st = stream_of(a[13], a[0], q);
         float *l = static_cast<float *>(ptr(lse));
         if (trace.defined()) {
@@ -222,7 +223,7 @@ const float *scale_array(PyObject *o, int32_t Hkv, const char *name)
 PyObject *decode_8bit(PyObject *, PyObject *const *a, Py_ssize_t n)
 {
     return guarded(n, 17, [&]() -> int {
-        const int32_t Hkv = int_of(a[14]);
+        const int32_t Hkv = index_of(a[14]);
         const int per_head = PyObject_IsTrue(a[16]);
         if (per_head < 0) throw Refused{};
         const float *k_scales = nullptr, *v_scales = nullptr;

@@ -36,3 +36,18 @@ def test_the_others():
         F.fairkv_pack(Q[None], Q[None], K, K, K, K, K, K, K)
     with pytest.raises(TypeError, match="16 arguments"):
         F._native().decode(Q)
+
+
+@pytest.mark.parametrize("Hkv", [1.0, 1.7, "1", None, np.float32(1)])
+def test_the_number_of_heads_is_an_integer(Hkv):
+    byte, wide = K.to(torch.uint8), Q.bfloat16()
+    with pytest.raises(TypeError, match="cannot be interpreted as an integer"):
+        F.fairkv_decode_attn(Q, K, K, K, ITEMS, SLOTS, 1, K, Q, None, 1.0, Hkv)
+    with pytest.raises(TypeError, match="cannot be interpreted as an integer"):
+        F.fairkv_decode_attn_kv8(wide, byte, byte, 1.0, 1.0, K, ITEMS, SLOTS, 1, K, Q, None, 1.0, Hkv)
+
+
+@pytest.mark.parametrize("Hkv", [1, True, np.int64(1), np.uint8(1), torch.tensor(1)])
+def test_any_integer_is_a_number_of_heads(Hkv):
+    with pytest.raises(ValueError, match="q must be a contiguous device tensor"):
+        F.fairkv_decode_attn(Q, K, K, K, ITEMS, SLOTS, 1, K, Q, None, 1.0, Hkv)
