@@ -77,14 +77,17 @@ int32_t low_word(PyObject *i)      // of an int, whose reference it takes
 }
 int32_t int_of(PyObject *o) { return low_word(PyNumber_Long(o)); }        // whatever int() takes
 int32_t index_of(PyObject *o) { return low_word(PyNumber_Index(o)); }     // integers only
-float float_of(PyObject *o)
+float float_of(PyObject *o)                                               // whatever float() takes
 {
-    const double v = PyFloat_AsDouble(o);
-    if (v == -1.0 && PyErr_Occurred()) throw Refused{};
+    PyObject *f = PyNumber_Float(o);
+    if (!f) throw Refused{};
+    const double v = PyFloat_AS_DOUBLE(f);
+    Py_DECREF(f);
     return static_cast<float>(v);
 }
 
-// The stream to enqueue on: the caller's, or what `current` (device number -> stream) says of the tensor's device.
+// The stream to enqueue on: the caller's, or what `current` (device number -> stream) says of the tensor's device.  A caller's is
+// whatever has a cuda_stream: a number, a ctypes.c_void_p, or None for the null stream.
 void *stream_of(PyObject *stream, PyObject *current, const at::Tensor &t)
 {
     PyObject *s = stream != Py_None ? PyObject_GetAttrString(stream, "cuda_stream") : nullptr;
@@ -93,8 +96,13 @@ void *stream_of(PyObject *stream, PyObject *current, const at::Tensor &t)
         s = device ? PyObject_CallOneArg(current, device) : nullptr;
         Py_XDECREF(device);
     }
+    if (s && s != Py_None && !PyLong_Check(s)) {
+        PyObject *value = PyObject_GetAttrString(s, "value");
+        Py_DECREF(s);
+        s = value;
+    }
     if (!s) throw Refused{};
-    void *p = PyLong_AsVoidPtr(s);
+    void *p = s == Py_None ? nullptr : PyLong_AsVoidPtr(s);
     Py_DECREF(s);
     if (!p && PyErr_Occurred()) throw Refused{};
     return p;

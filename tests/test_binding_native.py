@@ -1,5 +1,8 @@
 """The native part of the binding refuses what the library cannot take, by the argument's name (no GPU: nothing gets as far as
 a launch), and lets PyTorch's own errors through."""
+import ctypes
+import types
+
 import numpy as np
 import pytest
 
@@ -51,3 +54,28 @@ def test_the_number_of_heads_is_an_integer(Hkv):
 def test_any_integer_is_a_number_of_heads(Hkv):
     with pytest.raises(ValueError, match="q must be a contiguous device tensor"):
         F.fairkv_decode_attn(Q, K, K, K, ITEMS, SLOTS, 1, K, Q, None, 1.0, Hkv)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("scale", ["0.5", np.array(0.5), torch.tensor(0.5), np.float32(0.5)])
+@pytest.mark.parametrize("form", [int, ctypes.c_void_p, lambda s: None])
+def test_what_a_scale_and_a_stream_may_be(scale, form):
+    """A scale is whatever float() takes; a stream has a cuda_stream, which is a number, a pointer of ctypes or None."""
+    from paper_2502_15804_amd.runtime import DecodeLayer
+    from test_gpu_parity import make_case
+    w, off, q, k, v = make_case(1, 4, 2, 64, "bf16", np.array([[33, 90]], np.int32), seed=1)
+    layer = DecodeLayer(q.cuda(), k.cuda(), v.cuda(), off, np.array([[33, 90]], np.int32), 0.5)
+    want = [t.clone() for t in layer.run()]
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    torch.cuda.synchronize()
+    layer.scale = scale
+    layer.out.zero_(), layer.lse.zero_()
+    torch.cuda.synchronize()
+    layer.run(stream=types.SimpleNamespace(cuda_stream=form(side.cuda_stream)))
+    torch.cuda.synchronize()
+    assert torch.equal(layer.out, want[0]) and torch.equal(layer.lse, want[1])
+    with pytest.raises(AttributeError):
+        layer.run(stream=types.SimpleNamespace(cuda_stream="7"))
+    with pytest.raises(TypeError):
+        layer.run(stream=types.SimpleNamespace(cuda_stream=ctypes.c_double(0.0)))
