@@ -279,8 +279,9 @@ def _native():
                               f"`python -m paper_2502_15804_amd.build` (there is no fallback path)")
         _torch()                                             # the libraries that it is linked with
         from importlib import machinery, util
-        loader = machinery.ExtensionFileLoader("_binding", BINDING_PATH)
-        m = util.module_from_spec(util.spec_from_file_location("_binding", BINDING_PATH, loader=loader))
+        name = __name__ + "._binding"                        # the loader enters it in sys.modules: not under a name of the program's own
+        loader = machinery.ExtensionFileLoader(name, BINDING_PATH)
+        m = util.module_from_spec(util.spec_from_file_location(name, BINDING_PATH, loader=loader))
         loader.exec_module(m)
         m.init(ITEM_DTYPE, *(ctypes.cast(f, ctypes.c_void_p).value for f in (
             L.fairkv_decode_attn_multi, L.fairkv_decode_attn_static, L.fairkv_decode_attn_trace, L.fairkv_decode_attn_kv8,

@@ -1,6 +1,9 @@
 """The native part of the binding refuses what the library cannot take, by the argument's name (no GPU: nothing gets as far as
 a launch), and lets PyTorch's own errors through."""
 import ctypes
+import os
+import subprocess
+import sys
 import types
 
 import numpy as np
@@ -39,6 +42,12 @@ def test_the_others():
         F.fairkv_pack(Q[None], Q[None], K, K, K, K, K, K, K)
     with pytest.raises(TypeError, match="16 arguments"):
         F._native().decode(Q)
+
+
+def test_a_program_keeps_its_own_module_of_that_name():
+    program = ("import sys, types; sys.modules['_binding'] = mine = types.ModuleType('_binding'); import paper_2502_15804_amd as F; F._native(); "
+               "assert sys.modules['_binding'] is mine")
+    subprocess.run([sys.executable, "-c", program], cwd=os.path.dirname(os.path.dirname(F.__file__)), check=True)
 
 
 @pytest.mark.parametrize("Hkv", [1.0, 1.7, "1", None, np.float32(1)])
