@@ -1,8 +1,12 @@
 """Compile the HIP library in-tree for gfx950 (cross-compiles without a GPU)."""
 from __future__ import annotations
 
+import importlib.util
 import os
+import shutil
 import subprocess
+import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
@@ -15,21 +19,42 @@ SOURCES = [os.path.join(CSRC, "fairkv_api.hip"), os.path.join(CSRC, "fairkv_plan
 HEADERS = [os.path.join(ROOT, "include", "fairkv.h"), os.path.join(ROOT, "include", "fairkv_measure.h")] + [os.path.join(CSRC, h) for h in ("common.h", "decode_f32.h", "decode_mfma.h", "decode_valu.h", "pack.h", "stream_probe.h")]
 
 
+def _hipcc() -> str:
+    return os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+
+
 def is_stale() -> bool:
     def older(out, inputs):
         return not os.path.exists(out) or any(os.path.getmtime(f) > os.path.getmtime(out) for f in inputs)
-    return older(LIB, SOURCES + HEADERS) or older(BINDING, [BINDING_SOURCE] + HEADERS[:2])
+    return older(LIB, SOURCES + HEADERS) or (missing_for_binding() is None and older(BINDING, [BINDING_SOURCE] + HEADERS[:2]))
+
+
+def _compiler():
+    """The host compiler of the binding: CXX, g++, or the one that comes with hipcc."""
+    for name in (os.environ.get("CXX"), "g++", os.path.join(os.path.dirname(_hipcc()), "amdclang++")):
+        if name and shutil.which(name):
+            return name
+    return None
+
+
+def missing_for_binding():
+    """What this machine lacks to build the native part of the Python binding, or None.  Callers of the C library need none of it."""
+    if importlib.util.find_spec("torch") is None:
+        return "PyTorch"
+    if not os.path.exists(os.path.join(sysconfig.get_paths()["include"], "Python.h")):
+        return "the headers of Python"
+    if _compiler() is None:
+        return "a C++ compiler"
+    return None
 
 
 def build_binding() -> str:
     """The native part of the Python binding, against the PyTorch and numpy that import it."""
-    import sysconfig
-
     import numpy
     import torch
 
     at = os.path.dirname(torch.__file__)
-    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-Wall", "-Wextra",
+    cmd = [_compiler(), "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-Wall", "-Wextra",
            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch.compiled_with_cxx11_abi())}", "-I", os.path.join(ROOT, "include"),
            "-isystem", os.path.join(at, "include"), "-isystem", numpy.get_include(), "-isystem", sysconfig.get_paths()["include"],
            BINDING_SOURCE, "-o", BINDING, "-L", os.path.join(at, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"]
@@ -42,8 +67,7 @@ def build_binding() -> str:
 def build(force: bool = True, verbose: bool = False) -> str:
     if not force and not is_stale():
         return LIB
-    hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
-    cmd = [hipcc, "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
+    cmd = [_hipcc(), "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
            "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
            # MFMA accumulators in ordinary vector registers: the softmax rescales them with vector
            # instructions, and the accumulation-register form costs a copy in and out per tile
@@ -59,10 +83,13 @@ def build(force: bool = True, verbose: bool = False) -> str:
         raise RuntimeError("hipcc failed:\n" + err)
     if verbose and err:
         print(err)
-    build_binding()
+    missing = missing_for_binding()
+    if missing is None:
+        build_binding()
+    else:
+        print(f"{LIB} is built, the Python binding is not: {missing} not found", file=sys.stderr)
     return LIB
 
 
 if __name__ == "__main__":
-    import sys
     print(build(force=True, verbose="-v" in sys.argv))
