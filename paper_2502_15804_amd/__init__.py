@@ -278,6 +278,10 @@ def _native():
             raise ImportError(f"{BINDING_PATH} is missing: build it with "
                               f"`python -m paper_2502_15804_amd.build` (there is no fallback path)")
         _torch()                                             # the libraries that it is linked with
+        from .build import binding_is_made_for_this
+        if not binding_is_made_for_this():
+            raise ImportError(f"{BINDING_PATH} was built for another Python or PyTorch: build it again with "
+                              f"`python -m paper_2502_15804_amd.build`")
         from importlib import machinery, util
         name = __name__ + "._binding"                        # the loader enters it in sys.modules: not under a name of the program's own
         loader = machinery.ExtensionFileLoader(name, BINDING_PATH)

@@ -23,10 +23,32 @@ def _hipcc() -> str:
     return os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 
+def _older(out, inputs) -> bool:
+    return not os.path.exists(out) or any(os.path.getmtime(f) > os.path.getmtime(out) for f in inputs)
+
+
+def library_is_stale() -> bool:
+    return _older(LIB, SOURCES + HEADERS)
+
+
+def binding_is_stale() -> bool:
+    return _older(BINDING, [BINDING_SOURCE] + HEADERS[:2]) or not binding_is_made_for_this()
+
+
 def is_stale() -> bool:
-    def older(out, inputs):
-        return not os.path.exists(out) or any(os.path.getmtime(f) > os.path.getmtime(out) for f in inputs)
-    return older(LIB, SOURCES + HEADERS) or (missing_for_binding() is None and older(BINDING, [BINDING_SOURCE] + HEADERS[:2]))
+    return library_is_stale() or (missing_for_binding() is None and binding_is_stale())
+
+
+def _made_for() -> str:
+    """The interpreter and the PyTorch whose objects the binding reads; numpy looks at its own version when it is loaded."""
+    import torch
+    return f"binding made for {sysconfig.get_config_var('SOABI')} and PyTorch {torch.__version__};"
+
+
+def binding_is_made_for_this() -> bool:
+    """Whether the binding that is built carries the versions of the running Python and PyTorch (its file is looked at, not loaded)."""
+    with open(BINDING, "rb") as f:
+        return _made_for().encode() in f.read()
 
 
 def _compiler():
@@ -55,7 +77,7 @@ def build_binding() -> str:
 
     at = os.path.dirname(torch.__file__)
     cmd = [_compiler(), "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-Wall", "-Wextra",
-           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch.compiled_with_cxx11_abi())}", "-I", os.path.join(ROOT, "include"),
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch.compiled_with_cxx11_abi())}", f'-DMADE_FOR="{_made_for()}"', "-I", os.path.join(ROOT, "include"),
            "-isystem", os.path.join(at, "include"), "-isystem", numpy.get_include(), "-isystem", sysconfig.get_paths()["include"],
            BINDING_SOURCE, "-o", BINDING, "-L", os.path.join(at, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"]
     res = subprocess.run(cmd, capture_output=True, text=True)
@@ -64,9 +86,7 @@ def build_binding() -> str:
     return BINDING
 
 
-def build(force: bool = True, verbose: bool = False) -> str:
-    if not force and not is_stale():
-        return LIB
+def _build_library(verbose: bool) -> None:
     cmd = [_hipcc(), "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
            "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
            # MFMA accumulators in ordinary vector registers: the softmax rescales them with vector
@@ -83,9 +103,15 @@ def build(force: bool = True, verbose: bool = False) -> str:
         raise RuntimeError("hipcc failed:\n" + err)
     if verbose and err:
         print(err)
+
+
+def build(force: bool = True, verbose: bool = False) -> str:
+    if force or library_is_stale():
+        _build_library(verbose)
     missing = missing_for_binding()
     if missing is None:
-        build_binding()
+        if force or binding_is_stale():
+            build_binding()
     else:
         print(f"{LIB} is built, the Python binding is not: {missing} not found", file=sys.stderr)
     return LIB

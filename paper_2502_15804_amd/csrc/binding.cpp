@@ -341,6 +341,9 @@ PyObject *init(PyObject *, PyObject *args)
     Py_RETURN_NONE;
 }
 
+// What this file is compiled against (build.py), found in the built file before that is loaded.
+[[gnu::used]] const char made_for[] = MADE_FOR;
+
 PyMethodDef methods[] = {
     {"init", init, METH_VARARGS, nullptr},
     {"decode", reinterpret_cast<PyCFunction>(reinterpret_cast<void *>(decode)), METH_FASTCALL, nullptr},

@@ -1,12 +1,15 @@
-"""What the build needs of a machine (nothing is compiled here but the binding): the C library needs neither PyTorch nor the
-headers of Python."""
+"""What a build needs of a machine and what it builds (no compiler is run here): the C library needs neither PyTorch nor the headers
+of Python, and a binding belongs to one Python and one PyTorch."""
 import importlib.util
+import os
+import shutil
 import subprocess
 import sysconfig
 
 import pytest
 
-pytest.importorskip("torch")
+torch = pytest.importorskip("torch")
+import paper_2502_15804_amd as F
 from paper_2502_15804_amd import build as B
 
 
@@ -59,3 +62,37 @@ def test_the_binding_that_cannot_be_compiled_is_an_error(monkeypatch):
     monkeypatch.setattr(B.subprocess, "run", run)
     with pytest.raises(RuntimeError, match="no such type"):
         B.build()
+
+
+@pytest.fixture
+def own_binding(monkeypatch, tmp_path):
+    """A copy of the built binding, so that the one in use stays."""
+    copy = str(tmp_path / "_binding.so")
+    shutil.copyfile(B.BINDING, copy)
+    monkeypatch.setattr(B, "BINDING", copy)
+    return copy
+
+
+def test_a_binding_for_another_pytorch_or_python_is_stale_and_not_loaded(monkeypatch, own_binding):
+    monkeypatch.setattr(F, "_native_module", None)
+    assert not B.binding_is_stale() and F._native()
+    monkeypatch.setattr(F, "_native_module", None)
+    with monkeypatch.context() as m:
+        m.setattr(torch, "__version__", torch.__version__[:-1])      # what the version of the other starts with
+        assert B.binding_is_stale()
+        with pytest.raises(ImportError, match="another Python or PyTorch"):
+            F._native()
+    with monkeypatch.context() as m:
+        m.setattr(sysconfig, "get_config_var", lambda name: "cpython-399-x86_64-linux-gnu")
+        assert B.binding_is_stale()
+        with pytest.raises(ImportError, match="another Python or PyTorch"):
+            F._native()
+
+
+def test_only_what_is_stale_is_built(monkeypatch, commands, own_binding):
+    monkeypatch.setattr(B, "library_is_stale", lambda: False)
+    B.build(force=False)
+    assert commands == []
+    os.utime(own_binding, (0, 0))
+    B.build(force=False)
+    assert len(commands) == 1 and own_binding in commands[0]
