@@ -224,9 +224,11 @@ struct ArgLanes {
     {
         uint32_t w[kWords];
         __builtin_memcpy(w, &a, sizeof a);
+        // The wait states in front: a vector instruction may have written a word (a spilled one comes back with a v_readlane).  Behind: a
+        // v_readlane of the result may be next.
 #pragma unroll
-        for (int i = kFirst; i <= kLast; i += 4)      // the s_nop is the wait state between a vector instruction and a v_readlane of its result
-            asm("v_writelane_b32 %0, %1, %5\n\tv_writelane_b32 %0, %2, %5+1\n\tv_writelane_b32 %0, %3, %5+2\n\tv_writelane_b32 %0, %4, %5+3\n\ts_nop 0"
+        for (int i = kFirst; i <= kLast; i += 4)
+            asm("s_nop 1\n\tv_writelane_b32 %0, %1, %5\n\tv_writelane_b32 %0, %2, %5+1\n\tv_writelane_b32 %0, %3, %5+2\n\tv_writelane_b32 %0, %4, %5+3\n\ts_nop 0"
                 : "+v"(lanes) : "s"(w[i]), "s"(w[i + 1]), "s"(w[i + 2]), "s"(w[i + 3]), "n"(i));
     }
     __device__ __forceinline__ CallArgs get() const
@@ -251,7 +253,7 @@ __device__ __forceinline__ float lane_values(const float (&k)[kScaleHeads], cons
 #pragma unroll
     for (int i = 0; i < 2 * kScaleHeads; i += 4) {
         const float *w = i < kScaleHeads ? k + i : v + (i - kScaleHeads);
-        asm("v_writelane_b32 %0, %1, %5\n\tv_writelane_b32 %0, %2, %5+1\n\tv_writelane_b32 %0, %3, %5+2\n\tv_writelane_b32 %0, %4, %5+3\n\ts_nop 0"
+        asm("s_nop 1\n\tv_writelane_b32 %0, %1, %5\n\tv_writelane_b32 %0, %2, %5+1\n\tv_writelane_b32 %0, %3, %5+2\n\tv_writelane_b32 %0, %4, %5+3\n\ts_nop 0"
             : "+v"(lanes) : "s"(w[0]), "s"(w[1]), "s"(w[2]), "s"(w[3]), "n"(i));
     }
     return lanes;

@@ -1,14 +1,17 @@
 """Wait states that the hardware does not keep by itself, looked for in the compiler's gfx950 assembly (text only, no GPU).
 
 The compiler keeps them between its own instructions; it does not look inside inline assembly, where the decode kernels
-have their HBM -> LDS loads and the stores of their partials.  Looked for, along every path through a function:
+have their HBM -> LDS loads, the stores of their partials and the arguments that they keep in the lanes of a register.  Looked for, along every path through a function:
   - a memory instruction reading a scalar register less than 5 wait states after a vector instruction wrote it;
   - an LDS load less than 1 wait state after a scalar instruction wrote M0;
-  - a vector instruction writing the data registers of a store of more than 8 bytes less than 2 wait states after it.
+  - a vector instruction writing the data registers of a store of more than 8 bytes less than 2 wait states after it;
+  - a vector instruction reading a scalar register less than 2 wait states after a vector instruction wrote it, or taking the lane
+    of a v_readlane or v_writelane from it less than 4 after;
+  - a v_readlane or v_readfirstlane of a vector register less than 1 wait state after a vector instruction wrote it.
 An instruction is one wait state, s_nop N is N + 1."""
 import re
 
-SGPR_WAIT, M0_WAIT, DATA_WAIT = 5, 1, 2
+SGPR_WAIT, M0_WAIT, DATA_WAIT, SGPR_TO_VECTOR_WAIT, SGPR_TO_LANE_WAIT, VGPR_TO_READLANE_WAIT = 5, 1, 2, 2, 4, 1
 _LABEL = re.compile(r"^([\w.$]+):")
 _CARRY = re.compile(r"v_(add|sub|subrev|addc|subb|subbrev)_co|v_div_scale|v_mad_[ui]64")
 
@@ -47,11 +50,17 @@ def _step(text, wait, found):
             found.add((text, "m0"))
     if op.startswith("v_"):
         found.update((text, f"v{r}") for r in _regs(args[0], "v") if ("v", r) in wait)
+        for i, src in enumerate(args[2 if _CARRY.match(op) else 1:], 1):      # SGPR_WAIT less what is left of it have passed
+            least = SGPR_TO_LANE_WAIT if i == 2 and re.match(r"v_(read|write)lane_", op) else SGPR_TO_VECTOR_WAIT
+            found.update((text, f"s{r}") for r in _regs(src, "s") if SGPR_WAIT - wait.get(("s", r), 0) < least)
+        if op.startswith(("v_readlane", "v_readfirstlane")):
+            found.update((text, f"v{r}") for r in _regs(args[1], "v") if ("written v", r) in wait)
     passed = int(rest, 0) + 1 if op == "s_nop" else 1
     wait = {k: n - passed for k, n in wait.items() if n > passed}
     if op.startswith("v_"):
         for dst in args[:2] if _CARRY.match(op) else args[:1]:
             wait.update({("s", r): SGPR_WAIT for r in _regs(dst, "s")})
+        wait.update({("written v", r): VGPR_TO_READLANE_WAIT for r in _regs(args[0], "v")})
     elif op.startswith("s_") and not op.startswith(("s_cmp", "s_bitcmp", "s_cbranch", "s_nop", "s_waitcnt")):
         for r in _regs(args[0], "s"):
             wait.pop(("s", r), None)

@@ -1,5 +1,5 @@
-// The decode kernels' inline-assembly memory helpers behind the least favourable instruction in front of them: a vector
-// instruction (readfirstlane) that wrote the base they are given.  Compiled to assembly by test_inline_asm.py.
+// The decode kernels' inline-assembly helpers behind the least favourable instruction in front of them: a vector
+// instruction (readfirstlane) that wrote the base, or the words, that they are given.  Compiled to assembly by test_inline_asm.py.
 #include "decode_mfma.h"
 
 using namespace fairkv;
@@ -43,3 +43,25 @@ __device__ __forceinline__ void tile(const float *const *bases, float *out)
 }
 extern "C" __global__ void tile2(const float *const *bases, float *out) { tile<2>(bases, out); }
 extern "C" __global__ void tile4(const float *const *bases, float *out) { tile<4>(bases, out); }
+
+extern "C" __global__ void argument_lanes(const uint32_t *words, uint32_t *out)
+{
+    uint32_t w[sizeof(CallArgs) / 4];
+    for (int i = sizeof(CallArgs) / 4 - 1; i >= 0; --i) {      // the word that is used first is written last
+        w[i] = __builtin_amdgcn_readfirstlane(words[i * 64 + threadIdx.x % 64]);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    CallArgs a;
+    __builtin_memcpy(&a, w, sizeof a);
+    out[threadIdx.x] = ArgLanes(a).lanes;
+}
+extern "C" __global__ void factor_lanes(const float *words, float *out)
+{
+    float k[kScaleHeads], v[kScaleHeads];
+    for (int i = kScaleHeads - 1; i >= 0; --i) {
+        __builtin_amdgcn_sched_barrier(0);
+        k[i] = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(words[i * 64 + threadIdx.x % 64])));
+    }
+    for (int i = 0; i < kScaleHeads; ++i) v[i] = words[i];
+    out[threadIdx.x] = lane_values(k, v);
+}
