@@ -209,14 +209,14 @@ def test_full_size_workloads_every_output(name):
 
 
 def test_slot_lists_longer_than_the_item_table():
-    # 600 pairs on 2 slots: about 300 items per slot, so the kernel walks its list in three fills of its table of 128
+    # 600 pairs on 2 slots: about 300 items per slot, so the kernel walks its list in five batches of 64
     rng = np.random.default_rng(21)
     B, Hkv, G = 75, 8, 4
     lens = rng.integers(0, 90, size=(B, Hkv)).astype(np.int32)
     w, off, q, k, v = make_case(B, Hkv * G, Hkv, 128, "bf16", lens, seed=9, gap_rows=1)
     for policy in (0, 3):
         err, layer = check(w, q, k, v, off, lens, policy=policy, n_slots=2, calls=2)
-        assert np.diff(layer.plan.slot_ptr).max() > 2 * 128
+        assert np.diff(layer.plan.slot_ptr).max() > 4 * 64
 
 
 def test_many_cut_pieces_per_slot_and_per_pair():
