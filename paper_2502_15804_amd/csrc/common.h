@@ -110,7 +110,7 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t parts_rsrc(float *base, uint32
 
 constexpr int kScaleHeads = 8;            // KV heads that may carry scales of their own (8-bit caches)
 
-// What a kernel asks of its arguments at one time or another, 128 bytes: read whole, in one round trip (held_args).
+// What a kernel asks of its arguments at one time or another, 128 bytes: read whole, in one round trip (arrive_together).
 struct CallArgs {
     const void *q, *k, *v;
     const fairkv_item *items;   // grouped by slot

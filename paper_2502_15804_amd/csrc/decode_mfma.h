@@ -42,11 +42,8 @@
 namespace fairkv {
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_t;
-typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4_t;
 typedef __attribute__((ext_vector_type(4))) short i16x4_t;
 typedef __attribute__((ext_vector_type(4))) float f32x4_t;
-typedef __attribute__((ext_vector_type(8))) float f32x8_t;
-typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2_v;
 typedef __attribute__((ext_vector_type(2))) int i32x2_t;
 typedef __attribute__((ext_vector_type(2))) uint16_t u16x2_t;
 
@@ -120,34 +117,14 @@ __device__ __forceinline__ void wait_vmcnt()
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
 
-// Wait until at most `tiles` tile fetches (LOADS loads each) and `qs` query-block fetches
-// (QL loads each) are outstanding, i.e. everything requested before them has landed.
-template <int LOADS, int QL>
-__device__ __forceinline__ void wait_all_but(int tiles, int qs)
-{
-    static_assert(3 * (LOADS + QL) < 64, "vmcnt is a 6-bit counter");
-    switch (tiles * 4 + qs) {
-    case 4: wait_vmcnt<LOADS>(); break;
-    case 5: wait_vmcnt<LOADS + QL>(); break;
-    case 8: wait_vmcnt<2 * LOADS>(); break;
-    case 9: wait_vmcnt<2 * LOADS + QL>(); break;
-    case 10: wait_vmcnt<2 * LOADS + 2 * QL>(); break;
-    case 12: wait_vmcnt<3 * LOADS>(); break;
-    case 13: wait_vmcnt<3 * LOADS + QL>(); break;
-    case 14: wait_vmcnt<3 * LOADS + 2 * QL>(); break;
-    case 15: wait_vmcnt<3 * LOADS + 3 * QL>(); break;
-    default: wait_vmcnt<0>(); break;
-    }
-}
-
 // Eight E4M3 bytes widened to eight bf16 (exact; v_cvt_scalef32_pk_bf16_fp8 with scale 1 takes two bytes
 // at a time: the low or the high half of a dword).
 __device__ __forceinline__ bf16x8_t widen8(i32x2_t w)
 {
-    const bf16x2_v a0 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(w[0], 1.0f, false);
-    const bf16x2_v a1 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(w[0], 1.0f, true);
-    const bf16x2_v a2 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(w[1], 1.0f, false);
-    const bf16x2_v a3 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(w[1], 1.0f, true);
+    const bf16x2_t a0 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(w[0], 1.0f, false);
+    const bf16x2_t a1 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(w[0], 1.0f, true);
+    const bf16x2_t a2 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(w[1], 1.0f, false);
+    const bf16x2_t a3 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(w[1], 1.0f, true);
     return bf16x8_t{a0[0], a0[1], a1[0], a1[1], a2[0], a2[1], a3[0], a3[1]};
 }
 
@@ -176,7 +153,12 @@ __device__ __forceinline__ float quarters_sum(float x)
 // to fetch and the other two one tile each), so a slot of many short pairs had about one pair in flight at a time
 // and each cost a memory round trip; alone, four pairs stream side by side.
 constexpr int kSoloTokens = FAIRKV_SHORT_PAIR_TOKENS;
-constexpr int kList = 64;             // items per fill of a wave's list in registers (ItemList): one per lane
+
+// Items per fill of a wave's list in registers (ItemList): one per lane.  Between two fills the ring drains, and the list and the next tile
+// are waited for one after the other; with the 128 items of a table in LDS that came half as often.  us per layer with such a table and
+// now, 8 KV heads, 24 to 56 tokens a pair: slots of 63 items 82.2 and 81.6, 67 86.5 and 87.3, 75 96.4 and 94.9, 100 127.3 and 125.4, 133 186.6
+// and 182.5; on 8-bit caches 61.0 and 58.4, 63.6 and 62.4, 71.6 and 69.9, 89.8 and 89.0, 121.9 and 121.4.
+constexpr int kList = 64;
 
 // A wave's own copy of (part of) its slot's item list: lane j holds item j.  A field of an item is one v_readlane away,
 // where a table in LDS costs a wait of 130 cycles for each of the handful of fields that start an item, and a barrier
@@ -611,7 +593,7 @@ __global__ __launch_bounds__(kThreads, 1) void fairkv_decode_mfma_kernel(DecodeA
                     uint32_t pw[NS / 2];
 #pragma unroll
                     for (int r = 0; r < NS; r += 2) {
-                        pw[r / 2] = __builtin_bit_cast(uint32_t, __builtin_convertvector(f2_t{p[r], p[r + 1]}, bf16x2_v));
+                        pw[r / 2] = pack_bf16(p[r], p[r + 1]);
                         l_run = l_run + bf16_lo(pw[r / 2]) + bf16_hi(pw[r / 2]);
                     }
                     const bf16x8_t pb = __builtin_bit_cast(bf16x8_t, uint4{pw[0], pw[1], pw[2], pw[3]});
@@ -628,10 +610,9 @@ __global__ __launch_bounds__(kThreads, 1) void fairkv_decode_mfma_kernel(DecodeA
                     for (int r = 0; r < NS; r += 2) {
                         l_run = l_run + p[r] + p[r + 1];
                         upper[r / 2] = __builtin_amdgcn_perm(__float_as_uint(p[r + 1]), __float_as_uint(p[r]), 0x07060302u);
-                        const f2_t left_over = {p[r] - bf16_hi(__float_as_uint(p[r])), p[r + 1] - bf16_hi(__float_as_uint(p[r + 1]))};      // exact
+                        const float left0 = p[r] - bf16_hi(__float_as_uint(p[r])), left1 = p[r + 1] - bf16_hi(__float_as_uint(p[r + 1]));      // exact
                         const u16x2_t floor = __builtin_elementwise_min(__builtin_bit_cast(u16x2_t, upper[r / 2]), __builtin_bit_cast(u16x2_t, ones));
-                        rest[r / 2] = __builtin_bit_cast(uint32_t, __builtin_elementwise_max(
-                            __builtin_bit_cast(u16x2_t, __builtin_convertvector(left_over, bf16x2_v)), floor));
+                        rest[r / 2] = __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(u16x2_t, pack_bf16(left0, left1)), floor));
                     }
                     const bf16x8_t pb = __builtin_bit_cast(bf16x8_t, uint4{upper[0], upper[1], rest[0], rest[1]});
 #pragma unroll

@@ -7,6 +7,18 @@
 
 namespace fairkv {
 
+// Wait until at most `tiles` tile fetches of LOADS loads each are outstanding, i.e. everything requested before them has landed.
+template <int LOADS>
+__device__ __forceinline__ void wait_all_but(int tiles)
+{
+    switch (tiles) {
+    case 1: wait_vmcnt<LOADS>(); break;
+    case 2: wait_vmcnt<2 * LOADS>(); break;
+    case 3: wait_vmcnt<3 * LOADS>(); break;
+    default: wait_vmcnt<0>(); break;
+    }
+}
+
 struct ProbeArgs {
     const char *k, *v;
     int64_t bytes_per_workgroup;   // from each of k and v; a multiple of the tile size
@@ -44,7 +56,7 @@ __global__ __launch_bounds__(WAVES * 64, 1) void fairkv_stream_probe_kernel(Prob
             ++f_t;
             ++ahead;
         }
-        wait_all_but<LOADS, 1>(ahead - 1, 0);
+        wait_all_but<LOADS>(ahead - 1);
         acc ^= *reinterpret_cast<const uint32_t *>(lds + wave * (STAGES * STAGEB) + c_stage * STAGEB + lane * 4);
         c_stage = c_stage + 1 == STAGES ? 0 : c_stage + 1;
         --ahead;
