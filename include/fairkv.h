@@ -109,11 +109,13 @@ typedef struct {
 
 /* Defaults: n_slots = n_compute_units, tile 16, min_chunk 32, max_split 256, oversub 2,
  * overhead_tokens 160 (measured on MI355X: an extra item in a slot costs about as much as
- * streaming 120-160 tokens, and the time per launch is flat from 128 to 192), short_overhead_tokens 48
+ * streaming 120-160 tokens; large layers are within 1 % from 96 to 192), short_overhead_tokens 48
  * (a short pair costs a slot about a third of that), policy FAIR.  n_compute_units must be >= 1.
  * The token-valued fields are those of a bf16 cache with D = 128.  Where a token is fewer or more bytes the same item is worth
- * more or fewer tokens: measured good are tile 32, min_chunk 64, overhead_tokens 256, short_overhead_tokens 96 for an 8-bit
- * cache and overhead_tokens 80, short_overhead_tokens 32 for an fp32 cache (up to 22 % less time than with the defaults). */
+ * more or fewer tokens: measured good are tile 32, min_chunk 64, overhead_tokens 256, short_overhead_tokens 128 for an 8-bit
+ * cache and overhead_tokens 64, short_overhead_tokens 32 for an fp32 cache (up to 22 % less time than with the defaults).  On a
+ * bf16 cache of few or short pairs overhead_tokens 96 and min_chunk 64 or 128 are better (256 pairs of 64 tokens 7.3 -> 4.9 us, one
+ * sequence of eight pairs of 1024 9.4 -> 8.8), on large layers by at most 1 %. */
 int fairkv_default_params(fairkv_plan_params *p /*host, out*/, int32_t n_compute_units);
 
 /*
