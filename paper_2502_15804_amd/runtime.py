@@ -9,7 +9,7 @@ from __future__ import annotations
 
 import numpy as np
 
-from . import (FAIRKV_SHORT_PAIR_TOKENS, Plan, fairkv_decode_attn, fairkv_decode_attn_kv8, fairkv_default_params, fairkv_plan,
+from . import (FAIRKV_SHORT_PAIR_TOKENS, FAIRKV_STATIC_WORKSPACE_BYTES, Plan, fairkv_decode_attn, fairkv_decode_attn_kv8, fairkv_default_params, fairkv_plan,
                fairkv_workspace_bytes)
 
 
@@ -56,6 +56,16 @@ def _plan_params(n_cu, kv8, f32, D, lens):
     return p
 
 
+def _earlier_plan_params(n_cu, kv8, f32):
+    """What _plan_params gave before its figures were taken again.  Its plans may need more partial slots than these (fp32: up to 143
+    more over 1500 random layers, bf16 5, 8-bit 13), so a workspace of a given size that held a layer's plan still has one to hold."""
+    if kv8:
+        return fairkv_default_params(n_cu, tile=32, min_chunk=64, overhead_tokens=256, short_overhead_tokens=96)
+    if f32:
+        return fairkv_default_params(n_cu, overhead_tokens=80, short_overhead_tokens=32)
+    return fairkv_default_params(n_cu)
+
+
 class DecodeLayer:
     """One layer's packed ragged KV cache, its plan and its output buffers on the GPU."""
 
@@ -75,11 +85,21 @@ class DecodeLayer:
         self.Hkv = lens_h.shape[1]
         self.G = self.Hq // self.Hkv
         self.scale = float(scale)
-        if params is None:
-            params = _plan_params(device_compute_units(dev), self.kv8, q.dtype == torch.float32, self.D, lens_h)
-        self.plan: Plan = fairkv_plan(lens_h, off_h, self.B, self.Hkv, params)
+        given = params is not None
+        if not given:
+            kind = device_compute_units(dev), self.kv8, q.dtype == torch.float32
+            params = _plan_params(*kind, self.D, lens_h)
+        room = FAIRKV_STATIC_WORKSPACE_BYTES if static_workspace else None if workspace is None else workspace.numel()
+
+        def plan_and_need(params):
+            plan = fairkv_plan(lens_h, off_h, self.B, self.Hkv, params)
+            return plan, fairkv_workspace_bytes(plan.n_parts, self.B * self.Hkv, self.G * self.q_len, self.D)
+
+        plan, need = plan_and_need(params)
+        if not given and room is not None and need > room:
+            plan, need = plan_and_need(_earlier_plan_params(*kind))
+        self.plan: Plan = plan
         self.items_d = torch.from_numpy(self.plan.items.view(np.uint8).copy()).to(dev)
-        need = fairkv_workspace_bytes(self.plan.n_parts, self.B * self.Hkv, self.G * self.q_len, self.D)
         self.bf16_on_valu = bf16_on_valu
         if static_workspace:
             workspace = None                                               # the library's own (fairkv_decode_attn_static)
