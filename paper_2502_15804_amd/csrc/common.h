@@ -133,9 +133,13 @@ struct CallArgs {
 };
 static_assert(sizeof(CallArgs) == 128, "two cache lines");
 
+// 8-bit caches with a scale per KV head: further factors on scale_log2 and v_scale, indexed h % kScaleHeads (all 1 otherwise; read by the
+// 8-bit kernels only).
+struct HeadFactors {
+    float k[kScaleHeads], v[kScaleHeads];
+};
 struct DecodeArgs : CallArgs {
-    float k_head[kScaleHeads];  // 8-bit caches with a scale per KV head: further factors on scale_log2 and v_scale,
-    float v_head[kScaleHeads];  // indexed h % kScaleHeads (all 1 otherwise; read by the 8-bit kernels only)
+    HeadFactors factors;
     // What a workgroup needs before it has read anything from memory, riding in the kernel arguments.  Slot j has words
     // 3 j ...: the index of its first item (its last is the one before slot j + 1's first), the first K/V row of that
     // item, and in one word its query group (b * q_len * Hkv + h, bits 9..31) and min(tok_count, kEarlyTok) (bits

@@ -277,9 +277,17 @@ __global__ __launch_bounds__(kThreads, 1) void fairkv_decode_mfma_kernel(DecodeA
     const int lq = lane >> 4;       // which quarter of the contraction index this lane feeds
 
     if constexpr (TRACE) trace_stamp(args, kTraceStart, threadIdx.x == 0);
+    // The kernel arguments are asked for here and waited for below (arrive_together): what depends on the lane alone is worked out in between.  Without
+    // the barrier the compiler asks for them behind those 95 instructions.  With the rows of the first tile requested before its queries, and
+    // nothing made ready for an item that does not come, us per layer: Llama-70B shape 16.10 -> 15.80, the same with an 8-bit cache
+    // 10.97 -> 10.87, one sequence 8.56 -> 8.41, Pareto budgets at batch 128 20.84 -> 20.60, 24B shape 32.9 -> 32.7.
+    const SlotStart slot = slot_start(args);
+    const CallArgs held = args;
+    HeadFactors factors{};
+    if constexpr (KV8) factors = args.factors;
+    __builtin_amdgcn_sched_barrier(0);
     // Lane j of load i of a tile fills LDS slot (row i*RPI + j/PPR, column j%PPR); the piece it
-    // fetches is column ^ swizzle(row).  Byte offsets of that piece inside a full K and V tile (worked out while the kernel
-    // arguments are on their way):
+    // fetches is column ^ swizzle(row).  Byte offsets of that piece inside a full K and V tile:
     const int ld_row = lane / PPR, ld_col = lane % PPR;
     uint32_t k_off[LPT], v_off[LPT];
 #pragma unroll
@@ -329,11 +337,10 @@ __global__ __launch_bounds__(kThreads, 1) void fairkv_decode_mfma_kernel(DecodeA
 #pragma unroll
     for (int nb_ = 0; nb_ < NDB; ++nb_) asm volatile("" : "+v"(v_rd[nb_]));
 
-    const SlotStart slot = slot_start(args);
-    arrive_together(args, slot);
-    const char *const q_base = static_cast<const char *>(args.q), *const k_base = static_cast<const char *>(args.k);
-    const int64_t v_minus_k = static_cast<const char *>(args.v) - k_base;
-    const int g_shift = args.g_shift;
+    arrive_together(held, slot);
+    const char *const q_base = static_cast<const char *>(held.q), *const k_base = static_cast<const char *>(held.k);
+    const int64_t v_minus_k = static_cast<const char *>(held.v) - k_base;
+    const int g_shift = held.g_shift;
     const int i_begin = slot.i_begin, i_end = slot.i_end;
     if (i_end <= i_begin) return;   // an idle slot
     // Fetch of the kList items that start at `first`: one load by each wave, 32 items by waves 0 and 2, the next 32 by waves 1 and 3
@@ -341,7 +348,7 @@ __global__ __launch_bounds__(kThreads, 1) void fairkv_decode_mfma_kernel(DecodeA
     auto fetch_items = [&](const fairkv_item *items, int first) __attribute__((always_inline)) {
         load16_to_lds_keep(items + first, min(list_item, i_end - first - 1) * 32 + (lane & 1) * 16, raw_lds);
     };
-    fetch_items(args.items, i_begin);
+    fetch_items(held.items, i_begin);
 
     // The fetch cursor (f_*) stands on this wave's next tile of item f_item and runs ahead of the compute cursor, possibly into
     // later items: f_left tokens of the item from that tile on (none or less: the wave is through with the item), f_k the address
@@ -354,24 +361,9 @@ __global__ __launch_bounds__(kThreads, 1) void fairkv_decode_mfma_kernel(DecodeA
     uint64_t f_k = 0;
     bool f_new = true, next_q = false;
 
-    // Lane offsets of the G query rows of a query group: column c = (new token c >> g_shift, head c & mask) of
-    // q [B][q_len][Hq][D]: the heads of one new token are contiguous, the new tokens are Hq rows apart.
-    uint32_t q_off[QL];
-#pragma unroll
-    for (int i = 0; i < QL; ++i) {
-        const int o = min(i * 1024 + lane * 16, QBYTES - 16);      // byte o of the [G][QROWB] image in LDS
-        q_off[i] = col_row(g_shift, args.Hq, o / QROWB) * QROWB + o % QROWB;
-    }
     // The cursor's tile into the next stage: LOADS loads, QL more for the queries of another item.  Rows past the end of the item
     // re-read its last row (finite data with weight 0).
-    auto fetch_next = [&]() __attribute__((always_inline)) {
-        next_q = f_new;
-        if (f_new) {
-            const char *src = q_base + (static_cast<size_t>(f_qg) << g_shift) * QROWB;
-#pragma unroll
-            for (int i = 0; i < QL; ++i) load16_to_lds_keep(src, q_off[i], q_lds + f_stage * QBUF + i * 1024);
-            f_new = false;
-        }
+    auto fetch_rows = [&]() __attribute__((always_inline)) {
         const char *k = reinterpret_cast<const char *>(f_k), *v = k + v_minus_k;
         const uint32_t k_lds = ring_lds + f_stage * STAGEB, v_lds = k_lds + TILEB;
         if (f_left >= TOK) {
@@ -385,6 +377,15 @@ __global__ __launch_bounds__(kThreads, 1) void fairkv_decode_mfma_kernel(DecodeA
                 load16_to_lds(v, row * ROWB + (ld_col ^ ((2 * r) % PPR)) * 16, v_lds + i * 1024);
             }
         }
+    };
+    auto fetch_queries = [&](const uint32_t (&q_off)[QL]) __attribute__((always_inline)) {
+        const char *src = q_base + (static_cast<size_t>(f_qg) << g_shift) * QROWB;
+#pragma unroll
+        for (int i = 0; i < QL; ++i) load16_to_lds_keep(src, q_off[i], q_lds + f_stage * QBUF + i * 1024);
+    };
+    auto step_on = [&]() __attribute__((always_inline)) {
+        next_q = f_new;
+        f_new = false;
         f_left -= f_step;
         f_k += static_cast<uint32_t>(f_step) * ROWB;
         f_stage ^= 1;
@@ -394,27 +395,45 @@ __global__ __launch_bounds__(kThreads, 1) void fairkv_decode_mfma_kernel(DecodeA
 
     // Early start: the kernel arguments carry query group, first row and the first kEarlyTok tokens' worth of the length of the
     // slot's first item, so the item list, the first query
-    // block and the first tile are all requested at once, before anything has come back from memory.
+    // block and the first tile are all requested at once, before anything has come back from memory; the rows of the tile first, which need the
+    // least to be worked out.
     const int n0 = static_cast<int>(slot.np & 0x1ffu);
     if (n0 > 0) {
         f_qg = static_cast<int>(slot.np >> 9);
         f_k = row_address(static_cast<int64_t>(slot.row) + wave * TOK);      // the early start always shares the first item among the waves
         f_left = n0 - wave * TOK;
-        if (f_left > 0) fetch_next();
+        if (f_left > 0) fetch_rows();
     }
-    const ArgLanes arg_lanes(args);
+    // Lane offsets of the G query rows of a query group: column c = (new token c >> g_shift, head c & mask) of
+    // q [B][q_len][Hq][D]: the heads of one new token are contiguous, the new tokens are Hq rows apart.
+    uint32_t q_off[QL];
+#pragma unroll
+    for (int i = 0; i < QL; ++i) {
+        const int o = min(i * 1024 + lane * 16, QBYTES - 16);      // byte o of the [G][QROWB] image in LDS
+        q_off[i] = col_row(g_shift, held.Hq, o / QROWB) * QROWB + o % QROWB;
+    }
+    if (n0 > 0 && f_left > 0) {
+        fetch_queries(q_off);
+        step_on();
+    }
+    auto fetch_next = [&]() __attribute__((always_inline)) {
+        if (f_new) fetch_queries(q_off);
+        fetch_rows();
+        step_on();
+    };
+    const ArgLanes arg_lanes(held);
     auto call_args = [&]() __attribute__((always_inline)) {
         CallArgs a = arg_lanes.get();
         if constexpr (TRACE) a.trace = args.trace;
         return a;
     };
-    const float scale_log2 = args.scale_log2;
-    const int q_len = args.q_len, qg_stride = q_len * args.Hkv;      // query groups of a sequence
+    const float scale_log2 = held.scale_log2;
+    const int q_len = held.q_len, qg_stride = q_len * held.Hkv;      // query groups of a sequence
     // 8-bit caches: lane h holds scale_log2 times the K factor of KV head h (modulo kScaleHeads), lane kScaleHeads + h v_scale
     // times its V factor
     float head_mul = 0.f;
     if constexpr (KV8) {
-        head_mul = lane_values(args.k_head, args.v_head) * (lane < kScaleHeads ? scale_log2 : args.v_scale);
+        head_mul = lane_values(factors.k, factors.v) * (lane < kScaleHeads ? scale_log2 : held.v_scale);
     }
 
     const char *q_rd = q_ring + min(l16, G - 1) * QROWB + lq * 16;
@@ -638,13 +657,12 @@ __global__ __launch_bounds__(kThreads, 1) void fairkv_decode_mfma_kernel(DecodeA
             }
             // ---- fold the four token quarters of l, stage this wave's result, finish the item ------
             l_run = quarters_sum(l_run);
-            const CallArgs a = call_args();
-            const Piece pc = list.piece(a, ci, KV8 ? lane_value(head_mul, kScaleHeads + scale_h) : a.v_scale);
-            const bool valid = pc.n_chunks != 0;
             if (SOLO && owner >= 0) {
+                const CallArgs a = call_args();
+                const Piece pc = list.piece(a, ci, KV8 ? lane_value(head_mul, kScaleHeads + scale_h) : a.v_scale);
                 // This wave has seen the whole pair: out = O / l and lse straight from its registers.  A lane holds
                 // coordinates 16 nb + 4 lq .. + 3 of head l16.
-                if (l16 < G && valid) {
+                if (l16 < G && pc.n_chunks != 0) {
 #pragma unroll
                     for (int nb_ = 0; nb_ < NDB; ++nb_)
                         write_out4<D>(a, pc.qg, l16, 16 * nb_ + 4 * lq, make_float4(o[nb_][0], o[nb_][1], o[nb_][2], o[nb_][3]), m_run,
@@ -662,14 +680,16 @@ __global__ __launch_bounds__(kThreads, 1) void fairkv_decode_mfma_kernel(DecodeA
                     *reinterpret_cast<float2 *>(st_ml[set] + (wave * G + l16) * 2) = make_float2(m_run, l_run);
                 }
             }
-            if (valid) {
+            const CallArgs a = call_args();
+            const Piece pc = list.piece(a, ci, KV8 ? lane_value(head_mul, kScaleHeads + scale_h) : a.v_scale);
+            if (pc.n_chunks != 0) {
                 item_epilogue<D, G, DEEP, TRACE>(a, pc, st_o[set], st_ml[set], pend, n_pend, roles);
                 if constexpr (kSets == 2)
                     set ^= 1;
                 else
                     __syncthreads();
             }
-            begin_item();
+            if (batch + ci + 1 < i_end) begin_item();
             if constexpr (TRACE)
                 if (batch == i_begin && ci == 0) trace_stamp(args, kTraceItem0Done, threadIdx.x == 0);
         }

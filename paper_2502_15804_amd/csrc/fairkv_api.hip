@@ -432,8 +432,8 @@ int decode_common(const DecodeCall &c)
     a.scale_log2 = c.scale * kLog2e * c.k_scale;
     a.v_scale = c.v_scale;
     for (int h = 0; h < kScaleHeads; ++h) {     // a scale per KV head (at most kScaleHeads of them), else all 1
-        a.k_head[h] = c.k_head ? c.k_head[h % Hkv] : 1.f;
-        a.v_head[h] = c.v_head ? c.v_head[h % Hkv] : 1.f;
+        a.factors.k[h] = c.k_head ? c.k_head[h % Hkv] : 1.f;
+        a.factors.v[h] = c.v_head ? c.v_head[h % Hkv] : 1.f;
     }
     a.trace = c.trace;
 
