@@ -521,34 +521,44 @@ __device__ __forceinline__ void item_epilogue(const CallArgs &a, const Piece &pc
     const bool whole_pair = pc.n_chunks == 1;
     constexpr int D4 = D / 4;
     __syncthreads();
-    // a thread owns four consecutive coordinates of one column; all its LDS reads are issued together
-    for (int idx = threadIdx.x; idx < G * D4; idx += kThreads) {
-        const int g = idx / D4, d = (idx % D4) * 4;
-        float2 ml[kWaves];
-        float4 ow[kWaves];
+    // a thread owns four consecutive coordinates of one column (of two columns, when there are 16); all its LDS reads are issued together,
+    // with 16 columns both columns' (one column after the other in a loop: two waits, and a condition per lane on the second)
+    constexpr int NC4 = G * D4, IT = (NC4 + kThreads - 1) / kThreads;
+    static_assert(NC4 <= kThreads || NC4 % kThreads == 0, "all threads or the first of them");
+    if (NC4 >= kThreads || threadIdx.x < static_cast<unsigned>(NC4)) {
+        float2 ml[IT][kWaves];
+        float4 ow[IT][kWaves];
 #pragma unroll
-        for (int w = 0; w < kWaves; ++w) {
-            ml[w] = *reinterpret_cast<const float2 *>(st_ml + (w * G + g) * 2);
-            ow[w] = *reinterpret_cast<const float4 *>(st_o + (w * G + g) * kStRow<D> + d);
+        for (int it = 0; it < IT; ++it) {
+            const int idx = threadIdx.x + it * kThreads, g = idx / D4, d = (idx % D4) * 4;
+#pragma unroll
+            for (int w = 0; w < kWaves; ++w) {
+                ml[it][w] = *reinterpret_cast<const float2 *>(st_ml + (w * G + g) * 2);
+                ow[it][w] = *reinterpret_cast<const float4 *>(st_o + (w * G + g) * kStRow<D> + d);
+            }
         }
-        float m_star = -INFINITY;
 #pragma unroll
-        for (int w = 0; w < kWaves; ++w) m_star = fmaxf(m_star, ml[w].x);
-        float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-        float l_star = 0.f;
+        for (int it = 0; it < IT; ++it) {
+            const int idx = threadIdx.x + it * kThreads, g = idx / D4, d = (idx % D4) * 4;
+            float m_star = -INFINITY;
 #pragma unroll
-        for (int w = 0; w < kWaves; ++w) {
-            const float f = ml[w].x == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(ml[w].x - m_star);
-            acc.x += ow[w].x * f;
-            acc.y += ow[w].y * f;
-            acc.z += ow[w].z * f;
-            acc.w += ow[w].w * f;
-            l_star += ml[w].y * f;
-        }
-        if (whole_pair) {
-            write_out4<D>(a, pc.qg, g, d, acc, m_star, l_star, pc.v_mul);
-        } else {
-            publish_part<D, G>(a, pc.part, idx, acc, m_star, l_star);
+            for (int w = 0; w < kWaves; ++w) m_star = fmaxf(m_star, ml[it][w].x);
+            float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+            float l_star = 0.f;
+#pragma unroll
+            for (int w = 0; w < kWaves; ++w) {
+                const float f = ml[it][w].x == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(ml[it][w].x - m_star);
+                acc.x += ow[it][w].x * f;
+                acc.y += ow[it][w].y * f;
+                acc.z += ow[it][w].z * f;
+                acc.w += ow[it][w].w * f;
+                l_star += ml[it][w].y * f;
+            }
+            if (whole_pair) {
+                write_out4<D>(a, pc.qg, g, d, acc, m_star, l_star, pc.v_mul);
+            } else {
+                publish_part<D, G>(a, pc.part, idx, acc, m_star, l_star);
+            }
         }
     }
     if (!whole_pair) {

@@ -520,6 +520,11 @@ __global__ __launch_bounds__(kThreads, 1) void fairkv_decode_mfma_kernel(DecodeA
             const int hidden_max = last_chunk ? q_len - 1 : 0;
             const int hidden = last_chunk ? col_hidden : 0;
             bf16x8_t qb[NSL];
+            // What the end of the item needs, read out of the lanes here, where the wave waits for a tile anyway, and not behind the last tile, where
+            // these 35 instructions stand between it and the output.  With the fold's reads of both its columns in one go, us per layer:
+            // Llama-70B shape 15.74 -> 15.67, the same with an 8-bit cache 10.93 -> 10.84, 24B shape with 16 columns 37.27 -> 37.12.
+            const CallArgs a = call_args();
+            const Piece pc = list.piece(a, ci, KV8 ? lane_value(head_mul, kScaleHeads + scale_h) : a.v_scale);
 
             for (bool fresh = true; left > 0; fresh = false) {
                 // The tile has landed once no more is outstanding than was requested after it: the other tile of the ring
@@ -658,8 +663,6 @@ __global__ __launch_bounds__(kThreads, 1) void fairkv_decode_mfma_kernel(DecodeA
             // ---- fold the four token quarters of l, stage this wave's result, finish the item ------
             l_run = quarters_sum(l_run);
             if (SOLO && owner >= 0) {
-                const CallArgs a = call_args();
-                const Piece pc = list.piece(a, ci, KV8 ? lane_value(head_mul, kScaleHeads + scale_h) : a.v_scale);
                 // This wave has seen the whole pair: out = O / l and lse straight from its registers.  A lane holds
                 // coordinates 16 nb + 4 lq .. + 3 of head l16.
                 if (l16 < G && pc.n_chunks != 0) {
@@ -680,8 +683,6 @@ __global__ __launch_bounds__(kThreads, 1) void fairkv_decode_mfma_kernel(DecodeA
                     *reinterpret_cast<float2 *>(st_ml[set] + (wave * G + l16) * 2) = make_float2(m_run, l_run);
                 }
             }
-            const CallArgs a = call_args();
-            const Piece pc = list.piece(a, ci, KV8 ? lane_value(head_mul, kScaleHeads + scale_h) : a.v_scale);
             if (pc.n_chunks != 0) {
                 item_epilogue<D, G, DEEP, TRACE>(a, pc, st_o[set], st_ml[set], pend, n_pend, roles);
                 if constexpr (kSets == 2)
