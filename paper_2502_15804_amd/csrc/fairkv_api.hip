@@ -339,7 +339,7 @@ PlanCheck check_plan(const DecodeCall &c)
     // and without: 16 items 0.51 and 0.23, 256 1.55 and 0.87, 1073 7.5 and 3.6, 2048 13.5 and 6.7; an eager step of eight appends and
     // decode calls 104.5 and 102.0.
     {
-        auto u = [](int32_t v) { return static_cast<uint32_t>(v); };      // differences may wrap; of numbers that are not negative none does
+        auto u = [](int32_t v) { return static_cast<uint32_t>(v); };      // differences may wrap; those of two numbers that are not negative do not
         uint32_t bad = 0;                 // any bit: refused
         int32_t sign = 0;                 // negative: refused
         int64_t rows = 0;                 // the same
@@ -349,7 +349,8 @@ PlanCheck check_plan(const DecodeCall &c)
             const int32_t next = static_cast<int32_t>(u(it.chunk) + 1u);
             bad |= static_cast<uint32_t>((it.part ^ i) | (it.chunk ^ follows) | (follows == 0 ? 0 : it.n_chunks ^ n_chunks));
             sign |= it.b | static_cast<int32_t>(u(B) - 1u - u(it.b)) | it.h | static_cast<int32_t>(u(Hkv) - 1u - u(it.h)) | it.tok_count;
-            rows |= it.row | static_cast<int64_t>(static_cast<uint64_t>(c.n_rows) - static_cast<uint64_t>(it.row) - u(it.tok_count));
+            const uint64_t last_row = static_cast<uint64_t>(c.n_rows) - u(it.tok_count);      // that the item may begin at: negative if it is too long
+            rows |= it.row | static_cast<int64_t>(last_row) | static_cast<int64_t>(last_row - static_cast<uint64_t>(it.row));
             deepest = std::max(deepest, it.n_chunks);
             shortest = std::min(shortest, it.n_chunks == 1 ? it.tok_count : INT32_MAX);
             follows = next == it.n_chunks ? 0 : next;

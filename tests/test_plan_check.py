@@ -61,6 +61,18 @@ def test_one_wrong_field_is_refused_in_any_order(field, values):
                 assert not _verdict(order), (field, i, value)
 
 
+@pytest.mark.parametrize("row", [2 ** 63 - 1, 2 ** 63 - N_ROWS, 2 ** 63 - 2 ** 31 + N_ROWS + 2])
+@pytest.mark.parametrize("tokens", [1, N_ROWS, N_ROWS + 2, 2 ** 31 - 2, 2 ** 31 - 1])
+def test_a_first_row_near_the_largest_number_is_refused_in_any_order(row, tokens):
+    """The row behind the item, and the rows that are left in front of it, are numbers that 64 bits do not hold."""
+    items = _plan(1)
+    for i in (0, len(items) // 2, len(items) - 1):
+        wrong = items.copy()
+        wrong["row"][i], wrong["tok_count"][i] = row, tokens
+        for order in _orders(wrong, i):
+            assert not _verdict(order), i
+
+
 @pytest.mark.parametrize("seed", range(3))
 def test_missing_doubled_and_swapped_pieces_are_refused(seed):
     items = _plan(seed)
