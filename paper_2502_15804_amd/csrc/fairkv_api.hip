@@ -14,12 +14,12 @@
 #include <cmath>
 #include <cstdint>
 #include <cstdlib>
-#include <vector>
 
 #include "decode_f32.h"
 #include "decode_mfma.h"
 #include "decode_valu.h"
 #include "pack.h"
+#include "plan_check.h"
 #include "stream_probe.h"
 #include "fairkv.h"
 #include "fairkv_measure.h"
@@ -319,87 +319,6 @@ extern "C" int fairkv_decode_attn_static(const void *q, const void *k, const voi
 }
 
 namespace {
-// What the items of a plan are found to be.
-struct PlanCheck {
-    bool ok;
-    bool deep;      // a pair in very many pieces: the kernel with the two-level merge
-    bool solo;      // short whole pairs: the kernel that gives them to single waves
-};
-
-// Every cut pair must come with all its pieces, each exactly once: a piece that is missing would leave the
-// pair's arrival counter short for ever (no output, and a counter that is not zero for the next call); one
-// that comes twice would have two workgroups write one partial slot.
-PlanCheck check_plan(const DecodeCall &c)
-{
-    const int32_t B = c.B, Hkv = c.Hkv, q_len = c.q_len, n_items = c.n_items, n_parts = c.n_parts;
-    const fairkv_item *items_host = c.items_host;
-    PlanCheck r{true, false, false};
-    // A plan that lists its pieces in the order of their partial slots, as a line cut does, needs no counting: item i has slot i, and each
-    // piece follows its predecessor.  No branch and no store per item; what does not pass is looked at again, below.  us per call with counting
-    // and without: 16 items 0.51 and 0.23, 256 1.55 and 0.87, 1073 7.5 and 3.6, 2048 13.5 and 6.7; an eager step of eight appends and
-    // decode calls 104.5 and 102.0.
-    {
-        auto u = [](int32_t v) { return static_cast<uint32_t>(v); };      // differences may wrap; those of two numbers that are not negative do not
-        uint32_t bad = 0;                 // any bit: refused
-        int32_t sign = 0;                 // negative: refused
-        int64_t rows = 0;                 // the same
-        int32_t deepest = 0, shortest = INT32_MAX, follows = 0, n_chunks = 0;      // `follows`: chunk that the next item has to be
-        for (int32_t i = 0; i < n_items; ++i) {
-            const fairkv_item it = items_host[i];
-            const int32_t next = static_cast<int32_t>(u(it.chunk) + 1u);
-            bad |= static_cast<uint32_t>((it.part ^ i) | (it.chunk ^ follows) | (follows == 0 ? 0 : it.n_chunks ^ n_chunks));
-            sign |= it.b | static_cast<int32_t>(u(B) - 1u - u(it.b)) | it.h | static_cast<int32_t>(u(Hkv) - 1u - u(it.h)) | it.tok_count;
-            const uint64_t last_row = static_cast<uint64_t>(c.n_rows) - u(it.tok_count);      // that the item may begin at: negative if it is too long
-            rows |= it.row | static_cast<int64_t>(last_row) | static_cast<int64_t>(last_row - static_cast<uint64_t>(it.row));
-            deepest = std::max(deepest, it.n_chunks);
-            shortest = std::min(shortest, it.n_chunks == 1 ? it.tok_count : INT32_MAX);
-            follows = next == it.n_chunks ? 0 : next;
-            n_chunks = it.n_chunks;
-        }
-        if (q_len > 1)      // see below
-            for (int32_t i = 0; i < n_items; ++i) {
-                const fairkv_item &it = items_host[i];
-                bad |= static_cast<uint32_t>((it.n_chunks > 1) & (it.chunk == it.n_chunks - 1) & (it.tok_count < q_len - 1));
-            }
-        if (bad == 0 && sign >= 0 && rows >= 0 && follows == 0) {
-            r.deep = deepest >= kDeepFrom;
-            r.solo = shortest <= kSoloTokens;
-            return r;
-        }
-    }
-    // Any order: count[first slot of a pair] counts that pair's pieces; a piece's own slot must be used once.
-    r.ok = false;
-    std::vector<int32_t> count_own;
-    int32_t *count = c.count_scratch;
-    if (!count) {
-        count_own.assign(static_cast<size_t>(n_parts), 0);
-        count = count_own.data();
-    } else {
-        for (int32_t i = 0; i < n_parts; ++i) count[i] = 0;
-    }
-    for (int32_t i = 0; i < n_items; ++i) {
-        const fairkv_item &it = items_host[i];
-        r.deep |= it.n_chunks >= kDeepFrom;
-        r.solo |= it.n_chunks == 1 && it.tok_count <= kSoloTokens;
-        if (it.b < 0 || it.b >= B || it.h < 0 || it.h >= Hkv || it.row < 0 || it.tok_count < 0) return r;
-        if (it.row > c.n_rows - it.tok_count) return r;      // the kernel reads exactly these rows of K and V
-        if (it.n_chunks < 1 || it.chunk < 0 || it.chunk >= it.n_chunks) return r;
-        if (it.part < it.chunk || static_cast<int64_t>(it.part) - it.chunk + it.n_chunks > n_parts) return r;      // up to 2^31 - 1 each
-        // the rows new tokens hide from one another (the last q_len - 1 of a pair) must not reach
-        // back beyond the pair's last chunk: the kernel masks inside that chunk only
-        if (q_len > 1 && it.n_chunks > 1 && it.chunk == it.n_chunks - 1 && it.tok_count < q_len - 1) return r;
-        count[it.part - it.chunk] += 1 << 8;                 // pieces of the pair that starts at this slot
-        count[it.part] += 1;                                 // uses of this slot
-        if ((count[it.part] & 0xff) > 1 || (count[it.part - it.chunk] >> 8) > it.n_chunks) return r;
-    }
-    for (int32_t i = 0; i < n_items; ++i) {
-        const fairkv_item &it = items_host[i];
-        if ((count[it.part - it.chunk] >> 8) != it.n_chunks) return r;
-    }
-    r.ok = true;
-    return r;
-}
-
 int decode_common(const DecodeCall &c)
 {
     const int32_t B = c.B, Hq = c.Hq, Hkv = c.Hkv, D = c.D, q_len = c.q_len, n_items = c.n_items, n_slots = c.n_slots,
@@ -414,9 +333,10 @@ int decode_common(const DecodeCall &c)
     uint32_t falls = 0;
     for (int32_t j = 0; j < n_slots; ++j) falls |= static_cast<uint32_t>(slot_ptr[j] > slot_ptr[j + 1]);
     if (falls) return FAIRKV_EINVAL;
-    const PlanCheck plan = check_plan(c);
+    const PlanCheck plan = check_plan(PlanItems{items_host, n_items, n_parts, B, Hkv, q_len, c.n_rows}, c.count_scratch);
     if (!plan.ok) return FAIRKV_EINVAL;
-    const bool deep = plan.deep, solo = plan.solo;
+    const bool deep = plan.deepest >= kDeepFrom;         // a pair in very many pieces: the kernel with the two-level merge
+    const bool solo = plan.shortest <= kSoloTokens;      // short whole pairs: the kernel that gives them to single waves
     if (!finite(c.scale)) return FAIRKV_EINVAL;
     const bool on_valu = c.in_dtype == FAIRKV_BF16_VALU;     // bf16 on the vector-ALU kernel: A/B measurements
     const int32_t in_dtype = on_valu ? FAIRKV_BF16 : c.in_dtype;

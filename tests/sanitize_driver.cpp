@@ -11,6 +11,8 @@
 //         -> "attn rc sum(out) sum(lse over non-empty heads)" on data drawn from a small generator below
 //   grow  (a plan line's arguments) steps cap_slack
 //         -> "grow rc tok_count ..." after `steps` calls of fairkv_plan_grow
+//   check n_items n_parts B Hkv q_len n_rows scratch  (row tok b h chunk n_chunks part)[n_items]
+//         -> "check ok deepest shortest", what a decode call finds a plan to be; scratch 1: counts in an array of the caller's
 #include <cmath>
 #include <cstdint>
 #include <cstdio>
@@ -20,6 +22,7 @@
 #include <vector>
 
 #include "fairkv.h"
+#include "plan_check.h"
 
 extern "C" int fairkv_oracle_attn(const void *q, const void *k, const void *v, const int64_t *off, const int32_t *len,
                                   int B, int Hq, int Hkv, int D, int dtype, double scale, const int32_t *sel, int n_sel,
@@ -104,6 +107,21 @@ int main()
             std::printf(" |");
             for (int32_t x : part_base) std::printf(" %d", x);
             std::printf("\n");
+        } else if (cmd == "check") {
+            fairkv::PlanItems c{};
+            int scratch;
+            in >> c.n_items >> c.n_parts >> c.B >> c.Hkv >> c.q_len >> c.n_rows >> scratch;
+            if (!in || c.n_items < 1 || c.n_parts < c.n_items || c.n_parts > (1 << 20)) return 2;
+            std::vector<fairkv_item> items(static_cast<size_t>(c.n_items));
+            for (auto &it : items) in >> it.row >> it.tok_count >> it.b >> it.h >> it.chunk >> it.n_chunks >> it.part;
+            if (!in) return 2;
+            c.items = items.data();
+            std::vector<int32_t> count(scratch ? static_cast<size_t>(c.n_parts) : 0, -7);
+            const fairkv::PlanCheck r = fairkv::check_plan(c, scratch ? count.data() : nullptr);
+            if (r.ok)
+                std::printf("check 1 %d %d\n", r.deepest, r.shortest);
+            else
+                std::printf("check 0\n");
         } else if (cmd == "place") {
             int32_t n, B;
             fairkv_place_params p;

@@ -1,6 +1,6 @@
 """Host code under AddressSanitizer and UndefinedBehaviorSanitizer (CPU only, no GPU code involved).
 
-fairkv_plan.cpp, fairkv_place.cpp and the C oracle attn_ref.c are compiled with
+fairkv_plan.cpp, fairkv_place.cpp, plan_check.h and the C oracle attn_ref.c are compiled with
 -fsanitize=address,undefined into a small driver (sanitize_driver.cpp) whose buffers are sized exactly, so
 that any read or write past an array, any signed overflow or misaligned access aborts the run.  The
 planner and placement differential cases go through that build and are compared with the Python oracles
@@ -29,7 +29,7 @@ def driver(tmp_path_factory):
     obj = str(out / "attn_ref.o")
     subprocess.run(["gcc", "-std=c11", "-fopenmp", *san, "-c", os.path.join(ROOT, "oracle", "attn_ref.c"), "-o", obj],
                    check=True, capture_output=True, text=True)
-    res = subprocess.run(["g++", "-std=c++17", "-fopenmp", *san, "-static-libasan", "-I", os.path.join(ROOT, "include"),
+    res = subprocess.run(["g++", "-std=c++17", "-fopenmp", *san, "-static-libasan", "-I", os.path.join(ROOT, "include"), "-I", CSRC,
                           os.path.join(ROOT, "tests", "sanitize_driver.cpp"), os.path.join(CSRC, "fairkv_plan.cpp"),
                           os.path.join(CSRC, "fairkv_place.cpp"), obj, "-o", exe, "-lm"],
                          capture_output=True, text=True)
@@ -128,6 +128,65 @@ def test_placement_differential_cases_under_sanitizers(driver):
         assert [int(x) for x in head[1:]] == [0, s.den, s.delta_num, s.max_load_num, s.min_load_num, s.n_shares, s.exact]
         assert [int(x) for x in recs] == [v for x in shares for v in (x.head, x.gpu, x.copy, x.n_copies, x.row_begin, x.row_end)]
         assert [int(x) for x in ld] == loads
+
+
+FIELDS = ("row", "tok_count", "b", "h", "chunk", "n_chunks", "part")
+NO_WHOLE_PAIR = 2 ** 31 - 1
+
+
+def _found(items, n_parts, B, Hkv, q_len, n_rows):
+    """What the check has to find, in numbers that do not wrap around: None, or (most pieces of a pair, tokens of the shortest whole pair)."""
+    pieces, used = {}, set()
+    for row, tok, b, h, chunk, n, part in items:
+        if not (0 <= b < B and 0 <= h < Hkv and 0 <= row <= n_rows - tok and tok >= 0):
+            return None
+        if not (0 <= chunk < n and chunk <= part and part - chunk + n <= n_parts) or part in used:
+            return None
+        if n > 1 and chunk == n - 1 and tok < q_len - 1:      # the rows that new tokens hide lie in a pair's last piece
+            return None
+        used.add(part)
+        pieces.setdefault(part - chunk, []).append(n)
+    if any(n != len(ns) for ns in pieces.values() for n in ns):
+        return None
+    return max(it[5] for it in items), min((it[1] for it in items if it[5] == 1), default=NO_WHOLE_PAIR)
+
+
+def _check_plans(driver, cases):
+    """cases: (items, n_parts, B, Hkv, q_len, n_rows); what the check finds is compared and returned."""
+    lines = [f"check {len(items)} {n_parts} {B} {Hkv} {q_len} {n_rows} {i % 2} " + " ".join(str(x) for it in items for x in it)
+             for i, (items, n_parts, B, Hkv, q_len, n_rows) in enumerate(cases)]
+    want = [_found(*c) for c in cases]
+    for got, w, c in zip(_run(driver, lines), want, cases):
+        assert got == ("check 0" if w is None else f"check 1 {w[0]} {w[1]}"), c
+    return want
+
+
+def _check_cases(seed):
+    """Plans of every policy in the planner's order, backwards and shuffled."""
+    rng = np.random.default_rng(seed)
+    for B, Hkv, kw, lens, offs in _plan_cases(rng, 24):
+        kw = dict(kw, min_chunk=kw["tile"])
+        items = [(it.row, it.tok_count, it.b, it.h, it.chunk, it.n_chunks, it.part) for it in P.plan(lens, offs, B, Hkv, P.Params(**kw))[0]]
+        if items and len(items) < 600:
+            for order in (items, items[::-1], [items[i] for i in rng.permutation(len(items))]):
+                yield rng, order, B, Hkv, int(lens.sum()) + 10 * lens.size
+
+
+@pytest.mark.parametrize("q_len", [1, 4])
+def test_plan_check_under_sanitizers(driver, q_len):
+    cases, wrong = [], []
+    for rng, items, B, Hkv, n_rows in _check_cases(35):
+        cases.append((items, len(items) + int(rng.integers(0, 3)), B, Hkv, q_len, n_rows))
+        for field in range(len(FIELDS)):      # one field of one item: out of its range by one, by much, by all that its type holds
+            bits = 63 if field == 0 else 31
+            i = int(rng.integers(len(items)))
+            for value in (-1, items[i][field] + 1, 2 ** bits - 1, -2 ** bits):
+                it = list(items[i])
+                it[field] = value
+                wrong.append((items[:i] + [tuple(it)] + items[i + 1:], len(items), B, Hkv, q_len, n_rows))
+    found = _check_plans(driver, cases)
+    assert any(found) and (q_len > 1 or all(found))
+    assert sum(w is None for w in _check_plans(driver, wrong)) > len(wrong) // 2
 
 
 def _lcg_stream(seed, n):
