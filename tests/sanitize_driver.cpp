@@ -12,7 +12,7 @@
 //   grow  (a plan line's arguments) steps cap_slack
 //         -> "grow rc tok_count ..." after `steps` calls of fairkv_plan_grow
 //   check n_items n_parts B Hkv q_len n_rows scratch  (row tok b h chunk n_chunks part)[n_items]
-//         -> "check ok deepest shortest", what a decode call finds a plan to be; scratch 1: counts in an array of the caller's
+//         -> "check looks ok deepest shortest", what a decode call finds a plan to be and at how many items it looks; scratch 1: counts in an array of the caller's
 #include <cmath>
 #include <cstdint>
 #include <cstdio>
@@ -119,9 +119,9 @@ int main()
             std::vector<int32_t> count(scratch ? static_cast<size_t>(c.n_parts) : 0, -7);
             const fairkv::PlanCheck r = fairkv::check_plan(c, scratch ? count.data() : nullptr);
             if (r.ok)
-                std::printf("check 1 %d %d\n", r.deepest, r.shortest);
+                std::printf("check %d 1 %d %d\n", r.looks, r.deepest, r.shortest);
             else
-                std::printf("check 0\n");
+                std::printf("check %d 0\n", r.looks);
         } else if (cmd == "place") {
             int32_t n, B;
             fairkv_place_params p;

@@ -152,23 +152,29 @@ def _found(items, n_parts, B, Hkv, q_len, n_rows):
 
 
 def _check_plans(driver, cases):
-    """cases: (items, n_parts, B, Hkv, q_len, n_rows); what the check finds is compared and returned."""
+    """cases: (items, n_parts, B, Hkv, q_len, n_rows); what the check finds is compared and returned.  It looks at an item once if the plan is
+    in the order of its partial slots; those of the block of 64 in which that order ends, and of a pair that begins before it, twice."""
     lines = [f"check {len(items)} {n_parts} {B} {Hkv} {q_len} {n_rows} {i % 2} " + " ".join(str(x) for it in items for x in it)
              for i, (items, n_parts, B, Hkv, q_len, n_rows) in enumerate(cases)]
     want = [_found(*c) for c in cases]
     for got, w, c in zip(_run(driver, lines), want, cases):
-        assert got == ("check 0" if w is None else f"check 1 {w[0]} {w[1]}"), c
+        looks, verdict = got.split(" ", 2)[1:]
+        assert verdict == ("0" if w is None else f"1 {w[0]} {w[1]}"), c
+        in_order = all(it[6] == i for i, it in enumerate(c[0]))
+        assert w is None or int(looks) <= len(c[0]) + (0 if in_order else 64 + w[0]), c
     return want
 
 
 def _check_cases(seed):
-    """Plans of every policy in the planner's order, backwards and shuffled."""
+    """Plans of every policy in the planner's order, in that of their partial slots, backwards, shuffled and shuffled from some item on."""
     rng = np.random.default_rng(seed)
     for B, Hkv, kw, lens, offs in _plan_cases(rng, 24):
         kw = dict(kw, min_chunk=kw["tile"])
         items = [(it.row, it.tok_count, it.b, it.h, it.chunk, it.n_chunks, it.part) for it in P.plan(lens, offs, B, Hkv, P.Params(**kw))[0]]
         if items and len(items) < 600:
-            for order in (items, items[::-1], [items[i] for i in rng.permutation(len(items))]):
+            slots, cut = sorted(items, key=lambda it: it[6]), int(rng.integers(len(items)))
+            shuffled = [items[i] for i in rng.permutation(len(items))]
+            for order in (items, slots, slots[:cut] + [it for it in shuffled if it[6] >= cut], items[::-1], shuffled):
                 yield rng, order, B, Hkv, int(lens.sum()) + 10 * lens.size
 
 
@@ -180,7 +186,7 @@ def test_plan_check_under_sanitizers(driver, q_len):
         for field in range(len(FIELDS)):      # one field of one item: out of its range by one, by much, by all that its type holds
             bits = 63 if field == 0 else 31
             i = int(rng.integers(len(items)))
-            for value in (-1, items[i][field] + 1, 2 ** bits - 1, -2 ** bits):
+            for value in (-1, items[i][field] + 1, 2 ** bits - 1, -2 ** bits, items[int(rng.integers(len(items)))][field]):
                 it = list(items[i])
                 it[field] = value
                 wrong.append((items[:i] + [tuple(it)] + items[i + 1:], len(items), B, Hkv, q_len, n_rows))
