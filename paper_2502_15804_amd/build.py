@@ -16,7 +16,7 @@ BINDING = os.path.join(HERE, "_binding.so")
 BINDING_SOURCE = os.path.join(CSRC, "binding.cpp")
 SOURCES = [os.path.join(CSRC, "fairkv_api.hip"), os.path.join(CSRC, "fairkv_plan.cpp"),
            os.path.join(CSRC, "fairkv_place.cpp")]
-HEADERS = [os.path.join(ROOT, "include", "fairkv.h"), os.path.join(ROOT, "include", "fairkv_measure.h")] + [os.path.join(CSRC, h) for h in ("common.h", "decode_f32.h", "decode_mfma.h", "decode_valu.h", "pack.h", "plan_check.h", "stream_probe.h")]
+HEADERS = [os.path.join(ROOT, "include", "fairkv.h"), os.path.join(ROOT, "include", "fairkv_measure.h")] + [os.path.join(CSRC, h) for h in ("common.h", "decode_f32.h", "decode_mfma.h", "decode_valu.h", "pack.h", "plan_check.h", "rows.h", "stream_probe.h")]
 
 
 def _hipcc() -> str:

@@ -9,6 +9,7 @@
 #include <cstdint>
 
 #include "fairkv.h"
+#include "rows.h"
 
 namespace fairkv {
 

@@ -13,9 +13,9 @@ struct ItemSlot {
 };
 __device__ __forceinline__ ItemSlot item_slot(const CallArgs &a, const fairkv_item &it)
 {
-    const bool ok = it.b >= 0 && it.b < a.B && it.h >= 0 && it.h < a.Hkv && it.row >= 0 && it.part >= 0 &&
+    const bool ok = it.b >= 0 && it.b < a.B && it.h >= 0 && it.h < a.Hkv && it.part >= 0 &&
                     it.chunk >= 0 && it.chunk < it.n_chunks && it.chunk <= it.part &&
-                    it.part - it.chunk + it.n_chunks <= a.n_parts && it.row + max(it.tok_count, 0) <= a.n_rows;
+                    it.n_chunks <= a.n_parts && it.part - it.chunk <= a.n_parts - it.n_chunks && rows_within(it.row, max(it.tok_count, 0), a.n_rows);
     return ItemSlot{it.row, ok ? max(it.tok_count, 0) : 0, ok ? 1 : 0, ok ? it.b * a.q_len * a.Hkv + it.h : 0,
                     ok ? it.b * a.Hkv + it.h : 0, it.chunk, it.n_chunks, it.part};
 }

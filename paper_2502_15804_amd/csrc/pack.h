@@ -8,6 +8,7 @@
 #include <cstdint>
 
 #include "fairkv.h"
+#include "rows.h"
 
 namespace fairkv {
 
@@ -62,7 +63,7 @@ __global__ __launch_bounds__(256) void fairkv_pack_kernel(PackArgs a)
         const fairkv_item it = a.items[i];
         const int n = it.tok_count;
         if (n <= 0) continue;
-        bool ok = it.b >= 0 && it.b < a.B && it.h >= 0 && it.h < a.Hkv && it.row >= 0 && it.row + n <= a.n_rows;
+        bool ok = it.b >= 0 && it.b < a.B && it.h >= 0 && it.h < a.Hkv && rows_within(it.row, n, a.n_rows);
         int64_t pair = 0, begin = 0, first = 0;
         if (ok) {
             pair = static_cast<int64_t>(it.b) * a.Hkv + it.h;
@@ -70,7 +71,7 @@ __global__ __launch_bounds__(256) void fairkv_pack_kernel(PackArgs a)
             const int64_t at = a.off[pair], end = a.keep_ptr[pair + 1];
             first = a.keep_ptr[pair];
             begin = it.row - at;
-            ok = (begin >= 0) & (first >= 0) & (begin + n <= end - first);
+            ok = (begin >= 0) & (first >= 0) & (begin <= end - first - n);
         }
         if (!ok) {
             if (threadIdx.x == 0 && blockIdx.y == 0 && a.bad) atomicAdd(a.bad, 1);
@@ -131,10 +132,11 @@ __global__ __launch_bounds__(256) void fairkv_append_kernel(AppendArgs a)
     typedef __attribute__((ext_vector_type(4))) uint32_t u4;
     u4 kk = *reinterpret_cast<const u4 *>(a.k_new + pair * ROWB + piece * 16), vv = *reinterpret_cast<const u4 *>(a.v_new + pair * ROWB + piece * 16);
     const int32_t l = a.len[pair], cap = a.cap[pair];
-    const int64_t off = a.off[pair], row = off + l;
+    const int64_t off = a.off[pair];
+    const uint64_t row = static_cast<uint64_t>(off) + static_cast<uint32_t>(l);      // of numbers that are not negative: does not wrap around
     __builtin_amdgcn_sched_barrier(0);          // all five on their way before one is looked at
     asm volatile("" : "+v"(kk), "+v"(vv));      // needed here: the compiler would ask for them behind the branch
-    if ((l < 0) | (l >= cap) | (off < 0) | (row >= a.n_rows)) {
+    if ((l < 0) | (l >= cap) | (off < 0) | (row >= static_cast<uint64_t>(a.n_rows))) {
         if (piece == 0 && a.full) atomicAdd(a.full, 1);
         return;
     }

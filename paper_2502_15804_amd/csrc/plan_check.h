@@ -6,6 +6,7 @@
 #include <vector>
 
 #include "fairkv.h"
+#include "rows.h"
 
 namespace fairkv {
 
@@ -87,8 +88,8 @@ inline PlanCheck check_plan(const PlanItems &c, int32_t *count_scratch)
         const fairkv_item &it = c.items[i];
         r.deepest = std::max(r.deepest, it.n_chunks);
         if (it.n_chunks == 1) r.shortest = std::min(r.shortest, it.tok_count);
-        if (it.b < 0 || it.b >= B || it.h < 0 || it.h >= Hkv || it.row < 0 || it.tok_count < 0) return r;
-        if (it.row > c.n_rows - it.tok_count) return r;      // the kernel reads exactly these rows of K and V
+        if (it.b < 0 || it.b >= B || it.h < 0 || it.h >= Hkv || it.tok_count < 0) return r;
+        if (!rows_within(it.row, it.tok_count, c.n_rows)) return r;      // the kernel reads exactly these rows of K and V
         if (it.n_chunks < 1 || it.chunk < 0 || it.chunk >= it.n_chunks) return r;
         const int64_t first = static_cast<int64_t>(it.part) - it.chunk - whole, own = first + it.chunk;      // up to 2^31 - 1 each
         if (first < 0 || first + it.n_chunks > n_slots) return r;

@@ -233,3 +233,42 @@ def test_cache_of_8bit_floats_packed_grown_and_attended():
     torch.cuda.synchronize()
     ro, rl = OA.attention_kv8(W.to_numpy_bits(q), rk, rv, off, grown, w.scale, ks, vs)
     assert np.abs(out.float().cpu().numpy() - ro).max() <= w.tol and np.abs(lse.cpu().numpy() - rl).max() <= w.tol
+
+
+FAR = 2 ** 63 - 1
+
+
+@pytest.mark.gpu
+def test_pack_refuses_rows_and_offsets_whose_sums_wrap_around():
+    import torch
+    B, Hkv, T, D = 1, 2, 50, 128
+    lens = np.array([[20, 30]], np.int32)
+    kd, vd, keep_ptr, keep_t, off, total, plan = _case(B, Hkv, T, D, "bf16", lens, 0, seed=1, n_slots=4)
+    items = np.zeros(4, dtype=F.ITEM_DTYPE)
+    items[:3] = [(FAR, 5, 0, 1, 0, 1, 0), (FAR - total, 2 ** 31 - 1, 0, 1, 0, 1, 0), (FAR - 3, 4, 0, 0, 0, 1, 0)]
+    items[3] = (0, 5, 0, 0, 0, 1, 0)                            # row 0 less the offset of this pair is the largest number
+    far_off = off.reshape(-1).copy()
+    far_off[0] = -FAR
+    k = torch.zeros((total, D), dtype=torch.bfloat16, device="cuda")
+    v, bad = torch.zeros_like(k), torch.zeros(1, dtype=torch.int32, device="cuda")
+    F.fairkv_pack(kd.cuda(), vd.cuda(), torch.from_numpy(keep_ptr).cuda(), torch.from_numpy(keep_t).cuda(), torch.from_numpy(far_off).cuda(),
+                  torch.from_numpy(items.view(np.uint8).copy()).cuda(), torch.tensor([0, 1, 2, 3, 4], dtype=torch.int32, device="cuda"), k, v, bad)
+    torch.cuda.synchronize()
+    assert int(bad.item()) == 4 and not _bits(k).any() and not _bits(v).any()
+
+
+@pytest.mark.gpu
+def test_append_refuses_an_offset_whose_row_wraps_around():
+    import torch
+    n, D, rows = 4, 128, 40
+    off = torch.tensor([FAR, FAR - 2, rows, 0], dtype=torch.int64, device="cuda")
+    length = torch.tensor([5, 3, 0, 3], dtype=torch.int32, device="cuda")
+    cap = torch.full((n,), 10, dtype=torch.int32, device="cuda")
+    k = torch.zeros((rows, D), dtype=torch.bfloat16, device="cuda")
+    v, full = torch.zeros_like(k), torch.zeros(1, dtype=torch.int32, device="cuda")
+    new = torch.ones((1, n, D), dtype=torch.bfloat16, device="cuda")
+    F.fairkv_append(new, new, off, length, cap, k, v, full)
+    torch.cuda.synchronize()
+    assert int(full.item()) == 3 and length.tolist() == [5, 3, 0, 4]
+    for x in (k, v):
+        assert x[3].eq(1).all() and x.ne(0).sum().item() == D
