@@ -19,7 +19,7 @@ def device_compute_units(device=None) -> int:
                .multi_processor_count)
 
 
-def _plan_params(n_cu, kv8, f32, D, lens, cols=8, larger_pieces=True):
+def _plan_params(n_cu, kv8, f32, D, lens):
     """The planner's parameters for a layer that brings none: the library's defaults with what was measured for the kind of cache.
 
     The overheads are what an item costs in units of streamed tokens, so they fall with the bytes of a token; the values are
@@ -43,45 +43,34 @@ def _plan_params(n_cu, kv8, f32, D, lens, cols=8, larger_pieces=True):
     us per layer with the short pairs' own overhead and without: 256 pairs of 64 tokens on an 8-bit cache 7.49 and 5.33, of 40 on
     the average 8.34 and 6.15 (bf16 7.53 and 6.90), 200 of 100 8.48 and 7.53 (8.41 and 7.58), 64 of 90 6.98 and 7.04 (6.97 and 7.01);
     with 384 pairs of 50 8.62 and 8.72 (8.87 and 9.08), with 512 of 64 7.91 and 7.59 (8.33 and 8.38).  On an fp32 cache it is the
-    other way round: 200 pairs of 30 8.14 and 8.81, 256 of 40 9.24 and 9.57.
-
-    With 16 columns a piece's partial result is twice as large, so from 384 tokens per compute unit on pieces are.  us per layer with pieces
-    of at least 64, 128, 192 and 256 tokens (8 KV heads unless said, batch x tokens per pair): 24B shape, four new tokens 37.68, 36.89, 36.95,
-    36.70; 24 x 700 18.92, 18.42, 18.27, 18.30, equal 18.32, 17.53, 16.74, 15.08; 36 x 700 equal 25.05, 24.24, 23.67, 24.13; 60 x 700 equal with
-    D = 64 20.84, 19.28, 18.67, 18.03; 40 x 700, eight new tokens of two heads 27.06, 26.48, 26.26, 26.02; 64 x 2048, two heads 35.27,
-    35.31, 34.89, 34.91.  Error of an fp32 output of these layers 4.54e-6 to 4.73e-6 and 4.55e-6 to 4.74e-6.  Smaller layers are up to 4 %
-    faster with 128 than with 64, but that takes the error for one sequence from 3.3e-6 to 4.3e-6.  So do 8-bit caches with larger pieces (2
-    to 10 % faster with 192, the error of lse up to a quarter larger): not taken.
-
-    fp32 with pieces of 32, 64, 128: 30 x 700 equal 33.25, 32.23, 32.19, 60 x 700 equal 64.64, 59.93, 59.97, the same with D = 64 33.22, 32.30,
-    31.15, 100 x 300 52.86, 52.66, 52.35, but 24 x 700 29.91, 30.14, 30.90, Llama-70B shape 28.62, 28.77, 30.03, 4 x 700 12.1, 12.5, 14.1,
-    and 232 x 200 82.0, 82.2, 81.1: 64 from 600 tokens per compute unit on, up to four pairs per unit (error 2.7e-7 to 3.4e-7 either way)."""
-    tokens, pairs = int(lens.sum(dtype=np.int64)), int(np.count_nonzero(lens))
+    other way round: 200 pairs of 30 8.14 and 8.81, 256 of 40 9.24 and 9.57."""
     if f32:      # twice the bytes
-        return fairkv_default_params(n_cu, overhead_tokens=64, short_overhead_tokens=32,
-                                     min_chunk=64 if larger_pieces and tokens >= 600 * n_cu and pairs <= 4 * n_cu else 32)
+        return fairkv_default_params(n_cu, overhead_tokens=64, short_overhead_tokens=32)
     if kv8:      # half the bytes per token, and a step covers 32 tokens
         p = fairkv_default_params(n_cu, tile=32, min_chunk=64, overhead_tokens=256, short_overhead_tokens=128)
-    elif cols == 16 and larger_pieces and tokens >= 384 * n_cu:
-        p = fairkv_default_params(n_cu, overhead_tokens=96, min_chunk=256)
     else:
-        p = fairkv_default_params(n_cu, overhead_tokens=96, min_chunk=64 if D == 128 and tokens < 128 * n_cu else 128)
-    if pairs <= n_cu and ((lens > 0) & (lens <= FAIRKV_SHORT_PAIR_TOKENS)).any():      # (empty pairs alone: 0.6 % slower)
+        p = fairkv_default_params(n_cu, overhead_tokens=96,
+                                  min_chunk=64 if D == 128 and int(lens.sum(dtype=np.int64)) < 128 * n_cu else 128)
+    if np.count_nonzero(lens) <= n_cu and ((lens > 0) & (lens <= FAIRKV_SHORT_PAIR_TOKENS)).any():      # (empty pairs alone: 0.6 % slower)
         p.short_overhead_tokens = p.overhead_tokens
     return p
 
 
-def _earlier_plan_params(n_cu, kv8, f32, D, lens):
-    """What _plan_params gave before its figures were taken again, the latest first.  Plans of one set may need more partial slots than
-    those of another (the first against the second: fp32 up to 143 more over 1500 random layers, bf16 5, 8-bit 13; the present ones against
-    the first: fp32 4), so a workspace of a given size that held a layer's plan still has one to hold."""
-    yield _plan_params(n_cu, kv8, f32, D, lens, larger_pieces=False)
+def _other_plan_params(n_cu, kv8, f32, D, lens, cols):
+    """What layers were planned with at other times.  The plans of _plan_params may need more partial slots than these (against the
+    first, fp32: up to 143 more over 1500 random layers, bf16 5, 8-bit 13), so a workspace of a given size that held a layer's plan still
+    has one to hold.  The last makes larger pieces of large layers with 16 columns: up to a fifth faster with equal budgets, but an output's
+    error is up to 2 % larger, so such plans serve workspaces that hold no other."""
     if kv8:
         yield fairkv_default_params(n_cu, tile=32, min_chunk=64, overhead_tokens=256, short_overhead_tokens=96)
     elif f32:
         yield fairkv_default_params(n_cu, overhead_tokens=80, short_overhead_tokens=32)
     else:
         yield fairkv_default_params(n_cu)
+        if cols == 16 and int(lens.sum(dtype=np.int64)) >= 384 * n_cu:
+            p = _plan_params(n_cu, kv8, f32, D, lens)
+            p.min_chunk = 256
+            yield p
 
 
 class DecodeLayer:
@@ -106,7 +95,7 @@ class DecodeLayer:
         given = params is not None
         if not given:
             kind = device_compute_units(dev), self.kv8, q.dtype == torch.float32, self.D, lens_h
-            params = _plan_params(*kind, self.G * self.q_len)
+            params = _plan_params(*kind)
         room = FAIRKV_STATIC_WORKSPACE_BYTES if static_workspace else None if workspace is None else workspace.numel()
 
         def plan_and_need(params):
@@ -114,9 +103,9 @@ class DecodeLayer:
             return plan, fairkv_workspace_bytes(plan.n_parts, self.B * self.Hkv, self.G * self.q_len, self.D)
 
         plan, need = plan_and_need(params)
-        for earlier in () if given or room is None else _earlier_plan_params(*kind):
+        for other in () if given or room is None else _other_plan_params(*kind, self.G * self.q_len):
             if need > room:
-                plan, need = plan_and_need(earlier)
+                plan, need = plan_and_need(other)
         self.plan: Plan = plan
         self.items_d = torch.from_numpy(self.plan.items.view(np.uint8).copy()).to(dev)
         self.bf16_on_valu = bf16_on_valu
