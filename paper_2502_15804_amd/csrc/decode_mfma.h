@@ -690,7 +690,12 @@ __global__ __launch_bounds__(kThreads, 1) void fairkv_decode_mfma_kernel(DecodeA
                 else
                     __syncthreads();
             }
-            if (batch + ci + 1 < i_end) begin_item();
+            // Plans without short pairs have few items per slot: what the last one would make ready for a next is left out.  With short pairs the
+            // condition costs more than it saves, 30 vector registers among it.  us per layer with it everywhere, and now, 8 KV heads: 110
+            // sequences of 60 tokens a pair, one query head per KV head 10.84 and 10.60, two 11.09 and 10.81, eight 11.64 and 11.58, on 8-bit caches
+            // two 11.13 and 10.93, eight 12.07 and 11.89; Pareto budgets at batch 100 13.84 and 13.60, 14.35 and 14.03, 15.04 and 14.93, 12.17 and
+            // 12.04, 13.13 and 13.00.
+            if (SOLO || batch + ci + 1 < i_end) begin_item();
             if constexpr (TRACE)
                 if (batch == i_begin && ci == 0) trace_stamp(args, kTraceItem0Done, threadIdx.x == 0);
         }

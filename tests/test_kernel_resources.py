@@ -57,3 +57,9 @@ def test_vector_kernel_has_the_registers_of_a_whole_simd(compiled):
 def test_no_wait_state_is_broken(compiled):
     for name, (_, code) in compiled.items():
         assert asm_hazards.hazards(code) == set(), name
+
+
+def test_kernels_with_short_pairs_do_not_carry_a_second_set_of_outputs(compiled):
+    # what an item starts from is set behind every item, also the last: behind a condition it takes registers of its own (226 instead of 192)
+    val, _ = compiled["_ZN6fairkv25fairkv_decode_mfma_kernelILi128ELi8ELb0ELb0ELb1ELb0EEEvNS_10DecodeArgsE"]
+    assert val(" VGPRs") <= 200
