@@ -523,8 +523,15 @@ __global__ __launch_bounds__(kThreads, 1) void fairkv_decode_mfma_kernel(DecodeA
             // What the end of the item needs, read out of the lanes here, where the wave waits for a tile anyway, and not behind the last tile, where
             // these 35 instructions stand between it and the output.  With the fold's reads of both its columns in one go, us per layer:
             // Llama-70B shape 15.74 -> 15.67, the same with an 8-bit cache 10.93 -> 10.84, 24B shape with 16 columns 37.27 -> 37.12.
-            const CallArgs a = call_args();
-            const Piece pc = list.piece(a, ci, KV8 ? lane_value(head_mul, kScaleHeads + scale_h) : a.v_scale);
+            // Not with short pairs on 8-bit caches of D = 64: what is held takes up to 20 scalar registers more than there are (34 spilled instead of 9).
+            // us per layer ahead, behind, 8 KV heads, 110 sequences of 60 tokens a pair: 8 columns 9.93, 9.80, 16 columns 10.25, 10.17; Pareto
+            // budgets at batch 100: 10.92, 10.78 and 11.35, 11.19.  At D = 128 and on bf16 caches ahead is the faster by 0 to 1 %.
+            constexpr bool kEndAhead = !(KV8 && SOLO && D == 64);
+            auto piece = [&](const CallArgs &call) __attribute__((always_inline)) {
+                return list.piece(call, ci, KV8 ? lane_value(head_mul, kScaleHeads + scale_h) : call.v_scale);
+            };
+            const CallArgs a_ahead = kEndAhead ? call_args() : CallArgs{};
+            const Piece pc_ahead = kEndAhead ? piece(a_ahead) : Piece{};
 
             for (bool fresh = true; left > 0; fresh = false) {
                 // The tile has landed once no more is outstanding than was requested after it: the other tile of the ring
@@ -662,6 +669,8 @@ __global__ __launch_bounds__(kThreads, 1) void fairkv_decode_mfma_kernel(DecodeA
             }
             // ---- fold the four token quarters of l, stage this wave's result, finish the item ------
             l_run = quarters_sum(l_run);
+            const CallArgs a = kEndAhead ? a_ahead : call_args();
+            const Piece pc = kEndAhead ? pc_ahead : piece(a);
             if (SOLO && owner >= 0) {
                 // This wave has seen the whole pair: out = O / l and lse straight from its registers.  A lane holds
                 // coordinates 16 nb + 4 lq .. + 3 of head l16.
