@@ -522,8 +522,8 @@ __device__ __forceinline__ void item_epilogue(const CallArgs &a, const Piece &pc
     const bool whole_pair = pc.n_chunks == 1;
     constexpr int D4 = D / 4;
     __syncthreads();
-    // a thread owns four consecutive coordinates of one column (of two columns, when there are 16); all its LDS reads are issued together,
-    // with 16 columns both columns' (one column after the other in a loop: two waits, and a condition per lane on the second)
+    // a thread owns four consecutive coordinates of one column (of two columns, with 16 of them at D = 128); all its LDS reads are issued
+    // together, both columns' (one column after the other in a loop: two waits, and a condition per lane on the second)
     constexpr int NC4 = G * D4, IT = (NC4 + kThreads - 1) / kThreads;
     static_assert(NC4 <= kThreads || NC4 % kThreads == 0, "all threads or the first of them");
     if (NC4 >= kThreads || threadIdx.x < static_cast<unsigned>(NC4)) {

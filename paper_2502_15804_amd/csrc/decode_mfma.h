@@ -278,9 +278,9 @@ __global__ __launch_bounds__(kThreads, 1) void fairkv_decode_mfma_kernel(DecodeA
 
     if constexpr (TRACE) trace_stamp(args, kTraceStart, threadIdx.x == 0);
     // The kernel arguments are asked for here and waited for below (arrive_together): what depends on the lane alone is worked out in between.  Without
-    // the barrier the compiler asks for them behind those 95 instructions.  With the rows of the first tile requested before its queries, and
-    // nothing made ready for an item that does not come, us per layer: Llama-70B shape 16.10 -> 15.80, the same with an 8-bit cache
-    // 10.97 -> 10.87, one sequence 8.56 -> 8.41, Pareto budgets at batch 128 20.84 -> 20.60, 24B shape 32.9 -> 32.7.
+    // the barrier the compiler asks for them behind those 95 instructions.  With the rows of the first tile requested before its queries and
+    // the end of an item read ahead of its tiles (both below), us per layer: Llama-70B shape 16.03 -> 15.72, the same with an 8-bit cache
+    // 10.98 -> 10.78, one sequence 8.52 -> 8.40, Pareto budgets at batch 128 20.78 -> 20.44; the 24B shape (32.9) within the noise.
     const SlotStart slot = slot_start(args);
     const CallArgs held = args;
     HeadFactors factors{};

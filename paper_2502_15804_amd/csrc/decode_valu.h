@@ -27,7 +27,7 @@ __device__ __forceinline__ Piece piece_of(const ItemSlot &e, float v_mul)
 }
 
 // One wave per SIMD: the outputs, K and V of a tile take up to 512 registers.  Held to the 256 of two waves per SIMD,
-// which the 74 KB of LDS would let share a compute unit, <128, 8> spilled 792 of them instead of 356, and the traffic to
+// which the 74 KB of LDS would let share a compute unit, <128, 8> spilled 792 of them instead of 351, and the traffic to
 // scratch memory is what the time goes to.  us per layer with two waves and with one: Llama-70B shape 264 and
 // 174, the same with two query heads per KV head 63 and 25, the same with D = 64 87 and 30, 24B shape 273 and 84.
 template <int D, int G>
